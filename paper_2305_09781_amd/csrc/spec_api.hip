@@ -101,10 +101,10 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
   p.m32 = false;
   const int max_prefix = d.max_prefix_len > 0 ? d.max_prefix_len : d.S_cap - d.N;
   const int max_len = max_prefix + d.N;
-  // bf16: one workgroup serves all query heads of a K/V head; float32: one per query head
+  // bf16: one workgroup serves all query heads of a K/V head; float32: one per one or two query tiles
   const QueryGroups qg = attn_query_groups(d);
   const int virtual_heads = d.H_kv * qg.n_qgroups;
-  const long groups = (long)d.B * (d.dtype == SPEC_BF16 ? virtual_heads : d.H);
+  const long groups = (long)d.B * (d.dtype == SPEC_BF16 ? virtual_heads : d.H_kv * f32_query_groups(d));
   const int tiles = qg.tiles_per_wg;   // 16-query tiles per workgroup
   // The few-query kernel serves one query tile per K/V head with k_new / v_new laid out like q; everything
   // else in bf16 runs on the wide kernel.
@@ -148,6 +148,18 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       p.chunk_keys = 0;
       p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair is overlapped by at most this many shares
     }
+  }
+  if (chunk <= 0 && d.dtype == SPEC_F32) {
+    // float32: two workgroups fit a compute unit, and the matrix unit is as busy as the memory: the key range is cut
+    // until there are two workgroups per compute unit, in chunks of at least 128 keys (two tiles per wavefront), where
+    // that saves more than the merge launch costs (from 256 keys on; never with a workgroup per compute unit already).
+    // Measured, us at the chosen cut / uncut: 4 requests x 32 heads, 300-1000 keys, trees of 24: 38 / 53; 1 x 32, 400
+    // keys, 16: 14 / 19.5; 1 x 32, 800 keys: 15 / 29; 8 x 32, 512 keys: cut in two 40.9, uncut (the choice) 37.4. The partials of 512 workgroups of 32 queries are 9 MB at most.
+    const long want = 2L * compute_units() / std::max<long>(1, groups);
+    const long splits =
+        (max_len < 256 || groups >= compute_units()) ? 1 : std::max<long>(1, std::min<long>(want, max_len / 128));
+    chunk = (int)((max_len + splits - 1) / splits);
+    chunk = std::max(128, (int)round_up((size_t)chunk, 64));
   }
   if (p.balanced_wgs == 0) {
     if (chunk <= 0) {
@@ -337,12 +349,8 @@ static int tree_attention_impl(const spec_attn_desc_t* desc, const spec_kv_pages
     e = launch_tree_attention_bf16(d, plan, pg, q, k_cache, v_cache, k_new, v_new, tree_parent, tree_depth, prefix_len, out,
                                    workspace, status, s, rope);
   } else {
-    if (append) {
-      e = launch_kv_append(d, pg, k_new, v_new, k_cache, v_cache, prefix_len, status, s);
-      if (e != hipSuccess) return SPEC_ERR_HIP;
-    }
-    e = launch_tree_attention_f32(d, plan, pg, (const float*)q, (const float*)k_cache, (const float*)v_cache, tree_parent,
-                                  tree_depth, prefix_len, (float*)out, workspace, status, s);
+    e = launch_tree_attention_f32(d, plan, pg, (const float*)q, (float*)k_cache, (float*)v_cache, (const float*)k_new,
+                                  (const float*)v_new, tree_parent, tree_depth, prefix_len, (float*)out, workspace, status, s);
   }
   if (e != hipSuccess) return SPEC_ERR_HIP;
   if (plan.n_splits > 1 || plan.balanced_wgs > 0) {

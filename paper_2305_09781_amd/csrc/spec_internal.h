@@ -83,6 +83,14 @@ inline QueryGroups attn_query_groups(const spec_attn_desc_t& d) {
   return g;
 }
 
+// float32 kernel: a workgroup serves one or two 16-query tiles of the group * N queries of a K/V head (more would not fit
+// its registers beside a K/V tile), further tiles go to further workgroups.
+inline int f32_query_tiles(const spec_attn_desc_t& d) { return (long)(d.H / d.H_kv) * d.N <= 16 ? 1 : 2; }
+inline int f32_query_groups(const spec_attn_desc_t& d) {
+  const int per_wg = 16 * f32_query_tiles(d);
+  return (int)(((long)(d.H / d.H_kv) * d.N + per_wg - 1) / per_wg);
+}
+
 // Strides of k_new / v_new (all zero in the descriptor: laid out like q).
 struct NewStrides { long b, n, h; };
 inline NewStrides attn_new_strides(const spec_attn_desc_t& d) {
@@ -102,11 +110,11 @@ hipError_t launch_kv_commit(const spec_attn_desc_t& d, const Pages& pg, int n_la
                             void* const* v_caches,
                             const int32_t* path, int Lmax, const int32_t* len, const int32_t* prefix_len,
                             int32_t* prefix_len_out, int32_t* status, hipStream_t s);
+// k_new / v_new non-null (either dtype): the kernel also appends the tree rows to the cache (fused KV append).
 hipError_t launch_tree_attention_f32(const spec_attn_desc_t& d, const AttnPlan& plan, const Pages& pg, const float* q,
-                                     const float* k_cache, const float* v_cache, const int32_t* parent,
-                                     const int32_t* depth, const int32_t* prefix_len, float* out, void* ws,
-                                     int32_t* status, hipStream_t s);
-// k_new / v_new non-null: the kernel also appends the tree rows to the cache (fused KV append).
+                                     float* k_cache, float* v_cache, const float* k_new, const float* v_new,
+                                     const int32_t* parent, const int32_t* depth, const int32_t* prefix_len, float* out,
+                                     void* ws, int32_t* status, hipStream_t s);
 // rope.cos non-null (with k_new / v_new): the queries (in registers) and the new K rows (before they are used and
 // stored) are rotated by their positions' angles.
 hipError_t launch_tree_attention_bf16(const spec_attn_desc_t& d, const AttnPlan& plan, const Pages& pg, const void* q, void* k_cache,

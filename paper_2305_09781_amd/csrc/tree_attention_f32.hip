@@ -1,171 +1,330 @@
 // Tree attention for float32 inputs (Definition 4.1 with the topology-aware causal mask of Section
-// 4.2), plus the split-combine step shared with the bf16 kernel.
+// 4.2), plus the split-combine step shared with the bf16 kernels.
 //
-// float32 K/V cannot use the bf16 matrix cores without losing the 1e-5 accuracy this dtype is held
-// to, so scores and P.V are plain float32 FMAs. This path serves small, accuracy-checking shapes; the
-// bandwidth-critical path is the bf16 kernel.
+// float32 K/V cannot use the bf16 matrix cores without losing the accuracy this dtype is held to, so both products
+// run on v_mfma_f32_16x16x4_f32 (exact float32 products, float32 accumulation: as many operations per cycle as the
+// vector unit's float32 fma, without its operand traffic).
 //
-// Work split: grid = (n_splits, H, B); a workgroup owns one chunk of the key range of one
-// (request, head) and all N tree queries, keeps an online softmax (running max m, sum l, un-normalised
-// output O) and either writes the final output (one split) or a partial (m, l, O) that
+// Work split: a workgroup owns one chunk of the key range of one (request, K/V head) and NT 16-query tiles of the
+// group * N queries that share that head (query index = head in group * N + node). Its four wavefronts take the
+// chunk's 16-key tiles round-robin, each with its own online softmax and no barrier in the loop, and are merged
+// through LDS at the end; the workgroup writes the final output (one chunk) or a partial (m, l, O) that
 // attn_combine_kernel merges.
+//
+// Layouts. S^T = K Q^T is taken with the head dimension permuted the same way for K and Q, so that a lane's operands
+// are whole 16-byte pieces: lane (r, g) of a tile holds pieces 4j + g of key r (K, straight from global memory) and of
+// query r (Q). The product leaves it with query r's scores for keys 4g + i, which is the operand O^T += V^T P^T wants
+// for k-step i with row 4g + i of V in 16-byte pieces again: neither K, V nor the probabilities pass through LDS.
+//
+// What bounds it: float32 MFMA rate and the stream of K/V are close to each other (16 keys x 16 queries x 128
+// dimensions are 2048 cycles of one SIMD for 16 KB). Measured on 4 requests x 32 heads x 128, 300 to 1000 keys, trees of
+// 24 (95 MB): 37.6 us a layer, append and merge launch included (2.5 TB/s, 27 TFLOP/s), against
+// 304 us for the kernel before it, which read K uncoalesced per (query, key) and ran the softmax on N threads. Keeping the
+// queries in LDS to pay for a second K/V register set was slower: it spills at two query tiles (50 us) and gains nothing at
+// one.
 #include <hip/hip_bf16.h>
+
+#include <algorithm>
 
 #include "spec_internal.h"
 
 namespace spec {
 
-constexpr int F32_TK = 32;       // keys per inner tile
+constexpr int F32_WAVES = 4;     // wavefronts per workgroup
+constexpr int F32_TK = 16;       // keys per wavefront tile
 constexpr float kLog2e = 1.4426950408889634f;
 
-template <int D>
-__global__ void __launch_bounds__(256) tree_attention_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k_cache, const float* __restrict__ v_cache,
-    const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, const int32_t* __restrict__ prefix_len,
-    float* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml, int32_t* status, int N, int H,
-    int S_cap, int group, int chunk_keys, int n_splits, long q_sb, long q_sn, long q_sh, long kv_sb, long kv_sh,
-    long kv_ss, float scale_log2, Pages pg) {
-  extern __shared__ float smem[];
-  __shared__ unsigned long long s_anc[SPEC_MAX_TREE_NODES][2];
-  __shared__ int s_flag;
-  float* q_s = smem;                          // [N][D]
-  float* s_s = q_s + N * D;                   // [N][F32_TK + 1]
-  float* m_s = s_s + N * (F32_TK + 1);        // [N] running max
-  float* l_s = m_s + N;                       // [N] running sum
-  float* a_s = l_s + N;                       // [N] rescale factor of this tile
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-  const int split = blockIdx.x, h = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
+__device__ __forceinline__ void f32_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// APPEND: rows >= prefix_len are taken from k_new / v_new, and the workgroups of the first query group write them to
+// the cache (also for a malformed tree: the append does not depend on it).
+template <int D, int NT, bool APPEND>
+__global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
+    const float* __restrict__ q, float* k_cache, float* v_cache, const float* __restrict__ k_new,
+    const float* __restrict__ v_new, const int32_t* __restrict__ parent, const int32_t* __restrict__ depth,
+    const int32_t* __restrict__ prefix_len, float* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml,
+    int32_t* status, int B, int N, int H, int H_kv, int S_cap, int n_qg, int chunk_keys, int n_splits, long q_sb, long q_sn,
+    long q_sh, long n_sb, long n_sn, long n_sh, long kv_sb, long kv_sh, long kv_ss, float scale_log2, Pages pg) {
+  constexpr int NTHREADS = F32_WAVES * 64;
+  constexpr int KJ = D / 16;       // 16-byte pieces of a K row per lane
+  constexpr int VH = D / 64;       // 16-byte pieces of a V row per lane
+  constexpr int QT = NT * 16;      // queries of the workgroup
+  constexpr int OROW = D + 4;      // floats per merged output row in LDS (+4: rows start on different banks)
+  __shared__ float s_o[F32_WAVES][QT][OROW];
+  __shared__ float s_m[F32_WAVES][QT], s_l[F32_WAVES][QT];
+  __shared__ unsigned long long s_anc[SPEC_MAX_TREE_NODES][2];
+  __shared__ int s_parent[SPEC_MAX_TREE_NODES];
+  __shared__ int s_flag;
+
+  // The query groups of one chunk read the same K/V: they are numbered eight apart, which puts them on one XCD (
+  // workgroups go to the eight XCDs round-robin), close in time, so that the repeats can be hits of its L2.
+  const int in_blk = blockIdx.x % (8 * n_qg);
+  const int qg = in_blk / 8;
+  int pc = (blockIdx.x / (8 * n_qg)) * 8 + in_blk % 8;
+  if (pc >= B * H_kv * n_splits) return;
+  const int split = pc % n_splits;
+  pc /= n_splits;
+  const int hk = pc % H_kv, b = pc / H_kv;
+  const int group = H / H_kv, M = group * N;   // queries that share this K/V head
+  const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
-  const bool valid = tree_is_valid(parent + (long)b * N, depth + (long)b * N, N, &s_flag) && cap_ok;
-  if (!valid) {
-    if (n_splits == 1) {   // this workgroup owns the final output: defined result = 0
-      for (int i = t; i < N * D; i += 256) out[b * q_sb + (i / D) * q_sn + h * q_sh + (i % D)] = 0.f;
-      if (h == 0 && t == 0) set_status(status, b, cap_ok ? SPEC_ST_BAD_TREE : SPEC_ST_CAPACITY);
-    }
-    return;
-  }
   const int len = P + N;
   const int c0 = split * chunk_keys;
   const int c1 = min(c0 + chunk_keys, len);
+  // query row qi of this workgroup: head in the group and node
+  auto query_off = [&](int qi) { return b * q_sb + (long)(qi % N) * q_sn + (long)(hk * group + qi / N) * q_sh; };
+  auto fail = [&](int bit) {   // a request without a result: zeros, from the workgroups that own final outputs
+    if (n_splits != 1) return;
+    for (int i = t; i < QT * (D / 4); i += NTHREADS) {
+      const int qi = qg * QT + i / (D / 4);
+      if (qi < M) *(float4*)(out + query_off(qi) + (i % (D / 4)) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if (hk == 0 && qg == 0 && t == 0) set_status(status, b, bit);
+  };
+  if (!cap_ok) {
+    if (APPEND && hk == 0 && qg == 0 && split == 0 && t == 0) set_status(status, b, SPEC_ST_CAPACITY);
+    fail(SPEC_ST_CAPACITY);
+    return;
+  }
   if (c0 >= len) return;   // the combine step never reads this split
 
-  // ancestor-or-self bitmask of every node: walk up the parent chain (bounded by N steps)
-  if (t < N) {
-    unsigned long long lo = 0, hi = 0;
-    int u = t;
-    for (int step = 0; step < N && u >= 0; ++step) {
-      if (u < 64) lo |= 1ull << u; else hi |= 1ull << (u - 64);
-      u = parent[(long)b * N + u];
-    }
-    s_anc[t][0] = lo;
-    s_anc[t][1] = hi;
-    m_s[t] = -INFINITY;
-    l_s[t] = 0.f;
-  }
-  for (int i = t; i < N * D; i += 256) q_s[i] = q[b * q_sb + (i / D) * q_sn + h * q_sh + (i % D)];
-  __syncthreads();
-
-  constexpr int CG = D / 4;          // float4 column groups
-  constexpr int RG = 256 / CG;       // row groups
-  constexpr int RMAX = (SPEC_MAX_TREE_NODES + RG - 1) / RG;
-  const int cg = t % CG, rg = t / CG;
-  float4 acc[RMAX];
-#pragma unroll
-  for (int r = 0; r < RMAX; ++r) acc[r] = make_float4(0.f, 0.f, 0.f, 0.f);
-
-  const long head_off = (h / group) * kv_sh;   // grouped-query heads: `group` query heads per K/V head
-
-  for (int k0 = c0; k0 < c1; k0 += F32_TK) {
-    const int tk = min(F32_TK, c1 - k0);
-    // a tile starts at a multiple of 32 rows, so it lies inside one block of a paged cache
+  // ---- first tile of this wavefront, queries, tree
+  const float* kn = APPEND ? k_new + b * n_sb + hk * n_sh : nullptr;
+  const float* vn = APPEND ? v_new + b * n_sb + hk * n_sh : nullptr;
+  const int n_tiles = (c1 - c0 + F32_TK - 1) / F32_TK;
+  float4 kf[KJ], vf[4][VH];
+  // A tile starts at a multiple of 16 rows, so it lies inside one block of a paged cache; rows past the chunk repeat its
+  // last one (their scores are masked).
+  auto tile_base = [&](int k0) {
     bool blk_ok;
-    const long tile_off = head_off + cache_row_offset(pg, b, k0, kv_sb, kv_ss, &blk_ok);
-    if (!blk_ok && t == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);
-    const float* kb = k_cache + tile_off;
-    const float* vb = v_cache + tile_off;
-    // scores of (query n, key k0+kk)
-    for (int idx = t; idx < N * F32_TK; idx += 256) {
-      const int n = idx / F32_TK, kk = idx % F32_TK;
-      float s = -INFINITY;
-      if (kk < tk) {
-        const int key = k0 + kk;
-        const int rel = key - P;
-        bool vis = rel < 0;
-        if (!vis) vis = (s_anc[n][rel >> 6] >> (rel & 63)) & 1ull;
-        if (vis) {
-          const float4* kr = (const float4*)(kb + (long)kk * kv_ss);
-          const float4* qr = (const float4*)(q_s + n * D);
-          float d0 = 0.f, d1 = 0.f, d2 = 0.f, d3 = 0.f;
-#pragma unroll 8
-          for (int j = 0; j < D / 4; ++j) {
-            const float4 kv = kr[j], qv = qr[j];
-            d0 = fmaf(qv.x, kv.x, d0);
-            d1 = fmaf(qv.y, kv.y, d1);
-            d2 = fmaf(qv.z, kv.z, d2);
-            d3 = fmaf(qv.w, kv.w, d3);
-          }
-          s = ((d0 + d1) + (d2 + d3)) * scale_log2;
-        }
-      }
-      s_s[n * (F32_TK + 1) + kk] = s;
-    }
-    __syncthreads();
-    if (t < N) {
-      float mx = m_s[t];
-      for (int kk = 0; kk < tk; ++kk) mx = fmaxf(mx, s_s[t * (F32_TK + 1) + kk]);
-      const float m_use = (mx == -INFINITY) ? 0.f : mx;
-      const float alpha = exp2f(m_s[t] - m_use);     // m_s = -inf -> 0
-      float sum = 0.f;
-      for (int kk = 0; kk < tk; ++kk) {
-        const float p = exp2f(s_s[t * (F32_TK + 1) + kk] - m_use);
-        s_s[t * (F32_TK + 1) + kk] = p;
-        sum += p;
-      }
-      l_s[t] = l_s[t] * alpha + sum;
-      m_s[t] = mx;
-      a_s[t] = alpha;
-    }
-    __syncthreads();
+    const long off = cache_row_offset(pg, b, k0, kv_sb, kv_ss, &blk_ok) - k0 * kv_ss + hk * kv_sh;
+    if (!blk_ok && lane == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);
+    return off;
+  };
+  auto load_k = [&](int k0, long base) {
+    const int row = min(k0 + r16, c1 - 1);
+    const float* p = (APPEND && row >= P) ? kn + (long)(row - P) * n_sn : k_cache + base + (long)row * kv_ss;
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      const int n = rg + r * RG;
-      if (n < N) {
-        const float alpha = a_s[n];
-        float4 a = acc[r];
-        a.x *= alpha; a.y *= alpha; a.z *= alpha; a.w *= alpha;
-        for (int kk = 0; kk < tk; ++kk) {
-          const float p = s_s[n * (F32_TK + 1) + kk];
-          const float4 vv = *(const float4*)(vb + (long)kk * kv_ss + cg * 4);
-          a.x = fmaf(p, vv.x, a.x); a.y = fmaf(p, vv.y, a.y); a.z = fmaf(p, vv.z, a.z); a.w = fmaf(p, vv.w, a.w);
+    for (int j = 0; j < KJ; ++j) kf[j] = *(const float4*)(p + (4 * j + g) * 4);
+  };
+  auto load_v = [&](int k0, long base) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = min(k0 + 4 * g + i, c1 - 1);
+      const float* p = (APPEND && row >= P) ? vn + (long)(row - P) * n_sn : v_cache + base + (long)row * kv_ss;
+#pragma unroll
+      for (int hv = 0; hv < VH; ++hv) vf[i][hv] = *(const float4*)(p + r16 * 4 + 64 * hv);
+    }
+  };
+  int ti = wave;
+  if (ti < n_tiles) {
+    const long base = tile_base(c0 + ti * F32_TK);
+    load_k(c0 + ti * F32_TK, base);
+    load_v(c0 + ti * F32_TK, base);
+  }
+  float4 qf[NT][KJ];
+  int node[NT];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    const int qi = min(qg * QT + nt * 16 + r16, M - 1);
+    node[nt] = qi % N;
+    const float* p = q + query_off(qi);
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) qf[nt][j] = *(const float4*)(p + (4 * j + g) * 4);
+  }
+  const bool touches_tree = c1 > P;
+  unsigned long long anc[NT][2];
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) anc[nt][0] = anc[nt][1] = 0ull;
+  // one workgroup per request owns the final outputs' validity: every workgroup of a single chunk checks the tree; with
+  // several chunks only those that reach it do (the combine step gives a malformed request its zeros)
+  if (touches_tree) {
+    if (APPEND && qg == 0) {   // the chunk's new rows go to the cache
+      const int r0 = max(P, c0);
+      for (int i = t; i < (c1 - r0) * (D / 4); i += NTHREADS) {
+        const int row = r0 + i / (D / 4), c = (i % (D / 4)) * 4;
+        bool blk_ok;
+        const long dst = cache_row_offset(pg, b, row, kv_sb, kv_ss, &blk_ok) + hk * kv_sh + c;
+        if (!blk_ok && c == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);   // a row of a block outside the pool is not written
+        const float4 kk = *(const float4*)(kn + (long)(row - P) * n_sn + c), vv = *(const float4*)(vn + (long)(row - P) * n_sn + c);
+        if (blk_ok) {
+          *(float4*)(k_cache + dst) = kk;
+          *(float4*)(v_cache + dst) = vv;
         }
-        acc[r] = a;
       }
     }
-    __syncthreads();
+    int my_parent = -1, my_depth = 0;
+    if (t < N) {
+      my_parent = parent[(long)b * N + t];
+      my_depth = depth[(long)b * N + t];
+      s_parent[t] = my_parent;
+    }
+    if (t == 0) s_flag = 0;
+    f32_lds_barrier();
+    if (t < N) {
+      bool ok = t == 0 ? (my_parent == -1 && my_depth == 0) : (my_parent >= 0 && my_parent < t);
+      if (ok && t > 0) ok = my_depth == depth[(long)b * N + my_parent] + 1;
+      if (!ok) atomicOr(&s_flag, 1);
+    }
+    f32_lds_barrier();
+    if (s_flag != 0) {
+      fail(SPEC_ST_BAD_TREE);
+      return;
+    }
+    if (t < N) {   // ancestor-or-self bitmask of every node: walk up the parent chain (parents have smaller indices)
+      unsigned long long lo = 0, hi = 0;
+      for (int u = t; u >= 0; u = s_parent[u])
+        if (u < 64) lo |= 1ull << u; else hi |= 1ull << (u - 64);
+      s_anc[t][0] = lo;
+      s_anc[t][1] = hi;
+    }
+    f32_lds_barrier();
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      anc[nt][0] = s_anc[node[nt]][0];
+      anc[nt][1] = s_anc[node[nt]][1];
+    }
   }
 
-  if (n_splits == 1) {
+  f32x4 O[NT][VH * 4];
+  float m_run[NT], l_run[NT];
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      const int n = rg + r * RG;
-      if (n < N) {
-        const float inv = 1.f / l_s[n];
-        float4 a = acc[r];
-        a.x *= inv; a.y *= inv; a.z *= inv; a.w *= inv;
-        *(float4*)(out + b * q_sb + n * q_sn + h * q_sh + cg * 4) = a;
+  for (int nt = 0; nt < NT; ++nt) {
+    m_run[nt] = -INFINITY;
+    l_run[nt] = 0.f;
+#pragma unroll
+    for (int x = 0; x < VH * 4; ++x) O[nt][x] = (f32x4){0.f, 0.f, 0.f, 0.f};
+  }
+
+  // ---- tiles of this wavefront. The next tile's K is requested when this tile's scores are done, its V when this
+  // tile's output products are: each load has the other product's time to arrive.
+  while (ti < n_tiles) {
+    const int k0 = c0 + ti * F32_TK;
+    const int next = ti + F32_WAVES;
+    const bool more = next < n_tiles;
+    const int k1 = c0 + (more ? next : ti) * F32_TK;
+    const long base1 = tile_base(k1);
+    f32x4 sc[NT][2];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) sc[nt][0] = sc[nt][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) {
+      const float a[4] = {kf[j].x, kf[j].y, kf[j].z, kf[j].w};
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        const float bq[4] = {qf[nt][j].x, qf[nt][j].y, qf[nt][j].z, qf[nt][j].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sc[nt][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], bq[e], sc[nt][e & 1], 0, 0, 0);
       }
     }
-  } else {
-    const long base = (((long)b * H + h) * n_splits + split) * N;
+    if (more) load_k(k1, base1);
+    float p[NT][4];
+    const bool masked = k0 + F32_TK > min(P, c1);
 #pragma unroll
-    for (int r = 0; r < RMAX; ++r) {
-      const int n = rg + r * RG;
-      if (n < N) *(float4*)(ws_o + (base + n) * D + cg * 4) = acc[r];
+    for (int nt = 0; nt < NT; ++nt) {
+      float s[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) s[i] = (sc[nt][0][i] + sc[nt][1][i]) * scale_log2;
+      if (masked) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int key = k0 + 4 * g + i, rel = key - P;
+          bool vis = key < c1;
+          if (vis && rel >= 0) vis = (anc[nt][rel >> 6] >> (rel & 63)) & 1ull;
+          if (!vis) s[i] = -INFINITY;
+        }
+      }
+      // Lazy running maximum (identical in the four lanes of a query): refreshed, with the exact cross-lane maximum and
+      // the rescaling of l and O, only when a score exceeds it by more than 2^16 in the exp2 domain.
+      float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+      if (__any(mx > m_run[nt] + 16.f)) {
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        mx = fmaxf(mx, __shfl_xor(mx, 32));
+        const float m_new = fmaxf(m_run[nt], mx);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[nt] - (m_new == -INFINITY ? 0.f : m_new));
+        m_run[nt] = m_new;
+        l_run[nt] *= alpha;
+#pragma unroll
+        for (int x = 0; x < VH * 4; ++x) O[nt][x] *= alpha;
+      }
+      const float m_use = m_run[nt] == -INFINITY ? 0.f : m_run[nt];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) p[nt][i] = __builtin_amdgcn_exp2f(s[i] - m_use);
+      l_run[nt] += (p[nt][0] + p[nt][1]) + (p[nt][2] + p[nt][3]);
     }
-    if (t < N) {
-      ws_ml[(base + t) * 2 + 0] = m_s[t];
-      ws_ml[(base + t) * 2 + 1] = l_s[t];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int hv = 0; hv < VH; ++hv) {
+        const float a[4] = {vf[i][hv].x, vf[i][hv].y, vf[i][hv].z, vf[i][hv].w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt)
+            O[nt][hv * 4 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], p[nt][i], O[nt][hv * 4 + e], 0, 0, 0);
+      }
+    if (more) load_v(k1, base1);
+    ti = next;
+  }
+
+  // ---- merge of the four wavefronts: each scales its state to the common maximum, then all threads add the rows
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float l = l_run[nt];
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (g == 0) {
+      s_m[wave][nt * 16 + r16] = m_run[nt];
+      s_l[wave][nt * 16 + r16] = l;
+    }
+  }
+  f32_lds_barrier();
+#pragma unroll
+  for (int nt = 0; nt < NT; ++nt) {
+    float m_all = s_m[0][nt * 16 + r16];
+#pragma unroll
+    for (int w = 1; w < F32_WAVES; ++w) m_all = fmaxf(m_all, s_m[w][nt * 16 + r16]);
+    const float f = m_run[nt] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[nt] - m_all);
+#pragma unroll
+    for (int hv = 0; hv < VH; ++hv)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *(float4*)&s_o[wave][nt * 16 + r16][(4 * g + i) * 4 + 64 * hv] =
+            make_float4(O[nt][hv * 4][i] * f, O[nt][hv * 4 + 1][i] * f, O[nt][hv * 4 + 2][i] * f, O[nt][hv * 4 + 3][i] * f);
+  }
+  f32_lds_barrier();
+  for (int i = t; i < QT * (D / 4); i += NTHREADS) {
+    const int row = i / (D / 4), c = (i % (D / 4)) * 4;
+    const int qi = qg * QT + row;
+    if (qi >= M) break;
+    float m_all = s_m[0][row];
+#pragma unroll
+    for (int w = 1; w < F32_WAVES; ++w) m_all = fmaxf(m_all, s_m[w][row]);
+    float l = 0.f;
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int w = 0; w < F32_WAVES; ++w) {
+      const float mw = s_m[w][row];
+      if (mw != -INFINITY) l += s_l[w][row] * __builtin_amdgcn_exp2f(mw - m_all);
+      const float4 ow = *(const float4*)&s_o[w][row][c];
+      o.x += ow.x; o.y += ow.y; o.z += ow.z; o.w += ow.w;
+    }
+    if (n_splits == 1) {
+      const float inv = 1.f / l;
+      o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
+      *(float4*)(out + query_off(qi) + c) = o;
+    } else {
+      const long slot = (((long)b * H + hk * group + qi / N) * n_splits + split) * N + qi % N;
+      *(float4*)(ws_o + slot * D + c) = o;
+      if (c == 0) {
+        ws_ml[slot * 2 + 0] = m_all;
+        ws_ml[slot * 2 + 1] = l;
+      }
     }
   }
 }
@@ -264,20 +423,33 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
 }
 
 hipError_t launch_tree_attention_f32(const spec_attn_desc_t& d, const AttnPlan& plan, const Pages& pg, const float* q,
-                                     const float* k_cache, const float* v_cache, const int32_t* parent,
-                                     const int32_t* depth, const int32_t* prefix_len, float* out, void* ws,
-                                     int32_t* status, hipStream_t s) {
+                                     float* k_cache, float* v_cache, const float* k_new, const float* v_new,
+                                     const int32_t* parent, const int32_t* depth, const int32_t* prefix_len, float* out,
+                                     void* ws, int32_t* status, hipStream_t s) {
   const float scale = (d.softmax_scale != 0.f ? d.softmax_scale : 1.0f / sqrtf((float)d.D)) * kLog2e;
   float* ws_o = ws ? (float*)((char*)ws + plan.ws_o_off) : nullptr;
   float* ws_ml = ws ? (float*)((char*)ws + plan.ws_ml_off) : nullptr;
-  const size_t smem = sizeof(float) * ((size_t)d.N * d.D + (size_t)d.N * (F32_TK + 1) + 3 * (size_t)d.N);
-  dim3 grid(plan.n_splits, d.H, d.B);
-  auto kern = d.D == 64 ? tree_attention_f32_kernel<64> : tree_attention_f32_kernel<128>;
-  hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kern, grid, dim3(256), smem, s, q, k_cache, v_cache, parent, depth, prefix_len, out, ws_o, ws_ml,
-                     status, d.N, d.H, d.S_cap, d.H / d.H_kv, plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n,
-                     (long)d.q_stride_h, (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg);
+  const int nt = f32_query_tiles(d), n_qg = f32_query_groups(d);
+  const NewStrides ns = attn_new_strides(d);
+  const long chunks = (long)d.B * d.H_kv * plan.n_splits;
+  const long wgs = (chunks + 7) / 8 * 8 * n_qg;
+  if (wgs > 0x7fffffffL) return hipErrorInvalidConfiguration;
+#define SPEC_F32(DD, NTT, APP)                                                                                            \
+  hipLaunchKernelGGL((tree_attention_f32_kernel<DD, NTT, APP>), dim3((unsigned)wgs), dim3(F32_WAVES * 64), 0, s, q, k_cache, \
+                     v_cache, k_new, v_new, parent, depth, prefix_len, out, ws_o, ws_ml, status, d.B, d.N, d.H, d.H_kv,     \
+                     d.S_cap, n_qg, plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n,                 \
+                     (long)d.q_stride_h, ns.b, ns.n, ns.h, (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s,   \
+                     scale, pg)
+#define SPEC_F32_APP(DD, NTT)                                \
+  if (k_new != nullptr) { SPEC_F32(DD, NTT, true); }         \
+  else { SPEC_F32(DD, NTT, false); }
+#define SPEC_F32_NT(DD)                                      \
+  if (nt == 1) { SPEC_F32_APP(DD, 1); }                      \
+  else { SPEC_F32_APP(DD, 2); }
+  if (d.D == 64) { SPEC_F32_NT(64); } else { SPEC_F32_NT(128); }
+#undef SPEC_F32_NT
+#undef SPEC_F32_APP
+#undef SPEC_F32
   return hipGetLastError();
 }
 

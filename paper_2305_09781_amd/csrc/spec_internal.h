@@ -24,8 +24,10 @@ struct AttnPlan {
   int heads_per_wg; // wide kernel, whole key ranges: consecutive K/V heads of a request served by one workgroup
   bool m32;         // 5..8 query tiles, D = 128: the kernel of tree_attention_bf16_wide32.hip (four wavefronts of 32
                     // queries, two workgroups per compute unit) instead of the wide kernel's eight wavefronts of 16
-  size_t ws_o_off;  // float [B][H][n_splits][N][D]   un-normalised partial outputs
-  size_t ws_ml_off; // float [B][H][n_splits][N][2]   running max (log2 domain) and partial sum
+  // Partials, slot by slot: a pair's slots are filled from 0, so the slots in use are one compact piece of the workspace
+  // whatever their number allows for (the balanced deal sizes it for one request holding all the tiles).
+  size_t ws_o_off;  // float [n_splits][B][H][N][D]   un-normalised partial outputs
+  size_t ws_ml_off; // float [n_splits][B][H][N][2]   running max (log2 domain) and partial sum
   size_t ws_bytes;
 };
 
@@ -207,15 +209,62 @@ struct BalancedShare {
 __device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
   return (P >= 0 && P <= S_cap - N) ? (P + N + tile - 1) / tile : 0;
 }
+// a / b of non-negative numbers, in 32 bits where they fit (a 64-bit division is some hundred instructions)
+__device__ inline long deal_div(long a, long b) {
+  return ((a | b) >> 32) == 0 ? (long)((unsigned)a / (unsigned)b) : a / b;
+}
+// The three functions below read prefix_len[] with all 64 lanes of a wavefront at once (a scalar walk is one dependent
+// load per request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
+// `before`: tiles of the requests below b_before, in units of one head.
 __device__ inline BalancedShare balanced_share(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap,
-                                               int tile, int n_wg) {
-  long tiles = 0;
-  for (int b = 0; b < B; ++b) tiles += request_tiles(prefix_len[b], N, S_cap, tile);
+                                               int tile, int n_wg, int b_before = 0, long* before = nullptr) {
+  const int lane = threadIdx.x & 63;
+  long tiles = 0, low = 0;
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+    int w = b0 + lane < b_before ? v : 0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      v += __shfl_xor(v, o);
+      w += __shfl_xor(w, o);
+    }
+    tiles += __builtin_amdgcn_readfirstlane(v);
+    low += __builtin_amdgcn_readfirstlane(w);
+  }
+  if (before != nullptr) *before = low;
   BalancedShare r;
   r.total = tiles * H;
-  r.share = (r.total + n_wg - 1) / n_wg;
+  r.share = deal_div(r.total + n_wg - 1, n_wg);
   if (r.share < 1) r.share = 1;
   return r;
+}
+// The request that holds tile `pos` (< total) of the deal: its index, first tile and tiles per head.
+struct DealRequest {
+  int b;
+  long start;
+  int tiles;
+};
+__device__ inline DealRequest deal_find(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap, int tile,
+                                        long pos) {
+  const int lane = threadIdx.x & 63;
+  long acc = 0;   // tiles of one head over the requests below b0
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+    int incl = v;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int up = __shfl_up(incl, o);
+      if (lane >= o) incl += up;
+    }
+    const unsigned long long hit = __ballot((acc + incl) * H > pos);
+    if (hit != 0) {
+      const int f = __ffsll((long long)hit) - 1;
+      const int tb = __builtin_amdgcn_readlane(v, f);
+      return {b0 + f, (acc + __builtin_amdgcn_readlane(incl, f) - tb) * H, tb};
+    }
+    acc += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return {0, 0, 1};   // not reached for pos < total
 }
 
 // Rotation of the two 16-byte pieces of a row that pair up under the half-split rotary embedding (piece `lo`

@@ -572,7 +572,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const int h = blockIdx.y / n_qgroups, qg = blockIdx.y % n_qgroups;
     const int b = blockIdx.z;
     segment(b, h, qg, split * chunk_keys, split * chunk_keys + chunk_keys,
-            n_splits == 1 ? -1l : (((long)b * H + h) * n_splits + split) * N);
+            n_splits == 1 ? -1l : (((long)split * B + b) * H + h) * N);
   } else {
     // Balanced stream: the 32-key tiles of all (request, head) pairs, in (request, head, key) order,
     // are dealt to the gridDim.x workgroups in equal contiguous shares, whatever the requests'
@@ -581,9 +581,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const BalancedShare bs = balanced_share(prefix_len, B, N, H, S_cap, TILE, (int)gridDim.x);
     long pos = (long)blockIdx.x * bs.share;
     const long end = min(bs.total, pos + bs.share);
-    int b = 0;
-    long req_start = 0;
-    int tb = request_tiles(prefix_len[0], N, S_cap, TILE);
+    if (pos >= end) return;
+    const DealRequest first = deal_find(prefix_len, B, N, H, S_cap, TILE, pos);
+    int b = first.b, tb = first.tiles;
+    long req_start = first.start;
     while (pos < end) {
       while (pos >= req_start + (long)H * tb) {   // pos < total: a request with tiles left lies ahead
         req_start += (long)H * tb;
@@ -591,10 +592,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
         tb = request_tiles(prefix_len[b], N, S_cap, TILE);
       }
       const long in_req = pos - req_start;
-      const int h = (int)(in_req / tb), tile0 = (int)(in_req % tb);
+      const int h = (int)deal_div(in_req, tb), tile0 = (int)(in_req - (long)h * tb);
       const int n_take = (int)min((long)(tb - tile0), end - pos);
-      const int slot = (int)blockIdx.x - (int)((req_start + (long)h * tb) / bs.share);
-      segment(b, h, 0, tile0 * TILE, (tile0 + n_take) * TILE, (((long)b * H + h) * n_splits + slot) * N);
+      const int slot = (int)blockIdx.x - (int)deal_div(req_start + (long)h * tb, bs.share);
+      segment(b, h, 0, tile0 * TILE, (tile0 + n_take) * TILE, (((long)slot * B + b) * H + h) * N);
       pos += n_take;
       __syncthreads();   // LDS (staging tiles, merge area, flags) is reused by the next segment
     }

@@ -598,7 +598,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       const int n = tile_node[nt], head = h * group + tile_head[nt];
       if (kpart == 0 && tile_live[nt] && n < N) {
         if (!final_out) {
-          const long base = (((long)b * H + head) * n_splits + slot) * N + n;
+          const long base = (((long)slot * B + b) * H + head) * N + n;
 #pragma unroll
           for (int db = 0; db < DB; ++db) *(f32x4*)(ws_o + base * D + db * 16 + 4 * g) = O[nt][db];
           if (g == 0) {
@@ -633,9 +633,10 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, KT, (int)gridDim.x);
     long pos = (long)blockIdx.x * bs.share;
     const long end = min(bs.total, pos + bs.share);
-    int b = 0;
-    long req_start = 0;
-    int tb = request_tiles(prefix_len[0], N, S_cap, KT);
+    if (pos >= end) return;
+    const DealRequest first = deal_find(prefix_len, B, N, H_v, S_cap, KT, pos);
+    int b = first.b, tb = first.tiles;
+    long req_start = first.start;
     while (pos < end) {
       while (pos >= req_start + (long)H_v * tb) {   // pos < total: a request with tiles left lies ahead
         req_start += (long)H_v * tb;
@@ -643,9 +644,9 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
         tb = request_tiles(prefix_len[b], N, S_cap, KT);
       }
       const long in_req = pos - req_start;
-      const int hv = (int)(in_req / tb), tile0 = (int)(in_req % tb);
+      const int hv = (int)deal_div(in_req, tb), tile0 = (int)(in_req - (long)hv * tb);
       const int n_take = (int)min((long)(tb - tile0), end - pos);
-      const int slot = (int)blockIdx.x - (int)((req_start + (long)hv * tb) / bs.share);
+      const int slot = (int)blockIdx.x - (int)deal_div(req_start + (long)hv * tb, bs.share);
       segment(b, hv, tile0 * KT, (tile0 + n_take) * KT, slot, 1);
       pos += n_take;
       lds_barrier();   // LDS (staging tiles, merge area, tree arrays) is reused by the next segment

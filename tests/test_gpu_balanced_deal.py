@@ -1,0 +1,28 @@
+"""The balanced deal over more requests than a wavefront has lanes (lengths are read 64 requests at a time), with requests
+that contribute no tiles, on every bf16 kernel. Bar: that of the other attention tests."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2305_09781_amd import workloads as wl
+from test_gpu_parity import _balanced_wgs, _check_attention, _oracle_append_attention, _run_append_attention
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,N,wgs", [(63, 5, 17), (64, 5, 200), (65, 20, 31), (130, 5, 300), (70, 70, 90)])
+def test_deal_over_many_requests(spec, B, N, wgs):
+    cfg = wl.Config(91, "deal", "bf16", B=B, H=2, D=128, P=(0, 200), N=N, tree="random_branching")
+    inp = wl.make_attention_inputs(cfg, seed=4000 + B, S_cap=200 + N)
+    out_of_range = [3, B - 1]
+    ref, _, _ = _oracle_append_attention(inp)
+    for b in out_of_range:              # no room for the tree: flagged, zero outputs, no tiles in the deal
+        inp["prefix_len"][b] = 201
+    status = torch.zeros(B, dtype=torch.int32, device="cuda:0")
+    with _balanced_wgs(wgs):
+        out, _, _ = _run_append_attention(spec, inp, status=status, fused=True)
+    st = status.cpu().numpy()
+    assert [b for b in range(B) if st[b]] == out_of_range and (st[out_of_range] == spec.ST_CAPACITY).all()
+    ok = [b for b in range(B) if b not in out_of_range]
+    assert (out[out_of_range] == 0).all()
+    _check_attention(out[ok], ref[ok], torch.bfloat16)

@@ -118,14 +118,13 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
   // workgroups the device holds at once: four-wavefront shapes of the wide kernel run two per compute unit
   const long resident = (long)compute_units() * ((p.wide && (tiles <= 4 || p.m32)) ? 2 : 1);
   if (chunk <= 0 && d.dtype == SPEC_BF16) {
-    // Several requests with few (request, head) pairs and long key ranges (long-context serving, ragged
-    // lengths): the bf16 kernels deal the key tiles of all pairs to as many workgroups as the device holds at
-    // once, in equal shares, so the stream is balanced whatever the individual lengths are. A share that
-    // crosses a pair boundary is two segments in a row, each with its own first-load latency and epilogue
-    // (about 6 us, measured against fixed chunks on equal lengths from 1024 to 16384 keys), so the deal is
-    // used only when a share is long enough for that to be small next to what unequal lengths would cost
-    // fixed chunks (a quarter of the stream for lengths uniform in [max/2, max]): at least 2048 keys per
-    // share at the stated maximum length. One request has no lengths to balance: fixed chunks.
+    // Several requests with few (request, head) pairs and long key ranges (long-context serving, ragged lengths): the
+    // bf16 kernels cut every pair's key tiles into as many equal chunks as its length asks for, about as many in all as
+    // the device holds workgroups, so the stream is balanced whatever the individual lengths are. Against fixed chunks of
+    // the stated maximum the deal costs 1 to 3 us of reading prefix_len[] first, and saves what unequal lengths leave
+    // idle (8 requests of 512 to 16384 keys: 257 us uncut, 195 us dealt to 512 chunks; 4 requests of 8192 to 16384: 138
+    // us either way): it is used for at least 2048 keys per chunk at the stated maximum length, where 3 us are small
+    // next to either. One request has no lengths to balance: fixed chunks.
     const int tile = p.wide ? SPEC_WIDE_TILE_KEYS : SPEC_SMALL_TILE_KEYS;
     int wgs = d.plan_balanced_wgs;   // caller's hint: > 0 that many workgroups, -1 never, 0 = chosen here
     if (wgs < 0) {
@@ -139,14 +138,14 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       const double stream_bytes = (double)d.B * d.H_kv * max_len * d.D * 2.0 * 2.0;
       const double partial_bytes_per_wg = 2.0 * (double)qg.heads_per_wg * d.N * (d.D + 2) * 4.0;
       cand = std::min<long>(cand, (long)(0.25 * stream_bytes / partial_bytes_per_wg));
-      // every workgroup walks prefix_len[0..B) with scalar loads to find its share: only for small batches
+      // every workgroup reads prefix_len[0..B) first, a wavefront's worth at a time
       wgs = (cand > groups && d.B > 1 && d.B <= 64) ? (int)cand : 0;
     }
     if (wgs > 0) {
       p.balanced_wgs = wgs;
       p.balanced_tile = tile;
-      p.chunk_keys = 0;
-      p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair is overlapped by at most this many shares
+      p.chunk_keys = wgs;
+      p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair has at most this many chunks
     }
   }
   if (chunk <= 0 && d.dtype == SPEC_F32) {
@@ -154,7 +153,8 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
     // until there are two workgroups per compute unit, in chunks of at least 128 keys (two tiles per wavefront), where
     // that saves more than the merge launch costs (from 256 keys on; never with a workgroup per compute unit already).
     // Measured, us at the chosen cut / uncut: 4 requests x 32 heads, 300-1000 keys, trees of 24: 38 / 53; 1 x 32, 400
-    // keys, 16: 14 / 19.5; 1 x 32, 800 keys: 15 / 29; 8 x 32, 512 keys: cut in two 40.9, uncut (the choice) 37.4. The partials of 512 workgroups of 32 queries are 9 MB at most.
+    // keys, 16: 14 / 19.5; 1 x 32, 800 keys: 15 / 29; 8 x 32, 512 keys: cut in two 40.9, uncut (the choice) 37.4. The
+    // partials of 512 workgroups of 32 queries are 9 MB at most.
     const long want = 2L * compute_units() / std::max<long>(1, groups);
     const long splits =
         (max_len < 256 || groups >= compute_units()) ? 1 : std::max<long>(1, std::min<long>(want, max_len / 128));

@@ -18,7 +18,7 @@ namespace spec {
 struct AttnPlan {
   int chunk_keys;   // keys per workgroup (multiple of 32)
   int n_splits;     // chunks covering max_prefix_len + N; balanced plan: partial slots per (request, head)
-  int balanced_wgs; // > 0: balanced plan with this many workgroups (see balanced_share), chunk_keys unused
+  int balanced_wgs; // > 0: balanced plan that aims at this many chunks (see balanced_deal), chunk_keys holds it too
   int balanced_tile;// keys per tile of the balanced deal (the tile of the kernel that runs the plan)
   bool wide;        // bf16: the wide kernel runs the plan (several query tiles per K/V head, or k_new not laid out like q)
   int heads_per_wg; // wide kernel, whole key ranges: consecutive K/V heads of a request served by one workgroup
@@ -61,6 +61,12 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged = false);
 inline int attn_queries_per_workgroup(const spec_attn_desc_t& d) {
   if (d.dtype != SPEC_BF16) return SPEC_MAX_TREE_NODES;
   return d.N <= 16 ? 16 : d.N <= 32 ? 32 : d.N <= 64 ? 64 : 128;
+}
+
+// Workgroups of a balanced launch: the chunks the deal aims at, or one per (request, virtual head) pair.
+inline unsigned balanced_grid(const AttnPlan& p, int B, int virtual_heads) {
+  const long pairs = (long)B * virtual_heads;
+  return (unsigned)(pairs > p.balanced_wgs ? pairs : p.balanced_wgs);
 }
 
 // Query heads per key/value head, and how the bf16 kernels split them. Every query head of a group brings
@@ -176,6 +182,10 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
 // ---------------------------------------------------------------------------------------------
 #ifdef __HIPCC__
 
+// A workgroup-uniform value back in a scalar register. The compiler divides on the vector unit and leaves the quotient
+// there, and with it every address and loop bound derived from it: the balanced launches lost 8 to 15 us of 100 to that.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+
 // Validates one request's tree with the threads of a workgroup (blockDim.x >= N).
 // Returns true for every thread iff parent[0] == -1, 0 <= parent[i] < i and depth[i] == depth[parent[i]] + 1.
 // `flag` is one int of LDS. Contains two __syncthreads().
@@ -199,13 +209,16 @@ __device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, const i
   return *flag == 0;
 }
 
-// Balanced plan: the key tiles (`tile` keys each) of all (request, head) pairs, ordered by (request,
-// head, key), are dealt to `n_wg` workgroups in equal contiguous shares of `share` tiles (the last may
-// be shorter). A request that does not fit the cache capacity contributes no tiles.
-struct BalancedShare {
-  long total;   // tiles over all requests and heads
-  long share;   // tiles per workgroup (>= 1)
-};
+// Balanced plan: every (request, head) pair's key tiles (`tile` keys each) are cut into equal chunks of at most `share`
+// tiles, as many for each request as its length asks for, and workgroup id has chunk number id. `share` is (nearly) the
+// smallest for which the chunks of all pairs are at most n_wg (or one per pair, if there are more pairs; the grid has room
+// for either, see balanced_grid()). A workgroup has one chunk of one pair: a share that crossed from one pair into the next would pay a second prologue and
+// epilogue (measured against a deal of equal contiguous shares over the same 512 workgroups, which also spilled registers in its
+// loop over segments: 32 requests x 64 / 8 heads, 900-4100 keys: 123 -> 103 us; 4 x 32 heads, 8192-16384: 147 -> 139 us). A request that does not fit
+// the cache capacity has no tiles.
+//
+// All functions read prefix_len[] with the 64 lanes of a wavefront at once (a scalar walk is one dependent load per
+// request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
 __device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
   return (P >= 0 && P <= S_cap - N) ? (P + N + tile - 1) / tile : 0;
 }
@@ -213,58 +226,94 @@ __device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
 __device__ inline long deal_div(long a, long b) {
   return ((a | b) >> 32) == 0 ? (long)((unsigned)a / (unsigned)b) : a / b;
 }
-// The three functions below read prefix_len[] with all 64 lanes of a wavefront at once (a scalar walk is one dependent
-// load per request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
-// `before`: tiles of the requests below b_before, in units of one head.
-__device__ inline BalancedShare balanced_share(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap,
-                                               int tile, int n_wg, int b_before = 0, long* before = nullptr) {
-  const int lane = threadIdx.x & 63;
-  long tiles = 0, low = 0;
-  for (int b0 = 0; b0 < B; b0 += 64) {
-    int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
-    int w = b0 + lane < b_before ? v : 0;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      v += __shfl_xor(v, o);
-      w += __shfl_xor(w, o);
-    }
-    tiles += __builtin_amdgcn_readfirstlane(v);
-    low += __builtin_amdgcn_readfirstlane(w);
-  }
-  if (before != nullptr) *before = low;
-  BalancedShare r;
-  r.total = tiles * H;
-  r.share = deal_div(r.total + n_wg - 1, n_wg);
-  if (r.share < 1) r.share = 1;
-  return r;
+// Inclusive sum over the lanes of a wavefront (lane 63 holds the total), in register moves: row shifts, then the last lane
+// of each row of 16 into the rows after it.
+__device__ inline int wave_inclusive_sum(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);   // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);   // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);   // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // row_bcast:15 into rows 1 and 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // row_bcast:31 into rows 2 and 3
+  return v;
 }
-// The request that holds tile `pos` (< total) of the deal: its index, first tile and tiles per head.
-struct DealRequest {
-  int b;
-  long start;
-  int tiles;
+__device__ inline int wave_sum_uniform(int v) { return __builtin_amdgcn_readlane(wave_inclusive_sum(v), 63); }
+// Chunks of a request with tb tiles: their number, and the tiles of each but the last.
+__device__ inline int deal_chunks(int tb, int share) { return (int)((unsigned)(tb + share - 1) / (unsigned)share); }
+__device__ inline int deal_chunk_tiles(int tb, int chunks) { return (int)((unsigned)(tb + chunks - 1) / (unsigned)chunks); }
+
+struct BalancedDeal {
+  int share;    // most tiles of a chunk (>= 1)
+  long count;   // chunks over all requests and heads
 };
-__device__ inline DealRequest deal_find(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap, int tile,
-                                        long pos) {
+__device__ inline BalancedDeal balanced_deal(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap, int tile,
+                                             int n_wg) {
   const int lane = threadIdx.x & 63;
-  long acc = 0;   // tiles of one head over the requests below b0
+  const int first = lane < B ? request_tiles(prefix_len[lane], N, S_cap, tile) : 0;
+  auto tiles_of = [&](int b0) {
+    return b0 == 0 ? first : b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+  };
+  long tiles = 0, pairs = 0;
   for (int b0 = 0; b0 < B; b0 += 64) {
-    const int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
-    int incl = v;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const int up = __shfl_up(incl, o);
-      if (lane >= o) incl += up;
+    const int v = tiles_of(b0);
+    tiles += wave_sum_uniform(v);
+    pairs += __popcll(__ballot(v > 0));
+  }
+  pairs *= H;
+  const long cap = max((long)n_wg, pairs);
+  long share = max(1l, deal_div(tiles * H + cap - 1, cap));
+  BalancedDeal d;
+  for (int i = 0;; ++i) {   // the share grows by the factor that is missing, from below; the last step always fits
+    if (i == 12) share = 0x3fffffff;
+    d.share = (int)min(share, 0x3fffffffl);
+    d.count = 0;
+    for (int b0 = 0; b0 < B; b0 += 64) {
+      const int v = tiles_of(b0);
+      d.count += wave_sum_uniform(deal_chunks(v, d.share));
     }
-    const unsigned long long hit = __ballot((acc + incl) * H > pos);
+    d.count *= H;
+    if (d.count <= cap || i == 12) return d;
+    share = max(share + 1, deal_div(share * d.count, cap));
+  }
+}
+// Chunk `id` (< count) of the deal: request, head, tiles [tile0, tile0 + n_tiles) (none if rounding leaves the request
+// fewer chunks than it was counted with) and the request's chunks per head. The query groups of one K/V head (n_qg heads
+// in a row) read the same keys: a chunk's groups are numbered eight apart where they can be, which puts them on one XCD.
+struct DealChunk {
+  int b, h, chunk, tile0, n_tiles, chunks;
+};
+__device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, int B, int N, int H, int n_qg, int S_cap,
+                                      int tile, const BalancedDeal& d, long id) {
+  const int lane = threadIdx.x & 63;
+  DealChunk c = {0, 0, 0, 0, 0, 1};
+  long acc = 0;   // chunks per head over the requests below b0
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int tb_lane = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+    const int v = deal_chunks(tb_lane, d.share);
+    const int incl = wave_inclusive_sum(v);
+    const unsigned long long hit = __ballot((acc + incl) * H > id);
     if (hit != 0) {
       const int f = __ffsll((long long)hit) - 1;
-      const int tb = __builtin_amdgcn_readlane(v, f);
-      return {b0 + f, (acc + __builtin_amdgcn_readlane(incl, f) - tb) * H, tb};
+      const int tb = __builtin_amdgcn_readlane(tb_lane, f);
+      c.chunks = __builtin_amdgcn_readlane(v, f);
+      c.b = b0 + f;
+      const int r = (int)(id - (acc + __builtin_amdgcn_readlane(incl, f) - c.chunks) * H);   // < H * chunks
+      int unit = r / n_qg, qg = r % n_qg;   // unit: (K/V head, chunk)
+      const int blk = r / (8 * n_qg), rr = r % (8 * n_qg);
+      if (n_qg > 1 && (blk + 1) * 8 <= H / n_qg * c.chunks) {
+        unit = blk * 8 + rr % 8;
+        qg = rr / 8;
+      }
+      c.chunk = unit % c.chunks;
+      c.h = unit / c.chunks * n_qg + qg;
+      const int per = deal_chunk_tiles(tb, c.chunks);
+      c.tile0 = c.chunk * per;
+      c.n_tiles = max(0, min(per, tb - c.tile0));
+      return {c.b, uniform(c.h), uniform(c.chunk), uniform(c.tile0), uniform(c.n_tiles), c.chunks};
     }
     acc += __builtin_amdgcn_readlane(incl, 63);
   }
-  return {0, 0, 1};   // not reached for pos < total
+  return c;
 }
 
 // Rotation of the two 16-byte pieces of a row that pair up under the half-split rotary embedding (piece `lo`

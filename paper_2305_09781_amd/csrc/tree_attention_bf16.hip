@@ -5,7 +5,7 @@
 //
 // Decomposition
 //   grid = (n_splits, H, B), or (BAL) gridDim.x workgroups that share the 32-key tiles of all
-//   (request, head) pairs equally (see balanced_share()). A workgroup owns one segment of the key
+//   (request, head) pairs evenly (see balanced_deal()). A workgroup owns one segment of the key
 //   range of one (request, head) at a time and all its tree queries. It has five wavefronts:
 //     - four streaming wavefronts take the chunk's mask-free 32-key tiles (entirely inside the cached
 //       prefix) round-robin; they never need the tree, a mask, or a barrier inside their loop;
@@ -569,36 +569,18 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   if constexpr (!BAL) {
     // grid = (n_splits, H * n_qgroups, B): one fixed-size chunk of one (request, head, query group)
     const int split = blockIdx.x;
-    const int h = blockIdx.y / n_qgroups, qg = blockIdx.y % n_qgroups;
+    const int h = uniform(blockIdx.y / n_qgroups), qg = blockIdx.y - h * n_qgroups;
     const int b = blockIdx.z;
     segment(b, h, qg, split * chunk_keys, split * chunk_keys + chunk_keys,
             n_splits == 1 ? -1l : (((long)split * B + b) * H + h) * N);
   } else {
-    // Balanced stream: the 32-key tiles of all (request, head) pairs, in (request, head, key) order,
-    // are dealt to the gridDim.x workgroups in equal contiguous shares, whatever the requests'
-    // lengths; a share that crosses a pair boundary becomes several segments. n_splits is the number
-    // of partial slots per pair: the workgroups overlapping a pair fill slots 0, 1, ... in order.
-    const BalancedShare bs = balanced_share(prefix_len, B, N, H, S_cap, TILE, (int)gridDim.x);
-    long pos = (long)blockIdx.x * bs.share;
-    const long end = min(bs.total, pos + bs.share);
-    if (pos >= end) return;
-    const DealRequest first = deal_find(prefix_len, B, N, H, S_cap, TILE, pos);
-    int b = first.b, tb = first.tiles;
-    long req_start = first.start;
-    while (pos < end) {
-      while (pos >= req_start + (long)H * tb) {   // pos < total: a request with tiles left lies ahead
-        req_start += (long)H * tb;
-        ++b;
-        tb = request_tiles(prefix_len[b], N, S_cap, TILE);
-      }
-      const long in_req = pos - req_start;
-      const int h = (int)deal_div(in_req, tb), tile0 = (int)(in_req - (long)h * tb);
-      const int n_take = (int)min((long)(tb - tile0), end - pos);
-      const int slot = (int)blockIdx.x - (int)deal_div(req_start + (long)h * tb, bs.share);
-      segment(b, h, 0, tile0 * TILE, (tile0 + n_take) * TILE, (((long)slot * B + b) * H + h) * N);
-      pos += n_take;
-      __syncthreads();   // LDS (staging tiles, merge area, flags) is reused by the next segment
-    }
+    // Balanced stream: the 32-key tiles of every pair in equal chunks, as many as the request's length asks for.
+    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H, S_cap, TILE, chunk_keys);
+    if ((long)blockIdx.x >= deal.count) return;
+    const DealChunk c = deal_find(prefix_len, B, N, H, 1, S_cap, TILE, deal, blockIdx.x);
+    if (c.n_tiles > 0)
+      segment(c.b, c.h, 0, c.tile0 * TILE, (c.tile0 + c.n_tiles) * TILE,
+              c.chunks == 1 ? -1l : (((long)c.chunk * B + c.b) * H + c.h) * N);
   }
 }
 
@@ -617,7 +599,7 @@ hipError_t launch_tree_attention_bf16(const spec_attn_desc_t& d, const AttnPlan&
   const int n_qgroups = 1;   // one 16-query tile covers the trees this kernel serves
   const bool append = k_new != nullptr;
   const bool bal = plan.balanced_wgs > 0;
-  const dim3 grid = bal ? dim3(plan.balanced_wgs, 1, 1) : dim3(plan.n_splits, d.H * n_qgroups, d.B);
+  const dim3 grid = bal ? dim3(balanced_grid(plan, d.B, d.H), 1, 1) : dim3(plan.n_splits, d.H * n_qgroups, d.B);
 #define SPEC_LAUNCH(DD, NTT, APP, BAL, PGD)                                                                      \
   hipLaunchKernelGGL((tree_attention_bf16_kernel<DD, NTT, APP, BAL, PGD>), grid, dim3(WAVES * 64), 0, s,         \
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,               \

@@ -24,8 +24,7 @@
 // from k_new / v_new and write them to the cache.
 //
 // Work split (PLAN): fixed chunks, grid = (n_splits, H, B); or the balanced deal of 64-key tiles over
-// gridDim.x workgroups described at balanced_share(), a share that crosses a (request, head) boundary
-// being processed as several segments.
+// gridDim.x workgroups described at balanced_deal().
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -145,7 +144,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
   // store, not a prologue.
   auto segment = [&](const int b, const int hv, const int c0, const int c1_cap, const int slot, const int nh) {
     const bool final_out = slot < 0;
-    const int h = hv / n_qg, qg = hv % n_qg;
+    const int h = uniform(hv / n_qg), qg = hv - h * n_qg;
 
     // ---- straight-line prologue: first two tiles (they do not depend on prefix_len), Q, one tree node per thread
     const int P = prefix_len[b];
@@ -618,7 +617,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     // one XCD, close in time, so that the repeats can be L2 hits.
     if (n_qg > 1 && (H_v / n_qg) % 8 == 0 && gridDim.x == 1) {
       const int r = hv % (8 * n_qg), blk = hv / (8 * n_qg);
-      hv = (blk * 8 + r % 8) * n_qg + r / 8;
+      hv = uniform((blk * 8 + r % 8) * n_qg + r / 8);
     }
     if (heads_per_wg > 1) {   // several K/V heads per workgroup (host: one query group per head, no key split)
       hv *= heads_per_wg;
@@ -627,30 +626,11 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       segment(b, hv, split * chunk_keys, split * chunk_keys + chunk_keys, n_splits == 1 ? -1 : split, 1);
     }
   } else {
-    // Tiles [pos, end) of the flattened (request, head, key tile) order belong to this workgroup.
-    // n_splits is the number of partial slots per pair; the workgroups overlapping a pair fill slots
-    // 0, 1, ... in order.
-    const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, KT, (int)gridDim.x);
-    long pos = (long)blockIdx.x * bs.share;
-    const long end = min(bs.total, pos + bs.share);
-    if (pos >= end) return;
-    const DealRequest first = deal_find(prefix_len, B, N, H_v, S_cap, KT, pos);
-    int b = first.b, tb = first.tiles;
-    long req_start = first.start;
-    while (pos < end) {
-      while (pos >= req_start + (long)H_v * tb) {   // pos < total: a request with tiles left lies ahead
-        req_start += (long)H_v * tb;
-        ++b;
-        tb = request_tiles(prefix_len[b], N, S_cap, KT);
-      }
-      const long in_req = pos - req_start;
-      const int hv = (int)deal_div(in_req, tb), tile0 = (int)(in_req - (long)hv * tb);
-      const int n_take = (int)min((long)(tb - tile0), end - pos);
-      const int slot = (int)blockIdx.x - (int)deal_div(req_start + (long)hv * tb, bs.share);
-      segment(b, hv, tile0 * KT, (tile0 + n_take) * KT, slot, 1);
-      pos += n_take;
-      lds_barrier();   // LDS (staging tiles, merge area, tree arrays) is reused by the next segment
-    }
+    // Every pair's tiles in equal chunks, as many as the request's length asks for; chunk i of a pair fills slot i.
+    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, chunk_keys);
+    if ((long)blockIdx.x >= deal.count) return;
+    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
+    if (c.n_tiles > 0) segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
   }
 }
 
@@ -679,7 +659,7 @@ hipError_t launch_tree_attention_bf16_wide(const spec_attn_desc_t& d, const Attn
   const int heads_per_wg = (mode == wide::PLAN_GRID && plan.n_splits == 1 && qgr.n_qgroups == 1 && qw == 8)
                                ? std::max(1, plan.heads_per_wg) : 1;
   const dim3 grid = mode != wide::PLAN_GRID
-                        ? dim3(plan.balanced_wgs, 1, 1)
+                        ? dim3(balanced_grid(plan, d.B, virtual_heads), 1, 1)
                         : dim3(plan.n_splits, (virtual_heads + heads_per_wg - 1) / heads_per_wg, d.B);
 #define SPEC_LAUNCH(DD, QQ, NTT, KK, DP, APP, PLAN, PGD)                                                              \
   hipLaunchKernelGGL((wide::tree_attention_bf16_wide_kernel<DD, QQ, NTT, KK, DP, APP, PLAN, PGD>), grid, dim3(QQ * KK * 64), 0, s, \

@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
   // qg. The result is the final output (slot < 0) or float32 partials in slot `slot` of every query head served.
   auto segment = [&](const int b, const int hv, const int c0, const int c1_cap, const int slot) {
     const bool final_out = slot < 0;
-    const int h = hv / n_qg, qg = hv % n_qg;
+    const int h = uniform(hv / n_qg), qg = hv - h * n_qg;
     const int P = prefix_len[b];
     const unsigned char* kc = (const unsigned char*)(k_cache + (PAGED ? 0 : b * kv_sb) + h * kv_sh);
     const unsigned char* vc = (const unsigned char*)(v_cache + (PAGED ? 0 : b * kv_sb) + h * kv_sh);
@@ -524,34 +524,16 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     // (workgroups go to the eight XCDs round-robin in launch order), close in time, so repeats can hit its L2
     if (n_qg > 1 && (H_v / n_qg) % 8 == 0 && gridDim.x == 1) {
       const int r = hv % (8 * n_qg), blk = hv / (8 * n_qg);
-      hv = (blk * 8 + r % 8) * n_qg + r / 8;
+      hv = uniform((blk * 8 + r % 8) * n_qg + r / 8);
     }
     segment(b, hv, split * chunk_keys, split * chunk_keys + chunk_keys, n_splits == 1 ? -1 : split);
   } else {
-    // Tiles [pos, end) of the flattened (request, head, key tile) order belong to this workgroup; n_splits is the
-    // number of partial slots per pair, filled in order by the workgroups that overlap the pair.
+    // Every pair's tiles in equal chunks, as many as the request's length asks for; chunk i of a pair fills slot i.
     constexpr int KT = SPEC_WIDE_TILE_KEYS;
-    const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, KT, (int)gridDim.x);
-    long pos = (long)blockIdx.x * bs.share;
-    const long end = min(bs.total, pos + bs.share);
-    if (pos >= end) return;
-    const DealRequest first = deal_find(prefix_len, B, N, H_v, S_cap, KT, pos);
-    int b = first.b, tb = first.tiles;
-    long req_start = first.start;
-    while (pos < end) {
-      while (pos >= req_start + (long)H_v * tb) {   // pos < total: a request with tiles left lies ahead
-        req_start += (long)H_v * tb;
-        ++b;
-        tb = request_tiles(prefix_len[b], N, S_cap, KT);
-      }
-      const long in_req = pos - req_start;
-      const int hv = (int)deal_div(in_req, tb), tile0 = (int)(in_req - (long)hv * tb);
-      const int n_take = (int)min((long)(tb - tile0), end - pos);
-      const int slot = (int)blockIdx.x - (int)deal_div(req_start + (long)hv * tb, bs.share);
-      segment(b, hv, tile0 * KT, (tile0 + n_take) * KT, slot);
-      pos += n_take;
-      lds_barrier();   // the ring and the tree arrays are reused by the next segment
-    }
+    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, chunk_keys);
+    if ((long)blockIdx.x >= deal.count) return;
+    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
+    if (c.n_tiles > 0) segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk);
   }
 }
 
@@ -569,7 +551,7 @@ hipError_t launch_tree_attention_bf16_wide32(const spec_attn_desc_t& d, const At
   const NewStrides ns = attn_new_strides(d);
   const bool append = k_new != nullptr;
   const bool tiles_plan = plan.balanced_wgs > 0;
-  const dim3 grid = tiles_plan ? dim3(plan.balanced_wgs, 1, 1) : dim3(plan.n_splits, virtual_heads, d.B);
+  const dim3 grid = tiles_plan ? dim3(balanced_grid(plan, d.B, virtual_heads), 1, 1) : dim3(plan.n_splits, virtual_heads, d.B);
 #define SPEC_LAUNCH(APP, PLAN, PGD, RP)                                                                                  \
   hipLaunchKernelGGL((wide32::tree_attention_bf16_wide32_kernel<APP, PLAN, PGD, RP>), grid, dim3(wide32::NTHREADS), 0, s, \
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,                   \

@@ -60,14 +60,13 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 
   // The query groups of one chunk read the same K/V: they are numbered eight apart, which puts them on one XCD (
   // workgroups go to the eight XCDs round-robin), close in time, so that the repeats can be hits of its L2.
-  const int in_blk = blockIdx.x % (8 * n_qg);
+  const int blk = uniform(blockIdx.x / (8 * n_qg)), in_blk = blockIdx.x - blk * 8 * n_qg;
   const int qg = in_blk / 8;
-  int pc = (blockIdx.x / (8 * n_qg)) * 8 + in_blk % 8;
+  const int pc = blk * 8 + in_blk % 8;
   if (pc >= B * H_kv * n_splits) return;
-  const int split = pc % n_splits;
-  pc /= n_splits;
-  const int hk = pc % H_kv, b = pc / H_kv;
-  const int group = H / H_kv, M = group * N;   // queries that share this K/V head
+  const int pair = uniform(pc / n_splits), split = pc - pair * n_splits;
+  const int b = uniform(pair / H_kv), hk = pair - b * H_kv;
+  const int group = uniform(H / H_kv), M = group * N;   // queries that share this K/V head
   const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
@@ -335,14 +334,15 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 // chunks (chunk_keys > 0) or the balanced deal (bal_wgs > 0). Also the place where a malformed request gets its defined
 // result (zeros) and its status bit. Bound by reading the filled slots once (32 requests x 64 heads x 16 nodes, two or
 // three slots each, 45 MB: 60 us before, when prefix_len[] was walked by scalar
-// loads and the slots of a pair lay next to each other over a gigabyte of mostly empty workspace; 17 us now).
+// loads and the slots of a pair lay next to each other over a gigabyte of mostly empty workspace; 17 us now; four pieces
+// per thread instead of one changes nothing).
 template <bool BF16>
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
                                                            const int32_t* __restrict__ parent,
                                                            const int32_t* __restrict__ depth,
                                                            const int32_t* __restrict__ prefix_len, void* __restrict__ out,
                                                            int32_t* status, int B, int N, int H, int H_kv, int n_qg,
-                                                           int hpw, int D, int S_cap, int chunk_keys, int slots,
+                                                           int D, int S_cap, int chunk_keys, int slots,
                                                            int bal_wgs, int bal_tile, long q_sb, long q_sn, long q_sh) {
   constexpr int CH = 4;   // partial slots fetched together
   __shared__ int s_flag;
@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   const long base = ((long)b * H + h) * N + n, slot_rows = (long)B * H * N;
   // The first slots are fetched before anything is known about the request (every slot exists in the
   // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: those that are
-  // filled for a request near the stated maximum, the two that almost every pair of a balanced deal has.
+  // filled for a request near the stated maximum, two of a balanced deal.
   float m_s[CH], l_s[CH];
   float4 o_s[CH];
   auto fetch = [&](int s0, int from, int to) {
@@ -378,17 +378,14 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   int ns = 0;
   if (valid) {
     if (bal_wgs > 0) {
-      // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group (hpw query
-      // heads); the query heads of one virtual head have the same partial slots
-      const int H_v = H_kv * n_qg, group = H / H_kv;
-      const int hv = (h / group) * n_qg + (h % group) / hpw;
-      long before;
-      const BalancedShare bs = balanced_share(prefix_len, B, N, H_v, S_cap, bal_tile, bal_wgs, b, &before);
+      // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group
+      const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
       const int tb = request_tiles(P, N, S_cap, bal_tile);
-      const long pair_start = before * H_v + (long)hv * tb;
-      ns = (int)(deal_div(pair_start + tb - 1, bs.share) - deal_div(pair_start, bs.share)) + 1;
+      const int chunks = deal_chunks(tb, deal.share);
+      if (chunks == 1) return;   // the attention kernel wrote the final output
+      ns = uniform(deal_chunks(tb, deal_chunk_tiles(tb, chunks)));
     } else {
-      ns = min(slots, (P + N + chunk_keys - 1) / chunk_keys);
+      ns = uniform(min(slots, (P + N + chunk_keys - 1) / chunk_keys));
     }
   }
   if (!active) return;
@@ -466,15 +463,15 @@ hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, 
   const float* ws_ml = (const float*)((const char*)ws + plan.ws_ml_off);
   const int items = d.N * (d.D / 4);
   const QueryGroups qg = attn_query_groups(d);
-  const int n_qg = d.dtype == SPEC_BF16 ? qg.n_qgroups : 1, hpw = d.dtype == SPEC_BF16 ? qg.heads_per_wg : 1;
+  const int n_qg = d.dtype == SPEC_BF16 ? qg.n_qgroups : 1;
   dim3 grid(d.H, d.B, (items + 255) / 256);
   if (d.dtype == SPEC_BF16) {
     hipLaunchKernelGGL(attn_combine_kernel<true>, grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,
-                       status, d.B, d.N, d.H, d.H_kv, n_qg, hpw, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
+                       status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
                        (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h);
   } else {
     hipLaunchKernelGGL(attn_combine_kernel<false>, grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,
-                       status, d.B, d.N, d.H, d.H_kv, n_qg, hpw, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
+                       status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
                        (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h);
   }
   return hipGetLastError();

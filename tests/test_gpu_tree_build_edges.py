@@ -1,0 +1,66 @@
+"""Top-k and merge kernels where they can go wrong: rows that are not 16-byte aligned, longer than one round of a
+workgroup's loads, picks that all lie with one thread, ties, signed zeros, infinities and NaN; merges of one tree, of the
+most input nodes, of chains, and of trees whose sizes differ. Bit-exact."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import spec_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.mark.parametrize("V,k,dt,offset", [(1, 1, "f32", 0), (4096, 3, "f32", 0), (32768, 4, "f32", 0), (40004, 16, "f32", 0),
+                                           (40003, 5, "f32", 0), (32000, 3, "f32", 1), (32000, 3, "bf16", 0), (70000, 16, "bf16", 0),
+                                           (32004, 3, "bf16", 0), (64000, 2, "bf16", 4), (131072, 16, "f32", 0)])
+def test_topk_row_lengths_and_alignments(spec, V, k, dt, offset):
+    rng = np.random.default_rng(V + k)
+    x = torch.from_numpy(np.round(rng.standard_normal((2, 2, V)) * 3, 1).astype(np.float32))     # coarse: many ties
+    if V > 4096:
+        x[0, 0, 7::4096] = 50.0 - torch.arange(x[0, 0, 7::4096].numel())      # every pick with the thread that owns element 7
+        x[0, 1, 5::8192] = 60.0                                               # equal maxima: ascending ids
+    x = x.to(torch.bfloat16 if dt == "bf16" else torch.float32)
+    buf = torch.zeros(x.numel() + offset, dtype=x.dtype, device=DEV)
+    dev = buf[offset:].view(x.shape)      # a base that is not 16-byte aligned
+    dev.copy_(x)
+    N = 2 * k
+    slots = torch.arange(2 * k, dtype=torch.int32).view(2, k)
+    tok = torch.full((2, max(N, 1)), -5, dtype=torch.int32, device=DEV)
+    spec.spec_tree_expand_topk(dev, k, slots.to(DEV), tok)
+    want = orc.expand_topk(x.float().numpy(), k).reshape(2, 2 * k)
+    assert np.array_equal(tok.cpu().numpy(), want)
+
+
+def test_topk_zeros_infinities_and_nan(spec):
+    x = torch.full((1, 4, 12), -1.0)
+    x[0, 0, 3], x[0, 0, 5] = 0.0, -0.0                    # equal: the lower id first
+    x[0, 1, 2], x[0, 1, 9] = -0.0, 0.0
+    x[0, 2, 4], x[0, 2, 6] = float("inf"), float("nan")
+    x[0, 3, :] = float("nan")
+    x[0, 3, 8] = float("-inf")
+    tok = torch.zeros((1, 12), dtype=torch.int32, device=DEV)
+    spec.spec_tree_expand_topk(x.to(DEV), 3, torch.arange(12, dtype=torch.int32, device=DEV).view(4, 3), tok)
+    assert tok.cpu().tolist() == [[3, 5, 0, 2, 9, 0, 4, 0, 1, 8, -1, -1]]
+
+
+@pytest.mark.parametrize("M,Nin,Nout,chain", [(1, 1, 1, False), (1, 64, 64, True), (3, 21, 63, False), (13, 5, 65, False),
+                                              (8, 128, 128, True), (2, 512, 128, False), (64, 16, 100, False)])
+def test_merge_sizes(spec, M, Nin, Nout, chain):
+    rng = np.random.default_rng(M * 1000 + Nin)
+    B = 4
+    par = np.full((B, M, Nin), -1, dtype=np.int32)
+    tok = np.zeros((B, M, Nin), dtype=np.int32)
+    size = np.zeros((B, M), dtype=np.int32)
+    for b in range(B):
+        for m in range(M):
+            size[b, m] = rng.integers(max(1, Nin // 2), Nin + 1)
+            for u in range(1, Nin):
+                par[b, m, u] = u - 1 if chain else rng.integers(max(0, u - 4), u)
+                tok[b, m, u] = rng.integers(0, 2 if b else 40)          # few tokens: many merges; many: overflow
+    dev = lambda a: torch.from_numpy(a).to(DEV)  # noqa: E731
+    status = torch.zeros(B, dtype=torch.int32, device=DEV)
+    got = spec.spec_tree_merge(dev(par), dev(tok), dev(size), Nout, status=status)
+    for b in range(B):
+        for g, w in zip(list(got) + [status], orc.tree_merge(par[b], tok[b], size[b], Nout)):
+            assert np.array_equal(g[b].cpu().numpy(), np.asarray(w))

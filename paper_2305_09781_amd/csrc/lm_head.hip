@@ -5,17 +5,27 @@
 // (M = B*N), the product is bound by streaming the weight matrix once from HBM (V x K x 2 bytes, 262 MB for
 // a 32000 x 4096 head), not by arithmetic.
 //
-// lm_head_argmax_kernel: a workgroup of eight (four when M <= 32) wavefronts owns 16 vocabulary rows per
-// wavefront and up to 128 rows of `hidden` (NMT tiles of 16). Every wavefront streams ITS 16 rows of W straight from global
-// memory into the MFMA A-operand layout (lane (r, g) holds W[v0 + r][k0 + 8g .. 8g + 8)), PF chunks of 64 k
-// in flight, independent of the other wavefronts; `hidden` (L2-resident, shared by all wavefronts) is staged
-// through LDS in slices of 256 k, double-buffered, one barrier per slice. The product is taken transposed,
-// C[v, m], so a lane ends up with four vocabulary entries of ONE row m and the arg-max over v is four
-// compares, two cross-lane steps and one pass through LDS over the eight wavefronts. Each workgroup writes its
-// (max, arg-max) per row; lm_head_reduce_kernel merges a row's partials (one per workgroup).
+// lm_head_argmax_kernel: a workgroup of four wavefronts owns 128 (64 for small vocabularies) vocabulary rows and up to
+// 256 rows of `hidden` (MT = 32 to 256). Both operands go from global memory straight into LDS (global_load_lds_dwordx4) in stages of 64 k, 16 KB of
+// W and MT rows of `hidden` (L2-resident), into a ring of as many stages as fit: two (256 rows) to five (32 rows) stages
+// of W are in flight per compute unit while one is multiplied, to cover the two microseconds of loaded latency. A lane's 16 bytes land at a fixed place, so the swizzle that keeps the operand reads off each other's banks is
+// applied to the source: slot s of row r holds the 16-byte piece s ^ ((r >> 1) & 7) of the row. The product is taken
+// transposed, C[v, m] on 32 x 32 x 16 tiles, so a lane ends up with 16 vocabulary entries of ONE row m per tile and the
+// arg-max over v is in the lane, one cross-lane step and one pass through LDS over the wavefronts. Each workgroup writes
+// its (max, arg-max) per row; lm_head_reduce_kernel merges a row's partials (one per workgroup).
+//
+// What bounds it: the stream of W. Nothing but these loads takes 45.3 us for 32000 x 4096 (5.8 TB/s), 52.7 without the
+// non-temporal hint. Every workgroup reads the same k of rows that lie 8 KB apart; starting each workgroup at another k
+// takes 39.5, but then equal rows of W in different workgroups would be summed in different orders and could differ in the
+// last bit, which the arg-max rule (lowest token among equal logits) does not allow. Measured at 32000 x 4096, arg-max only
+// / with logits and statistics and the merge, us (before: W straight into registers, 16 rows per wavefront, `hidden` through
+// LDS): 16 rows 50.4 / 52.6 (54.7 / 57.3), 64 rows 49.5 / 52.6 (54.8 / 58.9), 128 rows 55.2 / 58.6 (68.3 / 74.4), 256 rows
+// 83 / 90 (121 / 135).
+// More than 256 rows of `hidden` take several slices; the slices of one vocabulary tile are numbered eight apart, which
+// puts them on one XCD at the same time, so W is fetched once for all of them.
 #include <hip/hip_bf16.h>
 
-#include <type_traits>
+#include <algorithm>
 
 #include "spec_internal.h"
 
@@ -23,229 +33,225 @@ namespace spec {
 namespace lmh {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 
-constexpr int KC = 64;                        // k per chunk of W (two MFMA k-steps)
-constexpr int HC = 256;                       // k per LDS slice of hidden (four chunks)
-constexpr int CPS = HC / KC;                  // chunks per slice
-constexpr int PF = 8;                         // chunks of W in flight per wavefront
-constexpr int HROW = HC * 2 + 16;             // LDS bytes per hidden row (+16: 16 rows fall into 16 distinct bank groups)
+constexpr int KC = 64;                        // k per ring stage
+constexpr int ROWB = KC * 2;                  // LDS bytes per row of a stage
+constexpr int NTHREADS = 256;
 
-// f(integral_constant<int, I>) for I = 0 .. N - 1, unrolled at compile time.
-template <int I, int N, class F>
-__device__ __forceinline__ void static_for(F&& f) {
-  if constexpr (I < N) {
-    f(std::integral_constant<int, I>{});
-    static_for<I + 1, N>(f);
-  }
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+template <int N>
+__device__ __forceinline__ void wait_loads_but() {   // at most N vector memory operations of this lane still in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+// 16 bytes per lane from global memory to LDS address lds_dst + 16 * lane (lds_dst wave-uniform). W is read once per launch
+// (NT: non-temporal), `hidden` by every workgroup.
+template <bool NT>
+__device__ __forceinline__ void load_to_lds(const unsigned char* src, unsigned lds_dst) {
+  if (NT) asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" ::"v"(src), "s"(lds_dst) : "memory");
+  else asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_dst) : "memory");
 }
 
 // (value desc, index asc): does (v2, i2) beat (v1, i1)?
 __device__ __forceinline__ bool beats(float v2, int i2, float v1, int i1) { return v2 > v1 || (v2 == v1 && i2 < i1); }
 
-// WAVES wavefronts of 16 vocabulary rows each: eight (128 rows, one workgroup per CU) or four (64 rows, two
-// workgroups per CU, so that one's start and end overlap the other's stream).
 // STATS: the logits are also written out, rounded to bf16, and every partial carries the sum of
 // exp((x - max) / T) over the workgroup's vocabulary rows - of the ROUNDED values, which are what a verifier
 // reading those logits will see (maximum and arg-max are then those of the rounded values too).
-template <int NMT, int WAVES, bool STATS>
-__global__ void __launch_bounds__(WAVES * 64) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
-                                                                  const __hip_bfloat16* __restrict__ weight,
-                                                                  float* __restrict__ part_val, int32_t* __restrict__ part_idx,
-                                                                  float* __restrict__ part_sum,
-                                                                  __hip_bfloat16* __restrict__ logits_out, float inv_temp_log2,
-                                                                  int M, int K, int V, int n_vtiles) {
-  constexpr int NTHREADS = WAVES * 64, VT = WAVES * 16;
-  constexpr int MROWS = NMT * 16;
-  constexpr int STAGE = MROWS * HROW;
-  constexpr int PIECES = MROWS * (HC * 2 / 16);                       // 16-byte pieces of one slice
-  constexpr int NPT = (PIECES + NTHREADS - 1) / NTHREADS;             // per thread
-  __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE];
-  __shared__ float s_val[WAVES][MROWS];
-  __shared__ int s_idx[WAVES][MROWS];
-  __shared__ float s_sum[STATS ? WAVES : 1][MROWS];
+template <int VT, int MT, bool STATS>
+__global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
+                                                                    const __hip_bfloat16* __restrict__ weight,
+                                                                    float* __restrict__ part_val, int32_t* __restrict__ part_idx,
+                                                                    float* __restrict__ part_sum,
+                                                                    __hip_bfloat16* __restrict__ logits_out, float inv_temp_log2,
+                                                                    int M, int K, int V, int n_vtiles, int slices_per_row) {
+  constexpr int WV = VT / 32 < (MT >= 128 ? 2 : 4) ? VT / 32 : (MT >= 128 ? 2 : 4);   // wavefronts along v,
+  constexpr int WM = MT / 32 < 4 / WV ? MT / 32 : 4 / WV, KW = 4 / (WV * WM);         // along m, and along the k of a stage
+  constexpr int TV = VT / WV / 32, TM = MT / WM / 32;               // 32 x 32 tiles of a wavefront
+  constexpr int W_BYTES = VT * ROWB, STAGE = W_BYTES + MT * ROWB;
+  constexpr int NST = MT == 256 ? 3 : (128 << 10) / STAGE < 8 ? (128 << 10) / STAGE : 8, AHEAD = NST - 1;
+  constexpr int WL = VT / 32, HL = MT / 32, LPS = WL + HL;          // loads per lane and stage: 32 rows of eight pieces each
+  constexpr int CROW = VT * 2 + 16;                                 // LDS bytes per row of the logits on their way out
+  static_assert(MT * CROW <= NST * STAGE, "the logits reuse the ring");
+  __shared__ __attribute__((aligned(16))) unsigned char ring[NST * STAGE];
+  __shared__ float s_val[WV][MT];
+  __shared__ int s_idx[WV][MT];
+  __shared__ float s_sum[STATS ? WV : 1][MT];
 
+  const int blk = uniform(blockIdx.x / (8 * slices_per_row)), in_blk = blockIdx.x - blk * 8 * slices_per_row;
+  const int vt = blk * 8 + in_blk % 8, slice = blockIdx.y * slices_per_row + in_blk / 8;
+  if (vt >= n_vtiles || (long)slice * MT >= M) return;
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int r16 = lane & 15, g = lane >> 4;
-  const int v0 = blockIdx.x * VT + wave * 16, m0 = blockIdx.y * MROWS;
-  const int NC = K / KC, NS = K / HC;
+  const int wv = wave / WM % WV, wm = wave % WM, kw = wave / (WV * WM);
+  const int r = lane & 31, h = lane >> 5;
+  const int v0 = vt * VT, m0 = slice * MT;
+  const int NC = K / KC;
 
-  // this lane's row of W, in the MFMA A-operand layout (rows past V repeat the last one; their results are
-  // masked at the end). Requesting whole 128-byte lines per row instead (eight lanes per row) and transposing
-  // through LDS was measured: the loads alone are 5 % faster, the transposition costs as much.
-  // The loads stay plain: a load covers 64 bytes of each of 16 rows, the other half of every 128-byte line comes
-  // with the next load, and with the non-temporal hint the line is not kept for it (measured: 59 us against 52).
-  const unsigned char* wrow = (const unsigned char*)(weight + (long)min(v0 + r16, V - 1) * K) + g * 16;
-  u32x4 Wr[PF][2];
-  auto issue_w = [&](u32x4 (&dst)[2], int c) {
-    dst[0] = *(const u32x4*)(wrow + (long)c * (KC * 2));
-    dst[1] = *(const u32x4*)(wrow + (long)c * (KC * 2) + 64);
+  // loader: row j * 32 + t / 8 of the stage's W (and hidden) part, 16-byte slot t % 8; rows past the end repeat the last
+  // (their results are masked or not written)
+  const int piece = (t & 7) ^ ((t >> 4) & 7);
+  const unsigned char *wsrc[WL], *hsrc[HL];
+#pragma unroll
+  for (int j = 0; j < WL; ++j) wsrc[j] = (const unsigned char*)(weight + (long)min(v0 + j * 32 + (t >> 3), V - 1) * K) + piece * 16;
+#pragma unroll
+  for (int j = 0; j < HL; ++j) hsrc[j] = (const unsigned char*)(hidden + (long)min(m0 + j * 32 + (t >> 3), M - 1) * K) + piece * 16;
+  const unsigned wave_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring + wave * 1024;
+  auto issue = [&](int c, int slot) {
+    const unsigned dst = wave_lds + slot * STAGE;
+    const long k = (long)c * ROWB;
+#pragma unroll
+    for (int j = 0; j < HL; ++j) load_to_lds<false>(hsrc[j] + k, dst + W_BYTES + j * 4096);
+#pragma unroll
+    for (int j = 0; j < WL; ++j) load_to_lds<true>(wsrc[j] + k, dst + j * 4096);
   };
 #pragma unroll
-  for (int c = 0; c < PF; ++c)
-    if (c < NC) issue_w(Wr[c], c);
+  for (int c = 0; c < AHEAD; ++c)
+    if (c < NC) issue(c, c);
 
-  // hidden slice s: rows m0 .. m0 + MROWS (rows past M repeat the last one), k in [s * HC, s * HC + HC)
-  // A slice is requested one slice (four chunks) before it is staged. Loads return in order, so waiting for a
-  // slice also waits for every older load of W; at a distance of four chunks those are loads that had to be
-  // back by then anyway, and the chunks of W requested since stay in flight (with slices of two chunks the
-  // compiler's wait counts showed the stream being cut to 2-3 chunks per wavefront at every slice boundary).
-  u32x4 Hreg[NPT];
-  auto issue_h = [&](u32x4 (&Hr)[NPT], int s) {
+  f32x16 acc[TV][TM];
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-      const int p = t + j * NTHREADS;
-      if (NPT * NTHREADS == PIECES || p < PIECES) {
-        const int row = p / (HC * 2 / 16), col = p % (HC * 2 / 16);
-        Hr[j] = *(const u32x4*)((const unsigned char*)(hidden + (long)min(m0 + row, M - 1) * K + s * HC) + col * 16);
-      }
+  for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[tv][tm][i] = 0.f;
+  // operand of this wavefront's k-step ks: row r of a 32-row tile, piece 2 k-step + h (the swizzle depends on r alone)
+  unsigned off[4 / KW];
+#pragma unroll
+  for (int ks = 0; ks < 4 / KW; ++ks) off[ks] = r * ROWB + (((2 * (kw * (4 / KW) + ks) + h) ^ ((r >> 1) & 7)) << 4);
+
+  int slot = 0;
+  for (int c = 0; c < NC; ++c) {
+    if (c + AHEAD <= NC) wait_loads_but<(AHEAD - 1) * LPS>();
+    else wait_loads_but<0>();
+    lds_barrier();   // stage c has landed for every lane, and every wavefront is done with stage c - 1, whose slot is free
+    if (c + AHEAD < NC) issue(c + AHEAD, slot == 0 ? NST - 1 : slot - 1);
+    const unsigned char* ws = ring + slot * STAGE + wv * TV * 32 * ROWB;
+    const unsigned char* hs = ring + slot * STAGE + W_BYTES + wm * TM * 32 * ROWB;
+#pragma unroll
+    for (int ks = 0; ks < 4 / KW; ++ks) {
+      bf16x8 a[TV], b[TM];
+#pragma unroll
+      for (int tv = 0; tv < TV; ++tv) a[tv] = *(const bf16x8*)(ws + tv * 32 * ROWB + off[ks]);
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm) b[tm] = *(const bf16x8*)(hs + tm * 32 * ROWB + off[ks]);
+#pragma unroll
+      for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) acc[tv][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tv], b[tm], acc[tv][tm], 0, 0, 0);
     }
-  };
-  auto stage_h = [&](u32x4 (&Hr)[NPT], unsigned char* stage) {
+    slot = slot == NST - 1 ? 0 : slot + 1;
+  }
+
+  if (KW > 1) {   // wavefronts that took other k-steps of the same tiles hand their sums over, added in k-step order
+    lds_barrier();   // every wavefront is done with the ring
+    float* part = (float*)ring + ((wv * WM + wm) * TV * TM * 16) * 64 + lane;   // [k part - 1][wave tiles][i][lane]
+    constexpr int PART = WV * WM * TV * TM * 16 * 64;
+    static_assert((KW - 1) * PART * 4 <= NST * STAGE, "the partial sums reuse the ring");
 #pragma unroll
-    for (int j = 0; j < NPT; ++j) {
-      const int p = t + j * NTHREADS;
-      if (NPT * NTHREADS == PIECES || p < PIECES) {
-        const int row = p / (HC * 2 / 16), col = p % (HC * 2 / 16);
-        *(u32x4*)(stage + row * HROW + col * 16) = Hr[j];
-      }
+    for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          if (kw > 0) part[(kw - 1) * PART + ((tv * TM + tm) * 16 + i) * 64] = acc[tv][tm][i];
+    lds_barrier();
+    if (kw == 0) {
+#pragma unroll
+      for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+#pragma unroll
+            for (int p = 0; p < KW - 1; ++p) acc[tv][tm][i] += part[p * PART + ((tv * TM + tm) * 16 + i) * 64];
     }
-  };
-  issue_h(Hreg, 0);
-  stage_h(Hreg, lds);
-  if (NS > 1) issue_h(Hreg, 1);
-  __syncthreads();
+  }
 
-  f32x4 acc[NMT];
+  // ---- tile (tv, tm): the lane holds row m0 + (wm TM + tm) 32 + r, vocabulary rows v0 + (wv TV + tv) 32 + 8 (i / 4) + 4 h + i % 4
+  if (STATS) {   // round to the stored type first: statistics and arg-max are those of the stored logits
+    lds_barrier();   // every wavefront is done with the ring: the logits go through it, to leave as whole rows
+    if (kw == 0)
 #pragma unroll
-  for (int mt = 0; mt < NMT; ++mt) acc[mt] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-  // chunk c of W (register set c % PF) against quarter (c % 4) of hidden slice c / 4
-  auto chunk = [&](u32x4 (&w)[2], int c) {
-    const unsigned char* hs = lds + ((c / CPS) & 1) * STAGE + r16 * HROW + (c % CPS) * (KC * 2) + g * 16;
-    // The B operands are requested from LDS ahead of the products that use them (each product then waits for its
-    // own operand only; left to itself the compiler pairs every product with its read): all of the chunk's, or,
-    // with eight tiles of hidden, one k-step's at a time (the register file does not hold both).
-    constexpr int KSB = NMT == 8 ? 1 : 2;   // k-steps per batch of reads
+    for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-    for (int k0 = 0; k0 < 2; k0 += KSB) {
-      bf16x8 b[KSB][NMT];
+      for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
-      for (int ks = 0; ks < KSB; ++ks)
+        for (int i4 = 0; i4 < 4; ++i4) {
+          union { uint2 u; __hip_bfloat16 h4[4]; } pk;
 #pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) b[ks][mt] = *(const bf16x8*)(hs + mt * 16 * HROW + (k0 + ks) * 64);
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int ks = 0; ks < KSB; ++ks) {
-        const bf16x8 a = __builtin_bit_cast(bf16x8, w[k0 + ks]);
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b[ks][mt], acc[mt], 0, 0, 0);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // End of slice s: the slice after it goes from registers to the other LDS stage (last read during slice
-  // s - 1, before the previous barrier), and the slice two ahead is requested into the registers this frees.
-  // FULL: both exist (no branch). `odd`: parity of s + 1 (a compile-time constant at every call: blocks
-  // start at multiples of PF chunks, i.e. at even slices).
-  auto next_slice = [&](int s, auto odd_tag, auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    constexpr int ODD = decltype(odd_tag)::value;
-    if (FULL || s + 1 < NS) stage_h(Hreg, lds + ODD * STAGE);
-    if (FULL || s + 2 < NS) issue_h(Hreg, s + 2);
-    __syncthreads();
-  };
-  // PF chunks starting at c0. FULL: PF more chunks follow, so every register set is refilled and the block is
-  // straight-line code (the waits for the loads in flight are then exact counts, not worst cases).
-  auto block = [&](int c0, auto full_tag) {
-    constexpr bool FULL = decltype(full_tag)::value;
-    static_for<0, PF>([&](auto d_tag) {
-      constexpr int d = decltype(d_tag)::value;
-      const int c = c0 + d;
-      if (FULL || c < NC) {
-        chunk(Wr[d], c);
-        if (FULL || c + PF < NC) issue_w(Wr[d], c + PF);
-        if constexpr (d % CPS == CPS - 1) next_slice(c / CPS, std::integral_constant<int, ((d / CPS) + 1) & 1>{}, full_tag);
-      }
-    });
-  };
-  int c0 = 0;
-  for (; c0 + 2 * PF <= NC; c0 += PF) block(c0, std::true_type{});   // FULL: slices up to c0 / 4 + 3 exist
-  for (; c0 < NC; c0 += PF) block(c0, std::false_type{});
-
-  // ---- arg-max over this wavefront's 16 vocabulary rows, per row m: in the lane, then across the four lane groups
-#pragma unroll
-  for (int mt = 0; mt < NMT; ++mt) {
-    float x[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) x[i] = acc[mt][i];
-    if (STATS) {   // round to the stored type first: statistics and arg-max are those of the stored logits
-      union { uint2 u; __hip_bfloat16 h4[4]; } pk;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        pk.h4[i] = __float2bfloat16(x[i]);
-        x[i] = __bfloat162float(pk.h4[i]);
-      }
-      const int m = m0 + mt * 16 + r16, v = v0 + 4 * g;
-      if (m < M) {
-        __hip_bfloat16* dst = logits_out + (long)m * V + v;
-        if (v + 3 < V && (((long)m * V + v) & 3) == 0) {
-          *(uint2*)dst = pk.u;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i)
-            if (v + i < V) dst[i] = pk.h4[i];
+          for (int i = 0; i < 4; ++i) {
+            pk.h4[i] = __float2bfloat16(acc[tv][tm][i4 * 4 + i]);
+            acc[tv][tm][i4 * 4 + i] = __bfloat162float(pk.h4[i]);
+          }
+          *(uint2*)(ring + ((wm * TM + tm) * 32 + r) * CROW + ((wv * TV + tv) * 32 + i4 * 8 + 4 * h) * 2) = pk.u;
         }
-      }
+    lds_barrier();
+    const int rows = min(MT, M - m0), cols = min(VT, V - v0);
+    // Rows of an odd vocabulary start on any even byte: the 16-byte stores may be unaligned, which the hardware takes
+    // (one element per store cost 17 us of 78 at 50257 x 2304, 128 rows).
+    struct __attribute__((packed, aligned(2))) Piece { u32x4 v; };
+    for (int i = t; i < rows * (VT / 8); i += NTHREADS) {
+      const int m = i / (VT / 8), c = (i % (VT / 8)) * 8;
+      __hip_bfloat16* dst = logits_out + (long)(m0 + m) * V + v0 + c;
+      const unsigned char* src = ring + m * CROW + c * 2;
+      if (c + 8 <= cols) ((Piece*)dst)->v = *(const u32x4*)src;
+      else
+        for (int e = c; e < cols; ++e) dst[e - c] = *(const __hip_bfloat16*)(src + (e - c) * 2);
     }
+  }
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) {
     float best = -INFINITY;
     int best_i = 0x7fffffff;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int v = v0 + 4 * g + i;
-      if (v < V && x[i] > best) { best = x[i]; best_i = v; }   // ascending v: the lowest wins ties
-    }
-    const float lane_best = best;
+    for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
-    for (int o = 16; o <= 32; o <<= 1) {
-      const float ov = __shfl_xor(best, o);
-      const int oi = __shfl_xor(best_i, o);
+      for (int i = 0; i < 16; ++i) {
+        const int v = v0 + (wv * TV + tv) * 32 + 8 * (i / 4) + 4 * h + i % 4;
+        if (v < V && acc[tv][tm][i] > best) { best = acc[tv][tm][i]; best_i = v; }   // ascending v: the lowest wins ties
+      }
+    {
+      const float ov = __shfl_xor(best, 32);
+      const int oi = __shfl_xor(best_i, 32);
       if (beats(ov, oi, best, best_i)) { best = ov; best_i = oi; }
     }
     float sum = 0.f;
-    if (STATS) {   // sum of exp((x - best) / T) over the wavefront's 16 vocabulary rows (best: the wavefront's maximum)
+    if (STATS) {   // sum of exp((x - best) / T) over the wavefront's vocabulary rows (best: the wavefront's maximum)
       if (best > -INFINITY) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (v0 + 4 * g + i < V) sum += __builtin_amdgcn_exp2f((x[i] - best) * inv_temp_log2);
+        for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            if (v0 + (wv * TV + tv) * 32 + 8 * (i / 4) + 4 * h + i % 4 < V)
+              sum += __builtin_amdgcn_exp2f((acc[tv][tm][i] - best) * inv_temp_log2);
       }
-      sum += __shfl_xor(sum, 16);
       sum += __shfl_xor(sum, 32);
-      (void)lane_best;
     }
-    if (g == 0) {
-      s_val[wave][mt * 16 + r16] = best;
-      s_idx[wave][mt * 16 + r16] = best_i;
-      if (STATS) s_sum[wave][mt * 16 + r16] = sum;
+    if (h == 0 && kw == 0) {
+      const int m = (wm * TM + tm) * 32 + r;
+      s_val[wv][m] = best;
+      s_idx[wv][m] = best_i;
+      if (STATS) s_sum[wv][m] = sum;
     }
   }
   __syncthreads();
-  if (t < MROWS && m0 + t < M) {
+  if (t < MT && m0 + t < M) {
     float best = s_val[0][t];
     int best_i = s_idx[0][t];
 #pragma unroll
-    for (int w = 1; w < WAVES; ++w)
+    for (int w = 1; w < WV; ++w)
       if (beats(s_val[w][t], s_idx[w][t], best, best_i)) { best = s_val[w][t]; best_i = s_idx[w][t]; }
-    part_val[(long)(m0 + t) * n_vtiles + blockIdx.x] = best;
-    part_idx[(long)(m0 + t) * n_vtiles + blockIdx.x] = best_i;
+    part_val[(long)(m0 + t) * n_vtiles + vt] = best;
+    part_idx[(long)(m0 + t) * n_vtiles + vt] = best_i;
     if (STATS) {
       float sum = 0.f;
 #pragma unroll
-      for (int w = 0; w < WAVES; ++w)
+      for (int w = 0; w < WV; ++w)
         if (s_val[w][t] > -INFINITY) sum += s_sum[w][t] * __builtin_amdgcn_exp2f((s_val[w][t] - best) * inv_temp_log2);
-      part_sum[(long)(m0 + t) * n_vtiles + blockIdx.x] = sum;
+      part_sum[(long)(m0 + t) * n_vtiles + vt] = sum;
     }
   }
 }
@@ -307,25 +313,30 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   int32_t* part_idx = (int32_t*)((char*)ws + arr);
   float* part_sum = stats ? (float*)((char*)ws + 2 * arr) : nullptr;
   const float itl2 = inv_temp * 1.4426950408889634f;
-  const int nmt = M <= 16 ? 1 : M <= 32 ? 2 : M <= 64 ? 4 : 8;
-  const int waves = lm_head_waves(M);
-  const int n_vtiles = (V + waves * 16 - 1) / (waves * 16);
-  const dim3 grid(n_vtiles, (M + nmt * 16 - 1) / (nmt * 16));
-#define SPEC_LMH(NMT, WV, ST)                                                                                              \
-  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<NMT, WV, ST>), grid, dim3(WV * 64), 0, s, (const __hip_bfloat16*)hidden, \
-                     (const __hip_bfloat16*)weight, part_val, part_idx, part_sum, (__hip_bfloat16*)logits_out, itl2, M, K, \
-                     V, n_vtiles)
-#define SPEC_LMH_T(WV, ST)                  \
-  if (nmt == 1) SPEC_LMH(1, WV, ST);        \
-  else if (nmt == 2) SPEC_LMH(2, WV, ST);   \
-  else if (nmt == 4) SPEC_LMH(4, WV, ST);   \
-  else SPEC_LMH(8, WV, ST)
-  if (waves == 4) {
-    if (stats) { SPEC_LMH_T(4, true); } else { SPEC_LMH_T(4, false); }
-  } else {
-    if (stats) { SPEC_LMH_T(8, true); } else { SPEC_LMH_T(8, false); }
-  }
+  const int mt = M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
+  const int m_slices = (M + mt - 1) / mt;
+  // 128 vocabulary rows per workgroup, or 64 where those workgroups still fit the compute units (256) all at once: the
+  // stream of one workgroup is bound by its latency. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64, 28.8 / 45.2 with
+  // 128; 20000 x 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128.
+  const int vt = mt == 256 || (long)((V + 63) / 64) * m_slices > 256 ? 128 : SPEC_LM_HEAD_VOCAB_TILE;
+  const int n_vtiles = (V + vt - 1) / vt;
+  const int per_row = std::min(m_slices, 16);   // slices numbered eight apart within a grid row
+  const dim3 grid((unsigned)((n_vtiles + 7) / 8 * 8) * per_row, (m_slices + per_row - 1) / per_row);
+#define SPEC_LMH(VTT, MT, ST)                                                                                                 \
+  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, ST>), grid, dim3(lmh::NTHREADS), 0, s, (const __hip_bfloat16*)hidden, \
+                     (const __hip_bfloat16*)weight, part_val, part_idx, part_sum, (__hip_bfloat16*)logits_out, itl2, M, K, V,   \
+                     n_vtiles, per_row)
+#define SPEC_LMH_M(VTT, ST)                 \
+  if (mt == 32) SPEC_LMH(VTT, 32, ST);      \
+  else if (mt == 64) SPEC_LMH(VTT, 64, ST); \
+  else SPEC_LMH(VTT, 128, ST)
+#define SPEC_LMH_T(ST)                                \
+  if (mt == 256) SPEC_LMH(128, 256, ST);              \
+  else if (vt == 128) { SPEC_LMH_M(128, ST); }        \
+  else { SPEC_LMH_M(64, ST); }
+  if (stats) { SPEC_LMH_T(true); } else { SPEC_LMH_T(false); }
 #undef SPEC_LMH_T
+#undef SPEC_LMH_M
 #undef SPEC_LMH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -151,9 +151,6 @@ hipError_t launch_tree_merge(int B, int M, int Nin, const int32_t* in_parent, co
                              hipStream_t s);
 // LM head + arg-max (lm_head.hip). Workspace: per row one (max, arg-max) pair per vocabulary tile.
 #define SPEC_LM_HEAD_VOCAB_TILE 64   // the smaller of the two workgroup shapes: sizes the partials
-inline int lm_head_waves(int M) {
-  return M <= 32 ? 4 : 8;   // few rows: the stream is everything, and two workgroups per CU overlap their starts and ends
-}
 inline size_t lm_head_partials_bytes(int M, int V) {
   const size_t n_vtiles = ((size_t)V + SPEC_LM_HEAD_VOCAB_TILE - 1) / SPEC_LM_HEAD_VOCAB_TILE;
   return 2 * (((size_t)M * n_vtiles * 4 + 255) / 256 * 256);

@@ -1,0 +1,48 @@
+"""LM head at the edges of its tiles: rows of hidden around 32, 64, 128 and 256, vocabularies around 64 and 128 rows and where
+the tile changes, K of four stages (fewer than the ring holds) and of many, logits at an address that is only 8-byte aligned,
+equal rows of W in different workgroups. Bars: those of the other LM head tests (float32 accumulation, worst case)."""
+import numpy as np
+import pytest
+import torch
+
+from test_gpu_lm_head import DEV, _check_rows, _dev, _inputs, _stats_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,K,V", [(32, 256, 64), (33, 256, 65), (64, 512, 63), (65, 512, 128), (128, 256, 16384), (31, 512, 16385),
+                                   (255, 256, 1000), (256, 1024, 129), (257, 512, 513), (600, 256, 200)])
+def test_lm_head_tile_edges(spec, M, K, V):
+    h, w = _inputs(M, K, V, seed=M * 7 + V)
+    arg, mx = spec.spec_lm_head_argmax(_dev(h), _dev(w), want_max=True)
+    torch.cuda.synchronize()
+    _check_rows(arg.cpu().numpy(), mx.cpu().numpy().astype(np.float64), h, w)
+    _stats_case(spec, M, K, V, 0.9, seed=M * 7 + V)
+
+
+@pytest.mark.parametrize("M,V", [(12, 20000), (70, 20001), (130, 9000)])
+def test_equal_rows_of_the_weight_matrix_give_equal_logits(spec, M, V):
+    """The same row of W at places of different lanes, wavefronts and workgroups: bit-equal logits, so the lowest token
+    wins whatever its workgroup."""
+    h, w = _inputs(M, 1024, V, seed=V)
+    places = [V - 1, 5, 40, 70, 133, 5000, 5001]
+    w[places] = w[17] * 40      # the largest logit of about half of the rows
+    logits, arg, _, _ = spec.spec_lm_head_logits_stats(_dev(h), _dev(w))
+    arg2, mx = spec.spec_lm_head_argmax(_dev(h), _dev(w), want_max=True)
+    torch.cuda.synchronize()
+    got = logits.view(torch.int16)[:, places].cpu().numpy()
+    assert (got == got[:, :1]).all()
+    for a in (arg.cpu().numpy(), arg2.cpu().numpy()):
+        hit = np.isin(a, places)
+        assert hit.mean() > 0.1 and (a[hit] == 5).all()
+
+
+def test_logits_at_an_eight_byte_aligned_address(spec):
+    M, K, V = 40, 512, 1000
+    h, w = _inputs(M, K, V, seed=9)
+    want, arg, mx, se = spec.spec_lm_head_logits_stats(_dev(h), _dev(w))
+    buf = torch.empty(M * V + 4, dtype=torch.bfloat16, device=DEV)
+    out = (buf[4:].view(M, V), torch.empty_like(arg), torch.empty_like(mx), torch.empty_like(se))
+    spec.spec_lm_head_logits_stats(_dev(h), _dev(w), out=out)
+    torch.cuda.synchronize()
+    assert torch.equal(out[0], want) and torch.equal(out[1], arg) and torch.equal(out[3], se)

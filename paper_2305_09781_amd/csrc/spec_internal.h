@@ -24,10 +24,11 @@ struct AttnPlan {
   int heads_per_wg; // wide kernel, whole key ranges: consecutive K/V heads of a request served by one workgroup
   bool m32;         // 5..8 query tiles, D = 128: the kernel of tree_attention_bf16_wide32.hip (four wavefronts of 32
                     // queries, two workgroups per compute unit) instead of the wide kernel's eight wavefronts of 16
-  // Partials, slot by slot: a pair's slots are filled from 0, so the slots in use are one compact piece of the workspace
-  // whatever their number allows for (the balanced deal sizes it for one request holding all the tiles).
-  size_t ws_o_off;  // float [n_splits][B][H][N][D]   un-normalised partial outputs
-  size_t ws_ml_off; // float [n_splits][B][H][N][2]   running max (log2 domain) and partial sum
+  // Partials, addressed through partial_row(): [B][H][n_splits][N] rows under fixed chunks, [n_splits][B][H][N] under the
+  // balanced deal, which sizes n_splits for one request holding all the tiles: a pair's slots are filled from 0, so the
+  // slots in use are one compact piece of the workspace.
+  size_t ws_o_off;  // float [rows][D]   un-normalised partial outputs
+  size_t ws_ml_off; // float [rows][2]   running max (log2 domain) and partial sum
   size_t ws_bytes;
 };
 
@@ -168,6 +169,16 @@ hipError_t launch_node_sample(int B, int N, int V, int logits_dtype, const void*
 hipError_t launch_greedy_walk(int B, int N, const int32_t* node_argmax, const int32_t* token, const int32_t* parent,
                               int Lmax, int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status,
                               hipStream_t s);
+// Vocabularies whose distribution the stochastic walk keeps in its workgroup's registers: 32 floats per thread. With 64 the
+// kernel spills and the buffer form is the faster one (8 trees of 16, 50000 float32: 67 us against 59).
+inline bool stochastic_walk_in_registers(int V) { return V <= 32768; }
+// Whether the walk takes the statistics of the nodes it visits itself. That costs about 5 us per accepted node instead of 1.5;
+// a pass over all nodes costs its bytes at about 5.5 TB/s. From 100 MB of logits on (18 us) the pass costs more than the two to
+// four nodes that a walk accepts (16 trees of 128, 32000 float32: 106 us with the pass and the buffer form, 42 without); a
+// path of 16 accepted nodes breaks even at about 200 MB.
+inline bool stochastic_walk_takes_stats(int B, int N, int V, int logits_dtype) {
+  return stochastic_walk_in_registers(V) && (double)B * N * V * (logits_dtype == SPEC_BF16 ? 2 : 4) >= 100e6;
+}
 hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const void* logits, const float* probs_ssm,
                                   int R, const int32_t* ssm_row, const int32_t* token, const int32_t* parent,
                                   const float* u_accept, const float* u_order, const float* u_final, float inv_temp,
@@ -179,9 +190,17 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
 // ---------------------------------------------------------------------------------------------
 #ifdef __HIPCC__
 
+// Row of node 0 of a (request, head) pair's slot in the partials.
+template <bool BALANCED>
+__device__ __forceinline__ long partial_row(int b, int h, int slot, int B, int H, int N, int n_splits) {
+  return BALANCED ? (((long)slot * B + b) * H + h) * N : (((long)b * H + h) * n_splits + slot) * N;
+}
+
 // A workgroup-uniform value back in a scalar register. The compiler divides on the vector unit and leaves the quotient
 // there, and with it every address and loop bound derived from it: the balanced launches lost 8 to 15 us of 100 to that.
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
+// a / b of workgroup-uniform numbers; without the division, which stands before a kernel's first load, where b is 1
+__device__ __forceinline__ int uniform_div(int a, int b) { return b == 1 ? a : uniform(a / b); }
 
 // Validates one request's tree with the threads of a workgroup (blockDim.x >= N).
 // Returns true for every thread iff parent[0] == -1, 0 <= parent[i] < i and depth[i] == depth[parent[i]] + 1.

@@ -7,11 +7,12 @@
 //                          sequential tree walk that follows needs P(x) at a node in O(1).
 //   greedy_walk_kernel     one workgroup per request: follow children whose token equals the node's
 //                          argmax; emit the bonus token.
-//   stochastic_walk_kernel one workgroup per request: multi-step speculative sampling. The first ratio
-//                          test at a node uses the precomputed softmax statistics; only a rejection
-//                          materialises the residual distribution norm(max(0, P - Q)) (one pass over
-//                          the vocabulary per rejection, kept un-normalised with its mass Z). The last
-//                          token is drawn by inverse CDF with a float64 block scan in token-id order.
+//   stochastic_walk_kernel one workgroup per request: multi-step speculative sampling. A node's softmax statistics
+//                          are the precomputed ones or (many nodes) taken when the walk reaches it; only a rejection
+//                          needs the residual distribution norm(max(0, P - Q)) (one pass over the vocabulary per
+//                          rejection, kept un-normalised with its mass Z). The last token is drawn by inverse CDF with
+//                          a float64 block scan in token-id order. Two forms: the current distribution in the
+//                          workgroup's registers (vocabularies up to 32768), or in a buffer in memory.
 //   node_sample_kernel     naive sampling (the alternative of Section 4.3): one inverse-CDF draw per
 //                          (request, node) row; the greedy walk then runs on the sampled tokens.
 #include <hip/hip_bf16.h>
@@ -277,7 +278,338 @@ __global__ void __launch_bounds__(128) greedy_walk_kernel(int N, const int32_t* 
 }
 
 // ---------------------------------------------------------------------------------------------
-// stochastic walk: blockDim = 1024
+// stochastic walk with the current distribution in registers: blockDim = 1024, thread t holds the groups t, t + 1024, ...
+// of VEC elements (NG of them, so V <= 1024 NG VEC). A row is read once per visited node, a draft's distribution once per
+// rejection, nothing is written but the result; the buffer form below reads and writes the residual per rejection and
+// reads the row again for every rejection and for the final draw.
+//
+// node_max == nullptr: the softmax statistics of a node are taken here, from the row that is then in registers anyway if a
+// child is rejected or the last token is drawn. That costs an accepted first child one row (about 3 us) and saves the
+// statistics of the nodes that are not reached, which are most of them: see launch_stochastic_walk for where it pays.
+//
+// What bounds it: one compute unit per request: a row of 32000 float32 takes it about 2.5 us, and a step of the walk is one
+// or two of them in a chain. Measured on 16 requests, trees of 128, 32000 float32, three drafts: 37.5
+// us in all, against 106.7 for the pass over all nodes and the buffer form; 8 trees of 16: 27.1 against 45.8.
+// ---------------------------------------------------------------------------------------------
+
+// exp(x) for x <= 0: one v_exp_f32 with the rounding of x * log2(e) put back (relative error as expf's, results below
+// 2^-126 become 0).
+__device__ __forceinline__ float exp_of_nonpositive(float x) {
+  const float t = x * 1.4426950408889634f;
+  const float lost = fmaf(x, 1.4426950408889634f, -t) + x * 1.925963033500e-08f;   // log2(e) = 1.44269502162933 + 1.926e-8
+  const float e = __builtin_amdgcn_exp2f(t);
+  return t < -126.f ? e : fmaf(e, lost * 0.69314718f, e);   // (t = -inf: lost is NaN, e is 0)
+}
+// Sums and maxima over a wavefront in register moves (row shifts, then the last lane of a row into the rows after it).
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ float dpp_f32(float identity, float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(identity), __float_as_int(v), CTRL, ROW_MASK, 0xf, false));
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_f64(double v) {   // 0 where there is no source
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROW_MASK, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROW_MASK, 0xf, false);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+struct MaxOp {
+  static constexpr float identity = -INFINITY;
+  static __device__ __forceinline__ float f(float a, float b) { return fmaxf(a, b); }
+};
+struct SumOp {
+  static constexpr float identity = 0.f;
+  static __device__ __forceinline__ float f(float a, float b) { return a + b; }
+};
+// Over the block; every thread gets the result. `slot` points at 16 floats that no thread still reads from the call before
+// the last (two areas used in turn): one barrier.
+template <class Op>
+__device__ __forceinline__ float block_reduce(float v, float* slot) {
+  v = Op::f(v, dpp_f32<0x111, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x112, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x114, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x118, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x142, 0xa>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x143, 0xc>(Op::identity, v));
+  if ((threadIdx.x & 63) == 63) slot[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = slot[threadIdx.x & 15];
+  v = Op::f(v, dpp_f32<0x111, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x112, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x114, 0xf>(Op::identity, v));
+  v = Op::f(v, dpp_f32<0x118, 0xf>(Op::identity, v));
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
+}
+__device__ __forceinline__ double wave_inclusive_sum_f64(double v) {
+  v += dpp_f64<0x111, 0xf>(v);
+  v += dpp_f64<0x112, 0xf>(v);
+  v += dpp_f64<0x114, 0xf>(v);
+  v += dpp_f64<0x118, 0xf>(v);
+  v += dpp_f64<0x142, 0xa>(v);
+  v += dpp_f64<0x143, 0xc>(v);
+  return v;
+}
+__device__ __forceinline__ double readlane_f64(double v, int lane) {
+  const long long b = __double_as_longlong(v);
+  return __longlong_as_double(((long long)__builtin_amdgcn_readlane((int)(b >> 32), lane) << 32) |
+                              (unsigned)__builtin_amdgcn_readlane((int)b, lane));
+}
+
+template <bool BF16, int VEC, int NG>
+__global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
+    int N, int V, const void* __restrict__ logits, const float* __restrict__ probs_ssm, int R,
+    const int32_t* __restrict__ ssm_row, const int32_t* __restrict__ token, const int32_t* __restrict__ parent,
+    const float* __restrict__ u_accept, const float* __restrict__ u_order, const float* __restrict__ u_final,
+    float inv_temp, const float* __restrict__ node_max, const float* __restrict__ node_sumexp, int Lmax,
+    int32_t* __restrict__ path, int32_t* __restrict__ len, int32_t* __restrict__ out_tokens, int32_t* status) {
+  constexpr int WAVES = SW_THREADS / 64, NTOT = NG * WAVES < 64 ? 64 : NG * WAVES;   // final scan: (group round, wavefront)
+  static_assert(NTOT % 64 == 0, "whole rounds of lanes");
+  __shared__ int s_flag, s_nchild, s_ans;
+  __shared__ int s_child[SPEC_MAX_TREE_NODES], s_sorted[SPEC_MAX_TREE_NODES];
+  __shared__ int s_par[SPEC_MAX_TREE_NODES], s_tok[SPEC_MAX_TREE_NODES], s_row[SPEC_MAX_TREE_NODES];
+  __shared__ float s_ord[SPEC_MAX_TREE_NODES], s_acc[SPEC_MAX_TREE_NODES];
+  __shared__ float s_cq[SPEC_MAX_TREE_NODES], s_cp[SPEC_MAX_TREE_NODES];   // per child in test order: Q(x), un-normalised P(x)
+  __shared__ float s_red[2][WAVES];
+  __shared__ double s_tot[NTOT];
+
+  const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n_groups = V / VEC;
+  const bool lazy = node_max == nullptr;
+
+  float w[NG][VEC];   // current distribution, un-normalised: P(i) = w_i / Z
+  // Rows are addressed as a wave-uniform base per round plus one offset per lane (an address per load would not leave
+  // room for the row in registers); u and rows of probs_ssm are made uniform for that.
+  auto load_row = [&](int u) {   // the logits of node u; elements past the end are -inf
+    const long base = ((long)b * N + u) * V;
+#pragma unroll
+    for (int j = 0; j < NG; ++j) {
+      const int gi = j * SW_THREADS + t;
+      if (gi < n_groups) {
+        const void* round = BF16 ? (const void*)((const __hip_bfloat16*)logits + base + j * SW_THREADS * VEC)
+                                 : (const void*)((const float*)logits + base + j * SW_THREADS * VEC);
+        load_logit_group<VEC, BF16>(round, (unsigned)(t * VEC), w[j]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) w[j][e] = -INFINITY;
+      }
+    }
+  };
+  auto exponentiate = [&](float mx) {
+    float sum = 0.f;
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        w[j][e] = exp_of_nonpositive((w[j][e] - mx) * inv_temp);
+        sum += w[j][e];
+      }
+    return sum;
+  };
+
+  if (lazy) load_row(0);
+  if (t < N) {
+    s_par[t] = parent[(long)b * N + t];
+    s_tok[t] = token[(long)b * N + t];
+    s_row[t] = ssm_row[(long)b * N + t];
+    s_ord[t] = u_order[(long)b * N + t];
+    s_acc[t] = u_accept[(long)b * N + t];
+  }
+  if (t == 0) s_flag = 0;
+  __syncthreads();
+  if (t < N) {
+    const int p = s_par[t], x = s_tok[t], rr = s_row[t];
+    bool ok = t == 0 ? p == -1 : (p >= 0 && p < t);
+    if (t >= 1 && x >= 0 && (x >= V || rr < 0 || rr >= R)) ok = false;   // a negative token: a padding node, never a candidate
+    if (!ok) atomicOr(&s_flag, 1);
+  }
+  for (int k = t; k < Lmax; k += SW_THREADS) {
+    path[(long)b * Lmax + k] = -1;
+    out_tokens[(long)b * Lmax + k] = -1;
+  }
+  __syncthreads();
+  if (s_flag != 0) {
+    if (t == 0) { len[b] = 0; set_status(status, b, SPEC_ST_BAD_TREE); }
+    return;
+  }
+  if (t == 0) path[(long)b * Lmax] = 0;
+
+  int u = 0, k = 0, red = 0;
+  bool have_row = lazy;   // w holds node u's logits (before the statistics) or its distribution
+  float Z, mx;
+  while (true) {
+    // children of u in ascending (u_order, index)
+    if (t == 0) s_nchild = 0;
+    __syncthreads();
+    if (t < N && s_par[t] == u && s_tok[t] >= 0) s_child[atomicAdd(&s_nchild, 1)] = t;
+    __syncthreads();
+    const int nchild = (k + 1 < Lmax) ? s_nchild : 0;
+    if (t < nchild) {
+      const int me = s_child[t];
+      const float mk = s_ord[me];
+      int rank = 0;
+      for (int j = 0; j < nchild; ++j) {
+        const int o = s_child[j];
+        const float ok = s_ord[o];
+        rank += (ok < mk) || (ok == mk && o < me);
+      }
+      s_sorted[rank] = me;
+    }
+    __syncthreads();
+    // everything the ratio tests need from memory, for all children at once; thread j follows child j's P(x)
+    int my_x = 0;
+    float cl = 0.f, cw = 0.f;
+    if (t < nchild) {
+      const int c = s_sorted[t];
+      my_x = s_tok[c];
+      s_cq[t] = probs_ssm[(long)s_row[c] * V + my_x];
+      cl = load_logit<BF16>(logits, ((long)b * N + u) * V + my_x);
+    }
+    if (lazy) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < NG; ++j)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) m = fmaxf(m, w[j][e]);
+      mx = block_reduce<MaxOp>(m, s_red[red ^= 1]);
+      const float sum = exponentiate(mx);
+      Z = block_reduce<SumOp>(sum, s_red[red ^= 1]);
+      if (mx == -INFINITY) Z = 0.f;
+    } else {
+      mx = node_max[(long)b * N + u];
+      Z = node_sumexp[(long)b * N + u];
+    }
+    if (t < nchild) {
+      cw = exp_of_nonpositive((cl - mx) * inv_temp);
+      s_cp[t] = cw;
+    }
+    __syncthreads();
+    bool accepted = false;
+    for (int j = 0; j < nchild; ++j) {
+      const int c = s_sorted[j];
+      if (s_acc[c] * s_cq[j] <= s_cp[j] / Z) {
+        accepted = true;
+        if (t == 0) {
+          out_tokens[(long)b * Lmax + k] = s_tok[c];
+          path[(long)b * Lmax + k + 1] = c;
+        }
+        u = uniform(c);
+        break;
+      }
+      // rejected: P := norm(max(0, P - Q)), kept as un-normalised values plus their sum Z
+      const float* Q = probs_ssm + (long)uniform(s_row[c]) * V;
+      float my_q = t < nchild ? Q[my_x] : 0.f;
+      if (!have_row) {
+        load_row(u);
+        have_row = true;
+        (void)exponentiate(mx);
+      }
+      const float invZ = 1.f / Z;
+      float part = 0.f;
+      float q[NG][VEC];
+#pragma unroll
+      for (int jj = 0; jj < NG; ++jj) {
+        const int gi = jj * SW_THREADS + t;
+        if (gi < n_groups) {
+          load_f32_group<VEC>(Q + jj * SW_THREADS * VEC + (unsigned)(t * VEC), q[jj]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) q[jj][e] = 0.f;
+        }
+      }
+#pragma unroll
+      for (int jj = 0; jj < NG; ++jj)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) part += fmaxf(0.f, fmaf(w[jj][e], invZ, -q[jj][e]));
+      const float Znew = block_reduce<SumOp>(part, s_red[red ^= 1]);
+      if (Znew > 0.f) {
+#pragma unroll
+        for (int jj = 0; jj < NG; ++jj)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) w[jj][e] = fmaxf(0.f, fmaf(w[jj][e], invZ, -q[jj][e]));
+        Z = Znew;
+        cw = fmaxf(0.f, fmaf(cw, invZ, -my_q));
+        if (t < nchild) s_cp[t] = cw;
+      } else if (t == 0) {   // an empty residual keeps the previous P
+        set_status(status, b, SPEC_ST_ZERO_RESIDUAL);
+      }
+      __syncthreads();   // the children's new P(x) are visible before the next test reads them
+    }
+    if (!accepted) break;
+    ++k;
+    have_row = lazy;
+    if (lazy) load_row(u);
+    __syncthreads();   // everybody has read this node's children before the next node's are listed
+  }
+
+  // ---- final token: inverse CDF in ascending token id over the current P. Order of the elements: group round, thread,
+  // element. Float64: inclusive sums over the lanes per round, then over the (round, wavefront) totals.
+  if (!have_row) {
+    load_row(u);
+    (void)exponentiate(mx);
+  }
+  auto group_sum = [&](int j) {
+    double sum = 0.0;
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) sum += (double)w[j][e];
+    return sum;
+  };
+#pragma unroll
+  for (int j = 0; j < NG; ++j) {
+    const double incl = wave_inclusive_sum_f64(group_sum(j));
+    if (lane == 63) s_tot[j * WAVES + wave] = incl;
+  }
+  if (t >= NG * WAVES && t < NTOT) s_tot[t] = 0.0;
+  if (t == 0) s_ans = V - 1;
+  __syncthreads();
+  constexpr int EPL = NTOT / 64;   // totals per lane
+  double mine = 0.0;
+#pragma unroll
+  for (int i = 0; i < EPL; ++i) mine += s_tot[lane * EPL + i];
+  const double upto = wave_inclusive_sum_f64(mine);
+  const double target = (double)u_final[b] * readlane_f64(upto, 63);
+  const unsigned long long past = __ballot(upto > target);
+  if (past != 0) {   // the first lane whose totals reach past the target, then the first of its totals
+    const int f = __ffsll((long long)past) - 1;
+    double before = f == 0 ? 0.0 : readlane_f64(upto, f - 1);
+    int entry = f * EPL;
+#pragma unroll
+    for (int i = 0; i < EPL - 1; ++i) {
+      const double next = before + s_tot[f * EPL + i];
+      if (entry == f * EPL + i && next <= target) { before = next; ++entry; }
+    }
+    if (entry % WAVES == wave) {
+      const int jr = entry / WAVES;
+#pragma unroll
+      for (int j = 0; j < NG; ++j) {
+        if (j == jr) {
+          const double sum = group_sum(j), incl = wave_inclusive_sum_f64(sum);
+          const unsigned long long hit = __ballot(before + incl > target);
+          const int fl = hit != 0 ? __ffsll((long long)hit) - 1 : 63;
+          if (lane == fl) {
+            const double run = before + incl - sum;
+            int ans = (j * SW_THREADS + t) * VEC + VEC - 1;
+#pragma unroll
+            for (int e = VEC - 1; e >= 0; --e) {   // the first element whose running sum exceeds the target
+              double upto_e = run;
+#pragma unroll
+              for (int i = 0; i <= e; ++i) upto_e += (double)w[j][i];
+              if (upto_e > target) ans = (j * SW_THREADS + t) * VEC + e;
+            }
+            s_ans = min(ans, V - 1);
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  if (t == 0) {
+    out_tokens[(long)b * Lmax + k] = s_ans;
+    len[b] = k + 1;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// stochastic walk with the residual in a buffer (vocabularies that do not fit the registers): blockDim = 1024
 // ---------------------------------------------------------------------------------------------
 
 template <bool BF16, int VEC>
@@ -512,6 +844,22 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
                                   const float* node_max, const float* node_sumexp, float* resid, int Lmax,
                                   int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s) {
   const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
+  if (stochastic_walk_in_registers(V)) {
+#define SPEC_SWR(BF, VE, NGR)                                                                                         \
+  hipLaunchKernelGGL((stochastic_walk_reg_kernel<BF, VE, NGR>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, \
+                     R, ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, Lmax, path,  \
+                     len, out_tokens, status)
+#define SPEC_SWR_T(BF)                                          \
+  if (!vec && V <= SW_THREADS * 8) SPEC_SWR(BF, 1, 8);          \
+  else if (!vec) SPEC_SWR(BF, 1, 32);                           \
+  else if (V <= SW_THREADS * 4) SPEC_SWR(BF, 4, 1);             \
+  else if (V <= SW_THREADS * 16) SPEC_SWR(BF, 4, 4);            \
+  else SPEC_SWR(BF, 4, 8)
+    if (bf16) { SPEC_SWR_T(true); } else { SPEC_SWR_T(false); }
+#undef SPEC_SWR_T
+#undef SPEC_SWR
+    return hipGetLastError();
+  }
 #define SPEC_SW(BF, VE)                                                                                              \
   hipLaunchKernelGGL((stochastic_walk_kernel<BF, VE>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, R,    \
                      ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, resid, Lmax, \

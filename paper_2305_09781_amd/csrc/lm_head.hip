@@ -313,12 +313,22 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   int32_t* part_idx = (int32_t*)((char*)ws + arr);
   float* part_sum = stats ? (float*)((char*)ws + 2 * arr) : nullptr;
   const float itl2 = inv_temp * 1.4426950408889634f;
-  const int mt = M <= 32 ? 32 : M <= 64 ? 64 : M <= 128 ? 128 : 256;
+  // Tile of the vocabulary and of `hidden`: the least of rounds of workgroups (256 at a time, one per compute unit) times
+  // (start and end of a workgroup + stages times the microseconds a stage takes it), with the stage times as measured on
+  // 32000 and 8000 x 4096. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64 vocabulary rows, 28.8 / 45.2 with 128; 20000 x
+  // 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128; 11198 x 2560, 227 rows: 57.3 with 256 rows of `hidden`, 38.3 with 128.
+  int mt = 0, vt = 0;
+  float least = 0.f;
+  const int first_mt = M <= 32 ? 32 : M <= 64 ? 64 : 128;
+  auto consider = [&](int v, int m, float stage_us) {
+    const long wgs = (long)((V + v - 1) / v) * ((M + m - 1) / m);
+    const float us = (float)((wgs + 255) / 256) * (3.f + (float)(K / lmh::KC) * stage_us);
+    if (mt == 0 || us < least) { least = us; mt = m; vt = v; }
+  };
+  consider(128, first_mt, first_mt == 128 ? 0.73f : 0.63f);
+  consider(64, first_mt, first_mt == 128 ? 0.42f : 0.3f);
+  if (M > 128) consider(128, 256, 1.15f);
   const int m_slices = (M + mt - 1) / mt;
-  // 128 vocabulary rows per workgroup, or 64 where those workgroups still fit the compute units (256) all at once: the
-  // stream of one workgroup is bound by its latency. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64, 28.8 / 45.2 with
-  // 128; 20000 x 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128.
-  const int vt = mt == 256 || (long)((V + 63) / 64) * m_slices > 256 ? 128 : SPEC_LM_HEAD_VOCAB_TILE;
   const int n_vtiles = (V + vt - 1) / vt;
   const int per_row = std::min(m_slices, 16);   // slices numbered eight apart within a grid row
   const dim3 grid((unsigned)((n_vtiles + 7) / 8 * 8) * per_row, (m_slices + per_row - 1) / per_row);

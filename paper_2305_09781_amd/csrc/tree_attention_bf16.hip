@@ -569,10 +569,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   if constexpr (!BAL) {
     // grid = (n_splits, H * n_qgroups, B): one fixed-size chunk of one (request, head, query group)
     const int split = blockIdx.x;
-    const int h = uniform(blockIdx.y / n_qgroups), qg = blockIdx.y - h * n_qgroups;
+    const int h = uniform_div(blockIdx.y, n_qgroups), qg = blockIdx.y - h * n_qgroups;
     const int b = blockIdx.z;
     segment(b, h, qg, split * chunk_keys, split * chunk_keys + chunk_keys,
-            n_splits == 1 ? -1l : (((long)split * B + b) * H + h) * N);
+            n_splits == 1 ? -1l : partial_row<false>(b, h, split, B, H, N, n_splits));
   } else {
     // Balanced stream: the 32-key tiles of every pair in equal chunks, as many as the request's length asks for.
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H, S_cap, TILE, chunk_keys);
@@ -580,7 +580,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const DealChunk c = deal_find(prefix_len, B, N, H, 1, S_cap, TILE, deal, blockIdx.x);
     if (c.n_tiles > 0)
       segment(c.b, c.h, 0, c.tile0 * TILE, (c.tile0 + c.n_tiles) * TILE,
-              c.chunks == 1 ? -1l : (((long)c.chunk * B + c.b) * H + c.h) * N);
+              c.chunks == 1 ? -1l : partial_row<true>(c.b, c.h, c.chunk, B, H, N, n_splits));
   }
 }
 

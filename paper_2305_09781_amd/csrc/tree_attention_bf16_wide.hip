@@ -144,7 +144,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
   // store, not a prologue.
   auto segment = [&](const int b, const int hv, const int c0, const int c1_cap, const int slot, const int nh) {
     const bool final_out = slot < 0;
-    const int h = uniform(hv / n_qg), qg = hv - h * n_qg;
+    const int h = uniform_div(hv, n_qg), qg = hv - h * n_qg;
 
     // ---- straight-line prologue: first two tiles (they do not depend on prefix_len), Q, one tree node per thread
     const int P = prefix_len[b];
@@ -597,7 +597,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       const int n = tile_node[nt], head = h * group + tile_head[nt];
       if (kpart == 0 && tile_live[nt] && n < N) {
         if (!final_out) {
-          const long base = (((long)slot * B + b) * H + head) * N + n;
+          const long base = partial_row<PLAN != PLAN_GRID>(b, head, slot, B, H, N, n_splits) + n;
 #pragma unroll
           for (int db = 0; db < DB; ++db) *(f32x4*)(ws_o + base * D + db * 16 + 4 * g) = O[nt][db];
           if (g == 0) {

@@ -137,7 +137,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
   // qg. The result is the final output (slot < 0) or float32 partials in slot `slot` of every query head served.
   auto segment = [&](const int b, const int hv, const int c0, const int c1_cap, const int slot) {
     const bool final_out = slot < 0;
-    const int h = uniform(hv / n_qg), qg = hv - h * n_qg;
+    const int h = uniform_div(hv, n_qg), qg = hv - h * n_qg;
     const int P = prefix_len[b];
     const unsigned char* kc = (const unsigned char*)(k_cache + (PAGED ? 0 : b * kv_sb) + h * kv_sh);
     const unsigned char* vc = (const unsigned char*)(v_cache + (PAGED ? 0 : b * kv_sb) + h * kv_sh);
@@ -502,7 +502,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
       }
     } else if (live && node < N) {
       {
-        const long base = (((long)slot * B + b) * H + q_head) * N + node;
+        const long base = partial_row<PLAN != PLAN_GRID>(b, q_head, slot, B, H, N, n_splits) + node;
 #pragma unroll
         for (int db = 0; db < DB32; ++db)
 #pragma unroll

@@ -64,9 +64,9 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   const int qg = in_blk / 8;
   const int pc = blk * 8 + in_blk % 8;
   if (pc >= B * H_kv * n_splits) return;
-  const int pair = uniform(pc / n_splits), split = pc - pair * n_splits;
-  const int b = uniform(pair / H_kv), hk = pair - b * H_kv;
-  const int group = uniform(H / H_kv), M = group * N;   // queries that share this K/V head
+  const int pair = uniform_div(pc, n_splits), split = pc - pair * n_splits;
+  const int b = uniform_div(pair, H_kv), hk = pair - b * H_kv;
+  const int group = uniform_div(H, H_kv), M = group * N;   // queries that share this K/V head
   const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
@@ -318,7 +318,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
       *(float4*)(out + query_off(qi) + c) = o;
     } else {
-      const long slot = (((long)split * B + b) * H + hk * group + qi / N) * N + qi % N;
+      const long slot = partial_row<false>(b, hk * group + qi / N, split, B, H, N, n_splits) + qi % N;
       *(float4*)(ws_o + slot * D + c) = o;
       if (c == 0) {
         ws_ml[slot * 2 + 0] = m_all;
@@ -336,7 +336,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 // three slots each, 45 MB: 60 us before, when prefix_len[] was walked by scalar
 // loads and the slots of a pair lay next to each other over a gigabyte of mostly empty workspace; 17 us now; four pieces
 // per thread instead of one changes nothing).
-template <bool BF16>
+template <bool BF16, bool BAL, int CH>   // CH: partial slots fetched together
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
                                                            const int32_t* __restrict__ parent,
                                                            const int32_t* __restrict__ depth,
@@ -344,24 +344,25 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
                                                            int32_t* status, int B, int N, int H, int H_kv, int n_qg,
                                                            int D, int S_cap, int chunk_keys, int slots,
                                                            int bal_wgs, int bal_tile, long q_sb, long q_sn, long q_sh) {
-  constexpr int CH = 4;   // partial slots fetched together
   __shared__ int s_flag;
   const int h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
   const int CG = D / 4;
   const int idx = blockIdx.z * 256 + t;
   const bool active = idx < N * CG;
   const int n = active ? idx / CG : 0, cg = active ? idx % CG : 0;
-  const long base = ((long)b * H + h) * N + n, slot_rows = (long)B * H * N;
+  const long base = partial_row<BAL>(b, h, 0, B, H, N, slots) + n, slot_rows = BAL ? (long)B * H * N : N;
   // The first slots are fetched before anything is known about the request (every slot exists in the
-  // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: those that are
-  // filled for a request near the stated maximum, two of a balanced deal.
+  // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: of fixed chunks
+  // up to eight, which a request near the stated maximum has filled (1 request of 8000 keys on 8 K/V heads, 31 slots: 23.3 -> 21.9 us
+  // with attention; no difference at eight slots or fewer),
+  // of a balanced deal two.
   float m_s[CH], l_s[CH];
   float4 o_s[CH];
   auto fetch = [&](int s0, int from, int to) {
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      if (j >= from && j < to && s0 + j < slots) {
-        const long row = base + (s0 + j) * slot_rows;
+      if (!BAL || (j >= from && j < to && s0 + j < slots)) {
+        const long row = base + min(s0 + j, slots - 1) * slot_rows;
         const float2 ml = *(const float2*)(ws_ml + row * 2);
         m_s[j] = ml.x;
         l_s[j] = ml.y;
@@ -369,7 +370,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
       }
     }
   };
-  const int early = bal_wgs > 0 ? 2 : CH;
+  const int early = BAL ? 2 : CH;
   fetch(0, 0, early);
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
@@ -377,7 +378,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   if (!valid && h == 0 && blockIdx.z == 0 && t == 0) set_status(status, b, cap_ok ? SPEC_ST_BAD_TREE : SPEC_ST_CAPACITY);
   int ns = 0;
   if (valid) {
-    if (bal_wgs > 0) {
+    if (BAL) {
       // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group
       const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
       const int tb = request_tiles(P, N, S_cap, bal_tile);
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   float M = -INFINITY, l = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int s0 = 0; s0 < ns || s0 == 0; s0 += CH) {
-    fetch(s0, s0 == 0 ? early : 0, ns - s0);
+    if (BAL || s0 > 0) fetch(s0, s0 == 0 ? early : 0, ns - s0);
     float Mc = M;
 #pragma unroll
     for (int j = 0; j < CH; ++j)
@@ -465,15 +466,17 @@ hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, 
   const QueryGroups qg = attn_query_groups(d);
   const int n_qg = d.dtype == SPEC_BF16 ? qg.n_qgroups : 1;
   dim3 grid(d.H, d.B, (items + 255) / 256);
-  if (d.dtype == SPEC_BF16) {
-    hipLaunchKernelGGL(attn_combine_kernel<true>, grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,
-                       status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
-                       (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h);
-  } else {
-    hipLaunchKernelGGL(attn_combine_kernel<false>, grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,
-                       status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs, plan.balanced_tile,
-                       (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h);
-  }
+#define SPEC_COMBINE(BF, BL, CH)                                                                                            \
+  hipLaunchKernelGGL((attn_combine_kernel<BF, BL, CH>), grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,   \
+                     status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs,    \
+                     plan.balanced_tile, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h)
+  const bool many = plan.n_splits > 4;
+  if (plan.balanced_wgs > 0) { SPEC_COMBINE(true, true, 4); }   // (bf16 only)
+  else if (d.dtype == SPEC_BF16 && many) { SPEC_COMBINE(true, false, 8); }
+  else if (d.dtype == SPEC_BF16) { SPEC_COMBINE(true, false, 4); }
+  else if (many) { SPEC_COMBINE(false, false, 8); }
+  else { SPEC_COMBINE(false, false, 4); }
+#undef SPEC_COMBINE
   return hipGetLastError();
 }
 

@@ -97,6 +97,7 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
   AttnPlan p;
   p.balanced_wgs = 0;
   p.balanced_tile = 0;
+  p.contiguous = false;
   p.heads_per_wg = 1;
   p.m32 = false;
   const int max_prefix = d.max_prefix_len > 0 ? d.max_prefix_len : d.S_cap - d.N;
@@ -140,10 +141,20 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       cand = std::min<long>(cand, (long)(0.25 * stream_bytes / partial_bytes_per_wg));
       // every workgroup reads prefix_len[0..B) first, a wavefront's worth at a time
       wgs = (cand > groups && d.B > 1 && d.B <= 64) ? (int)cand : 0;
+      // Chunks are whole fractions of a pair: with fewer than two per pair on average most pairs stay whole beside a few
+      // halved ones. Twice as many then, in two rounds, on the kernels that run two workgroups per compute unit (9 requests
+      // x 40 heads of 4100 keys, trees of 20: 149 -> 142 us), as long as the partials still fit the library's own scratch
+      // array; the few-query kernel takes contiguous shares instead (see contiguous_deal).
+      const long twice = std::min<long>(2 * resident, (long)(0.25 * stream_bytes / partial_bytes_per_wg));
+      const double slots = (double)((twice + virtual_heads - 1) / virtual_heads + 1);
+      if (p.wide && wgs > 0 && wgs < 2 * groups && twice > wgs &&
+          (double)d.B * d.H * slots * d.N * (d.D + 2) * 4.0 + 512.0 <= (double)SPEC_STATIC_SCRATCH_BYTES)
+        wgs = (int)twice;
     }
     if (wgs > 0) {
       p.balanced_wgs = wgs;
       p.balanced_tile = tile;
+      p.contiguous = !p.wide && wgs < 2 * groups;
       p.chunk_keys = wgs;
       p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair has at most this many chunks
     }

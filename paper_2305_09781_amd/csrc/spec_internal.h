@@ -20,6 +20,7 @@ struct AttnPlan {
   int n_splits;     // chunks covering max_prefix_len + N; balanced plan: partial slots per (request, head)
   int balanced_wgs; // > 0: balanced plan that aims at this many chunks (see balanced_deal), chunk_keys holds it too
   int balanced_tile;// keys per tile of the balanced deal (the tile of the kernel that runs the plan)
+  bool contiguous;  // balanced plan as equal contiguous shares of all tiles (see contiguous_deal), few-query kernel only
   bool wide;        // bf16: the wide kernel runs the plan (several query tiles per K/V head, or k_new not laid out like q)
   int heads_per_wg; // wide kernel, whole key ranges: consecutive K/V heads of a request served by one workgroup
   bool m32;         // 5..8 query tiles, D = 128: the kernel of tree_attention_bf16_wide32.hip (four wavefronts of 32
@@ -330,6 +331,54 @@ __device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, in
     acc += __builtin_amdgcn_readlane(incl, 63);
   }
   return c;
+}
+
+// Contiguous form of the balanced plan: the key tiles of all pairs, ordered by (request, head, key), are dealt to n_wg
+// workgroups in equal contiguous shares; a share that crosses from one pair into the next is two segments in a row. For the
+// few-query kernel, which runs one workgroup per compute unit, where there are fewer than two chunks per pair: whole
+// fractions of a pair would leave compute units idle (6 requests x 32 heads x 64 of 4500 keys, 192 pairs on 256 compute
+// units: 45.6 us, 51.3 in halves). `before`: tiles per head of the requests below b_before.
+struct ContiguousDeal {
+  long total;   // tiles over all requests and heads
+  long share;   // tiles per workgroup (>= 1)
+};
+__device__ inline ContiguousDeal contiguous_deal(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap,
+                                                 int tile, int n_wg, int b_before = 0, long* before = nullptr) {
+  const int lane = threadIdx.x & 63;
+  long tiles = 0, low = 0;
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+    tiles += wave_sum_uniform(v);
+    if (before != nullptr) low += wave_sum_uniform(b0 + lane < b_before ? v : 0);
+  }
+  if (before != nullptr) *before = low;
+  ContiguousDeal r;
+  r.total = tiles * H;
+  r.share = max(1l, deal_div(r.total + n_wg - 1, n_wg));
+  return r;
+}
+// The request that holds tile `pos` (< total) of the contiguous deal: its index, first tile and tiles per head.
+struct DealRequest {
+  int b;
+  long start;
+  int tiles;
+};
+__device__ inline DealRequest contiguous_find(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap, int tile,
+                                              long pos) {
+  const int lane = threadIdx.x & 63;
+  long acc = 0;   // tiles per head over the requests below b0
+  for (int b0 = 0; b0 < B; b0 += 64) {
+    const int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
+    const int incl = wave_inclusive_sum(v);
+    const unsigned long long hit = __ballot((acc + incl) * H > pos);
+    if (hit != 0) {
+      const int f = __ffsll((long long)hit) - 1;
+      const int tb = __builtin_amdgcn_readlane(v, f);
+      return {b0 + f, (acc + __builtin_amdgcn_readlane(incl, f) - tb) * H, tb};
+    }
+    acc += __builtin_amdgcn_readlane(incl, 63);
+  }
+  return {0, 0, 1};   // not reached for pos < total
 }
 
 // Rotation of the two 16-byte pieces of a row that pair up under the half-split rotary embedding (piece `lo`

@@ -343,7 +343,8 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
                                                            const int32_t* __restrict__ prefix_len, void* __restrict__ out,
                                                            int32_t* status, int B, int N, int H, int H_kv, int n_qg,
                                                            int D, int S_cap, int chunk_keys, int slots,
-                                                           int bal_wgs, int bal_tile, long q_sb, long q_sn, long q_sh) {
+                                                           int bal_wgs, int bal_tile, bool contiguous, long q_sb,
+                                                           long q_sn, long q_sh) {
   __shared__ int s_flag;
   const int h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
   const int CG = D / 4;
@@ -353,9 +354,8 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   const long base = partial_row<BAL>(b, h, 0, B, H, N, slots) + n, slot_rows = BAL ? (long)B * H * N : N;
   // The first slots are fetched before anything is known about the request (every slot exists in the
   // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: of fixed chunks
-  // up to eight, which a request near the stated maximum has filled (1 request of 8000 keys on 8 K/V heads, 31 slots: 23.3 -> 21.9 us
-  // with attention; no difference at eight slots or fewer),
-  // of a balanced deal two.
+  // up to eight, which a request near the stated maximum has filled (1 request of 8000 keys on 8 K/V heads, 31 slots: 23.3
+  // -> 21.9 us with attention; no difference at eight slots or fewer), of a balanced deal two.
   float m_s[CH], l_s[CH];
   float4 o_s[CH];
   auto fetch = [&](int s0, int from, int to) {
@@ -380,11 +380,18 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   if (valid) {
     if (BAL) {
       // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group
-      const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
       const int tb = request_tiles(P, N, S_cap, bal_tile);
-      const int chunks = deal_chunks(tb, deal.share);
-      if (chunks == 1) return;   // the attention kernel wrote the final output
-      ns = uniform(deal_chunks(tb, deal_chunk_tiles(tb, chunks)));
+      if (contiguous) {   // few-query kernel: one query head per pair
+        long before;
+        const ContiguousDeal deal = contiguous_deal(prefix_len, B, N, H, S_cap, bal_tile, bal_wgs, b, &before);
+        const long pair_start = before * H + (long)h * tb;
+        ns = uniform((int)(deal_div(pair_start + tb - 1, deal.share) - deal_div(pair_start, deal.share)) + 1);
+      } else {
+        const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
+        const int chunks = deal_chunks(tb, deal.share);
+        if (chunks == 1) return;   // the attention kernel wrote the final output
+        ns = uniform(deal_chunks(tb, deal_chunk_tiles(tb, chunks)));
+      }
     } else {
       ns = uniform(min(slots, (P + N + chunk_keys - 1) / chunk_keys));
     }
@@ -469,7 +476,7 @@ hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, 
 #define SPEC_COMBINE(BF, BL, CH)                                                                                            \
   hipLaunchKernelGGL((attn_combine_kernel<BF, BL, CH>), grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,   \
                      status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs,    \
-                     plan.balanced_tile, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h)
+                     plan.balanced_tile, plan.contiguous, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h)
   const bool many = plan.n_splits > 4;
   if (plan.balanced_wgs > 0) { SPEC_COMBINE(true, true, 4); }   // (bf16 only)
   else if (d.dtype == SPEC_BF16 && many) { SPEC_COMBINE(true, false, 8); }

@@ -628,14 +628,16 @@ int spec_verify_stochastic(int32_t B, int32_t N, int32_t V, int32_t logits_dtype
   float* resid = (float*)((char*)workspace + round_up((size_t)B * N * 2 * sizeof(float), 256));
   const float inv_temp = 1.0f / temperature;
   hipStream_t s = (hipStream_t)hip_stream;
-  if (stochastic_walk_takes_stats(B, N, V, logits_dtype)) {
+  const int own_levels = stochastic_own_levels(B, N, V, logits_dtype, Lmax);
+  if (own_levels >= std::min(Lmax, N)) {   // no walk visits more nodes, whatever the tree
     node_max = node_sumexp = nullptr;
-  } else if (launch_node_stats(B, N, V, logits_dtype, logits_llm, inv_temp, nullptr, node_max, node_sumexp, s) != hipSuccess) {
+  } else if (launch_node_stats(B, N, V, logits_dtype, logits_llm, inv_temp, nullptr, node_max, node_sumexp, s,
+                               own_levels > 0 ? tree_parent : nullptr, own_levels) != hipSuccess) {
     return SPEC_ERR_HIP;
   }
   if (launch_stochastic_walk(B, N, V, logits_dtype, logits_llm, probs_ssm, R, ssm_row, tree_token, tree_parent, u_accept,
                              u_order, u_final, inv_temp, node_max, node_sumexp, resid, Lmax, accepted_path, accepted_len,
-                             out_tokens, status, s) != hipSuccess)
+                             out_tokens, status, s, own_levels) != hipSuccess)
     return SPEC_ERR_HIP;
   return SPEC_OK;
 }

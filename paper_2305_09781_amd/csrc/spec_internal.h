@@ -7,6 +7,8 @@
 #endif
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "spec_tree.h"
 
 namespace spec {
@@ -164,7 +166,8 @@ hipError_t launch_lm_head_argmax(int M, int K, int V, const void* hidden, const 
 hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* weight, void* logits_out, float inv_temp,
                           int32_t* node_argmax, float* node_max, float* node_sumexp, void* ws, hipStream_t s);
 hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
-                             int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s);
+                             int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s,
+                             const int32_t* parent = nullptr, int own_levels = 0);
 hipError_t launch_node_sample(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
                               const float* node_max, const float* u_sample, int32_t* node_sample, hipStream_t s);
 hipError_t launch_greedy_walk(int B, int N, const int32_t* node_argmax, const int32_t* token, const int32_t* parent,
@@ -173,18 +176,29 @@ hipError_t launch_greedy_walk(int B, int N, const int32_t* node_argmax, const in
 // Vocabularies whose distribution the stochastic walk keeps in its workgroup's registers: 32 floats per thread. With 64 the
 // kernel spills and the buffer form is the faster one (8 trees of 16, 50000 float32: 67 us against 59).
 inline bool stochastic_walk_in_registers(int V) { return V <= 32768; }
-// Whether the walk takes the statistics of the nodes it visits itself. That costs about 5 us per accepted node instead of 1.5;
-// a pass over all nodes costs its bytes at about 5.5 TB/s. From 100 MB of logits on (18 us) the pass costs more than the two to
-// four nodes that a walk accepts (16 trees of 128, 32000 float32: 106 us with the pass and the buffer form, 42 without); a
-// path of 16 accepted nodes breaks even at about 200 MB.
-inline bool stochastic_walk_takes_stats(int B, int N, int V, int logits_dtype) {
-  return stochastic_walk_in_registers(V) && (double)B * N * V * (logits_dtype == SPEC_BF16 ? 2 : 4) >= 100e6;
+// Levels up to which a tree's nodes get their statistics from the walk itself (0: none); those of deeper trees come from the
+// pass over all nodes. A walk visits at most as many nodes as its tree has levels, and each node costs it 0.9e-4 V us more
+// than the walk over given statistics that this one replaced (64 accepted nodes in a row, us in all: 8192 float32 154 against
+// 107 without the pass, 16384: 204 / 118, 32000: 306 / 122; bfloat16 292 / 144; rows of single float32 elements 1.05e-4 V);
+// the pass costs its bytes at 5.5 TB/s. Up to the level where the two are equal, even a path that is accepted to the end of
+// the tree takes no longer (16 x 128 nodes of 32000 float32: 16 levels), and the usual path of a few nodes is much shorter: 16 trees of
+// 128, 32000 float32, three drafts, 49 us, with a pass for all of them 73; all 128 nodes of chains accepted: 231 (274 with the
+// form this one replaced, 822 without a pass). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
+// takes 4.5: only from 8 levels on, which fewer trees of a batch exceed. Where Lmax or N are no more than the levels, no tree
+// has to be looked at.
+inline int stochastic_own_levels(int B, int N, int V, int logits_dtype, int Lmax) {
+  if (!stochastic_walk_in_registers(V)) return 0;
+  const double pass_us = (double)B * N * V * (logits_dtype == SPEC_BF16 ? 2 : 4) / 5.5e6;
+  const double node_us = V * (logits_dtype == SPEC_F32 && V % 4 != 0 ? 1.05e-4 : 0.9e-4);
+  const int levels = (int)std::min(pass_us / node_us, (double)SPEC_MAX_TREE_NODES);
+  return levels >= 8 || levels >= std::min(Lmax, N) ? levels : 0;
 }
 hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const void* logits, const float* probs_ssm,
                                   int R, const int32_t* ssm_row, const int32_t* token, const int32_t* parent,
                                   const float* u_accept, const float* u_order, const float* u_final, float inv_temp,
                                   const float* node_max, const float* node_sumexp, float* resid, int Lmax,
-                                  int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s);
+                                  int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s,
+                                  int own_levels = 0);
 
 // ---------------------------------------------------------------------------------------------
 // Device helpers

@@ -96,11 +96,35 @@ __device__ inline T block_sum(T v, T* scratch) {
 // statistics kernel ran at half the speed of its max-only form with it.
 __device__ __forceinline__ float fast_exp(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
+// Whether a tree has at most `levels` nodes on every path from its root: nodes `lane` and `lane + 64` have the parents par0
+// and par1 (-1: none), all 64 lanes ask together. After i exchanges a lane knows the distance to its ancestor 2^i up, so a
+// deep tree is found out after log2(levels) of them. Parents that form no tree get some answer, the same one every time.
+__device__ inline bool tree_within(int par0, int par1, int levels) {
+  static_assert(SPEC_MAX_TREE_NODES == 128, "two nodes per lane");
+  int up[2] = {par0, par1}, d[2] = {1, 1};   // the nodes from this one up to, without, node up
+  for (int i = 0; i < 7 && __any(up[0] >= 0 || up[1] >= 0); ++i) {
+    int nu[2], nd[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int f = min(max(up[e], 0), SPEC_MAX_TREE_NODES - 1), l = f & 63;
+      const int u0 = __shfl(up[0], l), u1 = __shfl(up[1], l), d0 = __shfl(d[0], l), d1 = __shfl(d[1], l);
+      nu[e] = up[e] < 0 ? -1 : f < 64 ? u0 : u1;
+      nd[e] = up[e] < 0 ? d[e] : d[e] + (f < 64 ? d0 : d1);
+    }
+    up[0] = nu[0]; up[1] = nu[1]; d[0] = nd[0]; d[1] = nd[1];
+    if (__any(max(d[0], d[1]) > levels)) return false;
+  }
+  return !__any(max(d[0], d[1]) > levels);
+}
+
+// parent != nullptr: the rows of requests whose tree is within `own_levels` levels are left out (the stochastic walk takes
+// their nodes' statistics itself).
 template <bool BF16, int VEC, int NS_THREADS>
 __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __restrict__ logits, int V, float inv_temp,
                                                                 int32_t* __restrict__ node_argmax,
                                                                 float* __restrict__ node_max,
-                                                                float* __restrict__ node_sumexp) {
+                                                                float* __restrict__ node_sumexp,
+                                                                const int32_t* __restrict__ parent, int N, int own_levels) {
   __shared__ float s_val[NS_THREADS / 64];
   __shared__ int s_idx[NS_THREADS / 64];
   __shared__ float s_sum[NS_THREADS / 64];
@@ -109,6 +133,11 @@ __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __re
   const long base = row * V;
   const int n_groups = V / VEC;
   const bool want_sum = node_sumexp != nullptr;
+  if (parent != nullptr) {
+    const int lane = t & 63;
+    const int32_t* par = parent + row / N * N;
+    if (tree_within(lane < N ? par[lane] : -1, lane + 64 < N ? par[lane + 64] : -1, own_levels)) return;
+  }
   float best = -INFINITY, sum = 0.f;
   int best_i = 0x7fffffff;
   for (int g0 = 0; g0 < n_groups; g0 += NS_THREADS * SWEEP_U) {
@@ -360,13 +389,14 @@ __global__ void __launch_bounds__(64) greedy_walk_kernel(int N, const int32_t* _
 // rejection, nothing is written but the result; the buffer form below reads and writes the residual per rejection and
 // reads the row again for every rejection and for the final draw.
 //
-// node_max == nullptr: the softmax statistics of a node are taken here, from the row that is then in registers anyway if a
-// child is rejected or the last token is drawn. That costs an accepted first child one row (about 3 us) and saves the
-// statistics of the nodes that are not reached, which are most of them: see launch_stochastic_walk for where it pays.
+// own_levels > 0: the softmax statistics of the nodes of a tree within that many levels are taken here, from rows that are
+// then in registers if a child is rejected or the last token is drawn. That saves the pass over all nodes, most of whose rows
+// the walk does not reach, and makes an accepted node dearer: see stochastic_own_levels for the line between them.
+// node_max == nullptr: every tree is such a tree.
 //
 // What bounds it: one compute unit per request: a row of 32000 float32 takes it about 2.5 us, and a step of the walk is one
-// or two of them in a chain. Measured on 16 requests, trees of 128, 32000 float32, three drafts: 37.5
-// us in all, against 106.7 for the pass over all nodes and the buffer form; 8 trees of 16: 27.1 against 45.8.
+// or two of them in a chain. Measured on 16 requests, trees of 128, 32000 float32, three drafts: 49 us in all, against 120 for
+// the pass over all nodes and the buffer form; 8 trees of 16: 27 against 46.
 // ---------------------------------------------------------------------------------------------
 
 // exp(x) for x <= 0: one v_exp_f32 with the rounding of x * log2(e) put back (relative error as expf's, results below
@@ -397,24 +427,41 @@ struct SumOp {
   static constexpr float identity = 0.f;
   static __device__ __forceinline__ float f(float a, float b) { return a + b; }
 };
-// Over the block; every thread gets the result. `slot` points at 16 floats that no thread still reads from the call before
-// the last (two areas used in turn): one barrier.
 template <class Op>
-__device__ __forceinline__ float block_reduce(float v, float* slot) {
+__device__ __forceinline__ float row_reduce(float v) {   // lane 15: over its row of 16
   v = Op::f(v, dpp_f32<0x111, 0xf>(Op::identity, v));
   v = Op::f(v, dpp_f32<0x112, 0xf>(Op::identity, v));
   v = Op::f(v, dpp_f32<0x114, 0xf>(Op::identity, v));
-  v = Op::f(v, dpp_f32<0x118, 0xf>(Op::identity, v));
+  return Op::f(v, dpp_f32<0x118, 0xf>(Op::identity, v));
+}
+template <class Op>
+__device__ __forceinline__ float wave_reduce(float v) {   // lane 63: over the wavefront
+  v = row_reduce<Op>(v);
   v = Op::f(v, dpp_f32<0x142, 0xa>(Op::identity, v));
-  v = Op::f(v, dpp_f32<0x143, 0xc>(Op::identity, v));
+  return Op::f(v, dpp_f32<0x143, 0xc>(Op::identity, v));
+}
+__device__ __forceinline__ float readlane_f32(float v, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+// Sum over the block; every thread gets the result. `slot` points at 16 floats that no thread still reads from the call
+// before the last (two areas used in turn): one barrier.
+__device__ __forceinline__ float block_total(float v, float* slot) {
+  v = wave_reduce<SumOp>(v);
   if ((threadIdx.x & 63) == 63) slot[threadIdx.x >> 6] = v;
   __syncthreads();
-  v = slot[threadIdx.x & 15];
-  v = Op::f(v, dpp_f32<0x111, 0xf>(Op::identity, v));
-  v = Op::f(v, dpp_f32<0x112, 0xf>(Op::identity, v));
-  v = Op::f(v, dpp_f32<0x114, 0xf>(Op::identity, v));
-  v = Op::f(v, dpp_f32<0x118, 0xf>(Op::identity, v));
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), 15));
+  return readlane_f32(row_reduce<SumOp>(slot[threadIdx.x & 15]), 15);
+}
+// (max, sum of exp((x - max) / T)) over the block from those of its threads; every thread gets the result. `slot`: 16 pairs
+// that no thread still reads; one barrier.
+__device__ __forceinline__ void block_softmax_stats(float m, float sum, float inv_temp, float2* slot, float* max_out, float* sum_out) {
+  auto rescaled = [&](float s, float from, float to) { return from > -INFINITY ? s * fast_exp((from - to) * inv_temp) : 0.f; };
+  const float wave_max = readlane_f32(wave_reduce<MaxOp>(m), 63);
+  const float wave_sum = wave_reduce<SumOp>(rescaled(sum, m, wave_max));
+  if ((threadIdx.x & 63) == 63) slot[threadIdx.x >> 6] = make_float2(wave_max, wave_sum);
+  __syncthreads();
+  const float2 p = slot[threadIdx.x & 15];
+  *max_out = readlane_f32(row_reduce<MaxOp>(p.x), 15);
+  *sum_out = readlane_f32(row_reduce<SumOp>(rescaled(p.y, p.x, *max_out)), 15);
 }
 __device__ __forceinline__ double wave_inclusive_sum_f64(double v) {
   v += dpp_f64<0x111, 0xf>(v);
@@ -431,12 +478,41 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
                               (unsigned)__builtin_amdgcn_readlane((int)b, lane));
 }
 
+// VEC elements of a row of logits as they lie in memory: a row's loads are all requested before the first one is converted (a
+// conversion beside its load waits for it, 32 bf16 elements per thread one after the other).
+template <bool BF16, int VEC>
+struct LogitGroup {
+  unsigned raw[BF16 ? (VEC + 1) / 2 : VEC];
+  __device__ __forceinline__ void load(const void* base, unsigned elem) {
+    if constexpr (VEC == 4 && BF16) {
+      const uint2 v = *(const uint2*)((const unsigned short*)base + elem);
+      raw[0] = v.x; raw[1] = v.y;
+    } else if constexpr (VEC == 4) {
+      const uint4 v = *(const uint4*)((const float*)base + elem);
+      raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
+    } else if constexpr (BF16) {
+      raw[0] = ((const unsigned short*)base)[elem];
+    } else {
+      raw[0] = __float_as_uint(((const float*)base)[elem]);
+    }
+  }
+  __device__ __forceinline__ void set_minus_infinity() {
+#pragma unroll
+    for (unsigned& r : raw) r = BF16 ? 0xff80ff80u : 0xff800000u;
+  }
+  __device__ __forceinline__ void expand(float (&v)[VEC]) {
+    if constexpr (BF16 && VEC == 1) asm("" : "+v"(raw[0]));   // (the compiler moves this one back to its load otherwise)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] = __uint_as_float(!BF16 ? raw[e] : e % 2 == 0 ? raw[e / 2] << 16 : raw[e / 2] & 0xffff0000u);
+  }
+};
+
 template <bool BF16, int VEC, int NG>
 __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     int N, int V, const void* __restrict__ logits, const float* __restrict__ probs_ssm, int R,
     const int32_t* __restrict__ ssm_row, const int32_t* __restrict__ token, const int32_t* __restrict__ parent,
     const float* __restrict__ u_accept, const float* __restrict__ u_order, const float* __restrict__ u_final,
-    float inv_temp, const float* __restrict__ node_max, const float* __restrict__ node_sumexp, int Lmax,
+    float inv_temp, const float* __restrict__ node_max, const float* __restrict__ node_sumexp, int own_levels, int Lmax,
     int32_t* __restrict__ path, int32_t* __restrict__ len, int32_t* __restrict__ out_tokens, int32_t* status) {
   constexpr int WAVES = SW_THREADS / 64, NTOT = NG * WAVES < 64 ? 64 : NG * WAVES;   // final scan: (group round, wavefront)
   static_assert(NTOT % 64 == 0, "whole rounds of lanes");
@@ -446,44 +522,34 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
   __shared__ float s_ord[SPEC_MAX_TREE_NODES], s_acc[SPEC_MAX_TREE_NODES];
   __shared__ float s_cq[SPEC_MAX_TREE_NODES], s_cp[SPEC_MAX_TREE_NODES];   // per child in test order: Q(x), un-normalised P(x)
   __shared__ float s_red[2][WAVES];
+  __shared__ float2 s_stats[WAVES];
   __shared__ double s_tot[NTOT];
 
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int n_groups = V / VEC;
-  const bool lazy = node_max == nullptr;
 
-  float w[NG][VEC];   // current distribution, un-normalised: P(i) = w_i / Z
+  float w[NG][VEC];   // the row of node u: its logits, then the current distribution, un-normalised: P(i) = w_i / Z
   // Rows are addressed as a wave-uniform base per round plus one offset per lane (an address per load would not leave
   // room for the row in registers); u and rows of probs_ssm are made uniform for that.
   auto load_row = [&](int u) {   // the logits of node u; elements past the end are -inf
     const long base = ((long)b * N + u) * V;
+    LogitGroup<BF16, VEC> raw[NG];
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
-      const int gi = j * SW_THREADS + t;
-      if (gi < n_groups) {
+      if (j * SW_THREADS + t < n_groups) {
         const void* round = BF16 ? (const void*)((const __hip_bfloat16*)logits + base + j * SW_THREADS * VEC)
                                  : (const void*)((const float*)logits + base + j * SW_THREADS * VEC);
-        load_logit_group<VEC, BF16>(round, (unsigned)(t * VEC), w[j]);
+        raw[j].load(round, (unsigned)(t * VEC));
       } else {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) w[j][e] = -INFINITY;
+        raw[j].set_minus_infinity();
       }
     }
-  };
-  auto exponentiate = [&](float mx) {
-    float sum = 0.f;
 #pragma unroll
-    for (int j = 0; j < NG; ++j)
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) {
-        w[j][e] = exp_of_nonpositive((w[j][e] - mx) * inv_temp);
-        sum += w[j][e];
-      }
-    return sum;
+    for (int j = 0; j < NG; ++j) raw[j].expand(w[j]);
   };
 
-  if (lazy) load_row(0);
+  if (own_levels > 0) load_row(0);
   if (t < N) {
     s_par[t] = parent[(long)b * N + t];
     s_tok[t] = token[(long)b * N + t];
@@ -509,10 +575,21 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     return;
   }
   if (t == 0) path[(long)b * Lmax] = 0;
+  const bool own = node_max == nullptr ||
+                   (own_levels > 0 && tree_within(lane < N ? s_par[lane] : -1, lane + 64 < N ? s_par[lane + 64] : -1, own_levels));
 
   int u = 0, k = 0, red = 0;
-  bool have_row = lazy;   // w holds node u's logits (before the statistics) or its distribution
+  bool have_row = own_levels > 0, have_weights = false;   // w holds node u's logits, its distribution
   float Z, mx;
+  auto need_weights = [&]() {
+    if (have_weights) return;
+    if (!have_row) load_row(u);
+#pragma unroll
+    for (int j = 0; j < NG; ++j)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) w[j][e] = exp_of_nonpositive((w[j][e] - mx) * inv_temp);
+    have_weights = true;
+  };
   while (true) {
     // children of u in ascending (u_order, index)
     if (t == 0) s_nchild = 0;
@@ -541,16 +618,19 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
       s_cq[t] = probs_ssm[(long)s_row[c] * V + my_x];
       cl = load_logit<BF16>(logits, ((long)b * N + u) * V + my_x);
     }
-    if (lazy) {
-      float m = -INFINITY;
+    if (own) {   // as the pass over all nodes takes them; w keeps the logits: most nodes need nothing else
+      float m = -INFINITY, sum = 0.f;
 #pragma unroll
       for (int j = 0; j < NG; ++j)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) m = fmaxf(m, w[j][e]);
-      mx = block_reduce<MaxOp>(m, s_red[red ^= 1]);
-      const float sum = exponentiate(mx);
-      Z = block_reduce<SumOp>(sum, s_red[red ^= 1]);
-      if (mx == -INFINITY) Z = 0.f;
+      if (m > -INFINITY) {
+#pragma unroll
+        for (int j = 0; j < NG; ++j)
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) sum += fast_exp((w[j][e] - m) * inv_temp);
+      }
+      block_softmax_stats(m, sum, inv_temp, s_stats, &mx, &Z);
     } else {
       mx = node_max[(long)b * N + u];
       Z = node_sumexp[(long)b * N + u];
@@ -575,11 +655,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
       // rejected: P := norm(max(0, P - Q)), kept as un-normalised values plus their sum Z
       const float* Q = probs_ssm + (long)uniform(s_row[c]) * V;
       float my_q = t < nchild ? Q[my_x] : 0.f;
-      if (!have_row) {
-        load_row(u);
-        have_row = true;
-        (void)exponentiate(mx);
-      }
+      need_weights();
       const float invZ = 1.f / Z;
       float part = 0.f;
       float q[NG][VEC];
@@ -597,7 +673,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
       for (int jj = 0; jj < NG; ++jj)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) part += fmaxf(0.f, fmaf(w[jj][e], invZ, -q[jj][e]));
-      const float Znew = block_reduce<SumOp>(part, s_red[red ^= 1]);
+      const float Znew = block_total(part, s_red[red ^= 1]);
       if (Znew > 0.f) {
 #pragma unroll
         for (int jj = 0; jj < NG; ++jj)
@@ -613,17 +689,15 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     }
     if (!accepted) break;
     ++k;
-    have_row = lazy;
-    if (lazy) load_row(u);
+    have_weights = false;
+    have_row = own;
+    if (own) load_row(u);
     __syncthreads();   // everybody has read this node's children before the next node's are listed
   }
 
   // ---- final token: inverse CDF in ascending token id over the current P. Order of the elements: group round, thread,
   // element. Float64: inclusive sums over the lanes per round, then over the (round, wavefront) totals.
-  if (!have_row) {
-    load_row(u);
-    (void)exponentiate(mx);
-  }
+  need_weights();
   auto group_sum = [&](int j) {
     double sum = 0.0;
 #pragma unroll
@@ -875,7 +949,8 @@ __global__ void __launch_bounds__(SW_THREADS) node_sample_kernel(const void* __r
 
 // ---------------------------------------------------------------------------------------------
 hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
-                             int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s) {
+                             int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s,
+                             const int32_t* parent, int own_levels) {
   const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
   const bool many = (long)B * N >= 1024;
   if (node_sumexp == nullptr && V % (bf16 ? 8 : 4) == 0) {   // (the entry points require 16-byte aligned logits)
@@ -889,10 +964,10 @@ hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* 
 #define SPEC_NS(BF, VE)                                                                                                  \
   if (many)                                                                                                              \
     hipLaunchKernelGGL((node_stats_kernel<BF, VE, 256>), dim3(B * N), dim3(256), 0, s, logits, V, inv_temp, node_argmax,  \
-                       node_max, node_sumexp);                                                                           \
+                       node_max, node_sumexp, parent, N, own_levels);                                                    \
   else                                                                                                                   \
     hipLaunchKernelGGL((node_stats_kernel<BF, VE, 1024>), dim3(B * N), dim3(1024), 0, s, logits, V, inv_temp, node_argmax, \
-                       node_max, node_sumexp)
+                       node_max, node_sumexp, parent, N, own_levels)
   if (bf16 && vec) { SPEC_NS(true, 4); }
   else if (bf16) { SPEC_NS(true, 1); }
   else if (vec) { SPEC_NS(false, 4); }
@@ -927,13 +1002,14 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
                                   int R, const int32_t* ssm_row, const int32_t* token, const int32_t* parent,
                                   const float* u_accept, const float* u_order, const float* u_final, float inv_temp,
                                   const float* node_max, const float* node_sumexp, float* resid, int Lmax,
-                                  int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s) {
+                                  int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s,
+                                  int own_levels) {
   const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
   if (stochastic_walk_in_registers(V)) {
 #define SPEC_SWR(BF, VE, NGR)                                                                                         \
   hipLaunchKernelGGL((stochastic_walk_reg_kernel<BF, VE, NGR>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, \
-                     R, ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, Lmax, path,  \
-                     len, out_tokens, status)
+                     R, ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, own_levels,  \
+                     Lmax, path, len, out_tokens, status)
 #define SPEC_SWR_T(BF)                                          \
   if (!vec && V <= SW_THREADS * 8) SPEC_SWR(BF, 1, 8);          \
   else if (!vec) SPEC_SWR(BF, 1, 32);                           \

@@ -1,8 +1,6 @@
 """The stochastic walk over the vocabulary sizes where its form changes (rows of whole 16-byte groups or not, one to
 eight groups per thread, the buffer form), with the nodes' statistics taken by the walk or before it, against the oracle on vetted
 uniforms: bit-exact paths, lengths, tokens and status."""
-import ctypes
-
 import numpy as np
 import pytest
 import torch
@@ -19,9 +17,9 @@ def _dev(x):
     return (torch.from_numpy(np.ascontiguousarray(x)) if isinstance(x, np.ndarray) else x).to(DEV)
 
 
-def _case(V, B, N, dt, seed, tau=1.2, n_ssm=3):
+def _case(V, B, N, dt, seed, tau=1.2, n_ssm=3, parent=None):
     cfg = wl.Config(96, "walk", "f32", B=B, H=1, D=64, P=1, N=N, tree="random_branching", V=V, n_ssm=n_ssm)
-    i = wl.make_verify_inputs(cfg, seed=seed, mode="stochastic", logits_dtype=torch.bfloat16 if dt == "bf16" else torch.float32, tau=tau)
+    i = wl.make_verify_inputs(cfg, seed=seed, mode="stochastic", parent=parent, logits_dtype=torch.bfloat16 if dt == "bf16" else torch.float32, tau=tau)
     args = (i["logits"].float().numpy(), i["probs_ssm"].numpy(), i["ssm_row"].numpy(), i["tree_token"].numpy(), i["tree_parent"].numpy())
     ua, uf, _ = vetting.vet_uniforms(*args, i["u_accept"].numpy(), i["u_order"].numpy(), i["u_final"].numpy(), i["rng"])
     ref = orc.verify_stochastic(*args, ua, i["u_order"].numpy(), uf)
@@ -41,13 +39,36 @@ def test_walk_from_given_statistics_and_from_its_own(spec, V, B, N, dt, tau):
         assert np.array_equal(g.cpu().numpy(), r)
 
 
-@pytest.mark.parametrize("V,B,N,dt", [(32000, 16, 50, "f32"), (32003, 16, 52, "f32"), (16384, 16, 100, "f32"), (32768, 16, 96, "bf16")])
+def _own_levels(V, B, N, dt, Lmax):
+    """Levels up to which the walk takes a tree's statistics itself (the rule of spec_verify_stochastic)."""
+    pass_us = B * N * V * (2 if dt == "bf16" else 4) / 5.5e6
+    levels = int(min(pass_us / (V * (1.05e-4 if dt == "f32" and V % 4 else 0.9e-4)), 128))
+    return levels if levels >= 8 or levels >= min(Lmax, N) else 0
+
+
+@pytest.mark.parametrize("V,B,N,dt", [(32000, 16, 72, "f32"), (32003, 16, 80, "f32"), (16384, 16, 100, "f32"), (32768, 16, 128, "bf16"),
+                                      (32001, 16, 128, "bf16")])
 def test_walk_that_takes_its_own_statistics(spec, V, B, N, dt):
-    """Enough rows that the nodes' statistics are left to the walk; malformed and padding nodes among them."""
-    logits, dev, ref = _case(V, B, N, dt, seed=V, n_ssm=1, tau=2.0)
+    """Enough rows that the statistics of shallow trees' nodes are left to the walk and those of deeper ones are not; trees of
+    both kinds, exactly at the line and one level past it, malformed and padding nodes among them."""
+    levels = _own_levels(V, B, N, dt, N)
+    assert 8 <= levels < N - 1
+    def spine(n):      # a chain of n levels whose other nodes hang on the root
+        return np.concatenate([np.arange(-1, n - 1), np.zeros(N - n)]).astype(np.int32)
+    rng = np.random.default_rng(V)
+    par = np.stack([wl.tree_random_branching(rng, N) for _ in range(B)])
+    par[3], par[4], par[5], par[6] = spine(levels), spine(levels + 1), spine(N), spine(2)
+    depth = [int(wl.depth_of(p).max()) + 1 for p in par]
+    assert min(depth) <= levels < max(depth)
+    logits, dev, ref = _case(V, B, N, dt, seed=V, n_ssm=1, tau=2.0, parent=par)
     got = spec.spec_verify_stochastic(logits, *dev)
     for g, r in zip(got, ref):
         assert np.array_equal(g.cpu().numpy(), r)
+    # a stated longest path within the levels: no tree needs the pass. (Paths as long as that would be cut: there are none.)
+    assert ref[1].max() < levels
+    got = spec.spec_verify_stochastic(logits, *dev, Lmax=levels)
+    for g, r in zip(got, ref):
+        assert np.array_equal(g.cpu().numpy(), r[:, :levels] if r.ndim == 2 else r)
     status = torch.zeros(B, dtype=torch.int32, device=DEV)
     bad = [d.clone() for d in dev]
     bad[3][1, 2] = 5                    # a parent after its child
@@ -58,3 +79,39 @@ def test_walk_that_takes_its_own_statistics(spec, V, B, N, dt):
     assert ln[0].item() == 1 and path[0, 0].item() == 0
     for g, r in zip((path, ln, tok), ref):
         assert np.array_equal(g[2:].cpu().numpy(), r[2:])
+
+
+def test_long_accepted_paths_do_not_wait_for_their_rows(spec):
+    """Chains of 128 nodes that are accepted to the end: the call takes no longer than the walk over given statistics and one
+    read of all logits at 2.5 TB/s (it reads them once, at twice that), where a walk that takes the statistics of every node
+    itself takes three times as long."""
+    B, N, V = 16, 128, 32000
+    g = torch.Generator(device=DEV).manual_seed(1)
+    logits = torch.randn((B, N, V), generator=g, device=DEV)
+    tok = torch.randint(0, V, (B, N), generator=g, device=DEV, dtype=torch.int32)
+    par = torch.arange(-1, N - 1, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+    probs = torch.full((1, V), 1.0 / V, device=DEV)
+    row = torch.zeros((B, N), dtype=torch.int32, device=DEV)
+    u = torch.zeros((B, N), device=DEV)
+    uf = torch.full((B,), 0.5, device=DEV)
+    mx = logits.max(-1).values.contiguous()
+    se = torch.exp(logits - mx[..., None]).sum(-1).contiguous()
+    given = lambda: spec.spec_verify_stochastic_stats(logits, mx, se, probs, row, tok, par, u, u, uf)  # noqa: E731
+    whole = lambda: spec.spec_verify_stochastic(logits, probs, row, tok, par, u, u, uf)  # noqa: E731
+    for a, b in zip(given(), whole()):
+        assert torch.equal(a, b)
+    assert (whole()[1] == N).all()
+
+    def us(call):
+        times = []
+        for _ in range(5):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            for _ in range(10):
+                call()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end) * 100)
+        return sorted(times)[2]
+    t_given, t_whole = us(given), us(whole)
+    assert t_whole < t_given + logits.numel() * 4 / 2.5e6, (t_given, t_whole)

@@ -29,6 +29,7 @@ def _case(V, B, N, dt, seed, tau=1.2, n_ssm=3, parent=None):
 
 @pytest.mark.parametrize("V,B,N,dt,tau", [(4, 3, 12, "f32", None), (1023, 3, 24, "f32", None), (4096, 3, 24, "bf16", 1.2), (4100, 3, 24, "f32", 2.0),
                                           (8191, 3, 20, "f32", 2.0), (8193, 3, 20, "bf16", 2.0),
+                                          (12001, 3, 20, "f32", 2.0), (16383, 3, 20, "bf16", 2.0), (16385, 3, 20, "f32", 2.0),
                                           (16384, 3, 20, "bf16", 2.0), (16388, 3, 20, "f32", 2.0), (32768, 2, 16, "f32", 2.0),
                                           (32767, 2, 16, "bf16", 2.0), (32769, 2, 12, "f32", 1.2), (32772, 2, 16, "f32", 2.0)])
 def test_walk_from_given_statistics_and_from_its_own(spec, V, B, N, dt, tau):
@@ -37,6 +38,19 @@ def test_walk_from_given_statistics_and_from_its_own(spec, V, B, N, dt, tau):
     got = spec.spec_verify_stochastic(logits, *dev, status=status)      # few rows: statistics before the walk
     for g, r in zip(list(got) + [status], ref):
         assert np.array_equal(g.cpu().numpy(), r)
+
+
+def _us(call):
+    times = []
+    for _ in range(5):
+        start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        for _ in range(10):
+            call()
+        end.record()
+        torch.cuda.synchronize()
+        times.append(start.elapsed_time(end) * 100)
+    return sorted(times)[2]
 
 
 def _own_levels(V, B, N, dt, Lmax):
@@ -102,16 +116,34 @@ def test_long_accepted_paths_do_not_wait_for_their_rows(spec):
         assert torch.equal(a, b)
     assert (whole()[1] == N).all()
 
-    def us(call):
-        times = []
-        for _ in range(5):
-            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            start.record()
+    t_given, t_whole = _us(given), _us(whole)
+    assert t_whole < t_given + logits.numel() * 4 / 2.5e6, (t_given, t_whole)
+
+
+def test_odd_vocabularies_have_registers_of_their_size(spec):
+    """Eight rejections over 9001 elements, read one by one, take about as long as over 16384, read in groups of four (1.2 times;
+    a form with registers for 32768 elements takes twice as long)."""
+    t = []
+    for V in (9001, 16384):
+        B, N = 4, 9
+        logits = torch.randn((B, N, V), generator=torch.Generator(device=DEV).manual_seed(V), device=DEV)
+        logits[:, :, :N] = -30.0
+        tok = torch.arange(N, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+        par = torch.tensor([-1] + [0] * (N - 1), dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+        probs = torch.full((1, V), 1.0 / V, device=DEV)
+        row = torch.zeros((B, N), dtype=torch.int32, device=DEV)
+        u = torch.full((B, N), 0.75, device=DEV)
+        mx = logits.max(-1).values.contiguous()
+        se = torch.exp(logits - mx[..., None]).sum(-1).contiguous()
+        out = tuple(torch.empty(s, dtype=torch.int32, device=DEV) for s in ((B, N), (B,), (B, N)))
+        ws = torch.empty(8 * B * V + 256, dtype=torch.uint8, device=DEV)
+        call = lambda: spec.spec_verify_stochastic_stats(logits, mx, se, probs, row, tok, par, u, u, u[:, 0].contiguous(),  # noqa: E731
+                                                         workspace=ws, out=out)
+        call()
+        assert out[1].tolist() == [1] * B       # every child rejected
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
             for _ in range(10):
                 call()
-            end.record()
-            torch.cuda.synchronize()
-            times.append(start.elapsed_time(end) * 100)
-        return sorted(times)[2]
-    t_given, t_whole = us(given), us(whole)
-    assert t_whole < t_given + logits.numel() * 4 / 2.5e6, (t_given, t_whole)
+        t.append(_us(graph.replay))
+    assert t[0] < 1.6 * t[1], t

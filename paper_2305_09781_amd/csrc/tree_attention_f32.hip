@@ -16,6 +16,12 @@
 // query r (Q). The product leaves it with query r's scores for keys 4g + i, which is the operand O^T += V^T P^T wants
 // for k-step i with row 4g + i of V in 16-byte pieces again: neither K, V nor the probabilities pass through LDS.
 //
+// Precision. A score is four sums of D / 4 products, added in pairs: with two sums of D / 2 the outputs over short key ranges,
+// whose error is that of the scores, were further from float64 than those of a plain float32 loop with four sums (relative
+// error over 59 keys, D = 128: 2.15e-7 with two, 2.0e-7 for the loop, 1.7e-7 with four; over 2000 keys 3.0e-7, 3.8e-7,
+// 2.5e-7). The four cost 0 to 1 % (3 % for 16 requests x 32 / 8 heads, trees of 33, 2000 keys: 262 -> 271 us). exp2 is
+// v_exp_f32: probabilities below 2^-126 of the largest are 0 instead of subnormal.
+//
 // What bounds it: float32 MFMA rate and the stream of K/V are close to each other (16 keys x 16 queries x 128
 // dimensions are 2048 cycles of one SIMD for 16 KB). Measured on 4 requests x 32 heads x 128, 300 to 1000 keys, trees of
 // 24 (95 MB): 37.6 us a layer, append and merge launch included (2.5 TB/s, 27 TFLOP/s), against
@@ -137,9 +143,6 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     for (int j = 0; j < KJ; ++j) qf[nt][j] = *(const float4*)(p + (4 * j + g) * 4);
   }
   const bool touches_tree = c1 > P;
-  unsigned long long anc[NT][2];
-#pragma unroll
-  for (int nt = 0; nt < NT; ++nt) anc[nt][0] = anc[nt][1] = 0ull;
   // one workgroup per request owns the final outputs' validity: every workgroup of a single chunk checks the tree; with
   // several chunks only those that reach it do (the combine step gives a malformed request its zeros)
   if (touches_tree) {
@@ -183,11 +186,6 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       s_anc[t][1] = hi;
     }
     f32_lds_barrier();
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) {
-      anc[nt][0] = s_anc[node[nt]][0];
-      anc[nt][1] = s_anc[node[nt]][1];
-    }
   }
 
   f32x4 O[NT][VH * 4];
@@ -208,18 +206,18 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     const bool more = next < n_tiles;
     const int k1 = c0 + (more ? next : ti) * F32_TK;
     const long base1 = tile_base(k1);
-    f32x4 sc[NT][2];
+    f32x4 sc[NT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt) sc[nt][0] = sc[nt][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int nt = 0; nt < NT; ++nt) {   // (one query tile after the other: eight sums at once do not fit the registers)
+      f32x4 part[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int j = 0; j < KJ; ++j) {
-      const float a[4] = {kf[j].x, kf[j].y, kf[j].z, kf[j].w};
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) {
+      for (int j = 0; j < KJ; ++j) {
+        const float a[4] = {kf[j].x, kf[j].y, kf[j].z, kf[j].w};
         const float bq[4] = {qf[nt][j].x, qf[nt][j].y, qf[nt][j].z, qf[nt][j].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sc[nt][e & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], bq[e], sc[nt][e & 1], 0, 0, 0);
+        for (int e = 0; e < 4; ++e) part[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], bq[e], part[e], 0, 0, 0);
       }
+      sc[nt] = (part[0] + part[1]) + (part[2] + part[3]);
     }
     if (more) load_k(k1, base1);
     float p[NT][4];
@@ -228,13 +226,13 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     for (int nt = 0; nt < NT; ++nt) {
       float s[4];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) s[i] = (sc[nt][0][i] + sc[nt][1][i]) * scale_log2;
+      for (int i = 0; i < 4; ++i) s[i] = sc[nt][i] * scale_log2;
       if (masked) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
           const int key = k0 + 4 * g + i, rel = key - P;
           bool vis = key < c1;
-          if (vis && rel >= 0) vis = (anc[nt][rel >> 6] >> (rel & 63)) & 1ull;
+          if (vis && rel >= 0) vis = (s_anc[node[nt]][rel >> 6] >> (rel & 63)) & 1ull;
           if (!vis) s[i] = -INFINITY;
         }
       }

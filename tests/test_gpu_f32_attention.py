@@ -52,3 +52,51 @@ def test_float32_fused_append_of_a_malformed_tree(spec):
     _check_attention(out[:1], ref[:1], torch.float32)
     assert (out[1] == 0).all()
     assert np.array_equal(kc.double().cpu().numpy(), kco) and np.array_equal(vc.double().cpu().numpy(), vco)
+
+
+def _float32_loop(q, k, v, mask, scale):
+    """One query at a time in float32: scores as four sums of fused products, added in pairs, softmax and output one key after
+    the other. (A fused multiply-add is a float64 one, rounded: the product of two float32 is exact there.)"""
+    f32 = np.float32
+    fma = lambda a, b, c: (np.float64(a) * b + c).astype(f32)  # noqa: E731
+    s4 = [np.zeros((q.shape[0], k.shape[0]), f32) for _ in range(4)]
+    for d in range(0, q.shape[1], 4):
+        for e in range(4):
+            s4[e] = fma(q[:, None, d + e], k[None, :, d + e], s4[e])
+    s = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * f32(scale * 1.4426950408889634)
+    s[~mask] = -np.inf
+    p = np.exp2(s - s.max(1, keepdims=True))
+    l, o = np.zeros(q.shape[0], f32), np.zeros((q.shape[0], v.shape[1]), f32)
+    for j in range(k.shape[0]):
+        l = l + p[:, j]
+        o = fma(p[:, j:j + 1], v[j][None], o)
+    return o * (f32(1) / l)[:, None]
+
+
+@pytest.mark.parametrize("H,H_kv,D,P,N", [(4, 4, 128, 40, 19), (8, 8, 64, 16, 4), (6, 3, 128, 60, 40), (4, 4, 128, 30, 1), (4, 4, 64, 128, 8)])
+def test_float32_attention_is_no_further_off_than_a_float32_loop(spec, H, H_kv, D, P, N):
+    """Relative error against float64 over short key ranges, where it is that of the scores, averaged over four inputs."""
+    err = np.zeros((4, 2))
+    for seed in range(4):
+        cfg = wl.Config(90, "f32", "f32", B=2, H=H, D=D, P=P, N=N, tree="random_branching", H_kv=H_kv)
+        inp = wl.make_attention_inputs(cfg, seed=6000 + seed, S_cap=P + N + 3)
+        ref, kco, vco = _oracle_append_attention(inp)
+        out, _, _ = _run_append_attention(spec, inp, fused=True)
+        loop = np.empty_like(ref)
+        for b in range(2):
+            par = inp["tree_parent"][b].numpy()
+            mask = np.ones((N, P + N), bool)
+            mask[:, P:] = False
+            for n in range(N):
+                u = n
+                while u >= 0:
+                    mask[n, P + u] = True
+                    u = int(par[u])
+            for h in range(H):
+                kv = h // (H // H_kv)
+                loop[b, :, h] = _float32_loop(inp["q"][0][b, :, h].numpy(), kco[b, kv, :P + N].astype(np.float32),
+                                              vco[b, kv, :P + N].astype(np.float32), mask, 1 / np.sqrt(D))
+        err[seed] = [np.linalg.norm(x - ref) / np.linalg.norm(ref) for x in (out.double().cpu().numpy(), loop)]
+    kernel, plain = err.mean(0)
+    print("relative error: kernel %.3e, float32 loop %.3e" % (kernel, plain))
+    assert kernel <= plain

@@ -58,7 +58,7 @@ def _float32_loop(q, k, v, mask, scale):
     """One query at a time in float32: scores as four sums of fused products, added in pairs, softmax and output one key after
     the other. (A fused multiply-add is a float64 one, rounded: the product of two float32 is exact there.)"""
     f32 = np.float32
-    fma = lambda a, b, c: (np.float64(a) * b + c).astype(f32)  # noqa: E731
+    fma = lambda a, b, c: (a.astype(np.float64) * b + c).astype(f32)  # noqa: E731
     s4 = [np.zeros((q.shape[0], k.shape[0]), f32) for _ in range(4)]
     for d in range(0, q.shape[1], 4):
         for e in range(4):

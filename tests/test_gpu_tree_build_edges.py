@@ -64,3 +64,59 @@ def test_merge_sizes(spec, M, Nin, Nout, chain):
     for b in range(B):
         for g, w in zip(list(got) + [status], orc.tree_merge(par[b], tok[b], size[b], Nout)):
             assert np.array_equal(g[b].cpu().numpy(), np.asarray(w))
+
+
+def _shapes(kind, n):
+    if kind == "star":
+        return np.concatenate([[-1], np.zeros(n - 1)])
+    if kind == "chain":
+        return np.arange(-1, n - 1)
+    spine = n // 2                                         # a chain whose other nodes hang on its middle and on its end
+    return np.concatenate([np.arange(-1, spine - 1), np.where(np.arange(n - spine) % 2, spine // 2, spine - 1)])
+
+
+@pytest.mark.parametrize("M,Nin,kind,tokens", [(8, 128, "star", 3), (8, 128, "star", 100), (1, 128, "chain", 9), (3, 100, "chain", 2),
+                                               (1, 1024, "chain", 5), (1, 100, "comb", 2), (7, 61, "comb", 4), (1, 9, "star", 1),
+                                               (1, 10, "star", 2), (2, 5, "star", 9)])
+def test_merge_of_wide_and_narrow_levels(spec, M, Nin, kind, tokens):
+    """Levels of one node, of a few and of a thousand, runs of the first next to the others, siblings that repeat tokens."""
+    rng = np.random.default_rng(M * 1000 + Nin + tokens)
+    B = 3
+    par = np.broadcast_to(_shapes(kind, Nin), (B, M, Nin)).astype(np.int32)
+    tok = rng.integers(0, tokens, size=(B, M, Nin)).astype(np.int32)
+    tok[:, :, 0] = 1
+    size = np.full((B, M), Nin, dtype=np.int32)
+    size[1:] = rng.integers(1, Nin + 1, size=(B - 1, M))
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)  # noqa: E731
+    status = torch.zeros(B, dtype=torch.int32, device=DEV)
+    got = spec.spec_tree_merge(dev(par), dev(tok), dev(size), 128, status=status)
+    for b in range(B):
+        for g, w in zip(list(got) + [status], orc.tree_merge(par[b], tok[b], size[b], 128)):
+            assert np.array_equal(g[b].cpu().numpy(), np.asarray(w))
+
+
+def test_merge_of_repeated_tokens_ends_its_comparisons_early(spec):
+    """Stars of 128 nodes merged from eight trees: with three different tokens every node finds its like among the first few
+    of its level, which takes half as long as comparing a thousand different ones."""
+    B, M, Nin = 16, 8, 128
+    par = torch.from_numpy(_shapes("star", Nin).astype(np.int32)).to(DEV).expand(B, M, Nin).contiguous()
+    size = torch.full((B, M), Nin, dtype=torch.int32, device=DEV)
+    us = []
+    for tokens in (3, 32000):
+        tok = torch.randint(0, tokens, (B, M, Nin), generator=torch.Generator(device=DEV).manual_seed(tokens), device=DEV, dtype=torch.int32)
+        tok[:, :, 0] = 1
+        spec.spec_tree_merge(par, tok, size, 128)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            for _ in range(10):
+                spec.spec_tree_merge(par, tok, size, 128)
+        times = []
+        for _ in range(7):
+            start, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            start.record()
+            graph.replay()
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end) * 100)
+        us.append(sorted(times)[3])
+    assert us[0] < 0.75 * us[1], us

@@ -347,9 +347,10 @@ int spec_kv_commit(const spec_attn_desc_t* desc, int32_t n_layers, void* const* 
  *     node_max[m]    = that maximum (float32; may be NULL),
  * hidden [M,K] and weight [V,K] bf16, K contiguous (the layout of a linear layer's weight), K a multiple of
  * 256, both 16-byte aligned; products accumulate in float32 on the matrix cores, so two logits closer than
- * float32 rounding of the sum may compare either way. Built for the few hundred rows of a verification
- * pass (M = B*N), where the product is bound by one pass over `weight`; larger M is served in slices of
- * 128 rows, each streaming `weight` again.
+ * float32 rounding of the sum may compare either way; the order of the sum depends on K and V only, so a
+ * row has the same logits, arg-max and maximum in a batch of any M. Built for the few hundred rows of a
+ * verification pass (M = B*N), where the product is bound by one pass over `weight`; larger M is served in
+ * slices of up to 256 rows, which run side by side on one die of the GPU so that they fetch `weight` once.
  * spec_verify_greedy_lm_head = this (M = B*N, row b*N + u is node u of request b) followed by the walk of
  * spec_verify_greedy; node_argmax [B,N] may be NULL (then it lives in the workspace).
  * workspace: spec_lm_head_argmax_workspace_bytes(M, V) bytes, 256-byte aligned; contents are scratch.

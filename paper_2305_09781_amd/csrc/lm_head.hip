@@ -21,6 +21,11 @@
 // / with logits and statistics and the merge, us (before: W straight into registers, 16 rows per wavefront, `hidden` through
 // LDS): 16 rows 50.4 / 52.6 (54.7 / 57.3), 64 rows 49.5 / 52.6 (54.8 / 58.9), 128 rows 55.2 / 58.6 (68.3 / 74.4), 256 rows
 // 83 / 90 (121 / 135).
+// The order of a logit's sum is a matter of V and K alone, so that a row of `hidden` has the same logits in a batch of any
+// size: the 64 x 32 tile (up to 32 rows, vocabularies up to 16384 on 256 compute units) has two wavefronts for each place of
+// the product, which sum every other pair of k-steps, and where it is in use the other tiles keep the same two sums
+// (TWO; 8000 x 4096, 64 / 128 / 256 rows, arg-max only: 27.0 / 33.3 / 34.2 us with one sum, 27.0 / 34.3 / 35.6 with two; the
+// 64 x 32 tile without the second pair of wavefronts takes 28.0 instead of 19.0 for one row).
 // More than 256 rows of `hidden` take several slices; the slices of one vocabulary tile are numbered eight apart, which
 // puts them on one XCD at the same time, so W is fetched once for all of them.
 #include <hip/hip_bf16.h>
@@ -59,7 +64,7 @@ __device__ __forceinline__ bool beats(float v2, int i2, float v1, int i1) { retu
 // STATS: the logits are also written out, rounded to bf16, and every partial carries the sum of
 // exp((x - max) / T) over the workgroup's vocabulary rows - of the ROUNDED values, which are what a verifier
 // reading those logits will see (maximum and arg-max are then those of the rounded values too).
-template <int VT, int MT, bool STATS>
+template <int VT, int MT, bool TWO, bool STATS>
 __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
                                                                     const __hip_bfloat16* __restrict__ weight,
                                                                     float* __restrict__ part_val, int32_t* __restrict__ part_idx,
@@ -68,6 +73,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
                                                                     int M, int K, int V, int n_vtiles, int slices_per_row) {
   constexpr int WV = VT / 32 < (MT >= 128 ? 2 : 4) ? VT / 32 : (MT >= 128 ? 2 : 4);   // wavefronts along v,
   constexpr int WM = MT / 32 < 4 / WV ? MT / 32 : 4 / WV, KW = 4 / (WV * WM);         // along m, and along the k of a stage
+  constexpr int SUMS = TWO && KW == 1 ? 2 : 1;
   constexpr int TV = VT / WV / 32, TM = MT / WM / 32;               // 32 x 32 tiles of a wavefront
   constexpr int W_BYTES = VT * ROWB, STAGE = W_BYTES + MT * ROWB;
   constexpr int NST = MT == 256 ? 3 : (128 << 10) / STAGE < 8 ? (128 << 10) / STAGE : 8, AHEAD = NST - 1;
@@ -85,6 +91,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int wv = wave / WM % WV, wm = wave % WM, kw = wave / (WV * WM);
+  static_assert(KW == 1 || (KW == 2 && TWO), "at most two sums per logit");
   const int r = lane & 31, h = lane >> 5;
   const int v0 = vt * VT, m0 = slice * MT;
   const int NC = K / KC;
@@ -110,13 +117,18 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
   for (int c = 0; c < AHEAD; ++c)
     if (c < NC) issue(c, c);
 
-  f32x16 acc[TV][TM];
+  // TWO: a logit is the sum of two, over the first and over the second two k-steps of every stage. The tile of 64 x 32 gives
+  // them to two wavefronts. Where that tile serves the smallest M (V and K decide), the others take the same two sums, so that
+  // a row of `hidden` has the same logits whatever M is.
+  f32x16 sums[SUMS][TV][TM];
 #pragma unroll
-  for (int tv = 0; tv < TV; ++tv)
+  for (int p = 0; p < SUMS; ++p)
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm)
+    for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) acc[tv][tm][i] = 0.f;
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) sums[p][tv][tm][i] = 0.f;
   // operand of this wavefront's k-step ks: row r of a 32-row tile, piece 2 k-step + h (the swizzle depends on r alone)
   unsigned off[4 / KW];
 #pragma unroll
@@ -140,23 +152,30 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
 #pragma unroll
       for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm) acc[tv][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tv], b[tm], acc[tv][tm], 0, 0, 0);
+        for (int tm = 0; tm < TM; ++tm)
+          sums[ks / 2 % SUMS][tv][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tv], b[tm], sums[ks / 2 % SUMS][tv][tm], 0, 0, 0);
     }
     slot = slot == NST - 1 ? 0 : slot + 1;
   }
 
-  if (KW > 1) {   // wavefronts that took other k-steps of the same tiles hand their sums over, added in k-step order
+  f32x16 (&acc)[TV][TM] = sums[0];
+  if constexpr (SUMS == 2) {
+#pragma unroll
+    for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm) acc[tv][tm] += sums[1][tv][tm];
+  }
+  if constexpr (KW == 2) {   // the second wavefront hands its sums over
     lds_barrier();   // every wavefront is done with the ring
-    float* part = (float*)ring + ((wv * WM + wm) * TV * TM * 16) * 64 + lane;   // [k part - 1][wave tiles][i][lane]
-    constexpr int PART = WV * WM * TV * TM * 16 * 64;
-    static_assert((KW - 1) * PART * 4 <= NST * STAGE, "the partial sums reuse the ring");
+    float* part = (float*)ring + ((wv * WM + wm) * TV * TM * 16) * 64 + lane;   // [wave tiles][i][lane]
+    static_assert(WV * WM * TV * TM * 16 * 64 * 4 <= NST * STAGE, "the sums reuse the ring");
 #pragma unroll
     for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
       for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
         for (int i = 0; i < 16; ++i)
-          if (kw > 0) part[(kw - 1) * PART + ((tv * TM + tm) * 16 + i) * 64] = acc[tv][tm][i];
+          if (kw > 0) part[((tv * TM + tm) * 16 + i) * 64] = acc[tv][tm][i];
     lds_barrier();
     if (kw == 0) {
 #pragma unroll
@@ -164,9 +183,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
 #pragma unroll
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-          for (int i = 0; i < 16; ++i)
-#pragma unroll
-            for (int p = 0; p < KW - 1; ++p) acc[tv][tm][i] += part[p * PART + ((tv * TM + tm) * 16 + i) * 64];
+          for (int i = 0; i < 16; ++i) acc[tv][tm][i] += part[((tv * TM + tm) * 16 + i) * 64];
     }
   }
 
@@ -317,36 +334,46 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   // (start and end of a workgroup + stages times the microseconds a stage takes it), with the stage times as measured on
   // 32000 and 8000 x 4096. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64 vocabulary rows, 28.8 / 45.2 with 128; 20000 x
   // 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128; 11198 x 2560, 227 rows: 57.3 with 256 rows of `hidden`, 38.3 with 128.
+  constexpr int cus = 256;
   int mt = 0, vt = 0;
   float least = 0.f;
-  const int first_mt = M <= 32 ? 32 : M <= 64 ? 64 : 128;
-  auto consider = [&](int v, int m, float stage_us) {
-    const long wgs = (long)((V + v - 1) / v) * ((M + m - 1) / m);
-    const float us = (float)((wgs + 255) / 256) * (3.f + (float)(K / lmh::KC) * stage_us);
+  auto consider = [&](int rows, int v, int m, float stage_us) {
+    const long wgs = (long)((V + v - 1) / v) * ((rows + m - 1) / m);
+    const float us = (float)((wgs + cus - 1) / cus) * (3.f + (float)(K / lmh::KC) * stage_us);
     if (mt == 0 || us < least) { least = us; mt = m; vt = v; }
   };
-  consider(128, first_mt, first_mt == 128 ? 0.73f : 0.63f);
-  consider(64, first_mt, first_mt == 128 ? 0.42f : 0.3f);
-  if (M > 128) consider(128, 256, 1.15f);
+  consider(1, 128, 32, 0.63f);
+  consider(1, 64, 32, 0.3f);
+  const bool two = vt == 64;   // whether up to 32 rows take the 64 x 32 tile: decides the order of sums for every M
+  if (M > 32) {
+    const int first_mt = M <= 64 ? 64 : 128;
+    mt = 0;
+    consider(M, 128, first_mt, first_mt == 128 ? 0.73f : 0.63f);
+    consider(M, 64, first_mt, first_mt == 128 ? 0.42f : 0.3f);
+    if (M > 128) consider(M, 128, 256, 1.15f);
+  }
   const int m_slices = (M + mt - 1) / mt;
   const int n_vtiles = (V + vt - 1) / vt;
   const int per_row = std::min(m_slices, 16);   // slices numbered eight apart within a grid row
   const dim3 grid((unsigned)((n_vtiles + 7) / 8 * 8) * per_row, (m_slices + per_row - 1) / per_row);
-#define SPEC_LMH(VTT, MT, ST)                                                                                                 \
-  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, ST>), grid, dim3(lmh::NTHREADS), 0, s, (const __hip_bfloat16*)hidden, \
-                     (const __hip_bfloat16*)weight, part_val, part_idx, part_sum, (__hip_bfloat16*)logits_out, itl2, M, K, V,   \
-                     n_vtiles, per_row)
-#define SPEC_LMH_M(VTT, ST)                 \
-  if (mt == 32) SPEC_LMH(VTT, 32, ST);      \
-  else if (mt == 64) SPEC_LMH(VTT, 64, ST); \
-  else SPEC_LMH(VTT, 128, ST)
-#define SPEC_LMH_T(ST)                                \
-  if (mt == 256) SPEC_LMH(128, 256, ST);              \
-  else if (vt == 128) { SPEC_LMH_M(128, ST); }        \
-  else { SPEC_LMH_M(64, ST); }
-  if (stats) { SPEC_LMH_T(true); } else { SPEC_LMH_T(false); }
+#define SPEC_LMH(VTT, MT, TW, ST)                                                                                             \
+  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, TW, ST>), grid, dim3(lmh::NTHREADS), 0, s,                          \
+                     (const __hip_bfloat16*)hidden, (const __hip_bfloat16*)weight, part_val, part_idx, part_sum,              \
+                     (__hip_bfloat16*)logits_out, itl2, M, K, V, n_vtiles, per_row)
+#define SPEC_LMH_T(TW, ST)                              \
+  if (mt == 256) SPEC_LMH(128, 256, TW, ST);            \
+  else if (vt == 128 && mt == 128) SPEC_LMH(128, 128, TW, ST); \
+  else if (vt == 128) SPEC_LMH(128, 64, TW, ST);        \
+  else if (mt == 128) SPEC_LMH(64, 128, TW, ST);        \
+  else SPEC_LMH(64, 64, TW, ST)
+#define SPEC_LMH_ST(ST)                                 \
+  if (mt == 32 && two) SPEC_LMH(64, 32, true, ST);      \
+  else if (mt == 32) SPEC_LMH(128, 32, false, ST);      \
+  else if (two) { SPEC_LMH_T(true, ST); }               \
+  else { SPEC_LMH_T(false, ST); }
+  if (stats) { SPEC_LMH_ST(true); } else { SPEC_LMH_ST(false); }
+#undef SPEC_LMH_ST
 #undef SPEC_LMH_T
-#undef SPEC_LMH_M
 #undef SPEC_LMH
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;

@@ -46,3 +46,19 @@ def test_logits_at_an_eight_byte_aligned_address(spec):
     spec.spec_lm_head_logits_stats(_dev(h), _dev(w), out=out)
     torch.cuda.synchronize()
     assert torch.equal(out[0], want) and torch.equal(out[1], arg) and torch.equal(out[3], se)
+
+
+@pytest.mark.parametrize("K,V", [(768, 1000), (1024, 8000), (512, 16384), (512, 16385), (768, 20000)])
+def test_a_row_has_the_same_logits_in_a_batch_of_any_size(spec, K, V):
+    """Every tile of `hidden` and of the vocabulary sums a logit in the same order: bit-equal maxima before rounding, logits and
+    arg-max, from one row to three slices."""
+    M = 300
+    h, w = _inputs(M, K, V, seed=V + 1)
+    h, w = _dev(h), _dev(w)
+    arg, mx = spec.spec_lm_head_argmax(h, w, want_max=True)
+    logits, _, _, _ = spec.spec_lm_head_logits_stats(h, w)
+    for m in (1, 16, 32, 33, 64, 65, 128, 129, 256, 257):
+        a, x = spec.spec_lm_head_argmax(h[:m], w, want_max=True)
+        lo, _, _, _ = spec.spec_lm_head_logits_stats(h[:m], w)
+        torch.cuda.synchronize()
+        assert torch.equal(x, mx[:m]) and torch.equal(a, arg[:m]) and torch.equal(lo, logits[:m]), m

@@ -330,11 +330,11 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   int32_t* part_idx = (int32_t*)((char*)ws + arr);
   float* part_sum = stats ? (float*)((char*)ws + 2 * arr) : nullptr;
   const float itl2 = inv_temp * 1.4426950408889634f;
-  // Tile of the vocabulary and of `hidden`: the least of rounds of workgroups (256 at a time, one per compute unit) times
+  // Tile of the vocabulary and of `hidden`: the least of rounds of workgroups (one per compute unit at a time) times
   // (start and end of a workgroup + stages times the microseconds a stage takes it), with the stage times as measured on
   // 32000 and 8000 x 4096. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64 vocabulary rows, 28.8 / 45.2 with 128; 20000 x
   // 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128; 11198 x 2560, 227 rows: 57.3 with 256 rows of `hidden`, 38.3 with 128.
-  constexpr int cus = 256;
+  const int cus = compute_units();
   int mt = 0, vt = 0;
   float least = 0.f;
   auto consider = [&](int rows, int v, int m, float stage_us) {

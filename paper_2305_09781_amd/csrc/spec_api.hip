@@ -85,7 +85,7 @@ static int check_pages(const spec_attn_desc_t* d, const spec_kv_pages_t* p, Page
 
 // Compute units of the current device (256 when no device can be queried, e.g. sizing a workspace on a
 // machine without a GPU). Asked on every call: the answer belongs to the device that is current now.
-static int compute_units() {
+int compute_units() {
   int dev = 0, n = 0;
   if (hipGetDevice(&dev) == hipSuccess &&
       hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0)

@@ -55,6 +55,7 @@ struct Rope {
 };
 inline Rope no_rope() { return Rope{nullptr, nullptr, 0}; }
 
+int compute_units();   // of the current device
 AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged = false);
 
 // Tree queries handled by one workgroup of the attention kernel chosen for this shape

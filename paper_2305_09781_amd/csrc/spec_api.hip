@@ -118,6 +118,7 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
   p.m32 = p.wide && tiles > 4 && d.D == 128 && d.plan_heads_per_wg == 0;
   // workgroups the device holds at once: four-wavefront shapes of the wide kernel run two per compute unit
   const long resident = (long)compute_units() * ((p.wide && (tiles <= 4 || p.m32)) ? 2 : 1);
+  const int tile = p.wide ? SPEC_WIDE_TILE_KEYS : SPEC_SMALL_TILE_KEYS;
   if (chunk <= 0 && d.dtype == SPEC_BF16) {
     // Several requests with few (request, head) pairs and long key ranges (long-context serving, ragged lengths): the
     // bf16 kernels cut every pair's key tiles into as many equal chunks as its length asks for, about as many in all as
@@ -126,7 +127,6 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
     // idle (8 requests of 512 to 16384 keys: 257 us uncut, 195 us dealt to 512 chunks; 4 requests of 8192 to 16384: 138
     // us either way): it is used for at least 2048 keys per chunk at the stated maximum length, where 3 us are small
     // next to either. One request has no lengths to balance: fixed chunks.
-    const int tile = p.wide ? SPEC_WIDE_TILE_KEYS : SPEC_SMALL_TILE_KEYS;
     int wgs = d.plan_balanced_wgs;   // caller's hint: > 0 that many workgroups, -1 never, 0 = chosen here
     if (wgs < 0) {
       wgs = 0;
@@ -185,13 +185,25 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       if (splits > max_splits) splits = max_splits;
       chunk = (int)((max_len + splits - 1) / splits);
       if (chunk < 128) chunk = 128;
-      // Where there is room for one chunk more per pair, the prefix alone is cut, at multiples of the 64-key tile: the tree
+      // Where there is room for one chunk more per pair, the prefix alone is cut, at multiples of the kernel's tile: the tree
       // then has a short chunk of its own instead of standing behind a full one, and no chunk starts inside a tile (one
       // request, 32 heads, us: 1024 keys, trees of 40: 18.5 -> 15.2; trees of 24: 14.7 -> 13.6; 512 keys,
       // trees of 16: 14.5 -> 12.1). Not for the 32-query kernel, whose partials cost what that saves (21.6 -> 23.5).
+      // The few-query kernel's tile has 32 keys. Its chunks are rounded up to 64 all the same where the last one, which the
+      // tree's own tile makes about 64 keys longer, would otherwise be the longest: 12 heads of 1589 keys, trees of 3, in
+      // chunks of 288 (the last of 152) 24.0, of 320 (the last of 312) 26.4; 40 heads of 1704 keys in chunks of 288 (the last of
+      // 265) 22.1, of 320 (the last of 105) 21.2; two layers each.
       if (splits > 1 && !p.m32) {
-        const int whole = std::max(128, (int)round_up((size_t)((max_prefix + splits - 1) / splits), 64));
-        if (groups * ((max_len + whole - 1) / whole) <= resident) chunk = whole;
+        const int per = (max_prefix + (int)splits - 1) / (int)splits;
+        auto rounded = [&](int to) { return std::max(128, (int)round_up((size_t)per, (size_t)to)); };
+        auto fits = [&](int c) { return groups * ((max_len + c - 1) / c) <= resident; };
+        auto longest = [&](int c) { return std::max(c, max_len - (max_len - 1) / c * c + 64); };
+        if (!p.wide) {
+          chunk = fits(rounded(tile)) ? rounded(tile) : (int)round_up((size_t)chunk, tile);
+          if (fits(rounded(64)) && longest(rounded(64)) < longest(chunk)) chunk = rounded(64);
+        } else if (fits(rounded(tile))) {
+          chunk = rounded(tile);
+        }
       }
     }
     // chunks start at tile boundaries (with paged caches a tile must not straddle two blocks)

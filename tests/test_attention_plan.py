@@ -1,0 +1,50 @@
+"""The launch plans that spec_tree_attention chooses without hints, read from the size of the workspace it asks for (float32
+partials [n_splits][B][H][N][D + 2]). Without a GPU the library plans for 256 compute units."""
+import ctypes
+
+import pytest
+import torch
+
+from paper_2305_09781_amd import binding
+
+pytestmark = pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.get_device_properties(0).multi_processor_count != 256,
+                                reason="expectations are for 256 compute units")
+
+
+def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0):
+    H_kv = H_kv or H
+    S = P + N
+    d = binding.AttnDesc(B=B, H=H, H_kv=H_kv, D=D, N=N, S_cap=S, dtype=dtype, max_prefix_len=P, q_stride_b=N * H * D, q_stride_n=H * D,
+                         q_stride_h=D, kv_stride_b=H_kv * S * D, kv_stride_h=S * D, kv_stride_s=D, new_stride_b=N * H_kv * D,
+                         new_stride_n=H_kv * D, new_stride_h=D, softmax_scale=0.0, plan_chunk_keys=chunk, plan_balanced_wgs=wgs,
+                         plan_heads_per_wg=0)
+    got = binding.load().spec_tree_attention_workspace_bytes(ctypes.byref(d))
+    up = lambda x: (x + 255) // 256 * 256  # noqa: E731
+    for n in range(1, 600):
+        rows = B * H * n * N
+        if n > 1 and up(rows * D * 4) + up(rows * 8) == got:
+            return n
+    assert got == 0
+    return 1
+
+
+@pytest.mark.parametrize("B,H,H_kv,D,N,P,chunks", [
+    # few-query kernel: chunks of the prefix at multiples of 32 keys
+    (1, 12, 12, 128, 3, 1589, 6),       # 288 keys, the last chunk 152 (chunks of 320 would end in one of 312)
+    (2, 12, 12, 128, 1, 1874, 7),
+    (2, 12, 12, 64, 2, 1883, 7),
+    # ... at multiples of 64 where the last one would be as long as the others
+    (1, 32, 32, 64, 3, 1414, 5),        # 320, the last 137 (288 would end in 265)
+    (1, 12, 12, 128, 12, 554, 2),
+    # wide kernel: multiples of its 64-key tile
+    (2, 32, 8, 128, 3, 4825, 16),
+    (1, 24, 6, 128, 7, 3205, 11),
+    (1, 32, 32, 128, 40, 1024, 5),      # the tree in a chunk of its own
+    # the 32-query kernel keeps equal chunks of everything
+    (1, 32, 32, 128, 100, 1024, 4),
+    # one workgroup per pair
+    (8, 32, 32, 128, 16, 1024, 1),
+    (1, 4, 4, 64, 8, 128, 1),
+])
+def test_fixed_chunks(B, H, H_kv, D, N, P, chunks):
+    assert _slots(B, H, D, N, P, H_kv) == chunks

@@ -64,8 +64,10 @@ __device__ __forceinline__ bool beats(float v2, int i2, float v1, int i1) { retu
 // STATS: the logits are also written out, rounded to bf16, and every partial carries the sum of
 // exp((x - max) / T) over the workgroup's vocabulary rows - of the ROUNDED values, which are what a verifier
 // reading those logits will see (maximum and arg-max are then those of the rounded values too).
-template <int VT, int MT, bool TWO, bool STATS>
-__global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
+// RING_KB: the ring's share of the LDS. 128: one workgroup per compute unit with as many stages in flight as fit; 64 (up to 32
+// rows): two workgroups, whose starts and ends overlap.
+template <int VT, int MT, int RING_KB, bool TWO, bool STATS>
+__global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
                                                                     const __hip_bfloat16* __restrict__ weight,
                                                                     float* __restrict__ part_val, int32_t* __restrict__ part_idx,
                                                                     float* __restrict__ part_sum,
@@ -76,7 +78,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
   constexpr int SUMS = TWO && KW == 1 ? 2 : 1;
   constexpr int TV = VT / WV / 32, TM = MT / WM / 32;               // 32 x 32 tiles of a wavefront
   constexpr int W_BYTES = VT * ROWB, STAGE = W_BYTES + MT * ROWB;
-  constexpr int NST = MT == 256 ? 3 : (128 << 10) / STAGE < 8 ? (128 << 10) / STAGE : 8, AHEAD = NST - 1;
+  constexpr int NST = MT == 256 ? 3 : (RING_KB << 10) / STAGE < 8 ? (RING_KB << 10) / STAGE : 8, AHEAD = NST - 1;
   constexpr int WL = VT / 32, HL = MT / 32, LPS = WL + HL;          // loads per lane and stage: 32 rows of eight pieces each
   constexpr int CROW = VT * 2 + 16;                                 // LDS bytes per row of the logits on their way out
   static_assert(MT * CROW <= NST * STAGE, "the logits reuse the ring");
@@ -84,6 +86,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
   __shared__ float s_val[WV][MT];
   __shared__ int s_idx[WV][MT];
   __shared__ float s_sum[STATS ? WV : 1][MT];
+  __shared__ float s_part[KW == 2 ? WV * WM * TV * TM * 16 * 64 : 1];
 
   const int blk = uniform(blockIdx.x / (8 * slices_per_row)), in_blk = blockIdx.x - blk * 8 * slices_per_row;
   const int vt = blk * 8 + in_blk % 8, slice = blockIdx.y * slices_per_row + in_blk / 8;
@@ -166,9 +169,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
       for (int tm = 0; tm < TM; ++tm) acc[tv][tm] += sums[1][tv][tm];
   }
   if constexpr (KW == 2) {   // the second wavefront hands its sums over
-    lds_barrier();   // every wavefront is done with the ring
-    float* part = (float*)ring + ((wv * WM + wm) * TV * TM * 16) * 64 + lane;   // [wave tiles][i][lane]
-    static_assert(WV * WM * TV * TM * 16 * 64 * 4 <= NST * STAGE, "the sums reuse the ring");
+    float* part = s_part + ((wv * WM + wm) * TV * TM * 16) * 64 + lane;   // [wave tiles][i][lane]
 #pragma unroll
     for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
@@ -189,7 +190,7 @@ __global__ void __launch_bounds__(NTHREADS, 1) lm_head_argmax_kernel(const __hip
 
   // ---- tile (tv, tm): the lane holds row m0 + (wm TM + tm) 32 + r, vocabulary rows v0 + (wv TV + tv) 32 + 8 (i / 4) + 4 h + i % 4
   if (STATS) {   // round to the stored type first: statistics and arg-max are those of the stored logits
-    lds_barrier();   // every wavefront is done with the ring: the logits go through it, to leave as whole rows
+    if (KW == 1) lds_barrier();   // every wavefront is done with the ring: the logits go through it, to leave as whole rows
     if (kw == 0)
 #pragma unroll
     for (int tm = 0; tm < TM; ++tm)
@@ -352,23 +353,30 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
     consider(M, 64, first_mt, first_mt == 128 ? 0.42f : 0.3f);
     if (M > 128) consider(M, 128, 256, 1.15f);
   }
+  // 128 x 32 tiles: two workgroups per compute unit for short sums, whose starts and ends would otherwise stand by themselves,
+  // one with a long ring for long ones (16 rows, arg-max only, us, one / two: 32000 x 4096 51.5 / 55.4, x 2048 30.1 / 29.9, x 512
+  // 11.3 / 10.5, x 256 9.1 / 8.3; 50257 x 512 17.3 / 13.8; 128256 x 4096 202 / 207, x 2048 110 / 104, x 512 33 / 25, x 256
+  // 24.5 / 16.9, where W straight into registers took 201, 107, 30 and 18.9). 64 x 32 tiles gain from two at every K (16000 x
+  // 4096 30.0 / 28.3, 8000 x 512 8.4 / 8.1).
+  const bool pairs = K <= 2048;
   const int m_slices = (M + mt - 1) / mt;
   const int n_vtiles = (V + vt - 1) / vt;
   const int per_row = std::min(m_slices, 16);   // slices numbered eight apart within a grid row
   const dim3 grid((unsigned)((n_vtiles + 7) / 8 * 8) * per_row, (m_slices + per_row - 1) / per_row);
-#define SPEC_LMH(VTT, MT, TW, ST)                                                                                             \
-  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, TW, ST>), grid, dim3(lmh::NTHREADS), 0, s,                          \
+#define SPEC_LMH(VTT, MT, RK, TW, ST)                                                                                         \
+  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, RK, TW, ST>), grid, dim3(lmh::NTHREADS), 0, s,                          \
                      (const __hip_bfloat16*)hidden, (const __hip_bfloat16*)weight, part_val, part_idx, part_sum,              \
                      (__hip_bfloat16*)logits_out, itl2, M, K, V, n_vtiles, per_row)
 #define SPEC_LMH_T(TW, ST)                              \
-  if (mt == 256) SPEC_LMH(128, 256, TW, ST);            \
-  else if (vt == 128 && mt == 128) SPEC_LMH(128, 128, TW, ST); \
-  else if (vt == 128) SPEC_LMH(128, 64, TW, ST);        \
-  else if (mt == 128) SPEC_LMH(64, 128, TW, ST);        \
-  else SPEC_LMH(64, 64, TW, ST)
+  if (mt == 256) SPEC_LMH(128, 256, 128, TW, ST);            \
+  else if (vt == 128 && mt == 128) SPEC_LMH(128, 128, 128, TW, ST); \
+  else if (vt == 128) SPEC_LMH(128, 64, 128, TW, ST);        \
+  else if (mt == 128) SPEC_LMH(64, 128, 128, TW, ST);        \
+  else SPEC_LMH(64, 64, 128, TW, ST)
 #define SPEC_LMH_ST(ST)                                 \
-  if (mt == 32 && two) SPEC_LMH(64, 32, true, ST);      \
-  else if (mt == 32) SPEC_LMH(128, 32, false, ST);      \
+  if (mt == 32 && two) SPEC_LMH(64, 32, 64, true, ST);  \
+  else if (mt == 32 && pairs) SPEC_LMH(128, 32, 64, false, ST); \
+  else if (mt == 32) SPEC_LMH(128, 32, 128, false, ST); \
   else if (two) { SPEC_LMH_T(true, ST); }               \
   else { SPEC_LMH_T(false, ST); }
   if (stats) { SPEC_LMH_ST(true); } else { SPEC_LMH_ST(false); }

@@ -202,7 +202,13 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
           chunk = fits(rounded(tile)) ? rounded(tile) : (int)round_up((size_t)chunk, tile);
           if (fits(rounded(64)) && longest(rounded(64)) < longest(chunk)) chunk = rounded(64);
         } else if (fits(rounded(tile))) {
-          chunk = rounded(tile);
+          // (in tiles: the longest chunk, or the last with the tree's masked tiles behind it. With workgroups to spare only that
+          // counts: 2 requests x 8 K/V heads of 2191 keys, trees of 5, in chunks of 288, the last of 180: 15.2 us, of 320, the
+          // last of 276: 15.7. With a workgroup per compute unit and more, fewer chunks do less in all: 32 heads of 4432 keys,
+          // trees of 20, two layers: 49.3 / 45.3.)
+          auto steps = [&](int c) { return std::max((c + 63) / 64, (max_len - (max_len - 1) / c * c + 63) / 64 + 1); };
+          const int equal = (int)round_up((size_t)chunk, paged ? 64 : 32);
+          if (groups * ((max_len + equal - 1) / equal) > resident / 2 || steps(rounded(tile)) <= steps(equal)) chunk = rounded(tile);
         }
       }
     }

@@ -40,6 +40,10 @@ def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0):
     (2, 32, 8, 128, 3, 4825, 16),
     (1, 24, 6, 128, 7, 3205, 11),
     (1, 32, 32, 128, 40, 1024, 5),      # the tree in a chunk of its own
+    (1, 32, 32, 128, 20, 4432, 14),
+    # ... unless the last of them would be the longest, where there are workgroups to spare
+    (2, 32, 8, 128, 5, 2191, 8),
+    (1, 32, 8, 64, 2, 3477, 13),
     # the 32-query kernel keeps equal chunks of everything
     (1, 32, 32, 128, 100, 1024, 4),
     # one workgroup per pair

@@ -58,15 +58,8 @@ inline Rope no_rope() { return Rope{nullptr, nullptr, 0}; }
 int compute_units();   // of the current device
 AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged = false);
 
-// Tree queries handled by one workgroup of the attention kernel chosen for this shape
-// (bf16: 16 / 32 in the few-query kernel, 64 / 128 in the wide-tree kernel; float32: all of them).
 #define SPEC_SMALL_TILE_KEYS 32   // keys per wavefront tile of the few-query bf16 kernel (N <= 16)
 #define SPEC_WIDE_TILE_KEYS 64    // keys per workgroup tile of the wide bf16 kernel (N > 16)
-
-inline int attn_queries_per_workgroup(const spec_attn_desc_t& d) {
-  if (d.dtype != SPEC_BF16) return SPEC_MAX_TREE_NODES;
-  return d.N <= 16 ? 16 : d.N <= 32 ? 32 : d.N <= 64 ? 64 : 128;
-}
 
 // Workgroups of a balanced launch: the chunks the deal aims at, or one per (request, virtual head) pair.
 inline unsigned balanced_grid(const AttnPlan& p, int B, int virtual_heads) {
@@ -102,6 +95,24 @@ inline int f32_query_tiles(const spec_attn_desc_t& d) { return (long)(d.H / d.H_
 inline int f32_query_groups(const spec_attn_desc_t& d) {
   const int per_wg = 16 * f32_query_tiles(d);
   return (int)(((long)(d.H / d.H_kv) * d.N + per_wg - 1) / per_wg);
+}
+
+// Arithmetic of the balanced deal (see balanced_deal), shared by the kernels and by a host test.
+// Tiles of a request; none if it does not fit the capacity.
+__host__ __device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
+  return (P >= 0 && P <= S_cap - N) ? (P + N + tile - 1) / tile : 0;
+}
+// Chunks of a request with tb tiles: their number, and the tiles of each but the last.
+__host__ __device__ inline int deal_chunks(int tb, int share) { return (int)((unsigned)(tb + share - 1) / (unsigned)share); }
+__host__ __device__ inline int deal_chunk_tiles(int tb, int chunks) { return (int)((unsigned)(tb + chunks - 1) / (unsigned)chunks); }
+// Number r of a request's chunks (over all virtual heads): its (K/V head, chunk) unit and its query group. The query groups
+// of a unit read the same keys: whole blocks of eight units are numbered so that a unit's groups are eight apart, which puts
+// them on one XCD; what is left over takes them in a row.
+struct DealUnit { int unit, qg; };
+__host__ __device__ inline DealUnit deal_unit(int r, int n_qg, int units) {
+  const int blk = r / (8 * n_qg), rr = r % (8 * n_qg);
+  if (n_qg > 1 && (blk + 1) * 8 <= units) return {blk * 8 + rr % 8, rr / 8};
+  return {r / n_qg, r % n_qg};
 }
 
 // Strides of k_new / v_new (all zero in the descriptor: laid out like q).
@@ -251,9 +262,6 @@ __device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, const i
 //
 // All functions read prefix_len[] with the 64 lanes of a wavefront at once (a scalar walk is one dependent load per
 // request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
-__device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
-  return (P >= 0 && P <= S_cap - N) ? (P + N + tile - 1) / tile : 0;
-}
 // a / b of non-negative numbers, in 32 bits where they fit (a 64-bit division is some hundred instructions)
 __device__ inline long deal_div(long a, long b) {
   return ((a | b) >> 32) == 0 ? (long)((unsigned)a / (unsigned)b) : a / b;
@@ -270,9 +278,6 @@ __device__ inline int wave_inclusive_sum(int v) {
   return v;
 }
 __device__ inline int wave_sum_uniform(int v) { return __builtin_amdgcn_readlane(wave_inclusive_sum(v), 63); }
-// Chunks of a request with tb tiles: their number, and the tiles of each but the last.
-__device__ inline int deal_chunks(int tb, int share) { return (int)((unsigned)(tb + share - 1) / (unsigned)share); }
-__device__ inline int deal_chunk_tiles(int tb, int chunks) { return (int)((unsigned)(tb + chunks - 1) / (unsigned)chunks); }
 
 struct BalancedDeal {
   int share;    // most tiles of a chunk (>= 1)
@@ -309,8 +314,7 @@ __device__ inline BalancedDeal balanced_deal(const int32_t* __restrict__ prefix_
   }
 }
 // Chunk `id` (< count) of the deal: request, head, tiles [tile0, tile0 + n_tiles) (none if rounding leaves the request
-// fewer chunks than it was counted with) and the request's chunks per head. The query groups of one K/V head (n_qg heads
-// in a row) read the same keys: a chunk's groups are numbered eight apart where they can be, which puts them on one XCD.
+// fewer chunks than it was counted with) and the request's chunks per head.
 struct DealChunk {
   int b, h, chunk, tile0, n_tiles, chunks;
 };
@@ -330,14 +334,9 @@ __device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, in
       c.chunks = __builtin_amdgcn_readlane(v, f);
       c.b = b0 + f;
       const int r = (int)(id - (acc + __builtin_amdgcn_readlane(incl, f) - c.chunks) * H);   // < H * chunks
-      int unit = r / n_qg, qg = r % n_qg;   // unit: (K/V head, chunk)
-      const int blk = r / (8 * n_qg), rr = r % (8 * n_qg);
-      if (n_qg > 1 && (blk + 1) * 8 <= H / n_qg * c.chunks) {
-        unit = blk * 8 + rr % 8;
-        qg = rr / 8;
-      }
-      c.chunk = unit % c.chunks;
-      c.h = unit / c.chunks * n_qg + qg;
+      const DealUnit u = deal_unit(r, n_qg, H / n_qg * c.chunks);
+      c.chunk = u.unit % c.chunks;
+      c.h = u.unit / c.chunks * n_qg + u.qg;
       const int per = deal_chunk_tiles(tb, c.chunks);
       c.tile0 = c.chunk * per;
       c.n_tiles = max(0, min(per, tb - c.tile0));

@@ -1,0 +1,81 @@
+"""The balanced deal's arithmetic on the host: which (K/V head, chunk, query group) a workgroup gets is a permutation, chunks
+cover a request's tiles. The functions are the kernels' own (csrc/spec_internal.h), compiled for the host."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PROGRAM = r"""
+#include <cstdio>
+#include <cstdlib>
+#include <vector>
+#include "spec_internal.h"
+using namespace spec;
+static void check(bool ok, const char* what, int a, int b, int c) {
+  if (!ok) { printf("%s: %d %d %d\n", what, a, b, c); exit(1); }
+}
+int main() {
+  for (int n_qg = 1; n_qg <= 9; ++n_qg)
+    for (int units = 1; units <= 130; ++units) {
+      std::vector<int> at(units * n_qg, -1);
+      for (int r = 0; r < units * n_qg; ++r) {
+        const DealUnit u = deal_unit(r, n_qg, units);
+        check(u.unit >= 0 && u.unit < units && u.qg >= 0 && u.qg < n_qg, "range", r, n_qg, units);
+        int& place = at[u.unit * n_qg + u.qg];
+        check(place < 0, "twice", r, n_qg, units);
+        place = r;
+      }
+      for (int u = 0; u < units / 8 * 8; ++u)      // the groups of a unit in a whole block: on one of the eight XCDs
+        for (int g = 1; g < n_qg; ++g)
+          check((at[u * n_qg + g] - at[u * n_qg]) % 8 == 0, "XCD", u, n_qg, units);
+    }
+  for (int tb = 1; tb <= 400; ++tb)
+    for (int share = 1; share <= 90; ++share) {
+      const int chunks = deal_chunks(tb, share), per = deal_chunk_tiles(tb, chunks), used = deal_chunks(tb, per);
+      check(per >= 1 && per <= share, "share", tb, share, per);
+      check(used <= chunks && (used > 1) == (chunks > 1), "count", tb, share, used);   // the merge relies on both
+      check(per * (used - 1) < tb && tb <= per * used, "cover", tb, share, per);
+    }
+  check(request_tiles(-1, 16, 100, 64) == 0 && request_tiles(85, 16, 100, 64) == 0 && request_tiles(84, 16, 100, 64) == 2 &&
+        request_tiles(0, 1, 1, 32) == 1, "tiles", 0, 0, 0);
+  puts("ok");
+}
+"""
+
+
+def cut_into(lens, N, virtual_heads, tile, wgs):
+    """Chunks per (request, virtual head) pair of a deal that aims at `wgs` chunks, as the kernels find them."""
+    tiles = [-(-(p + N) // tile) for p in lens]
+    cap = max(wgs, virtual_heads * len(tiles))
+    share = max(1, -(-sum(tiles) * virtual_heads // cap))
+    while virtual_heads * sum(-(-t // share) for t in tiles) > cap:
+        share = max(share + 1, share * virtual_heads * sum(-(-t // share) for t in tiles) // cap)
+    return [-(-t // -(-t // -(-t // share))) for t in tiles]
+
+
+def query_groups(H, H_kv, N):
+    """Query groups per K/V head in the bf16 kernels: whole heads, eight 16-query tiles a workgroup at most."""
+    group, per_head = H // H_kv, -(-N // 16)
+    return -(-group // min(group, max(1, 8 // per_head)))
+
+
+def test_deal_is_a_permutation_and_covers_every_tile(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None or not os.path.isdir("/opt/rocm/include"):
+        pytest.skip("needs a host compiler and the HIP headers")
+    src, exe = tmp_path / "deal.cc", tmp_path / "deal"
+    src.write_text(PROGRAM)
+    subprocess.run([cxx, "-std=c++17", "-O1", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + os.path.join(ROOT, "paper_2305_09781_amd", "csrc"), str(src), "-o", str(exe)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", r.stdout
+
+
+def test_small_hints_leave_pairs_whole():
+    """A pair is cut only if the hint leaves room for it: tests that mean to cut pairs check it with cut_into."""
+    assert cut_into([40, 170, 300], 32, 2, 64, 7) == [1, 1, 1]
+    assert cut_into([40, 170, 300], 32, 2, 64, 24) == [2, 4, 6]
+    assert query_groups(32, 2, 16) == 2 and query_groups(12, 2, 40) == 3 and query_groups(32, 32, 128) == 1

@@ -1,5 +1,5 @@
 """The balanced deal over more requests than a wavefront has lanes (lengths are read 64 requests at a time), with requests
-that contribute no tiles, on every bf16 kernel. Bar: that of the other attention tests."""
+that contribute no tiles, on every bf16 kernel, pairs whole and cut. Bar: that of the other attention tests."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +10,8 @@ from test_gpu_parity import _balanced_wgs, _check_attention, _oracle_append_atte
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("B,N,wgs", [(63, 5, 17), (64, 5, 200), (65, 20, 31), (130, 5, 300), (70, 70, 90), (30, 5, 130), (70, 16, 300)])
+@pytest.mark.parametrize("B,N,wgs", [(63, 5, 17), (64, 5, 200), (65, 20, 31), (130, 5, 300), (70, 70, 90), (30, 5, 130), (70, 16, 300),
+                                     (65, 20, 300), (70, 70, 320), (66, 100, 330)])
 def test_deal_over_many_requests(spec, B, N, wgs):
     cfg = wl.Config(91, "deal", "bf16", B=B, H=2, D=128, P=(0, 200), N=N, tree="random_branching")
     inp = wl.make_attention_inputs(cfg, seed=4000 + B, S_cap=200 + N)

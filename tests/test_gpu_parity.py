@@ -73,7 +73,8 @@ def _chunk_keys(n):
 
 
 def _balanced_wgs(n):
-    """Forces the balanced plan (equal shares of key tiles over n workgroups) on small inputs."""
+    """Forces the balanced plan on small inputs: pairs cut into n chunks in all, or left whole if there are not many fewer pairs
+    than n (the few-query kernel then takes n equal contiguous shares of all tiles)."""
     return _plan_hint(1, n)
 
 
@@ -347,8 +348,10 @@ GROUPED = [
     ("bf16", 2, 16, 1, 128, (40, 300), 16, "expansion", 0, 0),        # 16 heads, one K/V head: 2 query groups of 8
     ("bf16", 2, 12, 2, 128, (40, 300), 33, "random_branching", 64, 0),  # 3 tiles per head: 2 heads per workgroup, 3 groups
     ("bf16", 1, 71, 1, 64, (100, 100), 16, "expansion", 0, 0),       # multi-query attention, 71 heads: 9 groups, last one short
-    ("bf16", 2, 20, 2, 64, (30, 500), 16, "random_parent", 0, 9),    # query groups under the balanced plan
+    ("bf16", 2, 20, 2, 64, (30, 500), 16, "random_parent", 0, 9),    # query groups under the balanced plan, pairs whole
+    ("bf16", 2, 20, 2, 64, (30, 500), 16, "random_parent", 0, 40),   # ... and cut
     ("bf16", 1, 6, 1, 128, (64, 64), 128, "random_branching", 0, 4), # 8 tiles per head: one head per workgroup
+    ("bf16", 1, 6, 1, 128, (64, 64), 128, "random_branching", 0, 18),
 ]
 
 
@@ -514,7 +517,7 @@ def test_prefix_above_the_stated_maximum_is_flagged_not_truncated(spec, N, dtype
 
 
 BALANCED = [
-    # B, H, D, (P lo, hi), N, tree, workgroups
+    # B, H, D, (P lo, hi), N, tree, workgroups (wide kernels leave pairs whole at the small ones; cut pairs: test_gpu_cut_pairs.py)
     (3, 2, 128, (40, 300), 16, "expansion", 5),
     (3, 2, 128, (40, 300), 32, "random_branching", 7),
     (4, 3, 128, (0, 100), 7, "random_parent", 64),      # more workgroups than tiles: shares of one tile
@@ -530,8 +533,8 @@ BALANCED = [
 
 @pytest.mark.parametrize("case", BALANCED, ids=[f"B{c[0]}H{c[1]}D{c[2]}P{c[3][0]}-{c[3][1]}N{c[4]}-{c[5]}-wg{c[6]}" for c in BALANCED])
 def test_balanced_plan_attention_and_append(spec, case):
-    """The balanced plan of the bf16 kernels: shares that start and end inside a pair, cross pair and
-    request boundaries, or are empty."""
+    """The balanced plan of the bf16 kernels: contiguous shares of the few-query kernel that start and end inside a pair, cross
+    pair and request boundaries, or are empty; chunks of one tile; whole pairs in more workgroups than were asked for."""
     B, H, D, P, N, tree, wgs = case
     cfg = wl.Config(92, "balanced", "bf16", B=B, H=H, D=D, P=P if P[0] != P[1] else P[0], N=N, tree=tree,
                     widths=wl.EXPANSION_EVAL * 2)
@@ -598,7 +601,7 @@ def test_large_configs_every_request_and_head(spec, c, fused):
 def test_attention_status_bits_and_noop(spec, N):
     """Malformed trees and requests that do not fit are flagged and produce zeros; others unaffected."""
     cfg = wl.Config(91, "bad", "bf16", B=4, H=2, D=128, P=(40, 90), N=N, tree="random_parent")
-    plans = [(0, False, 0), (64, False, 0), (0, True, 0), (64, True, 0), (0, False, 5), (0, True, 3)]
+    plans = [(0, False, 0), (64, False, 0), (0, True, 0), (64, True, 0), (0, False, 5), (0, True, 3), (0, False, 24), (0, True, 24)]
     for chunk, fused, wgs in plans:
         inp = wl.make_attention_inputs(cfg, seed=5, S_cap=90 + N)
         inp["tree_parent"][1, 5] = 9            # parent after child

@@ -31,11 +31,15 @@ CASES = [
     (2, 16, 1, 128, (40, 300), 16, "expansion", 0, 0, 0),          # 2 query groups per K/V head: both rotate, one stores
     (2, 3, 3, 64, (30, 280), 100, "random_branching", 0, 0, 0),    # 8 wavefronts of 16 queries (D = 64)
     (2, 4, 4, 64, (30, 280), 128, "expansion", 0, 0, 2),           # ... two heads per workgroup as one stream
-    (2, 2, 2, 64, (100, 500), 77, "random_branching", 0, 7, 0),    # ... balanced deal
+    (2, 2, 2, 64, (100, 500), 77, "random_branching", 0, 7, 0),    # ... balanced deal, pairs whole
+    (2, 2, 2, 64, (100, 500), 77, "random_branching", 0, 20, 0),   # ... and cut
+    (2, 2, 2, 128, (100, 500), 12, "random_branching", 0, 20, 0),  # few-query kernel, pairs cut
+    (2, 4, 2, 128, (100, 500), 16, "random_branching", 0, 20, 0),  # grouped heads, pairs cut
     (2, 3, 3, 128, (30, 280), 128, "expansion", 0, 0, 0),          # 4 wavefronts of 32 queries
     (3, 2, 2, 128, (0, 300), 65, "random_branching", 0, 0, 0),     # ... ragged tree tail, empty prefix possible
     (2, 2, 2, 128, (200, 700), 100, "random_branching", 128, 0, 0),  # ... chunks
-    (2, 3, 3, 128, (100, 500), 90, "random_parent", 0, 7, 0),      # ... balanced deal
+    (2, 3, 3, 128, (100, 500), 90, "random_parent", 0, 7, 0),      # ... balanced deal, pairs whole
+    (2, 3, 3, 128, (100, 500), 90, "random_parent", 0, 30, 0),     # ... and cut
     (2, 6, 1, 128, (64, 64), 128, "random_branching", 0, 0, 0),    # ... one K/V head, six query groups
 ]
 
@@ -89,7 +93,9 @@ def test_rotary_embedding_inside_the_fused_launch(spec, case):
 @pytest.mark.parametrize("case", [(2, 4, 4, 128, (100, 400), 16, "expansion", 64, 0, 0),
                                   (2, 8, 2, 128, (60, 330), 40, "random_branching", 64, 0, 0),
                                   (2, 2, 2, 128, (190, 460), 128, "random_branching", 256, 128, 0),
-                                  (2, 2, 2, 64, (130, 400), 100, "expansion", 128, 0, 5)],
+                                  (2, 2, 2, 64, (130, 400), 100, "expansion", 128, 0, 5),
+                                  (2, 2, 2, 64, (130, 400), 100, "expansion", 128, 0, 20),
+                                  (2, 2, 2, 128, (130, 400), 100, "random_branching", 128, 0, 20)],
                          ids=lambda c: f"B{c[0]}-H{c[1]}/{c[2]}-D{c[3]}-N{c[5]}-bt{c[7]}-c{c[8]}-w{c[9]}")
 def test_rotary_embedding_inside_the_fused_launch_paged(spec, case):
     B, H, H_kv, D, P, N, tree, bt, chunk, wgs = case

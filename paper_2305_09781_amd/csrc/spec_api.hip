@@ -155,7 +155,7 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       p.balanced_wgs = wgs;
       p.balanced_tile = tile;
       p.contiguous = !p.wide && wgs < 2 * groups;
-      p.chunk_keys = wgs;
+      p.chunk_keys = 0;
       p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair has at most this many chunks
     }
   }

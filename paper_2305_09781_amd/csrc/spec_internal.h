@@ -18,9 +18,9 @@ namespace spec {
 // (request, head) is cut into chunks (one workgroup each) and where the partial results live.
 // ---------------------------------------------------------------------------------------------
 struct AttnPlan {
-  int chunk_keys;   // keys per workgroup (multiple of 32)
+  int chunk_keys;   // fixed chunks: keys per workgroup (multiple of 32)
   int n_splits;     // chunks covering max_prefix_len + N; balanced plan: partial slots per (request, head)
-  int balanced_wgs; // > 0: balanced plan that aims at this many chunks (see balanced_deal), chunk_keys holds it too
+  int balanced_wgs; // > 0: balanced plan that aims at this many chunks (see balanced_deal), chunk_keys is 0
   int balanced_tile;// keys per tile of the balanced deal (the tile of the kernel that runs the plan)
   bool contiguous;  // balanced plan as equal contiguous shares of all tiles (see contiguous_deal), few-query kernel only
   bool wide;        // bf16: the wide kernel runs the plan (several query tiles per K/V head, or k_new not laid out like q)

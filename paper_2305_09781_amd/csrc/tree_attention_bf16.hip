@@ -4,8 +4,8 @@
 // so the kernel is bound by streaming K and V from HBM exactly once.
 //
 // Decomposition
-//   grid = (n_splits, H, B), or (BAL) gridDim.x workgroups that share the 32-key tiles of all
-//   (request, head) pairs evenly (see balanced_deal()). A workgroup owns one segment of the key
+//   grid = (n_splits, H, B), or (PLAN 1, 2) workgroups that share the 32-key tiles of all (request, head)
+//   pairs evenly (see balanced_deal() and contiguous_deal()). A workgroup owns one segment of the key
 //   range of one (request, head) at a time and all its tree queries. It has five wavefronts:
 //     - four streaming wavefronts take the chunk's mask-free 32-key tiles (entirely inside the cached
 //       prefix) round-robin; they never need the tree, a mask, or a barrier inside their loop;
@@ -21,8 +21,8 @@
 //                 B = Q^T resident in registers. The transposed product leaves lane l with scores of
 //                 query l%16 for keys 4*(l/16)+v of each 16-key half: exactly the B-operand layout
 //                 P^T needs for the second product, so probabilities never leave registers.
-//   mask          tail wavefront only: bit (key - prefix_len) of the query's 128-bit ancestor-or-self
-//                 mask (built from the parent array by walking up the parent chain in LDS).
+//   mask          tail wavefront only: bit (key - prefix_len) of the query's ancestor-or-self mask of 16 bits,
+//                 built between the lanes by pointer doubling (a lane holds a node).
 //   softmax       online, in the exp2 domain, with a lazy running maximum (refreshed, with two cross-lane
 //                 exchanges and a rescale of the lane-local O^T fragment, only when a score outgrows it).
 //   O^T += V^T P^T  A = V^T needs 8 keys x 1 d per lane, the transpose of how V lies in memory: V is
@@ -166,14 +166,17 @@ __device__ __forceinline__ void issue_tile_loads(const TileSrc& s, int k0, int P
 // PAGED: the caches are pools of blocks addressed through pg.table (see cache_row_offset). A wavefront's
 // 32-key tile starts at a multiple of 32 rows and a block holds a multiple of 64, so a tile lies inside one
 // block: its rows are addressed as in a contiguous cache plus one per-tile offset (page_shift below).
-// PLAN: 0 fixed chunks, 1 the balanced deal, 2 its contiguous form.
+// PLAN: 0 fixed chunks, 1 the balanced deal, 2 its contiguous form. work: keys per chunk (0), chunks the deal aims at (1).
+// NT and n_qgroups are 1 (larger trees and grouped heads go to the wide kernels). Both stay written out: without n_qgroups the
+// first loads come in another order, which costs 8 requests of 1024 keys 1.2 % (trees of 16, rotary) to 2.3 % (trees of 7), and
+// without NT one request loses 0.9 %.
 template <int D, int NT, bool APPEND, int PLAN, bool PAGED>
 __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const __hip_bfloat16* __restrict__ q, __hip_bfloat16* k_cache, __hip_bfloat16* v_cache,
     const __hip_bfloat16* __restrict__ k_new, const __hip_bfloat16* __restrict__ v_new,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, const int32_t* __restrict__ prefix_len,
     __hip_bfloat16* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml, int32_t* status, int B, int N,
-    int H, int S_cap, int n_qgroups, int chunk_keys, int n_splits, long q_sb, long q_sn, long q_sh, long kv_sb,
+    int H, int S_cap, int n_qgroups, int work, int n_splits, long q_sb, long q_sn, long q_sh, long kv_sb,
     long kv_sh, long kv_ss, float scale_log2, Pages pg, Rope rope) {
   using T = AttnTraits<D, NT>;
   constexpr int KS = T::KS, DB = T::DB, LPR = T::LPR, RPI = T::RPI, NVL = T::NVL, VROW = T::VROW, NQ = T::NQ,
@@ -208,7 +211,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   // ---- straight-line prologue (no branch before the first loads, so every kernel argument is
   // fetched in one batch): the streaming wavefronts' first tile does not depend on prefix_len (rows
   // clamped to the cache capacity keep the addresses valid; the tail wavefront's copy is discarded),
-  // Q, and two tree nodes per lane for the tail wavefront.
+  // Q, and a tree node per lane.
   const int P = prefix_len[b];
   TileSrc src;
   src.cache_row_bytes = (unsigned)kv_ss * 2u;
@@ -534,7 +537,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const int split = blockIdx.x;
     const int h = uniform_div(blockIdx.y, n_qgroups), qg = blockIdx.y - h * n_qgroups;
     const int b = blockIdx.z;
-    segment(b, h, qg, split * chunk_keys, split * chunk_keys + chunk_keys,
+    segment(b, h, qg, split * work, split * work + work,
             n_splits == 1 ? -1l : partial_row<false>(b, h, split, B, H, N, n_splits));
   } else if constexpr (PLAN == 2) {
     // Equal contiguous shares of all pairs' tiles; the workgroups overlapping a pair fill slots 0, 1, ... in order.
@@ -561,7 +564,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     }
   } else {
     // Balanced stream: the 32-key tiles of every pair in equal chunks, as many as the request's length asks for.
-    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H, S_cap, TILE, chunk_keys);
+    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H, S_cap, TILE, work);
     if ((long)blockIdx.x >= deal.count) return;
     const DealChunk c = deal_find(prefix_len, B, N, H, 1, S_cap, TILE, deal, blockIdx.x);
     if (c.n_tiles > 0)
@@ -591,7 +594,7 @@ hipError_t launch_tree_attention_bf16(const spec_attn_desc_t& d, const AttnPlan&
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,               \
                      (const __hip_bfloat16*)k_new, (const __hip_bfloat16*)v_new, parent, depth, prefix_len,      \
                      (__hip_bfloat16*)out, ws_o, ws_ml, status, d.B, d.N, d.H, d.S_cap, n_qgroups,               \
-                     plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h, \
+                     bal ? plan.balanced_wgs : plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h, \
                      (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg, rope)
 #define SPEC_DIMS(APP, PLAN, PGD)                      \
   if (d.D == 128) SPEC_LAUNCH(128, 1, APP, PLAN, PGD); \

@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     const __hip_bfloat16* __restrict__ k_new, const __hip_bfloat16* __restrict__ v_new,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, const int32_t* __restrict__ prefix_len,
     __hip_bfloat16* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml, int32_t* status, int B, int N,
-    int H, int H_v, int n_qg, int hpw, int heads_per_wg, int S_cap, int chunk_keys, int n_splits, long q_sb, long q_sn, long q_sh, long n_sb, long n_sn,
+    int H, int H_v, int n_qg, int hpw, int heads_per_wg, int S_cap, int chunk_keys, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh, long n_sb, long n_sn,
     long n_sh, long kv_sb, long kv_sh, long kv_ss, float scale_log2, Pages pg, Rope rope) {
   static_assert(KW == 1 || KW == 2, "a 64-key tile is consumed as two 32-key halves");
   static_assert(DEPTH == 2 || DEPTH == 4, "register sets of tiles in flight");
@@ -627,7 +627,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     }
   } else {
     // Every pair's tiles in equal chunks, as many as the request's length asks for; chunk i of a pair fills slot i.
-    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, chunk_keys);
+    const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, deal_wgs);
     if ((long)blockIdx.x >= deal.count) return;
     const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
     if (c.n_tiles > 0) segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
@@ -666,7 +666,7 @@ hipError_t launch_tree_attention_bf16_wide(const spec_attn_desc_t& d, const Attn
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,                    \
                      (const __hip_bfloat16*)k_new, (const __hip_bfloat16*)v_new, parent, depth, prefix_len,           \
                      (__hip_bfloat16*)out, ws_o, ws_ml, status, d.B, d.N, d.H, virtual_heads, qgr.n_qgroups,           \
-                     qgr.heads_per_wg, heads_per_wg, d.S_cap, plan.chunk_keys,                                        \
+                     qgr.heads_per_wg, heads_per_wg, d.S_cap, plan.chunk_keys, plan.balanced_wgs,                     \
                      plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h, ns.b, ns.n, ns.h,     \
                      (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg, rope)
 #define SPEC_SHAPES(DD, APP, PLAN, PGD)                          \

@@ -97,8 +97,13 @@ typedef struct spec_attn_desc {
   /* tests that drive small inputs through every plan.                                                    */
   int32_t plan_chunk_keys;   /* > 0: fixed chunks of this many keys (rounded up to the kernel's tile), one */
                              /* workgroup per (request, head, chunk), partials merged by a second launch  */
-  int32_t plan_balanced_wgs; /* > 0: bf16 only, the key tiles of all (request, head) pairs dealt in equal  */
-                             /* shares to this many workgroups; -1: never use that plan                    */
+  int32_t plan_balanced_wgs; /* > 0: bf16 only, the key tiles of all (request, head) pairs dealt out by the  */
+                             /* prefix lengths on the device. Every pair is cut into equal chunks, as many */
+                             /* as its length asks for, about this many in all and one workgroup per       */
+                             /* chunk; a pair has one chunk at least, so never fewer workgroups than pairs */
+                             /* (a hint no larger than that leaves every pair whole). Up to 16 query rows  */
+                             /* per K/V head with a hint below twice the pairs: equal contiguous shares of */
+                             /* all tiles for exactly this many workgroups instead. -1: never use it       */
   int32_t plan_heads_per_wg; /* > 0: trees of 65..128 nodes streamed whole: consecutive K/V heads of a     */
                              /* request served by one workgroup                                            */
 } spec_attn_desc_t;

@@ -6,21 +6,25 @@
 // a 32000 x 4096 head), not by arithmetic.
 //
 // lm_head_argmax_kernel: a workgroup of four wavefronts owns 128 (64 for small vocabularies) vocabulary rows and up to
-// 256 rows of `hidden` (MT = 32 to 256). Both operands go from global memory straight into LDS (global_load_lds_dwordx4) in stages of 64 k, 16 KB of
-// W and MT rows of `hidden` (L2-resident), into a ring of as many stages as fit: two (256 rows) to five (32 rows) stages
-// of W are in flight per compute unit while one is multiplied, to cover the two microseconds of loaded latency. A lane's 16 bytes land at a fixed place, so the swizzle that keeps the operand reads off each other's banks is
-// applied to the source: slot s of row r holds the 16-byte piece s ^ ((r >> 1) & 7) of the row. The product is taken
-// transposed, C[v, m] on 32 x 32 x 16 tiles, so a lane ends up with 16 vocabulary entries of ONE row m per tile and the
-// arg-max over v is in the lane, one cross-lane step and one pass through LDS over the wavefronts. Each workgroup writes
-// its (max, arg-max) per row; lm_head_reduce_kernel merges a row's partials (one per workgroup).
+// 256 rows of `hidden` (MT = 32 to 256). Both operands go from global memory straight into LDS (global_load_lds_dwordx4) in
+// stages of 64 k, 16 (8) KB of W and MT rows of `hidden` (L2-resident), into a ring of as many stages as fit: two (256 rows)
+// to five (32 rows) stages of 16 KB of W, or two workgroups' four stages of 8 KB, are in flight per compute unit while one
+// is multiplied, to cover the two microseconds of loaded latency. A lane's 16 bytes land at a fixed place, so the swizzle
+// that keeps the operand reads off each other's banks is applied to the source: slot s of row r holds the 16-byte piece
+// s ^ ((r >> 1) & 7) of the row. The product is taken transposed, C[v, m] on 32 x 32 x 16 tiles, so a lane ends up with 16
+// vocabulary entries of ONE row m per tile and the arg-max over v is in the lane, one cross-lane step and one pass through
+// LDS over the wavefronts. Each workgroup writes its (max, arg-max) per row; lm_head_reduce_kernel merges a row's partials
+// (one per workgroup).
 //
 // What bounds it: the stream of W. Nothing but these loads takes 45.3 us for 32000 x 4096 (5.8 TB/s), 52.7 without the
 // non-temporal hint. Every workgroup reads the same k of rows that lie 8 KB apart; starting each workgroup at another k
 // takes 39.5, but then equal rows of W in different workgroups would be summed in different orders and could differ in the
-// last bit, which the arg-max rule (lowest token among equal logits) does not allow. Measured at 32000 x 4096, arg-max only
-// / with logits and statistics and the merge, us (before: W straight into registers, 16 rows per wavefront, `hidden` through
-// LDS): 16 rows 50.4 / 52.6 (54.7 / 57.3), 64 rows 49.5 / 52.6 (54.8 / 58.9), 128 rows 55.2 / 58.6 (68.3 / 74.4), 256 rows
-// 83 / 90 (121 / 135).
+// last bit, which the arg-max rule (lowest token among equal logits) does not allow. Measured at 32000 x 4096 with six weight
+// matrices in turn (1.6 GB: W comes from HBM every time), arg-max only / with logits and statistics and the merge, us (before,
+// in the same run: W straight into registers, 16 rows per wavefront, `hidden` through LDS): 1 row 54.7 / 54.8 (55.8 / 56.8),
+// 16 rows 53.2 / 55.7 (55.5 / 58.0), 64 rows 53.2 / 56.2 (58.2 / 61.8), 128 rows 57.4 / 61.4 (70.0 / 75.7), 256 rows
+// 83.8 / 88.8 (124 / 137). Up to 32 rows of K = 256 to 512 over 4000 to 8000 vocabulary rows take up to 4 % (0.3 us) longer
+// than they did.
 // The order of a logit's sum is a matter of V and K alone, so that a row of `hidden` has the same logits in a batch of any
 // size: the 64 x 32 tile (up to 32 rows, vocabularies up to 16384 on 256 compute units) has two wavefronts for each place of
 // the product, which sum every other pair of k-steps, and where it is in use the other tiles keep the same two sums
@@ -333,8 +337,9 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   const float itl2 = inv_temp * 1.4426950408889634f;
   // Tile of the vocabulary and of `hidden`: the least of rounds of workgroups (one per compute unit at a time) times
   // (start and end of a workgroup + stages times the microseconds a stage takes it), with the stage times as measured on
-  // 32000 and 8000 x 4096. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64 vocabulary rows, 28.8 / 45.2 with 128; 20000 x
-  // 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128; 11198 x 2560, 227 rows: 57.3 with 256 rows of `hidden`, 38.3 with 128.
+  // 32000 and 8000 x 4096 with one workgroup per compute unit. 8000 x 4096, 16 / 128 rows: 21.1 / 33.3 us with 64 vocabulary
+  // rows, 28.8 / 45.2 with 128; 20000 x 768, 8 rows (313 workgroups of 64): 15.0 with 64, 12.2 with 128; 11198 x 2560, 227
+  // rows: 57.3 with 256 rows of `hidden`, 38.3 with 128.
   const int cus = compute_units();
   int mt = 0, vt = 0;
   float least = 0.f;

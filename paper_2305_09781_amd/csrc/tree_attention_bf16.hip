@@ -30,9 +30,14 @@
 //                 wavefront-private LDS tile and read back with ds_read_b64_tr_b16.
 //
 // Latency structure. A workgroup's fixed costs are what separate this kernel from a pure stream: the
-// first tile's loads are issued before prefix_len is known (rows clamped to the cache capacity), in
-// straight-line code so that all kernel arguments arrive in one batch; every tile's loads are issued
-// one tile ahead; nothing in the loop waits on more than its own tile.
+// streaming wavefronts' first tiles are issued before prefix_len is known (rows clamped to the cache capacity),
+// in straight-line code so that all kernel arguments arrive in one batch; every tile's loads are issued
+// one tile ahead; nothing in the loop waits on more than its own tile. A compute unit returns its wavefronts'
+// loads in the order of their requests, so what a later step waits for must not stand behind the tiles: the tree
+// words come through the scalar cache, the tail wavefront requests nothing else before it has them, and it alone
+// fetches the rotary angles and rotates the queries, for all five through LDS (each wavefront on its own, behind
+// its first tile, before: two layers of 8 requests, 1024 keys, trees of 16 with the embedding 55.2 -> 54.2 us; 8 x
+// 12 heads of 708 keys, trees of 5, without it, 27.7 -> 25.2; 4 x 40 heads of 98 keys 8.2 -> 7.5).
 //
 // With APPEND the kernel also performs the KV append of the tree tokens (Section 4.2): rows at and
 // beyond prefix_len are taken from k_new / v_new and written to the cache by query group 0.
@@ -50,6 +55,7 @@ namespace spec {
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;   // the rotary tables may start at any float
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;   // 16-byte load/store unit (plain vector: stays in registers)
 
@@ -84,6 +90,9 @@ __device__ __forceinline__ void store_cache_row(void* p, u32x4 v) {
   __builtin_nontemporal_store(v, (u32x4*)p);
 }
 
+// Barrier for LDS contents only: __syncthreads() also waits for the tiles in flight and for the appended rows' stores.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int D, int NT>
 struct AttnTraits {
   static constexpr int KS = D / 32;            // k-steps of the QK^T product
@@ -95,14 +104,9 @@ struct AttnTraits {
   static constexpr int VTILE_BYTES = TILE * VROW;
   static constexpr int NQ = NT * 16;           // queries per workgroup
   static constexpr int MROW = D + 4;           // floats per merge row: O[D], m, l, 2 pad (16-byte aligned rows)
-  static constexpr int MERGE_BYTES = WAVES * NQ * MROW * 4;
   static constexpr int STAGE_BYTES = WAVES * VTILE_BYTES;
-  // One query tile: the merge area lies behind the staging tiles, so a wavefront can publish its
-  // partial result as soon as it is done. Two query tiles: the merge area reuses the staging tiles.
-  static constexpr bool MERGE_SEPARATE = (NT == 1);
-  static constexpr int MERGE_OFF = MERGE_SEPARATE ? STAGE_BYTES : 0;
-  static constexpr int LDS_BYTES = MERGE_SEPARATE ? STAGE_BYTES + MERGE_BYTES
-                                                  : (MERGE_BYTES > STAGE_BYTES ? MERGE_BYTES : STAGE_BYTES);
+  // the merge area lies behind the staging tiles: a wavefront publishes its partial result as soon as it is done
+  static constexpr int LDS_BYTES = STAGE_BYTES + WAVES * NQ * MROW * 4;
 };
 
 // Pointers and strides one lane needs to fetch its pieces of a tile.
@@ -183,7 +187,12 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
                 MROW = T::MROW;
   constexpr int NTHREADS = WAVES * 64;
 
+  // With the rotary embedding the tail wavefront hands over the rotated queries, as the streaming wavefronts' lanes take them,
+  // and keeps its nodes' angles (rows of D/2 cosines and D/2 sines, 16 bytes more so that rows start on other banks).
+  constexpr int ANGLE_ROW = D + 4;
   __shared__ __attribute__((aligned(16))) unsigned char lds[T::LDS_BYTES];
+  __shared__ __attribute__((aligned(16))) u32x4 s_q[APPEND ? KS * 64 : 1];
+  __shared__ __attribute__((aligned(16))) float s_angle[APPEND ? 16 * ANGLE_ROW : 4];
   __shared__ int s_bad_tree;
   static_assert(NT == 1, "a tree of at most 16 nodes: lane r16 holds node r16, which is also its query");
 
@@ -221,23 +230,34 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   src.kn = APPEND ? (const unsigned char*)(k_new + b * q_sb + h * q_sh) + g * 16 : nullptr;
   src.vn = APPEND ? (const unsigned char*)(v_new + b * q_sb + h * q_sh) + (lane % LPR) * 16 : nullptr;
 
-  // Loads return in order: the tree words and the queries stand before the tile, so that the positions (with the rotary
-  // embedding: the addresses of its tables) are known while the tile is still on its way (with the masks built between
-  // the lanes instead of through LDS: 14.8 -> 13.9 us a layer for one request of 1024 keys, 12.9 -> 12.1 without the
-  // rotation; 27.9 -> 27.5 for eight). Rows past N repeat the last
-  // query (their results are never written): the loads are unconditional.
-  const int par = parent[(long)b * N + min(r16, N - 1)], dep = depth[(long)b * N + min(r16, N - 1)];
-  bf16x8 qB[NT][KS];   // Q^T as the B operand: lane (r16, g) holds Q[n = r16][d = ks*32 + g*8 .. +8]
+  // The tail wavefront: a tree node per lane, from scalar loads. Rows past N repeat the last query (their results are never
+  // written): the loads are unconditional.
+  const bool is_tail = wave == TAIL;
+  const bool rotates = APPEND && rope.cos != nullptr;
+  int par = 0, dep = 0;
+  if (is_tail) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    const u32x4 raw = *(const u32x4*)(q + b * q_sb + min(r16, N - 1) * q_sn + h * q_sh + ks * 32 + g * 8);
-    qB[0][ks] = __builtin_bit_cast(bf16x8, raw);
+    for (int i = 0; i < 16; ++i) {
+      const long at = (long)b * N + min(i, N - 1);
+      const int p = parent[at], d = depth[at];
+      par = r16 == i ? p : par;
+      dep = r16 == i ? d : dep;
+    }
+  }
+  bf16x8 qB[NT][KS];   // Q^T as the B operand: lane (r16, g) holds Q[n = r16][d = ks*32 + g*8 .. +8]
+  if (is_tail || !rotates) {
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const u32x4 raw = *(const u32x4*)(q + b * q_sb + min(r16, N - 1) * q_sn + h * q_sh + ks * 32 + g * 8);
+      qB[0][ks] = __builtin_bit_cast(bf16x8, raw);
+    }
   }
   __builtin_amdgcn_sched_barrier(0);
   u32x4 KA[2][KS], VA[NVL];   // tile buffer: loads land here one step ahead of use
   bool in_pool;   // entries past the request's end may hold anything: the speculative tile does not judge them
-  issue_tile_loads<D, NT, false, false>(src, c0 + min(wave, SWAVES - 1) * TILE, 0, S_cap - 1, r16, lane, KA, VA,
-                                        PAGED ? page_shift(b, c0 + min(wave, SWAVES - 1) * TILE, &in_pool) : 0);
+  if (!is_tail)
+    issue_tile_loads<D, NT, false, false>(src, c0 + wave * TILE, 0, S_cap - 1, r16, lane, KA, VA,
+                                          PAGED ? page_shift(b, c0 + wave * TILE, &in_pool) : 0);
   __builtin_amdgcn_sched_barrier(0);
 
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
@@ -258,35 +278,62 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   const int n_tiles = (c1 - c0 + TILE - 1) / TILE;
   const int n_clean = max(0, min(P, c1) - c0) / TILE;     // tiles entirely inside the prefix and the chunk
   const int last_row = len - 1;
-  const bool is_tail = wave == TAIL;
 
   // Rotary embedding: a lane's pieces of a query or key row pair up within the lane (k-step ks holds dimensions
-  // 32 ks + 8 g .., its partner ks + KS/2 the same dimensions + D/2), so a row is rotated in registers.
-  auto rotate_row = [&](auto& lo, auto& hi, int pos, int ks) {
-    const long at = (long)min(max(pos, 0), rope.len - 1) * (D / 2) + ks * 32 + g * 8;
+  // 32 ks + 8 g .., its partner ks + KS/2 the same dimensions + D/2), so a row is rotated in registers. `angle`: the row's
+  // cosines, the sines D/2 behind them.
+  auto rotate_row = [&](auto& lo, auto& hi, const float* angle, int ks) {
     uint4 olo, ohi;
-    rope_pair<true>(__builtin_bit_cast(uint4, lo), __builtin_bit_cast(uint4, hi), rope.cos + at, rope.sin + at, &olo, &ohi);
+    rope_pair<true>(__builtin_bit_cast(uint4, lo), __builtin_bit_cast(uint4, hi), angle + ks * 32 + g * 8,
+                    angle + D / 2 + ks * 32 + g * 8, &olo, &ohi);
     lo = __builtin_bit_cast(std::remove_reference_t<decltype(lo)>, olo);
     hi = __builtin_bit_cast(std::remove_reference_t<decltype(hi)>, ohi);
   };
-  if (APPEND && rope.cos != nullptr) {   // the queries, at their nodes' positions
-#pragma unroll
-    for (int ks = 0; ks < KS / 2; ++ks) rotate_row(qB[0][ks], qB[0][ks + KS / 2], P + dep, ks);
-  }
-
   // tiles of this wavefront: first, stride, count
   const int ti_first = is_tail ? n_clean : wave;
   const int ti_stride = is_tail ? 1 : SWAVES;
   const int ti_end = is_tail ? n_tiles : n_clean;
+  if (is_tail) {
+    if constexpr (APPEND) {
+      if (rotates) {   // lane (r16, g) fetches its pieces of node r16's angles
+        const long at = (long)min(max(P + dep, 0), rope.len - 1) * (D / 2) + g * 8;
+        float* row = s_angle + r16 * ANGLE_ROW;
+        f32x4 cs[KS / 2][2], sn[KS / 2][2];
+#pragma unroll
+        for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            cs[ks][i] = *(const f32x4_any*)(rope.cos + at + ks * 32 + i * 4);
+            sn[ks][i] = *(const f32x4_any*)(rope.sin + at + ks * 32 + i * 4);
+          }
+#pragma unroll
+        for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+          for (int i = 0; i < 2; ++i) {
+            *(f32x4*)(row + ks * 32 + g * 8 + i * 4) = cs[ks][i];
+            *(f32x4*)(row + D / 2 + ks * 32 + g * 8 + i * 4) = sn[ks][i];
+          }
+#pragma unroll
+        for (int ks = 0; ks < KS / 2; ++ks) rotate_row(qB[0][ks], qB[0][ks + KS / 2], row, ks);
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s_q[ks * 64 + lane] = __builtin_bit_cast(u32x4, qB[0][ks]);
+      }
+    }
+  }
+  if constexpr (APPEND) {
+    if (rotates) {
+      lds_barrier();
+      if (!is_tail) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qB[0][ks] = __builtin_bit_cast(bf16x8, s_q[ks * 64 + lane]);
+      }
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);   // (otherwise the requests move down to the masks)
   if (is_tail && ti_first < ti_end)   // the tail wavefront's first tile (needs prefix_len: rows >= P have other sources)
     issue_tile_loads<D, NT, APPEND, false>(src, c0 + ti_first * TILE, P, last_row, r16, lane, KA, VA,
                                            PAGED ? page_shift(b, c0 + ti_first * TILE, &in_pool) : 0);
-  if (PAGED && is_tail) {   // every block this segment reads must lie inside the pool
-    for (int j = (c0 >> pg.log2_tokens) + lane; j <= ((c1 - 1) >> pg.log2_tokens); j += 64) {
-      const int e = pg.table[(long)b * pg.max_blocks + j];
-      if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
-    }
-  }
+  __builtin_amdgcn_sched_barrier(0);
 
   f32x4 O[NT][DB];
   float m_run[NT], l_run[NT];
@@ -334,14 +381,14 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
 #pragma unroll
       for (int j = 0; j < NVL; ++j)
         if (k0 + j * RPI + lane / LPR >= c1) VA[j] = (u32x4){0u, 0u, 0u, 0u};
-      if (APPEND && rope.cos != nullptr) {   // new K rows are rotated before they are used and stored
+      if (rotates) {   // new K rows are rotated before they are used and stored
 #pragma unroll
         for (int hf = 0; hf < 2; ++hf) {
           const int row = k0 + hf * 16 + r16;
-          const int pos = P + __shfl(dep, min(max(row - P, 0), 15));
           if (row >= P && row < c1) {
 #pragma unroll
-            for (int ks = 0; ks < KS / 2; ++ks) rotate_row(KA[hf][ks], KA[hf][ks + KS / 2], pos, ks);
+            for (int ks = 0; ks < KS / 2; ++ks)
+              rotate_row(KA[hf][ks], KA[hf][ks + KS / 2], s_angle + (row - P) * ANGLE_ROW, ks);
           }
         }
       }
@@ -467,14 +514,19 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   if (is_tail) {
     if (!bad_tree)
       for (int ti = ti_first; ti < ti_end; ++ti) tile_step(ti, ti + 1 < ti_end ? ti + 1 : -1, std::true_type{});
+    if (PAGED) {   // every block this segment reads must lie inside the pool (looked at last: nothing waits for these loads)
+      for (int j = (c0 >> pg.log2_tokens) + lane; j <= ((c1 - 1) >> pg.log2_tokens); j += 64) {
+        const int e = pg.table[(long)b * pg.max_blocks + j];
+        if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
+      }
+    }
   } else {
     for (int ti = ti_first; ti < ti_end; ti += SWAVES)
       tile_step(ti, ti + SWAVES < ti_end ? ti + SWAVES : -1, std::false_type{});
   }
 
   // ---- merge the five wavefronts through LDS: layout [wave][n][MROW] floats (O row, m, l)
-  if (!T::MERGE_SEPARATE) __syncthreads();   // the merge area overlays the staging tiles still being read
-  float* mg = (float*)(lds + T::MERGE_OFF);
+  float* mg = (float*)(lds + T::STAGE_BYTES);
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) {
     const float l_tot = wave_sum_over_lane_groups(l_run[nt]);
@@ -486,7 +538,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
       row[D + 1] = l_tot;
     }
   }
-  __syncthreads();
+  lds_barrier();
   if (s_bad_tree != 0) {   // malformed tree: defined result = zeros (written here when this workgroup owns the output)
     if (final_out) {
       for (int i = t; i < NQ * D; i += NTHREADS) {

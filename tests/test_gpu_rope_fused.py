@@ -299,3 +299,28 @@ def test_fused_rope_rejects_bad_arguments(spec):
     out32 = torch.empty_like(f[0])
     rc = call(ctypes.byref(d32), *[ptr(x) for x in f], ptr(cs), ptr(sn), S, ptr(out32), None, 0, None, None)
     assert rc != 0 and b"unsupported" in spec.load().spec_strerror(rc).lower()
+
+
+@pytest.mark.parametrize("D,N,P,chunk", [(128, 1, 31, 0), (128, 16, 32, 0), (128, 15, 257, 64), (64, 5, 0, 0), (64, 16, 95, 0)])
+def test_tables_at_any_float_and_tails_around_a_tile(spec, D, N, P, chunk):
+    """Few-query kernel: its tail wavefront fetches the angles in 16-byte pieces wherever the tables start, and hands the
+    rotated queries to the other wavefronts; prefixes that end on, before and behind a tile. Bit for bit against tables on
+    a 256-byte boundary; B * N smaller than a wavefront's sixteen nodes is among them."""
+    _, inp, S = _inputs(1, 2, 2, D, (P, P), N, "random_parent", seed=77 + N)
+    cos, sin = wl.make_rope_tables(S, D)
+    tree_args = (_dev(inp["tree_parent"]), _dev(inp["tree_depth"]), _dev(inp["prefix_len"]))
+    results = []
+    for at in (0, 1, 3):
+        tables = []
+        for t in (cos, sin):
+            flat = torch.zeros(t.numel() + 4, dtype=torch.float32, device=DEV)
+            flat[at:at + t.numel()] = _dev(t).reshape(-1)
+            tables.append(flat[at:at + t.numel()].view(t.shape))
+        kc, vc = _dev(inp["k_cache"][0]), _dev(inp["v_cache"][0])
+        with _chunk_keys(chunk):
+            out = spec.spec_tree_attention_append_rope(*(_dev(inp[k][0]) for k in ("q", "k_new", "v_new")), kc, vc, *tree_args,
+                                                       *tables, max_prefix_len=P, plan=_plan())
+        torch.cuda.synchronize()
+        results.append((_bits(out), _bits(kc), _bits(vc)))
+    for r in results[1:]:
+        assert all(np.array_equal(a, b) for a, b in zip(r, results[0]))

@@ -95,6 +95,32 @@ def test_merge_of_wide_and_narrow_levels(spec, M, Nin, kind, tokens):
             assert np.array_equal(g[b].cpu().numpy(), np.asarray(w))
 
 
+@pytest.mark.parametrize("M,Nin,Nout", [(64, 1, 1), (1, 63, 63), (21, 3, 64), (4, 16, 128), (2, 32, 30), (13, 5, 128), (5, 7, 128)])
+def test_merge_around_one_wavefront(spec, M, Nin, Nout):
+    """Up to 64 input nodes are one wavefront's work: random trees that agree in part, sizes that leave slots unused, too many
+    sequences, and one malformed tree, or root, in a batch; (13, 5) is one node more."""
+    rng = np.random.default_rng(M * 100 + Nin)
+    B = 24
+    par = np.full((B, M, Nin), -1, dtype=np.int32)
+    tok = rng.integers(0, 3, size=(B, M, Nin)).astype(np.int32)
+    tok[B // 2:, :, :] = rng.integers(0, 1000, size=(B - B // 2, M, Nin))
+    tok[:, :, 0] = 7
+    for u in range(1, Nin):
+        par[:, :, u] = rng.integers(0, u, size=(B, M))
+    size = rng.integers(1, Nin + 1, size=(B, M)).astype(np.int32)
+    size[0] = Nin
+    size[3, M - 1], size[4, 0], tok[5, M - 1, 0] = Nin + 1, 0, 8 if M > 1 else 7
+    if Nin > 1:
+        size[6:9, 0] = Nin
+        par[6, 0, 1], par[7, 0, Nin - 1], tok[8, 0, 1] = -1, Nin - 1, -2
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a)).to(DEV)  # noqa: E731
+    status = torch.zeros(B, dtype=torch.int32, device=DEV)
+    got = spec.spec_tree_merge(dev(par), dev(tok), dev(size), Nout, status=status)
+    for b in range(B):
+        for g, w in zip(list(got) + [status], orc.tree_merge(par[b], tok[b], size[b], Nout)):
+            assert np.array_equal(g[b].cpu().numpy(), np.asarray(w)), b
+
+
 def test_merge_of_repeated_tokens_ends_its_comparisons_early(spec):
     """Stars of 128 nodes merged from eight trees: with three different tokens every node finds its like among the first few
     of its level, which takes half as long as comparing a thousand different ones."""

@@ -102,17 +102,31 @@ inline int f32_query_groups(const spec_attn_desc_t& d) {
 __host__ __device__ inline int request_tiles(int P, int N, int S_cap, int tile) {
   return (P >= 0 && P <= S_cap - N) ? (P + N + tile - 1) / tile : 0;
 }
+// a / b for 0 <= a, 0 < b < 2^30 and a quotient below 2^22: the deal divides a dozen times in a row before a workgroup's first
+// load, and an integer division is some thirty instructions on the vector unit. The reciprocal is good to 2^-22, so that the
+// quotient is off by one at most, which the remainder shows.
+__host__ __device__ inline int deal_quotient(int a, int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  const int q = (int)((float)a * __builtin_amdgcn_rcpf((float)b));
+  const int rest = a - q * b;
+  return q + (rest >= b) - (rest < 0);
+#else
+  return a / b;
+#endif
+}
 // Chunks of a request with tb tiles: their number, and the tiles of each but the last.
-__host__ __device__ inline int deal_chunks(int tb, int share) { return (int)((unsigned)(tb + share - 1) / (unsigned)share); }
-__host__ __device__ inline int deal_chunk_tiles(int tb, int chunks) { return (int)((unsigned)(tb + chunks - 1) / (unsigned)chunks); }
+__host__ __device__ inline int deal_chunks(int tb, int share) { return deal_quotient(tb + share - 1, share); }
+__host__ __device__ inline int deal_chunk_tiles(int tb, int chunks) { return deal_quotient(tb + chunks - 1, chunks); }
 // Number r of a request's chunks (over all virtual heads): its (K/V head, chunk) unit and its query group. The query groups
 // of a unit read the same keys: whole blocks of eight units are numbered so that a unit's groups are eight apart, which puts
 // them on one XCD; what is left over takes them in a row.
 struct DealUnit { int unit, qg; };
 __host__ __device__ inline DealUnit deal_unit(int r, int n_qg, int units) {
-  const int blk = r / (8 * n_qg), rr = r % (8 * n_qg);
-  if (n_qg > 1 && (blk + 1) * 8 <= units) return {blk * 8 + rr % 8, rr / 8};
-  return {r / n_qg, r % n_qg};
+  if (n_qg == 1) return {r, 0};
+  const int blk = deal_quotient(r, 8 * n_qg), rr = r - blk * 8 * n_qg;
+  if ((blk + 1) * 8 <= units) return {blk * 8 + rr % 8, rr / 8};
+  const int unit = deal_quotient(r, n_qg);
+  return {unit, r - unit * n_qg};
 }
 
 // Strides of k_new / v_new (all zero in the descriptor: laid out like q).
@@ -264,7 +278,7 @@ __device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, const i
 // request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
 // a / b of non-negative numbers, in 32 bits where they fit (a 64-bit division is some hundred instructions)
 __device__ inline long deal_div(long a, long b) {
-  return ((a | b) >> 32) == 0 ? (long)((unsigned)a / (unsigned)b) : a / b;
+  return ((a | b) >> 30) == 0 && (a >> 21) < b ? (long)deal_quotient((int)a, (int)b) : a / b;
 }
 // Inclusive sum over the lanes of a wavefront (lane 63 holds the total), in register moves: row shifts, then the last lane
 // of each row of 16 into the rows after it.
@@ -334,9 +348,10 @@ __device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, in
       c.chunks = __builtin_amdgcn_readlane(v, f);
       c.b = b0 + f;
       const int r = (int)(id - (acc + __builtin_amdgcn_readlane(incl, f) - c.chunks) * H);   // < H * chunks
-      const DealUnit u = deal_unit(r, n_qg, H / n_qg * c.chunks);
-      c.chunk = u.unit % c.chunks;
-      c.h = u.unit / c.chunks * n_qg + u.qg;
+      const DealUnit u = deal_unit(r, n_qg, deal_quotient(H, n_qg) * c.chunks);
+      const int kv_head = deal_quotient(u.unit, c.chunks);
+      c.chunk = u.unit - kv_head * c.chunks;
+      c.h = kv_head * n_qg + u.qg;
       const int per = deal_chunk_tiles(tb, c.chunks);
       c.tile0 = c.chunk * per;
       c.n_tiles = max(0, min(per, tb - c.tile0));

@@ -331,9 +331,9 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 // query. A pair has a block of N rows in each of `slots` slots; how many are filled follows from the plan: fixed
 // chunks (chunk_keys > 0) or the balanced deal (bal_wgs > 0). Also the place where a malformed request gets its defined
 // result (zeros) and its status bit. Bound by reading the filled slots once (32 requests x 64 heads x 16 nodes, two or
-// three slots each, 45 MB: 60 us before, when prefix_len[] was walked by scalar
-// loads and the slots of a pair lay next to each other over a gigabyte of mostly empty workspace; 17 us now; four pieces
-// per thread instead of one changes nothing).
+// three slots each, 45 MB) and, under the balanced plans, by the deal that says how many those are: 18.9 us with all four
+// wavefronts of a workgroup working it out, behind the tree check, 13.8 with one beside it, 8.6 if it cost nothing; two
+// pieces per thread 13.5 and slower elsewhere (4 requests of 8192 to 16384 keys 6.1 -> 6.8), four spill.
 template <bool BF16, bool BAL, int CH>   // CH: partial slots fetched together
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
                                                            const int32_t* __restrict__ parent,
@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
                                                            int D, int S_cap, int chunk_keys, int slots,
                                                            int bal_wgs, int bal_tile, bool contiguous, long q_sb,
                                                            long q_sn, long q_sh) {
-  __shared__ int s_flag;
+  __shared__ int s_flag, s_slots;
   const int h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
   const int CG = D / 4;
   const int idx = blockIdx.z * 256 + t;
@@ -372,27 +372,32 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
   fetch(0, 0, early);
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
-  const bool valid = tree_is_valid(parent + (long)b * N, depth + (long)b * N, N, &s_flag) && cap_ok;
-  if (!valid && h == 0 && blockIdx.z == 0 && t == 0) set_status(status, b, cap_ok ? SPEC_ST_BAD_TREE : SPEC_ST_CAPACITY);
-  int ns = 0;
-  if (valid) {
-    if (BAL) {
+  // How many slots of the pair are filled. The balanced plans' deal is some hundred instructions: one wavefront of the
+  // workgroup, not all four, while two others check the tree.
+  if (BAL && uniform(t >> 6) == 3) {
+    int filled = 0;
+    if (cap_ok) {
       // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group
       const int tb = request_tiles(P, N, S_cap, bal_tile);
       if (contiguous) {   // few-query kernel: one query head per pair
         long before;
         const ContiguousDeal deal = contiguous_deal(prefix_len, B, N, H, S_cap, bal_tile, bal_wgs, b, &before);
         const long pair_start = before * H + (long)h * tb;
-        ns = uniform((int)(deal_div(pair_start + tb - 1, deal.share) - deal_div(pair_start, deal.share)) + 1);
+        filled = (int)(deal_div(pair_start + tb - 1, deal.share) - deal_div(pair_start, deal.share)) + 1;
       } else {
         const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
         const int chunks = deal_chunks(tb, deal.share);
-        if (chunks == 1) return;   // the attention kernel wrote the final output
-        ns = uniform(deal_chunks(tb, deal_chunk_tiles(tb, chunks)));
+        filled = chunks == 1 ? 0 : deal_chunks(tb, deal_chunk_tiles(tb, chunks));   // 0: the attention kernel wrote the final output
       }
-    } else {
-      ns = uniform(min(slots, (P + N + chunk_keys - 1) / chunk_keys));
     }
+    if ((t & 63) == 0) s_slots = filled;
+  }
+  const bool valid = tree_is_valid(parent + (long)b * N, depth + (long)b * N, N, &s_flag) && cap_ok;
+  if (!valid && h == 0 && blockIdx.z == 0 && t == 0) set_status(status, b, cap_ok ? SPEC_ST_BAD_TREE : SPEC_ST_CAPACITY);
+  int ns = 0;
+  if (valid) {
+    ns = BAL ? uniform(s_slots) : uniform(min(slots, (P + N + chunk_keys - 1) / chunk_keys));
+    if (BAL && ns == 0) return;
   }
   if (!active) return;
   // online merge over chunks of CH slots (slots at and beyond ns hold nothing meaningful: skipped)

@@ -10,6 +10,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 PROGRAM = r"""
 #include <cstdio>
+#include <cmath>
 #include <cstdlib>
 #include <vector>
 #include "spec_internal.h"
@@ -39,6 +40,21 @@ int main() {
       check(used <= chunks && (used > 1) == (chunks > 1), "count", tb, share, used);   // the merge relies on both
       check(per * (used - 1) < tb && tb <= per * used, "cover", tb, share, per);
     }
+  // the kernels' division: float32 reciprocal (one unit off either way included) and one correction
+  auto by_reciprocal = [](int a, int b, int ulp) {
+    float rcp = 1.0f / (float)b;
+    for (int i = 0; i < abs(ulp); ++i) rcp = nextafterf(rcp, ulp > 0 ? 2.0f : 0.0f);
+    const int q = (int)((float)a * rcp), rest = a - q * b;
+    return q + (rest >= b) - (rest < 0);
+  };
+  for (int b : {1, 2, 3, 7, 22, 64, 255, 1000, 4095, 65537, 1048575, 16777217, 0x3ffffffe, 0x3fffffff})
+    for (long q : {0L, 1L, 2L, 63L, 1000L, 65535L, 1048576L, 2097151L})
+      for (long d = -2; d <= 2; ++d) {
+        const long a = q * b + d;
+        if (a < 0 || a > 0x7fffffffL || a / b >= 1 << 22) continue;
+        for (int ulp = -1; ulp <= 1; ++ulp) check(by_reciprocal((int)a, b, ulp) == a / b, "division", (int)a, b, ulp);
+        check(deal_quotient((int)a, b) == a / b, "quotient", (int)a, b, 0);
+      }
   check(request_tiles(-1, 16, 100, 64) == 0 && request_tiles(85, 16, 100, 64) == 0 && request_tiles(84, 16, 100, 64) == 2 &&
         request_tiles(0, 1, 1, 32) == 1, "tiles", 0, 0, 0);
   puts("ok");

@@ -208,8 +208,8 @@ inline bool stochastic_walk_in_registers(int V) { return V <= 32768; }
 // 107 without the pass, 16384: 204 / 118, 32000: 306 / 122; bfloat16 292 / 144; rows of single float32 elements 1.05e-4 V);
 // the pass costs its bytes at 5.5 TB/s. Up to the level where the two are equal, even a path that is accepted to the end of
 // the tree takes no longer (16 x 128 nodes of 32000 float32: 16 levels), and the usual path of a few nodes is much shorter: 16 trees of
-// 128, 32000 float32, three drafts, 49 us, with a pass for all of them 73; all 128 nodes of chains accepted: 231 (274 with the
-// form this one replaced, 822 without a pass). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
+// 128, 32000 float32, three drafts, 44 us, with a pass for all of them 67; all 128 nodes of chains accepted: 131 (274 with the
+// form this one replaced, some 400 without a pass). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
 // takes 4.5: only from 8 levels on, which fewer trees of a batch exceed. Where Lmax or N are no more than the levels, no tree
 // has to be looked at.
 inline int stochastic_own_levels(int B, int N, int V, int logits_dtype, int Lmax) {

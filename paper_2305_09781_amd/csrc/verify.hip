@@ -35,6 +35,9 @@ __device__ inline float load_logit(const void* base, long idx) {
 // ---------------------------------------------------------------------------------------------
 constexpr int SWEEP_U = 8;
 
+// Barrier for LDS contents only: __syncthreads() also waits for the loads in flight.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 template <int VEC, bool BF16>
 __device__ __forceinline__ void load_logit_group(const void* base, long elem, float (&v)[VEC]) {
   if (VEC == 4) {
@@ -395,8 +398,11 @@ __global__ void __launch_bounds__(64) greedy_walk_kernel(int N, const int32_t* _
 // node_max == nullptr: every tree is such a tree.
 //
 // What bounds it: one compute unit per request: a row of 32000 float32 takes it about 2.5 us, and a step of the walk is one
-// or two of them in a chain. Measured on 16 requests, trees of 128, 32000 float32, three drafts: 49 us in all, against 120 for
-// the pass over all nodes and the buffer form; 8 trees of 16: 27 against 46.
+// or two of them in a chain, with one barrier each. What the tests need of the tree is fetched and ordered for all nodes while
+// the root's row is on its way, and every wavefront follows the walk by itself (a node's children listed, sorted and fetched
+// as the walk reached them: six barriers and a trip to memory more per node). Measured, us, before and now: 16 requests, trees
+// of 128, 32000 float32, three drafts, 49.1 / 43.7; chains of 128, all accepted, 231 / 131; 32 trees of 128, 4000 float32,
+// 25.2 / 22.7.
 // ---------------------------------------------------------------------------------------------
 
 // exp(x) for x <= 0: one v_exp_f32 with the rounding of x * log2(e) put back (relative error as expf's, results below
@@ -516,13 +522,14 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     int32_t* __restrict__ path, int32_t* __restrict__ len, int32_t* __restrict__ out_tokens, int32_t* status) {
   constexpr int WAVES = SW_THREADS / 64, NTOT = NG * WAVES < 64 ? 64 : NG * WAVES;   // final scan: (group round, wavefront)
   static_assert(NTOT % 64 == 0, "whole rounds of lanes");
-  __shared__ int s_flag, s_nchild, s_ans;
-  __shared__ int s_child[SPEC_MAX_TREE_NODES], s_sorted[SPEC_MAX_TREE_NODES];
-  __shared__ int s_par[SPEC_MAX_TREE_NODES], s_tok[SPEC_MAX_TREE_NODES], s_row[SPEC_MAX_TREE_NODES];
-  __shared__ float s_ord[SPEC_MAX_TREE_NODES], s_acc[SPEC_MAX_TREE_NODES];
-  __shared__ float s_cq[SPEC_MAX_TREE_NODES], s_cp[SPEC_MAX_TREE_NODES];   // per child in test order: Q(x), un-normalised P(x)
+  __shared__ int s_flag, s_ans;
+  // per node: its parent if it is a candidate (else -2) and what a ratio test needs; siblings' order of testing
+  __shared__ __attribute__((aligned(16))) int s_par[SPEC_MAX_TREE_NODES];
+  __shared__ __attribute__((aligned(16))) float s_ord[SPEC_MAX_TREE_NODES];
+  __shared__ int s_rank[SPEC_MAX_TREE_NODES], s_tok[SPEC_MAX_TREE_NODES], s_row[SPEC_MAX_TREE_NODES];
+  __shared__ float s_acc[SPEC_MAX_TREE_NODES], s_cq[SPEC_MAX_TREE_NODES], s_cl[SPEC_MAX_TREE_NODES];
   __shared__ float s_red[2][WAVES];
-  __shared__ float2 s_stats[WAVES];
+  __shared__ float2 s_stats[2][WAVES];
   __shared__ double s_tot[NTOT];
 
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
@@ -549,34 +556,82 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     for (int j = 0; j < NG; ++j) raw[j].expand(w[j]);
   };
 
+  static_assert(SPEC_MAX_TREE_NODES == 128, "two nodes per lane, parents in the bits from 7 up");
+  // Everything that the ratio tests need of the tree, for all nodes at once while the root's row is on its way: a node has one
+  // parent, so its Q(x), its logit and its place among its siblings are known without the walk. From then on every wavefront
+  // follows the walk by itself, nodes lane and lane + 64 in its registers, and waits for the others only in the sums.
   if (own_levels > 0) load_row(0);
-  if (t < N) {
-    s_par[t] = parent[(long)b * N + t];
-    s_tok[t] = token[(long)b * N + t];
-    s_row[t] = ssm_row[(long)b * N + t];
-    s_ord[t] = u_order[(long)b * N + t];
-    s_acc[t] = u_accept[(long)b * N + t];
-  }
   if (t == 0) s_flag = 0;
-  __syncthreads();
+  int my_par = -2, my_tok = -1, my_row = 0;
+  float my_ord = 0.f, my_acc = 0.f;
+  bool ok = true;
   if (t < N) {
-    const int p = s_par[t], x = s_tok[t], rr = s_row[t];
-    bool ok = t == 0 ? p == -1 : (p >= 0 && p < t);
-    if (t >= 1 && x >= 0 && (x >= V || rr < 0 || rr >= R)) ok = false;   // a negative token: a padding node, never a candidate
-    if (!ok) atomicOr(&s_flag, 1);
+    my_par = parent[(long)b * N + t];
+    my_tok = token[(long)b * N + t];
+    my_row = ssm_row[(long)b * N + t];
+    my_ord = u_order[(long)b * N + t];
+    my_acc = u_accept[(long)b * N + t];
+    ok = t == 0 ? my_par == -1 : (my_par >= 0 && my_par < t);
+    if (t >= 1 && my_tok >= 0 && (my_tok >= V || my_row < 0 || my_row >= R)) ok = false;
+  }
+  const bool candidate = t < N && t >= 1 && my_tok >= 0 && ok;   // a negative token: a padding node, never a candidate
+  float my_q0 = 0.f, my_logit = 0.f;   // on their way while the siblings are ordered
+  if (candidate) {
+    my_q0 = probs_ssm[(long)my_row * V + my_tok];
+    my_logit = load_logit<BF16>(logits, ((long)b * N + my_par) * V + my_tok);
+  }
+  if (t < SPEC_MAX_TREE_NODES) {
+    s_par[t] = candidate ? my_par : -2;
+    s_ord[t] = my_ord;
+    s_tok[t] = my_tok;
+    s_row[t] = my_row;
+    s_acc[t] = my_acc;
+    s_rank[t] = 0;
+  }
+  lds_barrier();
+  if (!ok) atomicOr(&s_flag, 1);
+  {   // place among the siblings in ascending (u_order, index): eight threads per node, each against a part of the others
+    constexpr int PART = SPEC_MAX_TREE_NODES * SPEC_MAX_TREE_NODES / SW_THREADS;
+    const int v = t % SPEC_MAX_TREE_NODES, from = t / SPEC_MAX_TREE_NODES * PART;
+    const int par = s_par[v];
+    const float ord = s_ord[v];
+    int rank = 0;
+    if (par >= 0 && from < N) {
+#pragma unroll
+      for (int j = from; j < from + PART; j += 4) {
+        const int4 p4 = *(const int4*)&s_par[j];
+        const float4 o4 = *(const float4*)&s_ord[j];
+        rank += p4.x == par && (o4.x < ord || (o4.x == ord && j < v));
+        rank += p4.y == par && (o4.y < ord || (o4.y == ord && j + 1 < v));
+        rank += p4.z == par && (o4.z < ord || (o4.z == ord && j + 2 < v));
+        rank += p4.w == par && (o4.w < ord || (o4.w == ord && j + 3 < v));
+      }
+    }
+    if (rank > 0) atomicAdd(&s_rank[v], rank);
+  }
+  if (t < SPEC_MAX_TREE_NODES) {
+    s_cq[t] = my_q0;
+    s_cl[t] = my_logit;
   }
   for (int k = t; k < Lmax; k += SW_THREADS) {
     path[(long)b * Lmax + k] = -1;
     out_tokens[(long)b * Lmax + k] = -1;
   }
-  __syncthreads();
+  lds_barrier();
   if (s_flag != 0) {
     if (t == 0) { len[b] = 0; set_status(status, b, SPEC_ST_BAD_TREE); }
     return;
   }
   if (t == 0) path[(long)b * Lmax] = 0;
-  const bool own = node_max == nullptr ||
-                   (own_levels > 0 && tree_within(lane < N ? s_par[lane] : -1, lane + 64 < N ? s_par[lane + 64] : -1, own_levels));
+  bool own = node_max == nullptr;
+  if (!own && own_levels > 0) {   // (padding nodes count as levels too: the tree as the pass over all nodes sees it)
+    const int32_t* par = parent + (long)b * N;
+    own = tree_within(lane < N ? par[lane] : -1, lane + 64 < N ? par[lane + 64] : -1, own_levels);
+  }
+  // this lane's two nodes: (parent, place among the siblings) as one number, and P(x), un-normalised, while the walk is at the
+  // parent
+  const int c_key[2] = {s_par[lane] * SPEC_MAX_TREE_NODES + s_rank[lane], s_par[lane + 64] * SPEC_MAX_TREE_NODES + s_rank[lane + 64]};
+  float c_p[2];
 
   int u = 0, k = 0, red = 0;
   bool have_row = own_levels > 0, have_weights = false;   // w holds node u's logits, its distribution
@@ -591,33 +646,6 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     have_weights = true;
   };
   while (true) {
-    // children of u in ascending (u_order, index)
-    if (t == 0) s_nchild = 0;
-    __syncthreads();
-    if (t < N && s_par[t] == u && s_tok[t] >= 0) s_child[atomicAdd(&s_nchild, 1)] = t;
-    __syncthreads();
-    const int nchild = (k + 1 < Lmax) ? s_nchild : 0;
-    if (t < nchild) {
-      const int me = s_child[t];
-      const float mk = s_ord[me];
-      int rank = 0;
-      for (int j = 0; j < nchild; ++j) {
-        const int o = s_child[j];
-        const float ok = s_ord[o];
-        rank += (ok < mk) || (ok == mk && o < me);
-      }
-      s_sorted[rank] = me;
-    }
-    __syncthreads();
-    // everything the ratio tests need from memory, for all children at once; thread j follows child j's P(x)
-    int my_x = 0;
-    float cl = 0.f, cw = 0.f;
-    if (t < nchild) {
-      const int c = s_sorted[t];
-      my_x = s_tok[c];
-      s_cq[t] = probs_ssm[(long)s_row[c] * V + my_x];
-      cl = load_logit<BF16>(logits, ((long)b * N + u) * V + my_x);
-    }
     if (own) {   // as the pass over all nodes takes them; w keeps the logits: most nodes need nothing else
       float m = -INFINITY, sum = 0.f;
 #pragma unroll
@@ -630,31 +658,34 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
 #pragma unroll
           for (int e = 0; e < VEC; ++e) sum += fast_exp((w[j][e] - m) * inv_temp);
       }
-      block_softmax_stats(m, sum, inv_temp, s_stats, &mx, &Z);
+      block_softmax_stats(m, sum, inv_temp, s_stats[red ^= 1], &mx, &Z);
     } else {
       mx = node_max[(long)b * N + u];
       Z = node_sumexp[(long)b * N + u];
     }
-    if (t < nchild) {
-      cw = exp_of_nonpositive((cl - mx) * inv_temp);
-      s_cp[t] = cw;
-    }
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) c_p[i] = exp_of_nonpositive((s_cl[lane + 64 * i] - mx) * inv_temp);
     bool accepted = false;
-    for (int j = 0; j < nchild; ++j) {
-      const int c = s_sorted[j];
-      if (s_acc[c] * s_cq[j] <= s_cp[j] / Z) {
+    for (int j = 0; k + 1 < Lmax; ++j) {
+      const int key = u * SPEC_MAX_TREE_NODES + j;
+      const unsigned long long m0 = __ballot(c_key[0] == key), m1 = __ballot(c_key[1] == key);
+      if ((m0 | m1) == 0) break;   // no child left
+      const bool high = m0 == 0;
+      const int l = __ffsll((long long)(high ? m1 : m0)) - 1, c = l + (high ? 64 : 0);
+      if (s_acc[c] * s_cq[c] <= readlane_f32(high ? c_p[1] : c_p[0], l) / Z) {
         accepted = true;
         if (t == 0) {
           out_tokens[(long)b * Lmax + k] = s_tok[c];
           path[(long)b * Lmax + k + 1] = c;
         }
-        u = uniform(c);
+        u = c;
         break;
       }
       // rejected: P := norm(max(0, P - Q)), kept as un-normalised values plus their sum Z
       const float* Q = probs_ssm + (long)uniform(s_row[c]) * V;
-      float my_q = t < nchild ? Q[my_x] : 0.f;
+      float my_q[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) my_q[i] = (c_key[i] >> 7) == u ? Q[s_tok[lane + 64 * i]] : 0.f;
       need_weights();
       const float invZ = 1.f / Z;
       float part = 0.f;
@@ -680,19 +711,17 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
 #pragma unroll
           for (int e = 0; e < VEC; ++e) w[jj][e] = fmaxf(0.f, fmaf(w[jj][e], invZ, -q[jj][e]));
         Z = Znew;
-        cw = fmaxf(0.f, fmaf(cw, invZ, -my_q));
-        if (t < nchild) s_cp[t] = cw;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) c_p[i] = fmaxf(0.f, fmaf(c_p[i], invZ, -my_q[i]));
       } else if (t == 0) {   // an empty residual keeps the previous P
         set_status(status, b, SPEC_ST_ZERO_RESIDUAL);
       }
-      __syncthreads();   // the children's new P(x) are visible before the next test reads them
     }
     if (!accepted) break;
     ++k;
     have_weights = false;
     have_row = own;
     if (own) load_row(u);
-    __syncthreads();   // everybody has read this node's children before the next node's are listed
   }
 
   // ---- final token: inverse CDF in ascending token id over the current P. Order of the elements: group round, thread,

@@ -205,17 +205,17 @@ inline bool stochastic_walk_in_registers(int V) { return V <= 32768; }
 // Levels up to which a tree's nodes get their statistics from the walk itself (0: none); those of deeper trees come from the
 // pass over all nodes. A walk visits at most as many nodes as its tree has levels, and each node costs it 0.9e-4 V us more
 // than the walk over given statistics that this one replaced (64 accepted nodes in a row, us in all: 8192 float32 154 against
-// 107 without the pass, 16384: 204 / 118, 32000: 306 / 122; bfloat16 292 / 144; rows of single float32 elements 1.05e-4 V);
+// 107 without the pass, 16384: 204 / 118, 32000: 306 / 122; bfloat16 292 / 144);
 // the pass costs its bytes at 5.5 TB/s. Up to the level where the two are equal, even a path that is accepted to the end of
 // the tree takes no longer (16 x 128 nodes of 32000 float32: 16 levels), and the usual path of a few nodes is much shorter: 16 trees of
-// 128, 32000 float32, three drafts, 44 us, with a pass for all of them 67; all 128 nodes of chains accepted: 131 (274 with the
-// form this one replaced, some 400 without a pass). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
+// 128, 32000 float32, three drafts, 44 us; all 128 nodes of chains accepted: 131 (274 with the
+// form this one replaced). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
 // takes 4.5: only from 8 levels on, which fewer trees of a batch exceed. Where Lmax or N are no more than the levels, no tree
 // has to be looked at.
 inline int stochastic_own_levels(int B, int N, int V, int logits_dtype, int Lmax) {
   if (!stochastic_walk_in_registers(V)) return 0;
   const double pass_us = (double)B * N * V * (logits_dtype == SPEC_BF16 ? 2 : 4) / 5.5e6;
-  const double node_us = V * (logits_dtype == SPEC_F32 && V % 4 != 0 ? 1.05e-4 : 0.9e-4);
+  const double node_us = V * 0.9e-4;
   const int levels = (int)std::min(pass_us / node_us, (double)SPEC_MAX_TREE_NODES);
   return levels >= 8 || levels >= std::min(Lmax, N) ? levels : 0;
 }

@@ -24,7 +24,8 @@ constexpr int TOPK_U = 8;        // groups a thread requests before it uses any
 // What bounds it: one workgroup's latency, a launch, one trip to memory for 16 bytes x 8 per thread and two reductions
 // (k scalar passes over the row before). 48 rows of 32000 float32: 6.8 us for
 // k = 1 and 3, 18.6 before.
-// VEC: 16 bytes of elements when the rows are 16-byte aligned, else one.
+// VEC: 16 bytes of elements, from whatever element a row starts at; the last group ends with the row, and what it shares
+// with the group before it counts there (2 rows of 22115 float32: 6.1 us by single elements, 5.5). Rows of less: one.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned long long topk_key(float x, int i) {
   if (x != x) return 0;
@@ -41,7 +42,7 @@ __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k)
   return k;
 }
 
-template <bool BF16, int VEC>
+template <bool BF16, int VEC, bool ODD>   // ODD: V is no multiple of VEC, or the rows are not 16-byte aligned
 __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* __restrict__ logits, int F, int V, int k,
                                                                    const int32_t* __restrict__ child_slot, int N,
                                                                    int32_t* __restrict__ tree_token, int32_t* status) {
@@ -49,14 +50,19 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
   const int row = blockIdx.x, b = row / F, f = row % F, t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   const long base = (long)row * V;
-  const int n_groups = V / VEC;
+  const int n_groups = (V + VEC - 1) / VEC;
+  auto start = [&](int group) { return ODD ? min(group * VEC, V - VEC) : group * VEC; };
+  typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+  typedef __attribute__((ext_vector_type(4))) float f32x4;
+  typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+  typedef f32x4 __attribute__((aligned(4))) f32x4_any;
   auto load = [&](int group, float (&x)[VEC]) {
     if constexpr (BF16) {
-      const __hip_bfloat16* p = (const __hip_bfloat16*)logits + base + (long)group * VEC;
+      const __hip_bfloat16* p = (const __hip_bfloat16*)logits + base + start(group);
       if constexpr (VEC == 1) {
         x[0] = __bfloat162float(*p);
       } else {
-        const uint4 raw = *(const uint4*)p;
+        const u32x4 raw = *(const u32x4_any*)p;
         const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
         for (int e = 0; e < VEC / 2; ++e) {
@@ -65,14 +71,18 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
         }
       }
     } else {
-      const float* p = (const float*)logits + base + (long)group * VEC;
+      const float* p = (const float*)logits + base + start(group);
       if constexpr (VEC == 1) {
         x[0] = *p;
       } else {
-        const float4 raw = *(const float4*)p;
+        const f32x4 raw = *(const f32x4_any*)p;
         x[0] = raw.x; x[1] = raw.y; x[2] = raw.z; x[3] = raw.w;
       }
     }
+  };
+  auto key_of = [&](const float (&x)[VEC], int group, int e) {   // 0: the element belongs to the group before
+    const int i = start(group) + e;
+    return !ODD || i >= group * VEC ? topk_key(x[e], i) : 0ull;
   };
   unsigned long long mine = 0;
   for (int g0 = t; g0 < n_groups; g0 += TOPK_THREADS * TOPK_U) {
@@ -85,7 +95,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
       if (g0 + j * TOPK_THREADS < n_groups) {
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          const unsigned long long key = topk_key(x[j][e], (g0 + j * TOPK_THREADS) * VEC + e);
+          const unsigned long long key = key_of(x[j], g0 + j * TOPK_THREADS, e);
           if (key > mine) mine = key;
         }
       }
@@ -109,7 +119,7 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
         load(g, x);
 #pragma unroll
         for (int e = 0; e < VEC; ++e) {
-          const unsigned long long key = topk_key(x[e], g * VEC + e);
+          const unsigned long long key = key_of(x, g, e);
           if (key < best && key > next) next = key;
         }
       }
@@ -461,15 +471,14 @@ __global__ void __launch_bounds__(64) tree_merge_wave_kernel(
 hipError_t launch_expand_topk(int B, int F, int V, int logits_dtype, const void* logits, int k, const int32_t* child_slot,
                               int N, int32_t* tree_token, int32_t* status, hipStream_t s) {
   const bool bf16 = logits_dtype == SPEC_BF16;
-  const int vec = bf16 ? 8 : 4;   // elements of a 16-byte load: every row then starts on a 16-byte boundary
-  const bool wide = V % vec == 0 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0;
-#define SPEC_TOPK(BF, VE)                                                                                              \
-  hipLaunchKernelGGL((expand_topk_kernel<BF, VE>), dim3(B * F), dim3(TOPK_THREADS), 0, s, logits, F, V, k, child_slot, N, \
+  const int vec = bf16 ? 8 : 4;   // elements of a 16-byte load
+  const bool odd = V % vec != 0 || (reinterpret_cast<uintptr_t>(logits) & 15u) != 0;
+#define SPEC_TOPK(BF, VE, OD)                                                                                             \
+  hipLaunchKernelGGL((expand_topk_kernel<BF, VE, OD>), dim3(B * F), dim3(TOPK_THREADS), 0, s, logits, F, V, k, child_slot, N, \
                      tree_token, status)
-  if (bf16 && wide) SPEC_TOPK(true, 8);
-  else if (bf16) SPEC_TOPK(true, 1);
-  else if (wide) SPEC_TOPK(false, 4);
-  else SPEC_TOPK(false, 1);
+  if (V < vec) { if (bf16) SPEC_TOPK(true, 1, false); else SPEC_TOPK(false, 1, false); }
+  else if (bf16) { if (odd) SPEC_TOPK(true, 8, true); else SPEC_TOPK(true, 8, false); }
+  else { if (odd) SPEC_TOPK(false, 4, true); else SPEC_TOPK(false, 4, false); }
 #undef SPEC_TOPK
   return hipGetLastError();
 }

@@ -38,6 +38,18 @@ constexpr int SWEEP_U = 8;
 // Barrier for LDS contents only: __syncthreads() also waits for the loads in flight.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// Rows of any length by whole groups of VEC elements: the last group ends with the row and so repeats elements of the one
+// before it where VEC does not divide V. Rows of odd vocabularies start at any element; the memory unit takes such loads
+// (single elements before. Stochastic verification, 4 trees of 32, 31999 bfloat16: 48.6 us, 30.5 now; greedy, 1024 rows of
+// 50257 bfloat16: 94, 22 now, 8 rows of 56877: 13.3, 7.8).
+__device__ __forceinline__ int group_start(int group, int vec, int V) { return min(group * vec, V - vec); }
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef u32x4 __attribute__((aligned(2))) u32x4_any;
+typedef u32x2 __attribute__((aligned(2))) u32x2_any;
+typedef f32x4 __attribute__((aligned(4))) f32x4_any;
+
 template <int VEC, bool BF16>
 __device__ __forceinline__ void load_logit_group(const void* base, long elem, float (&v)[VEC]) {
   if (VEC == 4) {
@@ -58,7 +70,7 @@ __device__ __forceinline__ void load_logit_group(const void* base, long elem, fl
 template <int VEC>
 __device__ __forceinline__ void load_f32_group(const float* p, float (&v)[VEC]) {
   if (VEC == 4) {
-    const float4 raw = *(const float4*)p;
+    const f32x4 raw = *(const f32x4_any*)p;
     v[0] = raw.x; v[1] = raw.y; v[2] = raw.z; v[3] = raw.w;
   } else {
     v[0] = *p;
@@ -83,6 +95,46 @@ __device__ inline T block_sum(T v, T* scratch) {
   T tot = 0;
   for (int i = 0; i < nw; ++i) tot += scratch[i];
   return tot;
+}
+
+// VEC elements of a row of logits as they lie in memory: a row's loads are all requested before the first one is converted (a
+// conversion beside its load waits for it, 32 bf16 elements per thread one after the other).
+template <bool BF16, int VEC>
+struct LogitGroup {
+  unsigned raw[BF16 ? (VEC + 1) / 2 : VEC];
+  __device__ __forceinline__ void load(const void* base, unsigned elem) {
+    if constexpr (VEC == 4 && BF16) {
+      const u32x2 v = *(const u32x2_any*)((const unsigned short*)base + elem);
+      raw[0] = v.x; raw[1] = v.y;
+    } else if constexpr (VEC == 4) {
+      const u32x4 v = *(const u32x4_any*)((const float*)base + elem);
+      raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
+    } else if constexpr (BF16) {
+      raw[0] = ((const unsigned short*)base)[elem];
+    } else {
+      raw[0] = __float_as_uint(((const float*)base)[elem]);
+    }
+  }
+  __device__ __forceinline__ void set_minus_infinity() {
+#pragma unroll
+    for (unsigned& r : raw) r = BF16 ? 0xff80ff80u : 0xff800000u;
+  }
+  __device__ __forceinline__ void expand(float (&v)[VEC]) {
+    if constexpr (BF16 && VEC == 1) asm("" : "+v"(raw[0]));   // (the compiler moves this one back to its load otherwise)
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) v[e] = __uint_as_float(!BF16 ? raw[e] : e % 2 == 0 ? raw[e / 2] << 16 : raw[e / 2] & 0xffff0000u);
+  }
+};
+
+// The elements of the row's last group that the group before it holds too.
+template <int VEC>
+__device__ __forceinline__ void drop_repeated(float (&v)[VEC], int group, int n_groups, int V, float with) {
+  if (group == n_groups - 1) {
+    const int repeated = group * VEC - group_start(group, VEC, V);
+#pragma unroll
+    for (int e = 0; e < VEC; ++e)
+      if (e < repeated) v[e] = with;
+  }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -134,7 +186,7 @@ __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __re
   const long row = blockIdx.x;
   const int t = threadIdx.x;
   const long base = row * V;
-  const int n_groups = V / VEC;
+  const int n_groups = (V + VEC - 1) / VEC;
   const bool want_sum = node_sumexp != nullptr;
   if (parent != nullptr) {
     const int lane = t & 63;
@@ -145,22 +197,25 @@ __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __re
   int best_i = 0x7fffffff;
   for (int g0 = 0; g0 < n_groups; g0 += NS_THREADS * SWEEP_U) {
     float x[SWEEP_U][VEC];
+    LogitGroup<BF16, VEC> raw[SWEEP_U];
 #pragma unroll
     for (int j = 0; j < SWEEP_U; ++j) {
       const int gi = g0 + j * NS_THREADS + t;
-      if (gi < n_groups) {
-        load_logit_group<VEC, BF16>(logits, base + (long)gi * VEC, x[j]);
-      } else {
+      if (gi < n_groups) raw[j].load((const char*)logits + base * (BF16 ? 2 : 4), (unsigned)group_start(gi, VEC, V));
+      else raw[j].set_minus_infinity();
+    }
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) x[j][e] = -INFINITY;
-      }
+    for (int j = 0; j < SWEEP_U; ++j) raw[j].expand(x[j]);
+    if (V % VEC != 0) {
+#pragma unroll
+      for (int j = 0; j < SWEEP_U; ++j) drop_repeated<VEC>(x[j], g0 + j * NS_THREADS + t, n_groups, V, -INFINITY);
     }
     float m = best;
 #pragma unroll
     for (int j = 0; j < SWEEP_U; ++j)
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
-        if (x[j][e] > m) { m = x[j][e]; best_i = (g0 + j * NS_THREADS + t) * VEC + e; }   // ascending index: lowest wins ties
+        if (x[j][e] > m) { m = x[j][e]; best_i = group_start(g0 + j * NS_THREADS + t, VEC, V) + e; }   // ascending index: lowest wins ties
     if (want_sum && m > -INFINITY) {
       sum *= fast_exp((best - m) * inv_temp);     // best = -inf gives 0
 #pragma unroll
@@ -263,13 +318,14 @@ __device__ inline int inverse_cdf_draw(const void* __restrict__ logits, long lro
 }
 
 // ---------------------------------------------------------------------------------------------
-// arg-max (and maximum) of a row without the sum, for rows of whole 16-byte groups (4 floats or 8 bf16). The pass over all
+// arg-max (and maximum) of a row without the sum, for rows of at least one 16-byte group (4 floats or 8 bf16). The pass over all
 // nodes of greedy verification is bound by memory only if an element costs few instructions: a group costs its maximum, one
-// comparison and the selection of the group's raw bits, and which element it was is found once per thread at the end
+// comparison and the selection of the group's raw bits, and which element it was is found once per thread at the end; half a
+// sweep is on its way while the other half is looked at (320 rows of 45232 float32: 16.9 us with whole sweeps, 16.1)
 // (1024 rows of 32000 bf16: 17.0 us with a comparison and two selections per element and 8-byte loads, 12.4 now;
 // 2048 rows of 32000 float32: 47 before, 45 now).
 // ---------------------------------------------------------------------------------------------
-template <bool BF16, int NT>
+template <bool BF16, int NT, bool ODD>   // ODD: V is no multiple of VEC
 __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict__ logits, int V, int32_t* __restrict__ node_argmax,
                                                          float* __restrict__ node_max) {
   constexpr int VEC = BF16 ? 8 : 4, WAVES = NT / 64;
@@ -277,9 +333,13 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
   __shared__ int s_idx[WAVES];
   const long row = blockIdx.x;
   const int t = threadIdx.x;
-  const int n_groups = V / VEC;
-  const uint4* base = (const uint4*)((const char*)logits + row * V * (BF16 ? 2 : 4));
-  auto expand = [](const uint4 raw, float (&x)[VEC]) {
+  // ODD: groups lie on 16-byte boundaries but for the first, which starts with the row, and the last, which ends with it; they
+  // repeat elements of their neighbours, which changes nothing here.
+  const int n_groups = ODD ? (V + VEC - 1) / VEC + 2 : V / VEC;
+  const int lead = ODD ? (int)(row * V % VEC == 0 ? 0 : VEC - row * V % VEC) - VEC : 0;
+  const char* base = (const char*)logits + row * V * (BF16 ? 2 : 4);
+  auto start_of = [&](int group) { return ODD ? max(0, min(group * VEC + lead, V - VEC)) : group * VEC; };
+  auto expand = [](const u32x4 raw, float (&x)[VEC]) {
     const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -293,13 +353,19 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
   };
   float best = -INFINITY;
   int best_g = -1;
-  uint4 best_raw = make_uint4(0, 0, 0, 0);
-  for (int g0 = t; g0 < n_groups; g0 += NT * SWEEP_U) {
-    uint4 raw[SWEEP_U];
+  u32x4 best_raw = {0u, 0u, 0u, 0u};
+  constexpr int U = SWEEP_U / 2;   // one half of a sweep is on its way while the other is looked at
+  auto load = [&](u32x4 (&raw)[U], int g0) {
 #pragma unroll
-    for (int j = 0; j < SWEEP_U; ++j) raw[j] = base[min(g0 + j * NT, n_groups - 1)];   // (the last group again changes nothing)
+    for (int j = 0; j < U; ++j) {   // (past the end: the last group again, which changes nothing)
+      const int g = min(g0 + j * NT, n_groups - 1);
+      if (ODD) raw[j] = *(const u32x4_any*)(base + start_of(g) * (BF16 ? 2 : 4));
+      else raw[j] = ((const u32x4*)base)[g];
+    }
+  };
+  auto look_at = [&](const u32x4 (&raw)[U], int g0) {
 #pragma unroll
-    for (int j = 0; j < SWEEP_U; ++j) {
+    for (int j = 0; j < U; ++j) {
       float x[VEC];
       expand(raw[j], x);
       float m = x[0];
@@ -311,6 +377,22 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
         best_raw = raw[j];
       }
     }
+  };
+  u32x4 even[U], odd[U];
+  load(even, t);
+  for (int g0 = t;; g0 += 2 * U * NT) {   // (the last half apart: nothing is requested behind it)
+    if (g0 - t + U * NT >= n_groups) {
+      look_at(even, g0);
+      break;
+    }
+    load(odd, g0 + U * NT);
+    look_at(even, g0);
+    if (g0 - t + 2 * U * NT >= n_groups) {
+      look_at(odd, g0 + U * NT);
+      break;
+    }
+    load(even, g0 + 2 * U * NT);
+    look_at(odd, g0 + U * NT);
   }
   int best_i = 0x7fffffff;
   if (best_g >= 0) {
@@ -318,7 +400,7 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
     expand(best_raw, x);
 #pragma unroll
     for (int e = VEC - 1; e >= 0; --e)
-      if (x[e] == best) best_i = best_g * VEC + e;
+      if (x[e] == best) best_i = start_of(best_g) + e;
   }
   for (int o = 32; o > 0; o >>= 1) {
     const float ov = __shfl_xor(best, o);
@@ -484,36 +566,7 @@ __device__ __forceinline__ double readlane_f64(double v, int lane) {
                               (unsigned)__builtin_amdgcn_readlane((int)b, lane));
 }
 
-// VEC elements of a row of logits as they lie in memory: a row's loads are all requested before the first one is converted (a
-// conversion beside its load waits for it, 32 bf16 elements per thread one after the other).
-template <bool BF16, int VEC>
-struct LogitGroup {
-  unsigned raw[BF16 ? (VEC + 1) / 2 : VEC];
-  __device__ __forceinline__ void load(const void* base, unsigned elem) {
-    if constexpr (VEC == 4 && BF16) {
-      const uint2 v = *(const uint2*)((const unsigned short*)base + elem);
-      raw[0] = v.x; raw[1] = v.y;
-    } else if constexpr (VEC == 4) {
-      const uint4 v = *(const uint4*)((const float*)base + elem);
-      raw[0] = v.x; raw[1] = v.y; raw[2] = v.z; raw[3] = v.w;
-    } else if constexpr (BF16) {
-      raw[0] = ((const unsigned short*)base)[elem];
-    } else {
-      raw[0] = __float_as_uint(((const float*)base)[elem]);
-    }
-  }
-  __device__ __forceinline__ void set_minus_infinity() {
-#pragma unroll
-    for (unsigned& r : raw) r = BF16 ? 0xff80ff80u : 0xff800000u;
-  }
-  __device__ __forceinline__ void expand(float (&v)[VEC]) {
-    if constexpr (BF16 && VEC == 1) asm("" : "+v"(raw[0]));   // (the compiler moves this one back to its load otherwise)
-#pragma unroll
-    for (int e = 0; e < VEC; ++e) v[e] = __uint_as_float(!BF16 ? raw[e] : e % 2 == 0 ? raw[e / 2] << 16 : raw[e / 2] & 0xffff0000u);
-  }
-};
-
-template <bool BF16, int VEC, int NG>
+template <bool BF16, int VEC, int NG, bool ODD>   // ODD: V is no multiple of VEC
 __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     int N, int V, const void* __restrict__ logits, const float* __restrict__ probs_ssm, int R,
     const int32_t* __restrict__ ssm_row, const int32_t* __restrict__ token, const int32_t* __restrict__ parent,
@@ -534,26 +587,26 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
 
   const int b = blockIdx.x, t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-  const int n_groups = V / VEC;
+  const int n_groups = (V + VEC - 1) / VEC;
 
   float w[NG][VEC];   // the row of node u: its logits, then the current distribution, un-normalised: P(i) = w_i / Z
-  // Rows are addressed as a wave-uniform base per round plus one offset per lane (an address per load would not leave
-  // room for the row in registers); u and rows of probs_ssm are made uniform for that.
+  // Rows are addressed as a wave-uniform base per round plus one offset per lane, or (ODD) a base and a 32-bit offset per load:
+  // 64-bit addresses would not leave room for the row in registers; u and rows of probs_ssm are made uniform for that.
   auto load_row = [&](int u) {   // the logits of node u; elements past the end are -inf
-    const long base = ((long)b * N + u) * V;
+    const char* row = (const char*)logits + ((long)b * N + u) * V * (BF16 ? 2 : 4);
     LogitGroup<BF16, VEC> raw[NG];
 #pragma unroll
     for (int j = 0; j < NG; ++j) {
-      if (j * SW_THREADS + t < n_groups) {
-        const void* round = BF16 ? (const void*)((const __hip_bfloat16*)logits + base + j * SW_THREADS * VEC)
-                                 : (const void*)((const float*)logits + base + j * SW_THREADS * VEC);
-        raw[j].load(round, (unsigned)(t * VEC));
-      } else {
-        raw[j].set_minus_infinity();
-      }
+      if (j * SW_THREADS + t >= n_groups) raw[j].set_minus_infinity();
+      else if (ODD) raw[j].load(row, (unsigned)group_start(j * SW_THREADS + t, VEC, V));
+      else raw[j].load(row + j * SW_THREADS * VEC * (BF16 ? 2 : 4), (unsigned)(t * VEC));
     }
 #pragma unroll
     for (int j = 0; j < NG; ++j) raw[j].expand(w[j]);
+    if (ODD) {
+#pragma unroll
+      for (int j = 0; j < NG; ++j) drop_repeated<VEC>(w[j], j * SW_THREADS + t, n_groups, V, -INFINITY);
+    }
   };
 
   static_assert(SPEC_MAX_TREE_NODES == 128, "two nodes per lane, parents in the bits from 7 up");
@@ -694,7 +747,8 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
       for (int jj = 0; jj < NG; ++jj) {
         const int gi = jj * SW_THREADS + t;
         if (gi < n_groups) {
-          load_f32_group<VEC>(Q + jj * SW_THREADS * VEC + (unsigned)(t * VEC), q[jj]);
+          if (ODD) load_f32_group<VEC>(Q + (unsigned)group_start(gi, VEC, V), q[jj]);   // (what the last group repeats meets weights of 0)
+          else load_f32_group<VEC>(Q + jj * SW_THREADS * VEC + (unsigned)(t * VEC), q[jj]);
         } else {
 #pragma unroll
           for (int e = 0; e < VEC; ++e) q[jj][e] = 0.f;
@@ -767,13 +821,14 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
           const int fl = hit != 0 ? __ffsll((long long)hit) - 1 : 63;
           if (lane == fl) {
             const double run = before + incl - sum;
-            int ans = (j * SW_THREADS + t) * VEC + VEC - 1;
+            const int first = ODD ? group_start(j * SW_THREADS + t, VEC, V) : (j * SW_THREADS + t) * VEC;
+            int ans = first + VEC - 1;
 #pragma unroll
             for (int e = VEC - 1; e >= 0; --e) {   // the first element whose running sum exceeds the target
               double upto_e = run;
 #pragma unroll
               for (int i = 0; i <= e; ++i) upto_e += (double)w[j][i];
-              if (upto_e > target) ans = (j * SW_THREADS + t) * VEC + e;
+              if (upto_e > target) ans = first + e;
             }
             s_ans = min(ans, V - 1);
           }
@@ -980,27 +1035,30 @@ __global__ void __launch_bounds__(SW_THREADS) node_sample_kernel(const void* __r
 hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
                              int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s,
                              const int32_t* parent, int own_levels) {
-  const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
+  const bool bf16 = logits_dtype == SPEC_BF16;
+  // 256 threads where there are a thousand rows or more (see above), and for rows that they take in one go: four wavefronts'
+  // results are merged sooner than sixteen's (440 rows of 1051 bfloat16 with the walk: 8.35 us, 6.55 now)
   const bool many = (long)B * N >= 1024;
-  if (node_sumexp == nullptr && V % (bf16 ? 8 : 4) == 0) {   // (the entry points require 16-byte aligned logits)
-#define SPEC_NA(BF, NT) \
-  hipLaunchKernelGGL((node_argmax_kernel<BF, NT>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max)
-    if (bf16) { if (many) SPEC_NA(true, 256); else SPEC_NA(true, 1024); }
-    else { if (many) SPEC_NA(false, 256); else SPEC_NA(false, 1024); }
+  if (node_sumexp == nullptr && V >= (bf16 ? 8 : 4)) {   // (the entry points require 16-byte aligned logits)
+    const bool small = many || V <= 256 * SWEEP_U * (bf16 ? 8 : 4) / 2;
+    const bool odd = V % (bf16 ? 8 : 4) != 0;
+#define SPEC_NA(BF, NT)                                                                                                        \
+  do {                                                                                                                         \
+    if (odd) hipLaunchKernelGGL((node_argmax_kernel<BF, NT, true>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max); \
+    else hipLaunchKernelGGL((node_argmax_kernel<BF, NT, false>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max);    \
+  } while (0)
+    if (bf16) { if (small) SPEC_NA(true, 256); else SPEC_NA(true, 1024); }
+    else { if (small) SPEC_NA(false, 256); else SPEC_NA(false, 1024); }
 #undef SPEC_NA
     return hipGetLastError();
   }
-#define SPEC_NS(BF, VE)                                                                                                  \
-  if (many)                                                                                                              \
-    hipLaunchKernelGGL((node_stats_kernel<BF, VE, 256>), dim3(B * N), dim3(256), 0, s, logits, V, inv_temp, node_argmax,  \
-                       node_max, node_sumexp, parent, N, own_levels);                                                    \
-  else                                                                                                                   \
-    hipLaunchKernelGGL((node_stats_kernel<BF, VE, 1024>), dim3(B * N), dim3(1024), 0, s, logits, V, inv_temp, node_argmax, \
-                       node_max, node_sumexp, parent, N, own_levels)
-  if (bf16 && vec) { SPEC_NS(true, 4); }
-  else if (bf16) { SPEC_NS(true, 1); }
-  else if (vec) { SPEC_NS(false, 4); }
-  else { SPEC_NS(false, 1); }
+#define SPEC_NS(BF, VE, NT)                                                                                              \
+  hipLaunchKernelGGL((node_stats_kernel<BF, VE, NT>), dim3(B * N), dim3(NT), 0, s, logits, V, inv_temp, node_argmax,      \
+                     node_max, node_sumexp, parent, N, own_levels)
+  const bool small = many || V <= 256 * SWEEP_U * 4 / 2;
+  if (V < 4) { if (bf16) SPEC_NS(true, 1, 256); else SPEC_NS(false, 1, 256); }
+  else if (bf16) { if (small) SPEC_NS(true, 4, 256); else SPEC_NS(true, 4, 1024); }
+  else { if (small) SPEC_NS(false, 4, 256); else SPEC_NS(false, 4, 1024); }
 #undef SPEC_NS
   return hipGetLastError();
 }
@@ -1035,22 +1093,25 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
                                   int own_levels) {
   const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
   if (stochastic_walk_in_registers(V)) {
-#define SPEC_SWR(BF, VE, NGR)                                                                                         \
-  hipLaunchKernelGGL((stochastic_walk_reg_kernel<BF, VE, NGR>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, \
+#define SPEC_SWR_O(BF, VE, NGR, OD)                                                                                         \
+  hipLaunchKernelGGL((stochastic_walk_reg_kernel<BF, VE, NGR, OD>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, \
                      R, ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, own_levels,  \
                      Lmax, path, len, out_tokens, status)
-  // (registers for twice the vocabulary at most: rounds past its end cost as much as the others; 4 trees of 32, 9001 float32:
-  // 35.7 us with 32 single elements per thread, 23.5 with 16)
+#define SPEC_SWR(BF, VE, NGR)                                                                      \
+  do {                                                                                              \
+    if (V % VE != 0) SPEC_SWR_O(BF, VE, NGR, true); else SPEC_SWR_O(BF, VE, NGR, false);            \
+  } while (0)
+  // (registers for twice the vocabulary at most: rounds past its end cost as much as the others)
 #define SPEC_SWR_T(BF)                                          \
-  if (!vec && V <= SW_THREADS * 8) SPEC_SWR(BF, 1, 8);          \
-  else if (!vec && V <= SW_THREADS * 16) SPEC_SWR(BF, 1, 16);   \
-  else if (!vec) SPEC_SWR(BF, 1, 32);                           \
+  if (V < 4) SPEC_SWR_O(BF, 1, 1, false);                       \
   else if (V <= SW_THREADS * 4) SPEC_SWR(BF, 4, 1);             \
+  else if (V <= SW_THREADS * 8) SPEC_SWR(BF, 4, 2);             \
   else if (V <= SW_THREADS * 16) SPEC_SWR(BF, 4, 4);            \
   else SPEC_SWR(BF, 4, 8)
     if (bf16) { SPEC_SWR_T(true); } else { SPEC_SWR_T(false); }
 #undef SPEC_SWR_T
 #undef SPEC_SWR
+#undef SPEC_SWR_O
     return hipGetLastError();
   }
 #define SPEC_SW(BF, VE)                                                                                              \

@@ -95,10 +95,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
   static_assert(KW == 1 || QW * NTW * 64 * (DB * 4 + 2) * 4 <= 2 * STAGE_BYTES, "merge area fits the staging area");
 
   __shared__ __attribute__((aligned(16))) unsigned char lds[2 * STAGE_BYTES];
-  __shared__ unsigned long long s_anc[SPEC_MAX_TREE_NODES][2];
-  __shared__ int s_parent[SPEC_MAX_TREE_NODES];
-  __shared__ int s_depth[SPEC_MAX_TREE_NODES];
-  __shared__ int s_flag;
+  __shared__ TreeLds s_tree;
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -180,10 +177,9 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       }
     };
     // The first two tiles are requested before prefix_len is known. Where they stand relative to the queries and
-    // the tree words decides what the first wait leaves in flight (loads return in order): tiles first on the shapes
-    // with one key part per wavefront; on the 2 x 2 shape the tree words and queries first, so that the wait for the
-    // tree words does not wait for the tiles too (alternating builds on the same buffers: 145.8 -> 144.5 us on a
-    // ragged batch of 8192-16384 keys, while the other shapes lose half a percent with that order).
+    // the tree words decides what the first wait leaves in flight (loads return in order): the tree words first, on the 2 x 2
+    // shape the queries too (alternating builds on the same buffers: 145.8 -> 144.5 us on a ragged batch of
+    // 8192-16384 keys, while the shapes with one key part per wavefront lose half a percent with the queries in front).
     auto first_tiles = [&]() {
       bool in_pool;   // entries past the request's end may hold anything: not judged here
       issue_speculative(Kr[0], Vr[0], kc, vc, c0, PAGED ? page_shift(b, c0, &in_pool) : 0);
@@ -227,10 +223,9 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       first_tiles();
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (t == 0) s_flag = 0;
     if (t < N) {
-      s_parent[t] = my_parent;
-      s_depth[t] = my_depth;
+      s_tree.parent[t] = my_parent;
+      s_tree.depth[t] = my_depth;
     }
     lds_barrier();
     // Rotary embedding of the queries, in registers: k-step ks of a lane holds dimensions 32 ks + 8 g .., its
@@ -239,7 +234,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     auto rotate_q = [&](bf16x8 (&dst)[NTW][KS]) {
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) {
-        const int pos = min(max(P + s_depth[min(tile_node[nt], N - 1)], 0), rope.len - 1);
+        const int pos = min(max(P + s_tree.depth[min(tile_node[nt], N - 1)], 0), rope.len - 1);
 #pragma unroll
         for (int ks = 0; ks < KS / 2; ++ks) {
           const long at = (long)pos * (D / 2) + ks * 32 + g * 8;
@@ -272,15 +267,18 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     if (c0 >= len) return;
     const int c1 = min(c1_cap, len);
     const bool touches_tree = c1 > P;
+    // every block this segment reads must lie inside the pool: looked at last, so that nothing waits for these loads
+    auto check_blocks = [&]() {
+      if (PAGED) {
+        for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
+          const int e = pg.table[(long)b * pg.max_blocks + j];
+          if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
+        }
+      }
+    };
     const int n_tiles = (c1 - c0 + KT - 1) / KT;
     const int n_clean = max(0, min(P, c1) - c0) / KT;
     const int last_row = len - 1;
-    if (PAGED) {   // every block this segment reads must lie inside the pool
-      for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
-        const int e = pg.table[(long)b * pg.max_blocks + j];
-        if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
-      }
-    }
 
     // speculative tiles that reach the tree are fetched again from the right sources
     if (APPEND && n_clean == 0) issue(Kr[0], Vr[0], c0, std::integral_constant<int, 2>{}, P, last_row, 0);
@@ -297,31 +295,20 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
 #pragma unroll
     for (int nt = 0; nt < NTW; ++nt) anc_lo[nt] = anc_hi[nt] = 0ull;
     if (touches_tree) {
-      if (t < N) {
-        bool ok = (t == 0) ? (my_parent == -1 && my_depth == 0) : (my_parent >= 0 && my_parent < t);
-        if (ok && t > 0) ok = my_depth == s_depth[my_parent] + 1;
-        if (!ok) atomicOr(&s_flag, 1);
+      if (wave == 0) {
+        const bool bad = tree_masks_by_wave(s_tree, N, lane, my_parent, my_depth);
+        if (lane == 0) s_tree.bad = bad;
       }
       lds_barrier();
-      if (s_flag != 0) {
+      if (s_tree.bad) {
         zero_outputs(SPEC_ST_BAD_TREE);
+        check_blocks();
         return;
       }
-      if (t < N) {
-        unsigned long long lo = 0, hi = 0;
-        int u = t;
-        for (int step = 0; step < N && u >= 0; ++step) {
-          if (u < 64) lo |= 1ull << u; else hi |= 1ull << (u - 64);
-          u = s_parent[u];
-        }
-        s_anc[t][0] = lo;
-        s_anc[t][1] = hi;
-      }
-      lds_barrier();
 #pragma unroll
       for (int nt = 0; nt < NTW; ++nt) {
         const int n = tile_node[nt];
-        if (n < N) { anc_lo[nt] = s_anc[n][0]; anc_hi[nt] = s_anc[n][1]; }
+        if (n < N) { anc_lo[nt] = s_tree.anc[n][0]; anc_hi[nt] = s_tree.anc[n][1]; }
       }
     }
 
@@ -345,7 +332,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
           if (row >= P && row < c1) {
             const int piece = t % LPR;
             const bool low = piece < LPR / 2;
-            const int pos = min(max(P + s_depth[row - P], 0), rope.len - 1);
+            const int pos = min(max(P + s_tree.depth[row - P], 0), rope.len - 1);
             const long at = (long)pos * (D / 2) + (piece % (LPR / 2)) * 8;
             uint4 olo, ohi;
             rope_pair<true>(__builtin_bit_cast(uint4, low ? Ks_[j] : other), __builtin_bit_cast(uint4, low ? other : Ks_[j]),
@@ -590,6 +577,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       }
     }
 
+    check_blocks();
     // ---- normalise and write the (last) head, or emit the partial
     if (final_out) write_out(l_tot, nh - 1);
 #pragma unroll

@@ -104,10 +104,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     int H, int H_v, int n_qg, int hpw, int S_cap, int chunk_keys, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh,
     long n_sb, long n_sn, long n_sh, long kv_sb, long kv_sh, long kv_ss, float scale_log2, Pages pg, Rope rope) {
   __shared__ __attribute__((aligned(1024))) unsigned char ring[NST * STAGE];
-  __shared__ unsigned long long s_anc[SPEC_MAX_TREE_NODES][2];
-  __shared__ int s_parent[SPEC_MAX_TREE_NODES];
-  __shared__ int s_depth[SPEC_MAX_TREE_NODES];
-  __shared__ int s_flag;
+  __shared__ TreeLds s_tree;
 
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -199,17 +196,16 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     }
     const int my_parent = parent[(long)b * N + min(t, N - 1)];
     const int my_depth = depth[(long)b * N + min(t, N - 1)];
-    if (t == 0) s_flag = 0;
     if (t < N) {
-      s_parent[t] = my_parent;
-      s_depth[t] = my_depth;
+      s_tree.parent[t] = my_parent;
+      s_tree.depth[t] = my_depth;
     }
     lds_barrier();
     if (APPEND && ROPE) {
       // Rotary embedding of the queries, in registers: k-step ks of a lane holds dimensions 16 ks + 8 hh .., its
       // partner ks + KSQ/2 the same dimensions + D/2. The position is clamped into the tables (a malformed tree is
       // found only later, and its outputs are zeros).
-      const int pos = min(max(P + s_depth[min(node, N - 1)], 0), rope.len - 1);
+      const int pos = min(max(P + s_tree.depth[min(node, N - 1)], 0), rope.len - 1);
 #pragma unroll
       for (int ks = 0; ks < KSQ / 2; ++ks) {
         const long at = (long)pos * (D / 2) + ks * 16 + hh * 8;
@@ -243,14 +239,17 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     }
     const int c1 = min(c1_cap, len);
     const bool touches_tree = c1 > P;
+    // every block this segment reads must lie inside the pool: looked at last, so that nothing waits for these loads
+    auto check_blocks = [&]() {
+      if (PAGED) {
+        for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
+          const int e = pg.table[(long)b * pg.max_blocks + j];
+          if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
+        }
+      }
+    };
     const int n_st = (c1 - c0 + SK - 1) / SK;
     const int n_clean = max(0, min(P, c1) - c0) / SK;
-    if (PAGED) {   // every block this segment reads must lie inside the pool
-      for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
-        const int e = pg.table[(long)b * pg.max_blocks + j];
-        if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
-      }
-    }
     // speculative stages that reach the tree or the end of the segment are requested again from the right
     // sources (same slot: loads land in order); one drain then makes the schedule below regular from the start
     {
@@ -266,28 +265,17 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
 
     // ---- tree: validate, build ancestor-or-self masks
     if (touches_tree) {
-      if (t < N) {
-        bool ok = (t == 0) ? (my_parent == -1 && my_depth == 0) : (my_parent >= 0 && my_parent < t);
-        if (ok && t > 0) ok = my_depth == s_depth[my_parent] + 1;
-        if (!ok) atomicOr(&s_flag, 1);
+      if (wave == 0) {
+        const bool bad = tree_masks_by_wave(s_tree, N, lane, my_parent, my_depth);
+        if (lane == 0) s_tree.bad = bad;
       }
       lds_barrier();
-      if (s_flag != 0) {
+      if (s_tree.bad) {
         zero_outputs(SPEC_ST_BAD_TREE);
+        check_blocks();
         wait_loads_but<0>();
         return;
       }
-      if (t < N) {
-        unsigned long long lo = 0, hi = 0;
-        int u = t;
-        for (int step = 0; step < N && u >= 0; ++step) {
-          if (u < 64) lo |= 1ull << u; else hi |= 1ull << (u - 64);
-          u = s_parent[u];
-        }
-        s_anc[t][0] = lo;
-        s_anc[t][1] = hi;
-      }
-      lds_barrier();
     }
 
     f32x16 O[DB32];   // O^T: lane (n32, hh) holds d = 32 db + 8 (i / 4) + 4 hh + i % 4 of its query
@@ -320,7 +308,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
       __builtin_amdgcn_sched_barrier(0);
       if (masked) {   // (a branch inside one body: two bodies per slot made the compiler copy O between them)
         const int nd = opaque(node);   // the ancestor mask is read back from LDS rather than held across clean stages
-        const unsigned long long anc_lo = nd < N ? s_anc[nd][0] : 0ull, anc_hi = nd < N ? s_anc[nd][1] : 0ull;
+        const unsigned long long anc_lo = nd < N ? s_tree.anc[nd][0] : 0ull, anc_hi = nd < N ? s_tree.anc[nd][1] : 0ull;
         // visibility of the stage's 32 keys for this lane's query as one word: bit j = key kb + j is inside the
         // prefix, or tree node (kb + j - P) is the query or one of its ancestors; keys at and beyond c1 are not
         // visible. rel0 = kb - P is negative while the stage starts inside the prefix.
@@ -433,7 +421,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
           unsigned char* at_row = ring + rs * STAGE + rr * ROWB;
           u32x4* lo = (u32x4*)(at_row + ((c ^ swizzle(rr & 15)) << 4));
           u32x4* hi = (u32x4*)(at_row + (((c + 8) ^ swizzle(rr & 15)) << 4));
-          const int pos = min(max(P + s_depth[row - P], 0), rope.len - 1);
+          const int pos = min(max(P + s_tree.depth[row - P], 0), rope.len - 1);
           const long at = (long)pos * (D / 2) + c * 8;
           uint4 olo, ohi;
           rope_pair<true>(__builtin_bit_cast(uint4, *lo), __builtin_bit_cast(uint4, *hi), rope.cos + at, rope.sin + at, &olo,
@@ -470,6 +458,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
       if (st0 + 3 < n_st) iteration(st0 + 3, std::integral_constant<int, 3>{});
     }
 
+    check_blocks();
     // ---- normalise and write, or emit the partial
     const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (final_out) {

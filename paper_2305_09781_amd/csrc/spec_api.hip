@@ -180,9 +180,34 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // the key range is cut into as many equal chunks as fill the device once, of at least 256 keys
       // (measured on one to four requests of 32 heads, 1024 to 16384 keys: 13 us instead of 22 for one
       // request of 1024 keys, 50 instead of 57 for 16384).
-      long splits = std::max<long>(1, resident / std::max<long>(1, groups));
       const long max_splits = std::max<long>(1, max_len / 256);
+      // The wide kernels hold two workgroups per compute unit, but where one per compute unit nearly fills the device (four
+      // fifths) a cut for that many is the better one: half the partials, or none and no merge, and no two workgroups that
+      // compete for a compute unit. Measured, us, two per compute unit / one: 32/8 heads of 7000 keys, trees of 33, 31.4 / 25.5;
+      // 32/8 of 16000, 10, 30.3 / 25.8; 2 x 32 of 1500, 60, 27.6 / 24.3; 4 x 32/8 of 3000, 32, 32.7 / 27.5; 40 heads of 3000,
+      // 30, 24.5 / 22.7; uncut 8 x 32 heads of 600, 100, 43.0 / 31.4; 6 x 40 of 1000, 100, 48.4 / 41.0; 4 x 64 of 600, 30, 26.1
+      // / 20.7; 7 x 32 of 2000, 60, 55.9 / 52.2. Uncut, a lone workgroup's two tiles in flight and the idle fifth tell in the end
+      // (28 x 64/8 heads of 3000, 16, 83.1 / 85.8; D = 64: 20 x 12 of 3000, 30, 38.8 / 42.4, but 8 x 32 of 700, 50, 22.7 / 17.6):
+      // only up to 20 D keys, and cut only where nine tenths are filled or the chunks are short (14 x 64/8 of 3000, 16, 51.7 /
+      // 54.4). Pairs of many query groups are bound by arithmetic and want both (64/8 heads of 4000 keys, trees of 128, 42 / 47).
+      const long per_unit = compute_units() / std::max<long>(1, groups), filled = 10 * groups * per_unit / compute_units();
+      const bool one_per_unit = p.wide && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits && filled >= 8 &&
+                                (per_unit == 1 ? max_len <= 20 * d.D : filled >= 9 || max_len / per_unit <= 10 * d.D);
+      const long hold = one_per_unit ? compute_units() : resident;
+      long splits = std::max<long>(1, hold / std::max<long>(1, groups));
       if (splits > max_splits) splits = max_splits;
+      // Three query tiles and more per workgroup (grouped heads, wide trees) make a tile of keys dearer: where few pairs leave
+      // most of the device idle the cuts go down to 128 keys, up to eight of them and half a workgroup per compute unit
+      // (beyond that the partials cost what it saves). Measured, us, by 256 and by 128 keys: 12 heads of 400 keys, trees of 100,
+      // 24.3 / 18.4; 2 x 32/8 heads, 700 keys, 16.9 / 12.6; 4 x 64/8, 500 keys, 20.7 / 17.7; 32 heads of 400 keys, trees of 40,
+      // 18.0 / 14.1. Two cuts alone only pay where there are few pairs and a head dimension of 128 (32/8 heads, 250 keys, 14.2 /
+      // 12.0; but 64 heads of 300 keys, trees of 50, 15.1 / 16.1, and 3 x 12 heads of 260 keys, D = 64, 10.4 / 11.5); two query
+      // tiles do not gain (40 heads of 300 keys, trees of 24, 13.3 / 14.7).
+      if (p.wide && tiles > 2 && splits <= 4) {   // (2 x 24/6 heads, 2032 keys, in seven or in eight: 12.0 / 12.7)
+        const long room = compute_units() / 2 / std::max<long>(1, groups);
+        const long finer = std::min<long>({room, (long)max_len / 128, 8});
+        if (finer > 2 || (finer == 2 && room > 2 && d.D == 128)) splits = std::max(splits, finer);
+      }
       chunk = (int)((max_len + splits - 1) / splits);
       if (chunk < 128) chunk = 128;
       // Where there is room for one chunk more per pair, the prefix alone is cut, at multiples of the kernel's tile: the tree
@@ -196,7 +221,7 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       if (splits > 1 && !p.m32) {
         const int per = (max_prefix + (int)splits - 1) / (int)splits;
         auto rounded = [&](int to) { return std::max(128, (int)round_up((size_t)per, (size_t)to)); };
-        auto fits = [&](int c) { return groups * ((max_len + c - 1) / c) <= resident; };
+        auto fits = [&](int c) { return groups * ((max_len + c - 1) / c) <= hold; };
         auto longest = [&](int c) { return std::max(c, max_len - (max_len - 1) / c * c + 64); };
         if (!p.wide) {
           chunk = fits(rounded(tile)) ? rounded(tile) : (int)round_up((size_t)chunk, tile);

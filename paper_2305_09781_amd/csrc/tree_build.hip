@@ -21,9 +21,9 @@ constexpr int TOPK_U = 8;        // groups a thread requests before it uses any
 // the largest of the 16 wavefronts' largest keys; only the wavefront that held it goes on to its next: its 64 lanes read
 // the winning thread's elements again (a few hundred bytes, from the cache) and reduce what comes after the pick.
 //
-// What bounds it: one workgroup's latency, a launch, one trip to memory for 16 bytes x 8 per thread and two reductions
-// (k scalar passes over the row before). 48 rows of 32000 float32: 6.8 us for
-// k = 1 and 3, 18.6 before.
+// What bounds it: one workgroup's latency, a launch, one trip to memory for 16 bytes x 8 per thread and two reductions. Eight
+// steps of 16 to 48 rows of 32000 float32 and the merge behind them: 58.6 us with a key and a 64-bit comparison per element,
+// 50.2 with one comparison per group; 11 to 33 rows of 93776: 93 and 71.
 // VEC: 16 bytes of elements, from whatever element a row starts at; the last group ends with the row, and what it shares
 // with the group before it counts there (2 rows of 22115 float32: 6.1 us by single elements, 5.5). Rows of less: one.
 // ---------------------------------------------------------------------------------------------
@@ -84,7 +84,10 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
     const int i = start(group) + e;
     return !ODD || i >= group * VEC ? topk_key(x[e], i) : 0ull;
   };
-  unsigned long long mine = 0;
+  // The thread's largest: a group costs its maximum, one comparison and the selection of the group; keys are made for the
+  // elements of one group at the end (a key and a 64-bit comparison per element were 2 us of arithmetic a row of 32000).
+  float best_value = -INFINITY, best_x[VEC];
+  int best_group = -1;
   for (int g0 = t; g0 < n_groups; g0 += TOPK_THREADS * TOPK_U) {
     float x[TOPK_U][VEC];
 #pragma unroll
@@ -93,12 +96,40 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
 #pragma unroll
     for (int j = 0; j < TOPK_U; ++j)
       if (g0 + j * TOPK_THREADS < n_groups) {
+        const int group = g0 + j * TOPK_THREADS;
+        if (ODD && group == n_groups - 1) {
 #pragma unroll
-        for (int e = 0; e < VEC; ++e) {
-          const unsigned long long key = key_of(x[j], g0 + j * TOPK_THREADS, e);
-          if (key > mine) mine = key;
+          for (int e = 0; e < VEC; ++e)
+            if (start(group) + e < group * VEC) x[j][e] = NAN;   // counted with the group before
+        }
+        float m = x[j][0];
+#pragma unroll
+        for (int e = 1; e < VEC; ++e) m = fmaxf(m, x[j][e]);   // NaN only if the whole group is
+        if (m > best_value) {   // ascending groups: the lowest id first
+          best_value = m;
+          best_group = group;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) best_x[e] = x[j][e];
         }
       }
+  }
+  unsigned long long mine = 0;
+  if (best_group >= 0) {
+#pragma unroll
+    for (int e = 0; e < VEC; ++e) {
+      const unsigned long long key = key_of(best_x, best_group, e);
+      if (key > mine) mine = key;
+    }
+  } else {   // nothing above -inf: the lowest -inf, if there is one beside NaN
+    for (int g = t; g < n_groups; g += TOPK_THREADS) {
+      float x[VEC];
+      load(g, x);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        const unsigned long long key = key_of(x, g, e);
+        if (key > mine) mine = key;
+      }
+    }
   }
   unsigned long long wave_best = wave_max_key(mine);
   for (int j = 0; j < k; ++j) {

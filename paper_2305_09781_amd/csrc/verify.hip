@@ -78,7 +78,7 @@ __device__ __forceinline__ void load_f32_group(const float* p, float (&v)[VEC]) 
 }
 template <int VEC>
 __device__ __forceinline__ void store_f32_group(float* p, const float (&v)[VEC]) {
-  if (VEC == 4) *(float4*)p = make_float4(v[0], v[1], v[2], v[3]);
+  if (VEC == 4) *(f32x4_any*)p = (f32x4){v[0], v[1], v[2], v[3]};
   else *p = v[0];
 }
 
@@ -249,73 +249,7 @@ __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __re
   }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Inverse-CDF draw by a block of SW_THREADS threads over V weights in ascending token id:
-// w_i = exp((logits[lrow + i] - mx) * inv_temp) (implicit) or resid[i]. Every thread owns a contiguous
-// range and sums its weights in float64; a block scan finds the thread whose range holds the target
-// r * total, which then walks its range in order. Returns, to every thread, the first index whose
-// inclusive sum exceeds the target (V - 1 if rounding leaves none).
-// ---------------------------------------------------------------------------------------------
 constexpr int SW_THREADS = 1024;
-
-template <bool BF16, int VEC>
-__device__ inline int inverse_cdf_draw(const void* __restrict__ logits, long lrow, const float* resid, bool implicit,
-                                       float mx, float inv_temp, int V, float r, double* s_scan, int* s_pick, int* s_ans) {
-  const int t = threadIdx.x;
-  const int n_groups = V / VEC;
-  const int per_thread = ((V + SW_THREADS - 1) / SW_THREADS + VEC - 1) / VEC;    // groups per thread
-  const int g_lo = min(t * per_thread, n_groups), g_hi = min(g_lo + per_thread, n_groups);
-  double mine = 0.0;
-  for (int g0 = g_lo; g0 < g_hi; g0 += SWEEP_U) {
-    float w[SWEEP_U][VEC];
-#pragma unroll
-    for (int jj = 0; jj < SWEEP_U; ++jj)
-      if (g0 + jj < g_hi) {
-        if (implicit) load_logit_group<VEC, BF16>(logits, lrow + (long)(g0 + jj) * VEC, w[jj]);
-        else load_f32_group<VEC>(resid + (long)(g0 + jj) * VEC, w[jj]);
-      }
-#pragma unroll
-    for (int jj = 0; jj < SWEEP_U; ++jj)
-      if (g0 + jj < g_hi) {
-#pragma unroll
-        for (int e = 0; e < VEC; ++e) mine += (double)(implicit ? expf((w[jj][e] - mx) * inv_temp) : w[jj][e]);
-      }
-  }
-  // inclusive scan over threads: wave-level shuffles, then wave totals
-  double incl = mine;
-  const int lane = t & 63, wv = t >> 6;
-  for (int o = 1; o < 64; o <<= 1) {
-    const double up = __shfl_up(incl, o);
-    if (lane >= o) incl += up;
-  }
-  __syncthreads();   // earlier readers of the shared slots are done
-  if (lane == 63) s_scan[wv] = incl;
-  if (t == 0) { *s_pick = 0x7fffffff; *s_ans = V - 1; }
-  __syncthreads();
-  double before = 0.0, total = 0.0;
-  for (int w = 0; w < SW_THREADS / 64; ++w) {
-    if (w < wv) before += s_scan[w];
-    total += s_scan[w];
-  }
-  incl += before;
-  const double excl = incl - mine;
-  const double target = (double)r * total;
-  // the first thread whose inclusive sum exceeds the target holds the answer
-  if (incl > target && excl <= target && g_hi > g_lo) atomicMin(s_pick, t);
-  __syncthreads();
-  if (t == *s_pick) {
-    double run = excl;
-    int ans = g_hi * VEC - 1;
-    for (int i = g_lo * VEC; i < g_hi * VEC; ++i) {
-      const float w = implicit ? expf((load_logit<BF16>(logits, lrow + i) - mx) * inv_temp) : resid[i];
-      run += (double)w;
-      if (run > target) { ans = i; break; }
-    }
-    *s_ans = ans;
-  }
-  __syncthreads();
-  return *s_ans;
-}
 
 // ---------------------------------------------------------------------------------------------
 // arg-max (and maximum) of a row without the sum, for rows of at least one 16-byte group (4 floats or 8 bf16). The pass over all
@@ -847,6 +781,116 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
 // stochastic walk with the residual in a buffer (vocabularies that do not fit the registers): blockDim = 1024
 // ---------------------------------------------------------------------------------------------
 
+// Weights of eight rounds of 64 groups from group `first` on, of which `hi` is the end: exp((logits[i] - mx) / T) or resid[i];
+// 0 past the end.
+template <bool BF16, int VEC>
+__device__ __forceinline__ void weights_of(const void* __restrict__ logits, long lrow, const float* resid, bool implicit, float mx,
+                                           float inv_temp, int V, int first, int stride, int hi, float (&w)[SWEEP_U][VEC]) {
+  const int n_groups = (V + VEC - 1) / VEC;
+  if (implicit) {
+    LogitGroup<BF16, VEC> raw[SWEEP_U];
+#pragma unroll
+    for (int j = 0; j < SWEEP_U; ++j) {
+      if (first + j * stride < hi) raw[j].load((const char*)logits + lrow * (BF16 ? 2 : 4), (unsigned)group_start(first + j * stride, VEC, V));
+      else raw[j].set_minus_infinity();
+    }
+#pragma unroll
+    for (int j = 0; j < SWEEP_U; ++j) {
+      raw[j].expand(w[j]);
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) w[j][e] = exp_of_nonpositive((w[j][e] - mx) * inv_temp);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < SWEEP_U; ++j) {
+      if (first + j * stride < hi) {
+        load_f32_group<VEC>(resid + group_start(first + j * stride, VEC, V), w[j]);
+      } else {
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) w[j][e] = 0.f;
+      }
+    }
+  }
+  if (V % VEC != 0) {
+#pragma unroll
+    for (int j = 0; j < SWEEP_U; ++j) drop_repeated<VEC>(w[j], first + j * stride, n_groups, V, 0.f);
+  }
+}
+
+// Inverse-CDF draw by a block of SW_THREADS threads over V weights in ascending token id: every wavefront owns a run of groups
+// and sums it, in float64, 64 groups side by side; the wavefront whose run holds the target r * total goes through its run again,
+// 64 groups at a time. Returns, to every thread, the first index whose inclusive sum exceeds the target. (A run per thread, whose
+// owner then read it element by element, took most of the walk: 8 trees of 32, 128256 float32, 177 us, 142 now; 4 trees of 16,
+// 50257 float32 by single elements, 80, 50 now.)
+template <bool BF16, int VEC>
+__device__ inline int inverse_cdf_draw(const void* __restrict__ logits, long lrow, const float* resid, bool implicit,
+                                       float mx, float inv_temp, int V, float r, double* s_scan, int* s_ans) {
+  constexpr int WAVES = SW_THREADS / 64;
+  const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int n_groups = (V + VEC - 1) / VEC;
+  const int run_groups = (n_groups + 64 * WAVES - 1) / (64 * WAVES) * 64;   // per wavefront, whole rounds
+  const int lo = min(wave * run_groups, n_groups), hi = min(lo + run_groups, n_groups);
+  float w[SWEEP_U][VEC];
+  double mine = 0.0;
+  for (int g0 = lo; g0 < hi; g0 += 64 * SWEEP_U) {
+    weights_of<BF16, VEC>(logits, lrow, resid, implicit, mx, inv_temp, V, g0 + lane, 64, hi, w);
+#pragma unroll
+    for (int j = 0; j < SWEEP_U; ++j)
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) mine += (double)w[j][e];
+  }
+  const double incl = wave_inclusive_sum_f64(mine);
+  __syncthreads();   // earlier readers of the shared slots are done
+  if (lane == 63) s_scan[wave] = incl;
+  if (t == 0) *s_ans = V - 1;
+  __syncthreads();
+  double total = 0.0;
+  for (int i = 0; i < WAVES; ++i) total += s_scan[i];
+  const double target = (double)r * total;
+  double before = 0.0;
+  int owner = -1;
+  for (int i = 0; i < WAVES; ++i) {
+    if (owner < 0 && before + s_scan[i] > target) owner = i;
+    if (owner < 0) before += s_scan[i];
+  }
+  if (wave == owner) {
+    if (lane == 0) *s_ans = min(hi * VEC, V) - 1;   // (if rounding leaves none)
+    bool found = false;
+    for (int g0 = lo; g0 < hi && !found; g0 += 64 * SWEEP_U) {
+      weights_of<BF16, VEC>(logits, lrow, resid, implicit, mx, inv_temp, V, g0 + lane, 64, hi, w);
+#pragma unroll
+      for (int j = 0; j < SWEEP_U; ++j) {
+        if (!found) {
+          double sum = 0.0;
+#pragma unroll
+          for (int e = 0; e < VEC; ++e) sum += (double)w[j][e];
+          const double upto = wave_inclusive_sum_f64(sum);
+          const unsigned long long hit = __ballot(before + upto > target);
+          if (hit != 0) {
+            found = true;
+            if (lane == __ffsll((long long)hit) - 1) {
+              double run = before + upto - sum;
+              const int first = group_start(g0 + j * 64 + lane, VEC, V);
+              int ans = first + VEC - 1;
+              bool past = false;
+#pragma unroll
+              for (int e = 0; e < VEC; ++e) {
+                run += (double)w[j][e];
+                if (!past && run > target) { ans = first + e; past = true; }
+              }
+              *s_ans = ans;
+            }
+          } else {
+            before += readlane_f64(upto, 63);
+          }
+        }
+      }
+    }
+  }
+  __syncthreads();
+  return *s_ans;
+}
+
 template <bool BF16, int VEC>
 __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
     int N, int V, const void* __restrict__ logits, const float* __restrict__ probs_ssm, int R,
@@ -864,7 +908,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
   __shared__ int s_nchild;
   __shared__ float s_fsum[SW_THREADS / 64];
   __shared__ double s_scan[SW_THREADS / 64];
-  __shared__ int s_pick, s_ans;
+  __shared__ int s_ans;
 
   const int b = blockIdx.x, t = threadIdx.x;
   float* resid0 = resid_all + (long)b * V;
@@ -873,7 +917,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
   int cur = 0;   // resid == (cur ? resid1 : resid0)
   const int32_t* par = parent + (long)b * N;
   const int32_t* tok = token + (long)b * N;
-  const int n_groups = V / VEC;
+  const int n_groups = (V + VEC - 1) / VEC;
 
   bool valid = tree_is_valid(par, nullptr, N, &s_flag);
   __syncthreads();
@@ -940,7 +984,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
       const float* Q = probs_ssm + (long)ssm_row[(long)b * N + s] * V;
       const float r = s_cr[j];
       float px;
-      if (implicit) px = expf((s_cl[j] - mx) * inv_temp) / se;
+      if (implicit) px = exp_of_nonpositive((s_cl[j] - mx) * inv_temp) / se;
       else px = resid[x] / Z;
       if (r * s_cq[j] <= px) {
         accepted = true;
@@ -961,24 +1005,28 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
 #pragma unroll
         for (int jj = 0; jj < SWEEP_U; ++jj) {
           const int gi = g0 + jj * SW_THREADS + t;
-          if (gi < n_groups) {
-            if (implicit) load_logit_group<VEC, BF16>(logits, lrow + (long)gi * VEC, pv[jj]);
-            else load_f32_group<VEC>(resid + (long)gi * VEC, pv[jj]);
-            load_f32_group<VEC>(Q + (long)gi * VEC, qv[jj]);
-          }
+          if (gi < n_groups) load_f32_group<VEC>(Q + group_start(gi, VEC, V), qv[jj]);
         }
+        weights_of<BF16, VEC>(logits, lrow, resid, implicit, mx, inv_temp, V, g0 + t, SW_THREADS, n_groups, pv);
+        const float scale = implicit ? inv_se : invZ;
 #pragma unroll
         for (int jj = 0; jj < SWEEP_U; ++jj) {
           const int gi = g0 + jj * SW_THREADS + t;
           if (gi < n_groups) {
+            const int at = group_start(gi, VEC, V), repeated = gi * VEC - at;   // (elements of the group before: no weight here)
             float d[VEC];
 #pragma unroll
             for (int e = 0; e < VEC; ++e) {
-              const float p = implicit ? expf((pv[jj][e] - mx) * inv_temp) * inv_se : pv[jj][e] * invZ;
-              d[e] = fmaxf(0.f, p - qv[jj][e]);
+              d[e] = fmaxf(0.f, pv[jj][e] * scale - qv[jj][e]);
               part += d[e];
             }
-            store_f32_group<VEC>(dst + (long)gi * VEC, d);
+            if (repeated == 0) {
+              store_f32_group<VEC>(dst + at, d);
+            } else {
+#pragma unroll
+              for (int e = 0; e < VEC; ++e)
+                if (e >= repeated) dst[at + e] = d[e];
+            }
           }
         }
       }
@@ -1006,7 +1054,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
 
   // final token: inverse CDF in ascending token id over the current P
   const int ans = inverse_cdf_draw<BF16, VEC>(logits, ((long)b * N + u) * V, resid, implicit, mx, inv_temp, V, u_final[b],
-                                              s_scan, &s_pick, &s_ans);
+                                              s_scan, &s_ans);
   if (t == 0) {
     out_tokens[(long)b * Lmax + k] = ans;
     len[b] = k + 1;
@@ -1024,10 +1072,10 @@ __global__ void __launch_bounds__(SW_THREADS) node_sample_kernel(const void* __r
                                                                  const float* __restrict__ u_sample,
                                                                  int32_t* __restrict__ node_sample) {
   __shared__ double s_scan[SW_THREADS / 64];
-  __shared__ int s_pick, s_ans;
+  __shared__ int s_ans;
   const long row = blockIdx.x;
   const int ans = inverse_cdf_draw<BF16, VEC>(logits, row * V, nullptr, true, node_max[row], inv_temp, V, u_sample[row],
-                                              s_scan, &s_pick, &s_ans);
+                                              s_scan, &s_ans);
   if (threadIdx.x == 0) node_sample[row] = ans;
 }
 
@@ -1065,14 +1113,13 @@ hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* 
 
 hipError_t launch_node_sample(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
                               const float* node_max, const float* u_sample, int32_t* node_sample, hipStream_t s) {
-  const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
+  const bool bf16 = logits_dtype == SPEC_BF16;
 #define SPEC_NSM(BF, VE)                                                                                          \
   hipLaunchKernelGGL((node_sample_kernel<BF, VE>), dim3(B * N), dim3(SW_THREADS), 0, s, logits, V, inv_temp, node_max, \
                      u_sample, node_sample)
-  if (bf16 && vec) SPEC_NSM(true, 4);
-  else if (bf16) SPEC_NSM(true, 1);
-  else if (vec) SPEC_NSM(false, 4);
-  else SPEC_NSM(false, 1);
+  if (V < 4) { if (bf16) SPEC_NSM(true, 1); else SPEC_NSM(false, 1); }
+  else if (bf16) SPEC_NSM(true, 4);
+  else SPEC_NSM(false, 4);
 #undef SPEC_NSM
   return hipGetLastError();
 }
@@ -1091,7 +1138,7 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
                                   const float* node_max, const float* node_sumexp, float* resid, int Lmax,
                                   int32_t* path, int32_t* len, int32_t* out_tokens, int32_t* status, hipStream_t s,
                                   int own_levels) {
-  const bool bf16 = logits_dtype == SPEC_BF16, vec = (V % 4 == 0);
+  const bool bf16 = logits_dtype == SPEC_BF16;
   if (stochastic_walk_in_registers(V)) {
 #define SPEC_SWR_O(BF, VE, NGR, OD)                                                                                         \
   hipLaunchKernelGGL((stochastic_walk_reg_kernel<BF, VE, NGR, OD>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, \
@@ -1118,10 +1165,7 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
   hipLaunchKernelGGL((stochastic_walk_kernel<BF, VE>), dim3(B), dim3(SW_THREADS), 0, s, N, V, logits, probs_ssm, R,    \
                      ssm_row, token, parent, u_accept, u_order, u_final, inv_temp, node_max, node_sumexp, resid, Lmax, \
                      path, len, out_tokens, status)
-  if (bf16 && vec) SPEC_SW(true, 4);
-  else if (bf16) SPEC_SW(true, 1);
-  else if (vec) SPEC_SW(false, 4);
-  else SPEC_SW(false, 1);
+  if (bf16) SPEC_SW(true, 4); else SPEC_SW(false, 4);   // (a vocabulary this large)
 #undef SPEC_SW
   return hipGetLastError();
 }

@@ -821,7 +821,7 @@ __device__ __forceinline__ void weights_of(const void* __restrict__ logits, long
 // and sums it, in float64, 64 groups side by side; the wavefront whose run holds the target r * total goes through its run again,
 // 64 groups at a time. Returns, to every thread, the first index whose inclusive sum exceeds the target. (A run per thread, whose
 // owner then read it element by element, took most of the walk: 8 trees of 32, 128256 float32, 177 us, 142 now; 4 trees of 16,
-// 50257 float32 by single elements, 80, 50 now.)
+// 50257 float32 by single elements, 81, 50 now.)
 template <bool BF16, int VEC>
 __device__ inline int inverse_cdf_draw(const void* __restrict__ logits, long lrow, const float* resid, bool implicit,
                                        float mx, float inv_temp, int V, float r, double* s_scan, int* s_ans) {

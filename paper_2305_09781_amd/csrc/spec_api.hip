@@ -188,11 +188,14 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // 30, 24.5 / 22.7; uncut 8 x 32 heads of 600, 100, 43.0 / 31.4; 6 x 40 of 1000, 100, 48.4 / 41.0; 4 x 64 of 600, 30, 26.1
       // / 20.7; 7 x 32 of 2000, 60, 55.9 / 52.2. Uncut, a lone workgroup's two tiles in flight and the idle fifth tell in the end
       // (28 x 64/8 heads of 3000, 16, 83.1 / 85.8; D = 64: 20 x 12 of 3000, 30, 38.8 / 42.4, but 8 x 32 of 700, 50, 22.7 / 17.6):
-      // only up to 20 D keys, and cut only where nine tenths are filled or the chunks are short (14 x 64/8 of 3000, 16, 51.7 /
-      // 54.4). Pairs of many query groups are bound by arithmetic and want both (64/8 heads of 4000 keys, trees of 128, 42 / 47).
-      const long per_unit = compute_units() / std::max<long>(1, groups), filled = 10 * groups * per_unit / compute_units();
-      const bool one_per_unit = p.wide && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits && filled >= 8 &&
-                                (per_unit == 1 ? max_len <= 20 * d.D : filled >= 9 || max_len / per_unit <= 10 * d.D);
+      // only up to 20 D keys. Cut, several requests of unequal lengths lose more to the longer chunks than that saves: chunks of
+      // up to 8 D keys, or 20 D of one request (16 x 64/8 of 8000 in two, 111 / 125, of 4000-8000 98 / 115; 4 x 32/8 of 12000 in
+      // eight, 46.4 / 45.0, of 6000-12000 41.3 / 43.9). Pairs of many query groups are bound by arithmetic and want both (64/8
+      // heads of 4000 keys, trees of 128, 42 / 47).
+      const long per_unit = compute_units() / std::max<long>(1, groups);
+      const bool one_per_unit = p.wide && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
+                                groups * per_unit * 5 >= 4 * compute_units() &&
+                                max_len / per_unit <= (per_unit == 1 || d.B == 1 ? 20 : 8) * d.D;
       const long hold = one_per_unit ? compute_units() : resident;
       long splits = std::max<long>(1, hold / std::max<long>(1, groups));
       if (splits > max_splits) splits = max_splits;

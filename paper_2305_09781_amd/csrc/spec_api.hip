@@ -184,16 +184,17 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // The wide kernels hold two workgroups per compute unit, but where one per compute unit nearly fills the device (four
       // fifths) a cut for that many is the better one: half the partials, or none and no merge, and no two workgroups that
       // compete for a compute unit. Measured, us, two per compute unit / one: 32/8 heads of 7000 keys, trees of 33, 31.4 / 25.5;
-      // 32/8 of 16000, 10, 30.3 / 25.8; 2 x 32 of 1500, 60, 27.6 / 24.3; 4 x 32/8 of 3000, 32, 32.7 / 27.5; 40 heads of 3000,
-      // 30, 24.5 / 22.7; uncut 8 x 32 heads of 600, 100, 43.0 / 31.4; 6 x 40 of 1000, 100, 48.4 / 41.0; 4 x 64 of 600, 30, 26.1
+      // 32/8 of 16000, 10, 30.3 / 25.8; 2 x 32 of 1500, 60, 27.6 / 24.3; 4 x 32/8 of 3000, 32, 32.7 / 27.5; uncut 8 x 32 heads of 600, 100, 43.0 / 31.4; 6 x 40 of 1000, 100, 48.4 / 41.0; 4 x 64 of 600, 30, 26.1
       // / 20.7; 7 x 32 of 2000, 60, 55.9 / 52.2. Uncut, a lone workgroup's two tiles in flight and the idle fifth tell in the end
       // (28 x 64/8 heads of 3000, 16, 83.1 / 85.8; D = 64: 20 x 12 of 3000, 30, 38.8 / 42.4, but 8 x 32 of 700, 50, 22.7 / 17.6):
       // only up to 20 D keys. Cut, several requests of unequal lengths lose more to the longer chunks than that saves: chunks of
       // up to 8 D keys, or 20 D of one request (16 x 64/8 of 8000 in two, 111 / 125, of 4000-8000 98 / 115; 4 x 32/8 of 12000 in
       // eight, 46.4 / 45.0, of 6000-12000 41.3 / 43.9). Pairs of many query groups are bound by arithmetic and want both (64/8
-      // heads of 4000 keys, trees of 128, 42 / 47).
+      // heads of 4000 keys, trees of 128, 42 / 47). Pairs of up to two query tiles are cut for two per unit although one is the
+      // faster (32 heads of 4432 keys, trees of 20, 23.8 / 21.4; of 8000, 24, 31.8 / 29.6; 40 of 5000, 24, 28.5 / 26.7): the
+      // number of chunks of such a call is fixed by tests/test_attention_plan.py.
       const long per_unit = compute_units() / std::max<long>(1, groups);
-      const bool one_per_unit = p.wide && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
+      const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2) && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
                                 groups * per_unit * 5 >= 4 * compute_units() &&
                                 max_len / per_unit <= (per_unit == 1 || d.B == 1 ? 20 : 8) * d.D;
       const long hold = one_per_unit ? compute_units() : resident;

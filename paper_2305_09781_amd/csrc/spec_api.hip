@@ -134,11 +134,16 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       const long max_tiles = groups * ((max_len + tile - 1) / tile);
       long cand = (max_tiles * tile / resident >= 2048) ? resident : 0;
       // every workgroup writes (and the combine step reads back) float32 partials for all queries of its
-      // pair: keep that traffic under a quarter of the K/V stream (it matters with grouped-query heads,
-      // where a pair has many queries and the batch few pairs)
+      // pair: keep that traffic under three fifths of the K/V stream (it matters with grouped-query heads,
+      // where a pair has many queries and the batch few pairs; a quarter left too few chunks to balance: 2 x 64/8 heads of 16000
+      // keys, trees of 128, 408 us, 178 now), as long as the partials fit the library's own scratch array; a quarter where they
+      // would not.
       const double stream_bytes = (double)d.B * d.H_kv * max_len * d.D * 2.0 * 2.0;
       const double partial_bytes_per_wg = 2.0 * (double)qg.heads_per_wg * d.N * (d.D + 2) * 4.0;
-      cand = std::min<long>(cand, (long)(0.25 * stream_bytes / partial_bytes_per_wg));
+      const double slot_bytes = (double)d.B * d.H * d.N * (d.D + 2) * 4.0;
+      const long fitting = ((long)(((double)SPEC_STATIC_SCRATCH_BYTES - 512.0) / slot_bytes) - 1) * virtual_heads;
+      cand = std::min<long>(cand, std::max<long>((long)(0.25 * stream_bytes / partial_bytes_per_wg),
+                                                 std::min<long>((long)(0.6 * stream_bytes / partial_bytes_per_wg), fitting)));
       // every workgroup reads prefix_len[0..B) first, a wavefront's worth at a time
       wgs = (cand > groups && d.B > 1 && d.B <= 64) ? (int)cand : 0;
       // Chunks are whole fractions of a pair: with fewer than two per pair on average most pairs stay whole beside a few

@@ -421,13 +421,16 @@ __global__ void __launch_bounds__(64) greedy_walk_kernel(int N, const int32_t* _
 // 25.2 / 22.7.
 // ---------------------------------------------------------------------------------------------
 
-// exp(x) for x <= 0: one v_exp_f32 with the rounding of x * log2(e) put back (relative error as expf's, results below
-// 2^-126 become 0).
+// exp(x) for x <= 0, subnormal results included (a draw at 0 takes the first token that has any weight): 2^n 2^f with n the integer
+// nearest x log2(e), whose rest f is taken before anything is rounded away. n comes out of a sum with 1.5 * 2^23, as a float and
+// in that sum's last bits (an integer conversion is as slow as v_exp_f32); below 2^-200 it stops, so that -inf has a rest.
+// Largest relative error over [-87, 0] 8.5e-8, of subnormals one step. The walk of 16 trees of 128, 32000 float32, three drafts
+// takes 42.7 us; with expf, whose own error is 2.7e-6 when it is compiled with contraction, 45.8; with one v_exp_f32 of the whole
+// exponent and its rounding put back afterwards (1.4e-7, and 0 below 2^-126), 41.7.
 __device__ __forceinline__ float exp_of_nonpositive(float x) {
-  const float t = x * 1.4426950408889634f;
-  const float lost = fmaf(x, 1.4426950408889634f, -t) + x * 1.925963033500e-08f;   // log2(e) = 1.44269502162933 + 1.926e-8
-  const float e = __builtin_amdgcn_exp2f(t);
-  return t < -126.f ? e : fmaf(e, lost * 0.69314718f, e);   // (t = -inf: lost is NaN, e is 0)
+  const float shifted = fmaxf(fmaf(x, 1.44269502f, 12582912.f), 12582912.f - 200.f), n = shifted - 12582912.f;
+  const float f = fmaf(x, 1.925963033500e-08f, fmaf(x, 1.44269502f, -n));   // log2(e) = 1.44269502162933 + 1.926e-8
+  return ldexpf(__builtin_amdgcn_exp2f(f), (int)(__float_as_uint(shifted) - 0x4b400000u));
 }
 // Sums and maxima over a wavefront in register moves (row shifts, then the last lane of a row into the rows after it).
 template <int CTRL, int ROW_MASK>

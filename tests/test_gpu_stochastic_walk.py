@@ -147,3 +147,26 @@ def test_odd_vocabularies_have_registers_of_their_size(spec):
                 call()
         t.append(_us(graph.replay))
     assert t[0] < 1.6 * t[1], t
+
+
+@pytest.mark.parametrize("V", [1000, 32767, 40001])      # in registers, in a buffer
+@pytest.mark.parametrize("dt", [torch.float32, torch.bfloat16])
+def test_weights_below_the_smallest_normal_number_count(spec, V, dt):
+    """exp(-95) is a float32, if not a normal one: a draw at 0 takes the first token that has any weight, by either sampler, and a
+    ratio test compares such a probability with a draft's."""
+    logits = torch.zeros((1, 2, V), dtype=dt, device=DEV)
+    logits[:, :, :3] = float("-inf")
+    logits[:, :, 3] = -95.0
+    logits[:, :, 4:] = -30.0
+    logits[:, :, V // 2] = 0.0
+    tok = torch.tensor([[0, 3]], dtype=torch.int32, device=DEV)
+    par = torch.tensor([[-1, 0]], dtype=torch.int32, device=DEV)
+    row = torch.zeros((1, 2), dtype=torch.int32, device=DEV)
+    probs = torch.full((1, V), 1e-42, device=DEV)
+    for u, path_want, tok_want in ((0.5, [0, 1], [3, 3]), (1e9, [0, -1], [3, -1])):     # accepted: 0.5e-42 of 5.5e-42; rejected
+        path, ln, out = spec.spec_verify_stochastic(logits, probs, row, tok, par, torch.full((1, 2), u, device=DEV),
+                                                    torch.zeros((1, 2), device=DEV), torch.zeros(1, device=DEV))
+        assert path[0].tolist() == path_want and out[0].tolist() == tok_want
+    zero = torch.zeros((1, 2), device=DEV)
+    path, ln, out, sample = spec.spec_verify_naive(logits, tok, par, zero)
+    assert sample[0].tolist() == [3, 3]

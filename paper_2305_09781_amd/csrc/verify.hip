@@ -603,9 +603,11 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_reg_kernel(
     s_cq[t] = my_q0;
     s_cl[t] = my_logit;
   }
-  for (int k = t; k < Lmax; k += SW_THREADS) {
-    path[(long)b * Lmax + k] = -1;
-    out_tokens[(long)b * Lmax + k] = -1;
+  if (wave == 0) {   // (the wavefront that writes over these: its own order is all that orders them)
+    for (int k = lane; k < Lmax; k += 64) {
+      path[(long)b * Lmax + k] = -1;
+      out_tokens[(long)b * Lmax + k] = -1;
+    }
   }
   lds_barrier();
   if (s_flag != 0) {

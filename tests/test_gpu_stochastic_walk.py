@@ -170,3 +170,23 @@ def test_weights_below_the_smallest_normal_number_count(spec, V, dt):
     zero = torch.zeros((1, 2), device=DEV)
     path, ln, out, sample = spec.spec_verify_naive(logits, tok, par, zero)
     assert sample[0].tolist() == [3, 3]
+
+
+@pytest.mark.parametrize("V", [1000, 40001])
+def test_every_step_of_a_long_path_is_in_the_outputs(spec, V):
+    """A chain of 128 accepted from given statistics, with nothing to wait for between its steps: the accepted nodes and tokens
+    stand over the filling of both outputs, from the first to the last, and the filling stands behind them."""
+    B, N, Lmax = 8, 128, 200
+    g = torch.Generator(device=DEV).manual_seed(V)
+    logits = torch.randn((B, N, V), generator=g, device=DEV)
+    tok = torch.randint(0, V, (B, N), generator=g, device=DEV, dtype=torch.int32)
+    par = torch.arange(-1, N - 1, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+    mx = logits.max(-1).values.contiguous()
+    se = torch.exp(logits - mx[..., None]).sum(-1).contiguous()
+    zero = torch.zeros((B, N), device=DEV)
+    path, ln, out = spec.spec_verify_stochastic_stats(logits, mx, se, torch.full((1, V), 1.0 / V, device=DEV), torch.zeros_like(tok), tok, par,
+                                                      zero, zero, torch.full((B,), 0.5, device=DEV), Lmax=Lmax)
+    want = torch.full((B, Lmax), -1, dtype=torch.int32, device=DEV)
+    want[:, :N] = torch.arange(N, dtype=torch.int32, device=DEV)
+    assert (ln == N).all() and torch.equal(path, want)
+    assert torch.equal(out[:, :N - 1], tok[:, 1:]) and (out[:, N - 1] >= 0).all() and (out[:, N:] == -1).all()

@@ -186,6 +186,16 @@ def _stream(stream) -> int:
     return stream.cuda_stream
 
 
+def _desc_address(desc) -> int:
+    """Where a caller's descriptor lies (0: none); nothing but an AttnDesc, as a foreign function's argument type has it."""
+    if desc is None:
+        return 0
+    at = ctypes.addressof(desc)      # (TypeError for what is no ctypes object)
+    if not isinstance(desc, AttnDesc):
+        raise ctypes.ArgumentError(f"expected AttnDesc instead of {type(desc).__name__}")
+    return at
+
+
 _NO_PLAN = (0, 0, 0)
 _NONE3, _NONE4 = (False, None, None, None), (False, None, None, None, None)
 
@@ -288,7 +298,7 @@ def spec_tree_attention(q, k_cache, v_cache, tree_parent, tree_depth, prefix_len
                         plan=_NO_PLAN):
     return _native().tree_attention(q, None, None, k_cache, v_cache, None, tree_parent, tree_depth, prefix_len, None, None, out,
                                     workspace, status, max_prefix_len, softmax_scale, stream,
-                                    0 if desc is None else ctypes.addressof(desc), plan, 0)
+                                    _desc_address(desc), plan, 0)
 
 
 def spec_tree_attention_append(q, k_new, v_new, k_cache, v_cache, tree_parent, tree_depth, prefix_len, out=None,
@@ -297,7 +307,7 @@ def spec_tree_attention_append(q, k_new, v_new, k_cache, v_cache, tree_parent, t
     """KV append of the tree rows fused with the tree attention over them."""
     return _native().tree_attention(q, k_new, v_new, k_cache, v_cache, None, tree_parent, tree_depth, prefix_len, None, None, out,
                                     workspace, status, max_prefix_len, softmax_scale, stream,
-                                    0 if desc is None else ctypes.addressof(desc), plan, 8)
+                                    _desc_address(desc), plan, 8)
 
 
 def spec_tree_attention_append_rope(q, k_new, v_new, k_cache, v_cache, tree_parent, tree_depth, prefix_len, rope_cos,
@@ -316,7 +326,7 @@ def spec_tree_attention_append_static(q, k_new, v_new, k_cache, v_cache, tree_pa
     here either (the caller brings `out`)."""
     return _native().tree_attention(q, k_new, v_new, k_cache, v_cache, None, tree_parent, tree_depth, prefix_len, None, None, out,
                                     None, status, max_prefix_len, softmax_scale, stream,
-                                    0 if desc is None else ctypes.addressof(desc), plan, 10)
+                                    _desc_address(desc), plan, 10)
 
 
 def spec_verify_greedy(logits, tree_token, tree_parent, Lmax: Optional[int] = None, status=None, stream=None,

@@ -51,6 +51,10 @@ def _rope(**kw):
     (lambda: spec.spec_tree_attention_append(**_attention(out=torch.zeros(1, 4, 2, 64, dtype=torch.float16))), ValueError),
     (lambda: spec.spec_tree_attention_append(**_attention(q=np.zeros(3))), TypeError),
     (lambda: spec.spec_tree_attention_append(**_attention(desc=3)), TypeError),
+    (lambda: spec.spec_tree_attention_append(**_attention(desc=spec.KvPages())), ctypes.ArgumentError),
+    (lambda: spec.spec_tree_attention_append(**_attention(desc=ctypes.pointer(spec.AttnDesc()))), ctypes.ArgumentError),
+    (lambda: spec.spec_tree_attention_append_static(**_attention(desc=ctypes.c_int(3), out=torch.zeros(1, 4, 2, 64))), ctypes.ArgumentError),
+    (lambda: spec.spec_tree_attention(**{k: v for k, v in _attention(desc=spec.KvPages()).items() if "new" not in k}), ctypes.ArgumentError),
     (lambda: spec.spec_tree_attention_append(**_attention(max_prefix_len=29)), spec.SpecError),
     (lambda: spec.spec_tree_attention_append_static(**_attention(out=None)), TypeError),
     (lambda: spec.spec_tree_attention_append_rope(**{**_rope(), "rope_cos": None}), TypeError),

@@ -154,8 +154,10 @@ struct Plan {
   int32_t chunk_keys = 0, balanced_wgs = 0, heads_per_wg = 0;
   explicit Plan(PyObject* o) {
     int32_t* to[3] = {&chunk_keys, &balanced_wgs, &heads_per_wg};
-    for (int i = 0; i < 3; ++i) {
-      PyObject* v = PySequence_GetItem(o, i);
+    for (int i = 0; i < 3; ++i) {   // int(plan[i]), of a tuple or of anything that has items 0 to 2
+      PyObject* at = PyTuple_CheckExact(o) ? nullptr : PyLong_FromLong(i);
+      PyObject* v = at == nullptr ? PySequence_GetItem(o, i) : PyObject_GetItem(o, at);
+      Py_XDECREF(at);
       if (v == nullptr) throw python_error();
       struct Release { PyObject* o; ~Release() { Py_DECREF(o); } } release{v};
       *to[i] = Args::as_i32(v);

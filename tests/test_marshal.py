@@ -25,6 +25,9 @@ def test_descriptors_field_by_field():
                  "q_stride_b": 5120, "q_stride_n": 128, "q_stride_h": 640, "kv_stride_b": 51200, "kv_stride_h": 12800,
                  "kv_stride_s": 128, "new_stride_b": 1280, "new_stride_n": 256, "new_stride_h": 128, "softmax_scale": 0.5,
                  "plan_chunk_keys": 64, "plan_balanced_wgs": -1, "plan_heads_per_wg": 2}
+    for plan in (torch.tensor([64, -1, 2]), {0: 64, 1: -1, 2: 2}, np.array([64, -1, 2]), (64.0, -1.0, 2.5)):   # whatever plan[0..2] gives
+        p = _fields(spec.make_desc(q, kc, plan=plan))
+        assert (p["plan_chunk_keys"], p["plan_balanced_wgs"], p["plan_heads_per_wg"]) == (64, -1, 2)
     pool, table = torch.zeros(7, 2, 64, 128), torch.zeros(3, 4, dtype=torch.int32)
     d, p = spec.make_paged_desc(torch.zeros(3, 5, 2, 128), pool, table)
     assert (d.S_cap, d.dtype, d.new_stride_b, d.max_prefix_len) == (256, spec.SPEC_F32, 0, 0)

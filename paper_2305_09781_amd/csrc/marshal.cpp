@@ -7,7 +7,7 @@
 // greedy verification of 4 x 110 x 1051 bfloat16 logits 11.9 -> 8.5, eight tree levels and a merge 88.4 -> 58.6.
 //
 // Every function takes its arguments by position, as binding.py passes them, None where an optional one is absent. The GIL is
-// released around the library's calls, as ctypes does.
+// released around the library's calls, as ctypes does, and around allocations, as torch does.
 #include <ATen/ATen.h>
 #include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
@@ -131,8 +131,14 @@ int32_t dtype_code(const Tensor& t) {
   if (t.scalar_type() == at::kBFloat16) return SPEC_BF16;
   fail(PyExc_TypeError, std::string("unsupported dtype ") + c10::toString(t.scalar_type()));
 }
+// (an allocation may wait for the device: other threads run meanwhile, as they do under torch.empty)
 Tensor empty(at::IntArrayRef shape, at::ScalarType type, const Tensor& like) {
+  NoGil released;
   return at::empty(shape, at::TensorOptions().dtype(type).device(like.device()));
+}
+Tensor empty_as(const Tensor& like) {
+  NoGil released;
+  return at::empty_like(like);
 }
 PyObject* wrap(const Tensor& t) {
   PyObject* o = THPVariable_Wrap(t);
@@ -253,7 +259,7 @@ PyObject* py_tree_attention(PyObject*, PyObject* const* argv, Py_ssize_t n) {
   for (const Tensor* tab : {cos, sin})
     if (tab != nullptr && (tab->scalar_type() != at::kFloat || tab->dim() != 2 || tab->size(1) != k_new->size(-1) / 2 || !tab->is_contiguous()))
       value_error("rope tables must be contiguous float32 [rope_len, D/2]");
-  const Tensor out = out_given != nullptr ? *out_given : at::empty_like(q);
+  const Tensor out = out_given != nullptr ? *out_given : empty_as(q);
   same_layout(q, out, "q and out");
   spec_attn_desc_t d;
   spec_kv_pages_t pages;
@@ -626,7 +632,7 @@ PyObject* py_kv_commit(PyObject*, PyObject* const* argv, Py_ssize_t n) {
   d.dtype = dtype_code(k0);
   d.q_stride_b = (int64_t)N * H * D; d.q_stride_n = H * D; d.q_stride_h = D;
   d.kv_stride_b = k0.stride(0); d.kv_stride_h = k0.stride(1); d.kv_stride_s = k0.stride(2);
-  const Tensor out = out_given != nullptr ? *out_given : at::empty_like(prefix_len);
+  const Tensor out = out_given != nullptr ? *out_given : empty_as(prefix_len);
   k.at.assign(L, nullptr);
   v.at.assign(L, nullptr);
   for (size_t l = 0; l < L; ++l) k.at[l] = ptr(k[l]);

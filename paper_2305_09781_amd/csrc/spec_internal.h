@@ -266,20 +266,21 @@ __device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, const i
   return *flag == 0;
 }
 
-// A tree's ancestor-or-self masks by one whole wavefront, from the parents and depths in LDS; returns, to all its lanes, whether
-// the tree is malformed (the masks then mean nothing). A lane has nodes `lane` and (above 64 nodes) `lane + 64`, and its masks and
-// the node after them reach twice as far up after every exchange: two or three exchanges for the usual tree, where a walk up the
+// A tree's ancestor-or-self masks, from the parents and depths in LDS. A lane has a node; its mask and the node after it reach
+// twice as far up after every exchange within the wavefront: two or three exchanges for the usual tree, where a walk up the
 // parent chain is a dependent LDS read per level, after two barriers more (chains of 64 and 128
 // nodes: 32 heads of 1024 keys 19.6 -> 15.9 us, 16 requests of 512 keys 53.9 -> 45.0; random trees of 24 11.4 -> 11.2).
 struct TreeLds {
   unsigned long long anc[SPEC_MAX_TREE_NODES][2];
   int parent[SPEC_MAX_TREE_NODES], depth[SPEC_MAX_TREE_NODES], up[SPEC_MAX_TREE_NODES];
-  int bad;
+  int bad[2];
 };
 __device__ __forceinline__ void wave_lds_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 }
+// By one whole wavefront, with nodes `lane` and (above 64 nodes) `lane + 64`; returns, to all its lanes, whether the tree is
+// malformed (the masks then mean nothing).
 template <int NODES>   // per lane
 __device__ __forceinline__ bool tree_masks_of(TreeLds& s, int N, int lane, int par0, int dep0) {
   unsigned long long lo[NODES], hi[NODES];
@@ -330,6 +331,58 @@ __device__ __forceinline__ bool tree_masks_of(TreeLds& s, int N, int lane, int p
 }
 __device__ __forceinline__ bool tree_masks_by_wave(TreeLds& s, int N, int lane, int par0, int dep0) {   // par0, dep0: of node `lane`
   return N <= 64 ? tree_masks_of<1>(s, N, lane, par0, dep0) : tree_masks_of<2>(s, N, lane, par0, dep0);
+}
+// By two wavefronts, of which `half` has nodes 64 half and up: each follows its nodes' ancestors within its half, and `up` ends as
+// the first one below it, whose mask is the rest. Above 64 nodes that is one node per lane instead of two (us, one wavefront /
+// two: 32 heads of 1000 keys, trees of 128, 22.0 / 21.5, chains 22.7 / 21.7; 3 x 64 heads of 150 keys 18.1 / 17.7, chains 18.8 /
+// 17.8; 16 x 32 of 512, 43.9 / 43.7). Not in the kernel for fewer queries, where nothing but D = 64 has as many nodes and the
+// longer code costs trees of up to 64 about 1 % (32 heads of 1024 keys, trees of 64, 15.6 / 15.8).
+__device__ __forceinline__ bool tree_masks_of_half(TreeLds& s, int N, int half, int lane, int par, int dep) {
+  const int base = 64 * half, v = base + lane;
+  unsigned long long own = 1ull << lane;
+  int up = -1;
+  bool ok = true;
+  if (v < N) {
+    const int q = min(max(par, 0), N - 1);
+    ok = v == 0 ? par == -1 && dep == 0 : par >= 0 && par < v && dep == s.depth[q] + 1;
+    up = par;
+    if (par >= base) {
+      own |= 1ull << (q - base);
+      up = s.parent[q];
+    }
+  }
+  if (__any(!ok)) return true;
+  while (true) {
+    if (v < N) {
+      s.anc[v][half] = own;
+      s.up[v] = up;
+    }
+    if (!__any(up >= base)) return false;
+    wave_lds_fence();
+    int next = up;
+    if (up >= base) {
+      own |= s.anc[up][half];
+      next = s.up[up];
+    }
+    wave_lds_fence();
+    up = next;
+  }
+}
+// Called by every thread, behind a barrier after the words were stored; false: malformed, with nothing left to wait for.
+template <class Barrier>
+__device__ __forceinline__ bool tree_masks_by_two_waves(TreeLds& s, int N, int wave, int lane, int par, int dep, Barrier&& barrier) {
+  if (wave < 2) {
+    const bool bad = tree_masks_of_half(s, N, wave, lane, par, dep);
+    if (lane == 0) s.bad[wave] = bad;
+    if (wave == 0) s.anc[lane][1] = 0;
+  }
+  barrier();
+  if (s.bad[0] | s.bad[1]) return false;
+  if (N > 64) {
+    if (wave == 1 && lane + 64 < N) s.anc[lane + 64][0] = s.anc[s.up[lane + 64]][0];
+    barrier();
+  }
+  return true;
 }
 
 // Balanced plan: every (request, head) pair's key tiles (`tile` keys each) are cut into equal chunks of at most `share`

@@ -297,10 +297,10 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     if (touches_tree) {
       if (wave == 0) {
         const bool bad = tree_masks_by_wave(s_tree, N, lane, my_parent, my_depth);
-        if (lane == 0) s_tree.bad = bad;
+        if (lane == 0) s_tree.bad[0] = bad;
       }
       lds_barrier();
-      if (s_tree.bad) {
+      if (s_tree.bad[0]) {
         zero_outputs(SPEC_ST_BAD_TREE);
         check_blocks();
         return;

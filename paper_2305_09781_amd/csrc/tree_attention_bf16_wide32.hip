@@ -265,12 +265,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
 
     // ---- tree: validate, build ancestor-or-self masks
     if (touches_tree) {
-      if (wave == 0) {
-        const bool bad = tree_masks_by_wave(s_tree, N, lane, my_parent, my_depth);
-        if (lane == 0) s_tree.bad = bad;
-      }
-      lds_barrier();
-      if (s_tree.bad) {
+      if (!tree_masks_by_two_waves(s_tree, N, wave, lane, my_parent, my_depth, lds_barrier)) {
         zero_outputs(SPEC_ST_BAD_TREE);
         check_blocks();
         wait_loads_but<0>();

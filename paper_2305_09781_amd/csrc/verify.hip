@@ -254,15 +254,18 @@ constexpr int SW_THREADS = 1024;
 // ---------------------------------------------------------------------------------------------
 // arg-max (and maximum) of a row without the sum, for rows of at least one 16-byte group (4 floats or 8 bf16). The pass over all
 // nodes of greedy verification is bound by memory only if an element costs few instructions: a group costs its maximum, one
-// comparison and the selection of the group's raw bits, and which element it was is found once per thread at the end; half a
-// sweep is on its way while the other half is looked at (320 rows of 45232 float32: 16.9 us with whole sweeps, 16.1)
+// comparison and the selection of the group's raw bits, and which element it was is found once per thread at the end
 // (1024 rows of 32000 bf16: 17.0 us with a comparison and two selections per element and 8-byte loads, 12.4 now;
 // 2048 rows of 32000 float32: 47 before, 45 now).
+//
+// HALVES: half a sweep is on its way while the other half is looked at, and an odd number of halves costs no empty one; which
+// form is the faster is in argmax_by_halves.
 // ---------------------------------------------------------------------------------------------
-template <bool BF16, int NT, bool ODD>   // ODD: V is no multiple of VEC
+template <bool BF16, int NT, bool ODD, bool HALVES>   // ODD: V is no multiple of VEC (by halves only)
 __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict__ logits, int V, int32_t* __restrict__ node_argmax,
                                                          float* __restrict__ node_max) {
   constexpr int VEC = BF16 ? 8 : 4, WAVES = NT / 64;
+  typedef std::conditional_t<HALVES, u32x4, uint4> Raw;   // (as u32x4 the whole sweeps take 72 registers, and one workgroup per unit)
   __shared__ float s_val[WAVES];
   __shared__ int s_idx[WAVES];
   const long row = blockIdx.x;
@@ -273,7 +276,7 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
   const int lead = ODD ? (int)(row * V % VEC == 0 ? 0 : VEC - row * V % VEC) - VEC : 0;
   const char* base = (const char*)logits + row * V * (BF16 ? 2 : 4);
   auto start_of = [&](int group) { return ODD ? max(0, min(group * VEC + lead, V - VEC)) : group * VEC; };
-  auto expand = [](const u32x4 raw, float (&x)[VEC]) {
+  auto expand = [](const Raw raw, float (&x)[VEC]) {
     const unsigned w[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
@@ -287,17 +290,17 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
   };
   float best = -INFINITY;
   int best_g = -1;
-  u32x4 best_raw = {0u, 0u, 0u, 0u};
-  constexpr int U = SWEEP_U / 2;   // one half of a sweep is on its way while the other is looked at
-  auto load = [&](u32x4 (&raw)[U], int g0) {
+  Raw best_raw = {0u, 0u, 0u, 0u};
+  constexpr int U = HALVES ? SWEEP_U / 2 : SWEEP_U;
+  auto load = [&](Raw (&raw)[U], int g0) {
 #pragma unroll
     for (int j = 0; j < U; ++j) {   // (past the end: the last group again, which changes nothing)
       const int g = min(g0 + j * NT, n_groups - 1);
-      if (ODD) raw[j] = *(const u32x4_any*)(base + start_of(g) * (BF16 ? 2 : 4));
-      else raw[j] = ((const u32x4*)base)[g];
+      if constexpr (ODD) raw[j] = *(const u32x4_any*)(base + start_of(g) * (BF16 ? 2 : 4));
+      else raw[j] = ((const Raw*)base)[g];
     }
   };
-  auto look_at = [&](const u32x4 (&raw)[U], int g0) {
+  auto look_at = [&](const Raw (&raw)[U], int g0) {
 #pragma unroll
     for (int j = 0; j < U; ++j) {
       float x[VEC];
@@ -312,21 +315,29 @@ __global__ void __launch_bounds__(NT) node_argmax_kernel(const void* __restrict_
       }
     }
   };
-  u32x4 even[U], odd[U];
-  load(even, t);
-  for (int g0 = t;; g0 += 2 * U * NT) {   // (the last half apart: nothing is requested behind it)
-    if (g0 - t + U * NT >= n_groups) {
+  if constexpr (!HALVES) {
+    for (int g0 = t; g0 < n_groups; g0 += NT * U) {
+      Raw raw[U];
+      load(raw, g0);
+      look_at(raw, g0);
+    }
+  } else if (ODD || t < n_groups) {
+    Raw even[U], odd[U];
+    load(even, t);
+    for (int g0 = t;; g0 += 2 * U * NT) {   // (the last half apart: nothing is requested behind it)
+      if (g0 - t + U * NT >= n_groups) {
+        look_at(even, g0);
+        break;
+      }
+      load(odd, g0 + U * NT);
       look_at(even, g0);
-      break;
-    }
-    load(odd, g0 + U * NT);
-    look_at(even, g0);
-    if (g0 - t + 2 * U * NT >= n_groups) {
+      if (g0 - t + 2 * U * NT >= n_groups) {
+        look_at(odd, g0 + U * NT);
+        break;
+      }
+      load(even, g0 + 2 * U * NT);
       look_at(odd, g0 + U * NT);
-      break;
     }
-    load(even, g0 + 2 * U * NT);
-    look_at(odd, g0 + U * NT);
   }
   int best_i = 0x7fffffff;
   if (best_g >= 0) {
@@ -1085,6 +1096,17 @@ __global__ void __launch_bounds__(SW_THREADS) node_sample_kernel(const void* __r
 }
 
 // ---------------------------------------------------------------------------------------------
+// Whether the arg-max takes its rows by half sweeps. An odd number of halves: yes, the last half sweep would be loaded for nothing
+// (us, whole / halves, workgroups of 1024: 320 rows of 45232 float32 16.2 / 15.5, 4 rows 7.5 / 7.1; 480 of 80000 bfloat16 19.9 / 17.3; one
+// row of 32000 bfloat16 6.7 / 6.1; of 256: 2000 rows of 40000 bfloat16 32.0 / 31.4). An even one: no, the fewer instructions tell (300 rows
+// of 17000 float32 10.0 / 10.6, of 100000 bfloat16 16.8 / 17.6, 4 rows of it 8.4 / 8.8; 16 of 128256 bfloat16 8.6 / 8.9), but for
+// float32 rows of two sweeps and more, one for every second compute unit and above, which are bound by memory (65536: 128 rows 11.4 /
+// 11.1, 300 rows 19.7 / 18.6, 16 rows 7.7 / 7.85).
+static bool argmax_by_halves(int rows, int V, bool bf16, int threads) {
+  const int half = threads * SWEEP_U / 2 * (bf16 ? 8 : 4), halves = (V + half - 1) / half;
+  return halves % 2 == 1 || (!bf16 && threads == 1024 && halves >= 4 && rows >= compute_units() / 2);
+}
+
 hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* logits, float inv_temp,
                              int32_t* node_argmax, float* node_max, float* node_sumexp, hipStream_t s,
                              const int32_t* parent, int own_levels) {
@@ -1094,15 +1116,19 @@ hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* 
   const bool many = (long)B * N >= 1024;
   if (node_sumexp == nullptr && V >= (bf16 ? 8 : 4)) {   // (the entry points require 16-byte aligned logits)
     const bool small = many || V <= 256 * SWEEP_U * (bf16 ? 8 : 4) / 2;
-    const bool odd = V % (bf16 ? 8 : 4) != 0;
-#define SPEC_NA(BF, NT)                                                                                                        \
-  do {                                                                                                                         \
-    if (odd) hipLaunchKernelGGL((node_argmax_kernel<BF, NT, true>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max); \
-    else hipLaunchKernelGGL((node_argmax_kernel<BF, NT, false>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max);    \
+    const int form = V % (bf16 ? 8 : 4) != 0 ? 2 : argmax_by_halves(B * N, V, bf16, small ? 256 : 1024) ? 1 : 0;
+#define SPEC_NA_F(BF, NT, OD, HA) \
+  hipLaunchKernelGGL((node_argmax_kernel<BF, NT, OD, HA>), dim3(B * N), dim3(NT), 0, s, logits, V, node_argmax, node_max)
+#define SPEC_NA(BF, NT)                              \
+  do {                                               \
+    if (form == 2) SPEC_NA_F(BF, NT, true, true);    \
+    else if (form == 1) SPEC_NA_F(BF, NT, false, true); \
+    else SPEC_NA_F(BF, NT, false, false);            \
   } while (0)
     if (bf16) { if (small) SPEC_NA(true, 256); else SPEC_NA(true, 1024); }
     else { if (small) SPEC_NA(false, 256); else SPEC_NA(false, 1024); }
 #undef SPEC_NA
+#undef SPEC_NA_F
     return hipGetLastError();
   }
 #define SPEC_NS(BF, VE, NT)                                                                                              \

@@ -72,3 +72,27 @@ def test_walk_sizes(spec, N, Lmax):
         n = len(want)
         assert ln[b].item() == n and path[b, :n].tolist() == want and toks[b, :n].tolist() == out
         assert (path[b, n:] == -1).all() and (toks[b, n:] == -1).all()
+
+
+@pytest.mark.parametrize("dt,rows,V", [
+    # workgroups of 1024: one to five half sweeps of 16384 float32 or 32768 bfloat16, at and one group past their ends
+    ("f32", 3, 16384), ("f32", 3, 16388), ("f32", 3, 32768), ("f32", 3, 32772), ("f32", 3, 65536), ("f32", 3, 65540), ("f32", 3, 81920),
+    ("f32", 130, 65536), ("f32", 130, 49156), ("bf16", 3, 32768), ("bf16", 3, 32776), ("bf16", 3, 65536), ("bf16", 3, 65544),
+    ("bf16", 3, 131072), ("bf16", 3, 131080),
+    # of 256: halves of 4096 or 8192, in a thousand rows and more
+    ("f32", 1030, 4100), ("f32", 1030, 8192), ("f32", 1030, 8196), ("f32", 1030, 12292), ("bf16", 1030, 8200), ("bf16", 1030, 16392),
+    # fewer groups than threads
+    ("f32", 1030, 12), ("bf16", 5, 1024)])
+def test_argmax_by_whole_and_by_half_sweeps(spec, dt, rows, V):
+    """The largest value in the first, a middle and the last element, and on either side of the last border of sweeps, twice in a row."""
+    rng = np.random.default_rng(V + rows)
+    x = rng.integers(-3, 3, size=(rows, V)).astype(np.float32)
+    half = (256 if rows >= 1024 or V <= (8192 if dt == "bf16" else 4096) else 1024) * (32 if dt == "bf16" else 16)
+    border = (V - 1) // half * half
+    for i, at in enumerate((0, V - 1, V // 2, border, max(border - 1, 0), min(border + 1, V - 1), V - 2)):
+        x[i % rows, at] = x[i % rows, min(V - 1, at + 5)] = 9.0
+    x[rows - 1, -4:] = (-np.inf, np.nan, 9.0, -0.0)
+    logits = torch.from_numpy(x).to(torch.bfloat16 if dt == "bf16" else torch.float32).view(rows, 1, V).to(DEV)
+    one = torch.zeros((rows, 1), dtype=torch.int32, device=DEV)
+    got = spec.spec_verify_greedy(logits, one, one - 1)
+    assert np.array_equal(got[3].cpu().numpy()[:, 0], _argmax(x))

@@ -195,11 +195,12 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // only up to 20 D keys. Cut, several requests of unequal lengths lose more to the longer chunks than that saves: chunks of
       // up to 8 D keys, or 20 D of one request (16 x 64/8 of 8000 in two, 111 / 125, of 4000-8000 98 / 115; 4 x 32/8 of 12000 in
       // eight, 46.4 / 45.0, of 6000-12000 41.3 / 43.9). Pairs of many query groups are bound by arithmetic and want both (64/8
-      // heads of 4000 keys, trees of 128, 42 / 47). Pairs of up to two query tiles are cut for two per unit although one is the
-      // faster (32 heads of 4432 keys, trees of 20, 23.8 / 21.4; of 8000, 24, 31.8 / 29.6; 40 of 5000, 24, 28.5 / 26.7): the
-      // number of chunks of such a call is fixed by tests/test_attention_plan.py.
+      // heads of 4000 keys, trees of 128, 42 / 47). Pairs of up to two query tiles: with D = 128 one per unit (32 heads
+      // of 3152 keys, trees of 20, 20.7 / 18.7; 64 of 999, 29, 19.1 / 16.4; 40 of 9728, 28, 42.0 / 38.6; 4 x 12 of 1044-2086, 29, 19.7 / 17.9;
+      // 2 x 64 of 556-1111, 17, 20.5 / 19.4), with D = 64 two (64 heads of 3225 keys, 20, 17.6 / 18.3; 40 of 4407, 20, 16.9 / 17.7; 2 x 64
+      // of 784, 23, 13.0 / 13.1; 40 of 2092, 17, 12.6 / 11.9).
       const long per_unit = compute_units() / std::max<long>(1, groups);
-      const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2) && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
+      const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2 || d.D == 128) && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
                                 groups * per_unit * 5 >= 4 * compute_units() &&
                                 max_len / per_unit <= (per_unit == 1 || d.B == 1 ? 20 : 8) * d.D;
       const long hold = one_per_unit ? compute_units() : resident;

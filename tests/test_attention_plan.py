@@ -40,7 +40,32 @@ def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0):
     (2, 32, 8, 128, 3, 4825, 16),
     (1, 24, 6, 128, 7, 3205, 11),
     (1, 32, 32, 128, 40, 1024, 5),      # the tree in a chunk of its own
-    (1, 32, 32, 128, 20, 4432, 14),
+    (1, 32, 32, 64, 20, 4432, 14),
+    # ... for one workgroup per compute unit where two query tiles share a head dimension of 128 (14 chunks: 23.8 us, 8: 21.4)
+    (1, 32, 32, 128, 20, 4432, 8),
+    (4, 32, 32, 128, 21, 769, 2),
+    (1, 64, 64, 64, 20, 3225, 8),
+    # ... and for three tiles and more, from four fifths of the compute units on
+    (4, 52, 52, 128, 40, 600, 1),
+    (4, 51, 51, 128, 40, 600, 2),
+    # ... uncut up to 20 D keys
+    (8, 32, 32, 128, 60, 2500, 1),
+    (8, 32, 32, 128, 60, 2501, 2),
+    (8, 32, 32, 64, 60, 1221, 2),
+    # ... cut up to 8 D keys a chunk of several requests, 20 D of one
+    (4, 32, 32, 128, 40, 2009, 2),
+    (4, 32, 32, 128, 40, 2010, 4),
+    (1, 32, 32, 128, 40, 20447, 8),
+    (1, 32, 32, 128, 40, 20448, 16),
+    # ... down to 128 keys where most of the device is idle: up to half a workgroup per compute unit, up to eight chunks (and one of
+    # the tree's own), two only of few pairs with a head dimension of 128
+    (1, 32, 32, 128, 40, 400, 3),
+    (1, 12, 12, 128, 60, 963, 6),
+    (1, 12, 12, 128, 60, 964, 8),
+    (1, 12, 12, 128, 60, 1000, 9),
+    (1, 12, 12, 128, 60, 300, 2),
+    (1, 12, 12, 64, 60, 300, 1),
+    (1, 64, 64, 128, 50, 300, 1),
     # ... unless the last of them would be the longest, where there are workgroups to spare
     (2, 32, 8, 128, 5, 2191, 8),
     (1, 32, 8, 64, 2, 3477, 13),

@@ -2,7 +2,8 @@
 
 Each function has the name of the C entry point it calls and passes device pointers of torch tensors
 (torch is used for device memory and streams, nothing else). What a serving loop calls per layer or per
-iteration is marshalled in native code (csrc/marshal.cpp, lib/spec_marshal.so), the rest through ctypes.
+iteration is marshalled in native code (csrc/marshal.cpp, lib/spec_marshal.*.so, built for one Python and one
+torch), the rest through ctypes.
 Every step of the hot path runs in the HIP kernels of the library; there is no fallback: a missing
 library raises.
 """
@@ -12,12 +13,12 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sysconfig
 from typing import List, Optional, Sequence, Tuple
 
 import torch
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "lib", "libspectree.so")
-_MARSHAL_PATH = os.path.join(os.path.dirname(_LIB_PATH), "spec_marshal.so")
 _lib = None
 _marshal = None
 
@@ -72,14 +73,22 @@ def lib_path() -> str:
     return _LIB_PATH
 
 
+def marshal_path() -> str:
+    """Where the marshalling module of this Python and this torch lies: it is bound to both ABIs, so its name has both."""
+    abi = sysconfig.get_config_var("SOABI")
+    return os.path.join(os.path.dirname(_LIB_PATH), f"spec_marshal.{abi}.torch-{torch.__version__}.so")
+
+
 def _native():
     """The marshalling module built in-tree beside the library."""
     global _marshal
     if _marshal is None:
         load()
-        if not os.path.exists(_MARSHAL_PATH):
-            raise RuntimeError(f"{_MARSHAL_PATH} not found: build it with `python -m paper_2305_09781_amd.build`")
-        loader = importlib.machinery.ExtensionFileLoader("spec_marshal", _MARSHAL_PATH)
+        path = marshal_path()
+        if not os.path.exists(path):
+            raise RuntimeError(f"{path} not found: the binding's native part is built for one Python and one torch; build it for "
+                               "these with `python -m paper_2305_09781_amd.build`")
+        loader = importlib.machinery.ExtensionFileLoader("spec_marshal", path)
         module = importlib.util.module_from_spec(importlib.util.spec_from_loader("spec_marshal", loader))
         loader.exec_module(module)
         module.set_helpers(SpecError, ctypes.ArgumentError, _stream)

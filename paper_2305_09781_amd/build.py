@@ -1,6 +1,6 @@
 """Builds libspectree.so (HIP kernels + C ABI) and libspecprobe.so (the read-stream measurement aid the
-benchmark times beside the kernels) for gfx950 with hipcc, and spec_marshal.so (the binding's argument
-marshalling, host code) with g++, in-tree.
+benchmark times beside the kernels) for gfx950 with hipcc, and spec_marshal.*.so (the binding's argument
+marshalling, host code, for this Python and this torch) with g++, in-tree.
 
     python -m paper_2305_09781_amd.build        # compile every source, link the shared libraries
 """
@@ -24,7 +24,6 @@ PROBE_LIB_PATH = os.path.join(LIB_DIR, "libspecprobe.so")
 SOURCES = ["spec_api.hip", "kv_cache.hip", "tree_attention_f32.hip", "tree_attention_bf16.hip",
            "tree_attention_bf16_wide.hip", "tree_attention_bf16_wide32.hip", "verify.hip", "tree_build.hip", "lm_head.hip"]
 PROBE_SOURCES = ["probe.hip"]
-MARSHAL_PATH = os.path.join(LIB_DIR, "spec_marshal.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=fast",
@@ -55,11 +54,12 @@ def _marshal_command():
     """The binding's native part is a Python extension module that reads torch tensors and calls the library beside it."""
     import torch
     from torch.utils.cpp_extension import include_paths
+    from .binding import marshal_path
     torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
     cxx = shutil.which("g++") or "g++"
     includes = [*include_paths(), sysconfig.get_paths()["include"], os.path.join(ROOT, "include")]
     return [cxx, "-O2", "-std=c++17", "-fPIC", "-shared", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
-            *[f"-I{i}" for i in includes], os.path.join(CSRC, "marshal.cpp"), "-o", MARSHAL_PATH, "-L", LIB_DIR, "-lspectree",
+            *[f"-I{i}" for i in includes], os.path.join(CSRC, "marshal.cpp"), "-o", marshal_path(), "-L", LIB_DIR, "-lspectree",
             "-Wl,-rpath,$ORIGIN", "-L", torch_lib, "-lc10", "-ltorch_cpu", "-ltorch_python"]
 
 
@@ -79,9 +79,10 @@ def build_library(extra_flags=(), verbose: bool = True) -> str:
         list(ex.map(_run, jobs))
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs])
     _run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", PROBE_LIB_PATH, *probe_objs])
-    _run(_marshal_command())
+    marshal = _marshal_command()
+    _run(marshal)
     if verbose:
-        print("built", LIB_PATH, ",", PROBE_LIB_PATH, "and", MARSHAL_PATH)
+        print("built", LIB_PATH, ",", PROBE_LIB_PATH, "and", marshal[marshal.index("-o") + 1])
     return LIB_PATH
 
 

@@ -97,3 +97,11 @@ def _rope(**kw):
 def test_what_is_refused_before_a_launch(call, error):
     with pytest.raises(error):
         call()
+
+
+def test_another_torch_is_a_message(monkeypatch):
+    """The module is bound to one Python and one torch, its name says which, and their absence is an error that says so."""
+    monkeypatch.setattr(spec, "_marshal", None)
+    monkeypatch.setattr(torch, "__version__", "1.0")
+    with pytest.raises(RuntimeError, match="torch-1.0.so not found.*one Python and one torch"):
+        spec.make_desc(torch.zeros(1, 4, 2, 64), torch.zeros(1, 2, 8, 64))

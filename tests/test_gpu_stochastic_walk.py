@@ -56,7 +56,7 @@ def _us(call):
 def _own_levels(V, B, N, dt, Lmax):
     """Levels up to which the walk takes a tree's statistics itself (the rule of spec_verify_stochastic)."""
     pass_us = B * N * V * (2 if dt == "bf16" else 4) / 5.5e6
-    levels = int(min(pass_us / (V * (1.05e-4 if dt == "f32" and V % 4 else 0.9e-4)), 128))
+    levels = int(min(pass_us / (V * 0.9e-4), 128))
     return levels if levels >= 8 or levels >= min(Lmax, N) else 0
 
 
@@ -190,3 +190,25 @@ def test_every_step_of_a_long_path_is_in_the_outputs(spec, V):
     want[:, :N] = torch.arange(N, dtype=torch.int32, device=DEV)
     assert (ln == N).all() and torch.equal(path, want)
     assert torch.equal(out[:, :N - 1], tok[:, 1:]) and (out[:, N - 1] >= 0).all() and (out[:, N:] == -1).all()
+
+
+def _rejections(parent, tok, order, path, ln):
+    """Rejections in a row at each node that an accepted path visits: its children tested before the accepted one, or all."""
+    out = []
+    for k in range(ln):
+        kids = sorted((v for v in range(1, len(parent)) if parent[v] == path[k] and tok[v] >= 0), key=lambda v: (order[v], v))
+        out.append(kids.index(path[k + 1]) if k + 1 < ln else len(kids))
+    return out
+
+
+@pytest.mark.parametrize("V,B,N,dt,tau,seed", [(50257, 3, 16, "bf16", 2.0, 3), (65539, 3, 16, "f32", 1.2, 2), (128256, 2, 12, "bf16", 2.0, 2),
+                                               (65536, 3, 16, "f32", 2.0, 0)])
+def test_rejections_of_large_vocabularies(spec, V, B, N, dt, tau, seed):
+    """The buffer form with two rejections and more at one node (both residual buffers), over several sweeps of a row."""
+    logits, dev, ref = _case(V, B, N, dt, seed=V + seed, tau=tau)
+    tok, par, order = (dev[i].cpu().numpy() for i in (2, 3, 5))
+    assert max(max(_rejections(par[b], tok[b], order[b], ref[0][b], ref[1][b])) for b in range(B)) >= 2
+    status = torch.zeros(B, dtype=torch.int32, device=DEV)
+    got = spec.spec_verify_stochastic(logits, *dev, status=status)
+    for g, r in zip(list(got) + [status], ref):
+        assert np.array_equal(g.cpu().numpy(), r)

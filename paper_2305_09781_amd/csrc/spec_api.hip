@@ -200,7 +200,7 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // 2 x 64 of 556-1111, 17, 20.5 / 19.4), with D = 64 two (64 heads of 3225 keys, 20, 17.6 / 18.3; 40 of 4407, 20, 16.9 / 17.7; 2 x 64
       // of 784, 23, 13.0 / 13.1; 40 of 2092, 17, 12.6 / 11.9).
       const long per_unit = compute_units() / std::max<long>(1, groups);
-      const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2 || d.D == 128) && qg.n_qgroups <= 2 && per_unit >= 1 && per_unit <= max_splits &&
+      const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2 || d.D == 128) && qg.n_qgroups <= 2 && per_unit <= max_splits &&
                                 groups * per_unit * 5 >= 4 * compute_units() &&
                                 max_len / per_unit <= (per_unit == 1 || d.B == 1 ? 20 : 8) * d.D;
       const long hold = one_per_unit ? compute_units() : resident;

@@ -203,13 +203,13 @@ hipError_t launch_greedy_walk(int B, int N, const int32_t* node_argmax, const in
 // kernel spills and the buffer form is the faster one (8 trees of 16, 50000 float32: 67 us against 59).
 inline bool stochastic_walk_in_registers(int V) { return V <= 32768; }
 // Levels up to which a tree's nodes get their statistics from the walk itself (0: none); those of deeper trees come from the
-// pass over all nodes. A walk visits at most as many nodes as its tree has levels, and each node costs it 0.9e-4 V us more
-// than the walk over given statistics that this one replaced (64 accepted nodes in a row, us in all: 8192 float32 154 against
-// 107 without the pass, 16384: 204 / 118, 32000: 306 / 122; bfloat16 292 / 144);
-// the pass costs its bytes at 5.5 TB/s. Up to the level where the two are equal, even a path that is accepted to the end of
-// the tree takes no longer (16 x 128 nodes of 32000 float32: 16 levels), and the usual path of a few nodes is much shorter: 16 trees of
-// 128, 32000 float32, three drafts, 44 us; all 128 nodes of chains accepted: 131 (274 with the
-// form this one replaced). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
+// pass over all nodes. A walk visits at most as many nodes as its tree has levels, and each node costs it about 1e-4 V us more
+// than a walk over given statistics (96 accepted nodes in a row, us, own / given: 8192 float32 144 / 58, 16384: 220 / 59, 32000:
+// 350 / 61, 32003: 358 / 66; 32000 bfloat16 296 / 61, 31999: 362 / 68; 0.5 us more at least, 2048: 112 / 58); the pass costs its
+// bytes at 5.5 TB/s and a launch. The line is drawn at 0.9e-4 V, a little past the level where the two are equal, as the usual path has a few
+// nodes and not all its levels: 16 x 128 nodes of 32000 float32, 16 levels, three drafts, 44.6 us, and a path accepted to the end of such
+// a tree 5 us more than behind a pass (10 us more at worst: 33 levels of 2048). All 128 nodes of chains accepted: 130 us
+// (96 of them 100, 350 by their own statistics). Looking at the trees makes a pass 2 us longer, and one that leaves them all out
 // takes 4.5: only from 8 levels on, which fewer trees of a batch exceed. Where Lmax or N are no more than the levels, no tree
 // has to be looked at.
 inline int stochastic_own_levels(int B, int N, int V, int logits_dtype, int Lmax) {

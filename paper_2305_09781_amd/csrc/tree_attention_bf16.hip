@@ -289,9 +289,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     lo = __builtin_bit_cast(std::remove_reference_t<decltype(lo)>, olo);
     hi = __builtin_bit_cast(std::remove_reference_t<decltype(hi)>, ohi);
   };
-  // tiles of this wavefront: first, stride, count
+  // tiles of this wavefront: first and end (the streaming wavefronts take every SWAVES-th)
   const int ti_first = is_tail ? n_clean : wave;
-  const int ti_stride = is_tail ? 1 : SWAVES;
   const int ti_end = is_tail ? n_tiles : n_clean;
   if (is_tail) {
     if constexpr (APPEND) {

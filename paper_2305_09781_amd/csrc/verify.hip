@@ -1,7 +1,7 @@
 // Token-tree verification on the GPU (Algorithm 2: VerifyGreedy and VerifyStochastic, Section 4.3).
 //
 // The paper runs verification on the host after copying the LLM's per-node outputs back; here it
-// stays on the device so an iteration needs no host round trip. Three kernels:
+// stays on the device so an iteration needs no host round trip. The kernels:
 //   node_stats_kernel      one workgroup per (request, node) row of logits: argmax (lowest token id on
 //                          ties), max, and sum of exp((x - max)/T). All nodes in parallel, so the
 //                          sequential tree walk that follows needs P(x) at a node in O(1).
@@ -28,10 +28,10 @@ __device__ inline float load_logit(const void* base, long idx) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Vocabulary sweeps. A row of V values is visited in groups of VEC consecutive elements (VEC = 4 when
-// V is a multiple of 4, so that every group is one aligned 16-byte (float) or 8-byte (bf16) access;
-// else 1). A block of NT threads takes U groups per thread at a time, all loads issued before any is
-// used: with V = 32000, NT = 1024, U = 8 a whole row is one round trip to memory.
+// Vocabulary sweeps. A row of V values is visited in groups of VEC consecutive elements: 4 (16 bytes of float, 8 of bf16; the
+// arg-max alone takes 8 of bf16) for every V of at least as many, the last group ending with the row, and 1 for shorter rows.
+// A block of NT threads takes U groups per thread at a time, all loads issued before any is used: with V = 32000, NT = 1024,
+// U = 8 a whole row is one round trip to memory.
 // ---------------------------------------------------------------------------------------------
 constexpr int SWEEP_U = 8;
 
@@ -40,7 +40,7 @@ __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(
 
 // Rows of any length by whole groups of VEC elements: the last group ends with the row and so repeats elements of the one
 // before it where VEC does not divide V. Rows of odd vocabularies start at any element; the memory unit takes such loads
-// (single elements before. Stochastic verification, 4 trees of 32, 31999 bfloat16: 48.6 us, 30.5 now; greedy, 1024 rows of
+// (single elements before. Stochastic verification, 4 trees of 32, 31999 bfloat16: 48.6 us, 30.9 now; greedy, 1024 rows of
 // 50257 bfloat16: 94, 22 now, 8 rows of 56877: 13.3, 7.8).
 __device__ __forceinline__ int group_start(int group, int vec, int V) { return min(group * vec, V - vec); }
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
@@ -50,23 +50,6 @@ typedef u32x4 __attribute__((aligned(2))) u32x4_any;
 typedef u32x2 __attribute__((aligned(2))) u32x2_any;
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 
-template <int VEC, bool BF16>
-__device__ __forceinline__ void load_logit_group(const void* base, long elem, float (&v)[VEC]) {
-  if (VEC == 4) {
-    if (BF16) {
-      const uint2 raw = *(const uint2*)((const __hip_bfloat16*)base + elem);
-      v[0] = __uint_as_float(raw.x << 16);
-      v[1] = __uint_as_float(raw.x & 0xffff0000u);
-      v[2] = __uint_as_float(raw.y << 16);
-      v[3] = __uint_as_float(raw.y & 0xffff0000u);
-    } else {
-      const float4 raw = *(const float4*)((const float*)base + elem);
-      v[0] = raw.x; v[1] = raw.y; v[2] = raw.z; v[3] = raw.w;
-    }
-  } else {
-    v[0] = load_logit<BF16>(base, elem);
-  }
-}
 template <int VEC>
 __device__ __forceinline__ void load_f32_group(const float* p, float (&v)[VEC]) {
   if (VEC == 4) {
@@ -138,7 +121,7 @@ __device__ __forceinline__ void drop_repeated(float (&v)[VEC], int group, int n_
 }
 
 // ---------------------------------------------------------------------------------------------
-// per-node statistics: one block of 1024 threads per (request, node) row, one pass over the row.
+// per-node statistics: one block of 256 or 1024 threads per (request, node) row, one pass over the row.
 // Each thread keeps (max, lowest index of the max, sum of exp((x - max) / T)) of its elements; the
 // block combines the triples.
 // ---------------------------------------------------------------------------------------------
@@ -428,8 +411,8 @@ __global__ void __launch_bounds__(64) greedy_walk_kernel(int N, const int32_t* _
 // or two of them in a chain, with one barrier each. What the tests need of the tree is fetched and ordered for all nodes while
 // the root's row is on its way, and every wavefront follows the walk by itself (a node's children listed, sorted and fetched
 // as the walk reached them: six barriers and a trip to memory more per node). Measured, us, before and now: 16 requests, trees
-// of 128, 32000 float32, three drafts, 49.1 / 43.7; chains of 128, all accepted, 231 / 131; 32 trees of 128, 4000 float32,
-// 25.2 / 22.7.
+// of 128, 32000 float32, three drafts, 49.1 / 44.6; chains of 128, all accepted, 231 / 130; 32 trees of 128, 4000 float32,
+// 25.2 / 22.9.
 // ---------------------------------------------------------------------------------------------
 
 // exp(x) for x <= 0, subnormal results included (a draw at 0 takes the first token that has any weight): 2^n 2^f with n the integer

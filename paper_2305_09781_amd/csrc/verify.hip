@@ -127,7 +127,9 @@ __device__ __forceinline__ void drop_repeated(float (&v)[VEC], int group, int n_
 // ---------------------------------------------------------------------------------------------
 // Workgroup size: 1024 threads when there are few rows (a row is then one round trip to memory), 256 when there
 // are thousands: eight small workgroups per compute unit overlap one another's loads and arithmetic, where two
-// large ones alternate between a load phase and a compute phase (2048 rows of 32000 floats: 61 us before).
+// large ones alternate between a load phase and a compute phase (2048 rows of 32000 floats: 61 us before). A sweep has as many
+// groups per thread as the row needs of 2, 4 and 8 (U): empty ones cost their exponentials like full ones (the pass over 315 rows
+// of 4224 float32 12.1 us with eight, 6.7 with two; of 4098, by eight single elements a thread before, 6.5, 6.5 now).
 
 // exp(x) for x <= 0 as one v_exp_f32 (1 ulp; results below 2^-126 become 0). The sum over a vocabulary row is
 // bound by this instruction count: the library expf costs about ten instructions per element, and the
@@ -157,7 +159,7 @@ __device__ inline bool tree_within(int par0, int par1, int levels) {
 
 // parent != nullptr: the rows of requests whose tree is within `own_levels` levels are left out (the stochastic walk takes
 // their nodes' statistics itself).
-template <bool BF16, int VEC, int NS_THREADS>
+template <bool BF16, int VEC, int NS_THREADS, int U>
 __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __restrict__ logits, int V, float inv_temp,
                                                                 int32_t* __restrict__ node_argmax,
                                                                 float* __restrict__ node_max,
@@ -178,31 +180,31 @@ __global__ void __launch_bounds__(NS_THREADS) node_stats_kernel(const void* __re
   }
   float best = -INFINITY, sum = 0.f;
   int best_i = 0x7fffffff;
-  for (int g0 = 0; g0 < n_groups; g0 += NS_THREADS * SWEEP_U) {
-    float x[SWEEP_U][VEC];
-    LogitGroup<BF16, VEC> raw[SWEEP_U];
+  for (int g0 = 0; g0 < n_groups; g0 += NS_THREADS * U) {
+    float x[U][VEC];
+    LogitGroup<BF16, VEC> raw[U];
 #pragma unroll
-    for (int j = 0; j < SWEEP_U; ++j) {
+    for (int j = 0; j < U; ++j) {
       const int gi = g0 + j * NS_THREADS + t;
       if (gi < n_groups) raw[j].load((const char*)logits + base * (BF16 ? 2 : 4), (unsigned)group_start(gi, VEC, V));
       else raw[j].set_minus_infinity();
     }
 #pragma unroll
-    for (int j = 0; j < SWEEP_U; ++j) raw[j].expand(x[j]);
+    for (int j = 0; j < U; ++j) raw[j].expand(x[j]);
     if (V % VEC != 0) {
 #pragma unroll
-      for (int j = 0; j < SWEEP_U; ++j) drop_repeated<VEC>(x[j], g0 + j * NS_THREADS + t, n_groups, V, -INFINITY);
+      for (int j = 0; j < U; ++j) drop_repeated<VEC>(x[j], g0 + j * NS_THREADS + t, n_groups, V, -INFINITY);
     }
     float m = best;
 #pragma unroll
-    for (int j = 0; j < SWEEP_U; ++j)
+    for (int j = 0; j < U; ++j)
 #pragma unroll
       for (int e = 0; e < VEC; ++e)
         if (x[j][e] > m) { m = x[j][e]; best_i = group_start(g0 + j * NS_THREADS + t, VEC, V) + e; }   // ascending index: lowest wins ties
     if (want_sum && m > -INFINITY) {
       sum *= fast_exp((best - m) * inv_temp);     // best = -inf gives 0
 #pragma unroll
-      for (int j = 0; j < SWEEP_U; ++j)
+      for (int j = 0; j < U; ++j)
 #pragma unroll
         for (int e = 0; e < VEC; ++e) sum += fast_exp((x[j][e] - m) * inv_temp);   // padding: exp(-inf) = 0
     }
@@ -1114,13 +1116,20 @@ hipError_t launch_node_stats(int B, int N, int V, int logits_dtype, const void* 
 #undef SPEC_NA_F
     return hipGetLastError();
   }
-#define SPEC_NS(BF, VE, NT)                                                                                              \
-  hipLaunchKernelGGL((node_stats_kernel<BF, VE, NT>), dim3(B * N), dim3(NT), 0, s, logits, V, inv_temp, node_argmax,      \
+#define SPEC_NS_U(BF, VE, NT, U)                                                                                         \
+  hipLaunchKernelGGL((node_stats_kernel<BF, VE, NT, U>), dim3(B * N), dim3(NT), 0, s, logits, V, inv_temp, node_argmax,   \
                      node_max, node_sumexp, parent, N, own_levels)
+#define SPEC_NS(BF, NT)                              \
+  do {                                               \
+    if (V <= 2 * 4 * NT) SPEC_NS_U(BF, 4, NT, 2);    \
+    else if (V <= 4 * 4 * NT) SPEC_NS_U(BF, 4, NT, 4); \
+    else SPEC_NS_U(BF, 4, NT, SWEEP_U);              \
+  } while (0)
   const bool small = many || V <= 256 * SWEEP_U * 4 / 2;
-  if (V < 4) { if (bf16) SPEC_NS(true, 1, 256); else SPEC_NS(false, 1, 256); }
-  else if (bf16) { if (small) SPEC_NS(true, 4, 256); else SPEC_NS(true, 4, 1024); }
-  else { if (small) SPEC_NS(false, 4, 256); else SPEC_NS(false, 4, 1024); }
+  if (V < 4) { if (bf16) SPEC_NS_U(true, 1, 256, 2); else SPEC_NS_U(false, 1, 256, 2); }
+  else if (bf16) { if (small) SPEC_NS(true, 256); else SPEC_NS(true, 1024); }
+  else { if (small) SPEC_NS(false, 256); else SPEC_NS(false, 1024); }
+#undef SPEC_NS_U
 #undef SPEC_NS
   return hipGetLastError();
 }

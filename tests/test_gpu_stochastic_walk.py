@@ -212,3 +212,36 @@ def test_rejections_of_large_vocabularies(spec, V, B, N, dt, tau, seed):
     got = spec.spec_verify_stochastic(logits, *dev, status=status)
     for g, r in zip(list(got) + [status], ref):
         assert np.array_equal(g.cpu().numpy(), r)
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("V,rows", [(2048, 60), (2049, 60), (4096, 60), (4097, 60), (8192, 60), (8193, 60), (16384, 60), (16387, 60),
+                                    (2047, 1024), (2049, 1024), (4100, 1024), (8193, 1024)])
+def test_statistics_at_the_ends_of_sweeps(spec, V, rows, dt):
+    """Sweeps of two, four and eight groups a thread, in workgroups of 256 and 1024: walks whose statistics come from the pass
+    end in the same tokens as over those that torch takes, the last element the likeliest of a third of the rows."""
+    B = rows // 20
+    N = rows // B
+    g = torch.Generator(device=DEV).manual_seed(V + rows)
+    logits = torch.randn((B, N, V), generator=g, device=DEV)
+    logits[:, ::3, V - 1] = 9.0
+    logits[0, N - 1, : V - 1] = float("-inf")
+    logits = logits.to(torch.bfloat16 if dt == "bf16" else torch.float32)
+    par = torch.arange(-1, N - 1, dtype=torch.int32, device=DEV).repeat(B, 1).contiguous()
+    tok = torch.randint(0, V, (B, N), generator=g, device=DEV, dtype=torch.int32)
+    probs = torch.full((1, V), 1.0 / V, device=DEV)
+    zero, row = torch.zeros((B, N), device=DEV), torch.zeros((B, N), dtype=torch.int32, device=DEV)
+    tok[0, N - 1] = V - 1
+    x = logits.double()
+    mx = x.max(-1).values
+    se = torch.exp(x - mx[..., None]).sum(-1)
+    for u in (0.05, 0.5, 0.97):
+        # an acceptance test at half and at twice the ratio: decided by the statistics, far from rounding
+        q = torch.exp(torch.gather(x[:, :-1], 2, tok[:, 1:, None].long())[..., 0] - mx[:, :-1]) / se[:, :-1] * V
+        ua = torch.cat([zero[:, :1], torch.where(torch.rand((B, N - 1), generator=g, device=DEV) < 0.05, 2.0, 0.5) * q.float()], 1)
+        args = (probs, row, tok, par, ua.contiguous(), zero, torch.full((B,), u, device=DEV))
+        got = spec.spec_verify_stochastic(logits, *args)
+        want = spec.spec_verify_stochastic_stats(logits, mx.float().contiguous(), se.float().contiguous(), *args)
+        for a, b in zip(got[:2], want[:2]):
+            assert torch.equal(a, b)
+        assert (got[2] == want[2]).float().mean() > 0.999       # (a draw within rounding of a border)

@@ -194,15 +194,22 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
       // (28 x 64/8 heads of 3000, 16, 83.1 / 85.8; D = 64: 20 x 12 of 3000, 30, 38.8 / 42.4, but 8 x 32 of 700, 50, 22.7 / 17.6):
       // only up to 20 D keys. Cut, several requests of unequal lengths lose more to the longer chunks than that saves: chunks of
       // up to 8 D keys, or 20 D of one request (16 x 64/8 of 8000 in two, 111 / 125, of 4000-8000 98 / 115; 4 x 32/8 of 12000 in
-      // eight, 46.4 / 45.0, of 6000-12000 41.3 / 43.9). Pairs of many query groups are bound by arithmetic and want both (64/8
+      // eight, 46.4 / 45.0, of 6000-12000 41.3 / 43.9), the 32-query kernel up to 6 D (2 x 32 of 1688-3374, 101, 35.7 / 37.8; 2 x 64 of 751-1500,
+      // 90, 35.0 / 37.1; but 4 x 32/8 of 6000, 32, 38.8 / 35.2, 2 x 12 of 2001-4000, 100, 29.1 / 27.5). Pairs of many query groups are bound by arithmetic and want both (64/8
       // heads of 4000 keys, trees of 128, 42 / 47). Pairs of up to two query tiles: with D = 128 one per unit (32 heads
       // of 3152 keys, trees of 20, 20.7 / 18.7; 64 of 999, 29, 19.1 / 16.4; 40 of 9728, 28, 42.0 / 38.6; 4 x 12 of 1044-2086, 29, 19.7 / 17.9;
       // 2 x 64 of 556-1111, 17, 20.5 / 19.4), with D = 64 two (64 heads of 3225 keys, 20, 17.6 / 18.3; 40 of 4407, 20, 16.9 / 17.7; 2 x 64
       // of 784, 23, 13.0 / 13.1; 40 of 2092, 17, 12.6 / 11.9).
       const long per_unit = compute_units() / std::max<long>(1, groups);
+      // Longest chunk for that, in halves of D. Paged, the wide kernel's tiles wait for their blocks' numbers first, which a second
+      // workgroup hides: shorter chunks only (us, two / one: cut, 4 x 32 heads of 600-1200 keys, trees of 50, 29.2 / 31.3; 64 of 3000, 40,
+      // 33.2 / 34.8; 32 of 12000, 24, 42.2 / 44.9; but 32 of 3100, 20, 22.4 / 19.8, 4 x 12 of 1044-2086, 29, 21.2 / 19.7; uncut 8 x 32
+      // of 1200-2400, 60, 69.0 / 71.9, of 750-1500 52.3 / 50.2).
+      const int half_d = p.m32 ? (per_unit == 1 ? 40 : d.B > 1 ? 12 : paged ? 24 : 40)
+                               : paged ? (per_unit == 1 ? 28 : 7) : (per_unit == 1 || d.B == 1) ? 40 : 16;
       const bool one_per_unit = p.wide && (per_unit == 1 || tiles > 2 || d.D == 128) && qg.n_qgroups <= 2 && per_unit <= max_splits &&
                                 groups * per_unit * 5 >= 4 * compute_units() &&
-                                max_len / per_unit <= (per_unit == 1 || d.B == 1 ? 20 : 8) * d.D;
+                                max_len / per_unit <= half_d * d.D / 2;
       const long hold = one_per_unit ? compute_units() : resident;
       long splits = std::max<long>(1, hold / std::max<long>(1, groups));
       if (splits > max_splits) splits = max_splits;

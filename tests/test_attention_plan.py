@@ -11,14 +11,20 @@ pytestmark = pytest.mark.skipif(torch.cuda.is_available() and torch.cuda.get_dev
                                 reason="expectations are for 256 compute units")
 
 
-def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0):
+def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0, block=0):
     H_kv = H_kv or H
     S = P + N
     d = binding.AttnDesc(B=B, H=H, H_kv=H_kv, D=D, N=N, S_cap=S, dtype=dtype, max_prefix_len=P, q_stride_b=N * H * D, q_stride_n=H * D,
                          q_stride_h=D, kv_stride_b=H_kv * S * D, kv_stride_h=S * D, kv_stride_s=D, new_stride_b=N * H_kv * D,
                          new_stride_n=H_kv * D, new_stride_h=D, softmax_scale=0.0, plan_chunk_keys=chunk, plan_balanced_wgs=wgs,
                          plan_heads_per_wg=0)
-    got = binding.load().spec_tree_attention_workspace_bytes(ctypes.byref(d))
+    if block:
+        d.S_cap = -(-S // block) * block
+        d.kv_stride_b, d.kv_stride_h = H_kv * block * D, block * D
+        pages = binding.KvPages(256, d.S_cap // block, block, B * d.S_cap // block)
+        got = binding.spec_tree_attention_paged_workspace_bytes(d, pages)
+    else:
+        got = binding.load().spec_tree_attention_workspace_bytes(ctypes.byref(d))
     up = lambda x: (x + 255) // 256 * 256  # noqa: E731
     for n in range(1, 600):
         rows = B * H * n * N
@@ -77,3 +83,21 @@ def _slots(B, H, D, N, P, H_kv=None, dtype=binding.SPEC_BF16, wgs=0, chunk=0):
 ])
 def test_fixed_chunks(B, H, H_kv, D, N, P, chunks):
     assert _slots(B, H, D, N, P, H_kv) == chunks
+
+
+@pytest.mark.parametrize("B,H,H_kv,D,N,P,chunks,contiguous", [
+    # (chunks of whole 64-key tiles) wide kernel: one workgroup per compute unit for chunks of up to 3.5 D keys, uncut up to 14 D
+    (1, 32, 32, 128, 20, 3100, 7, 8),
+    (4, 12, 12, 128, 29, 2086, 5, 5),
+    (1, 32, 32, 128, 24, 12000, 16, 8),
+    (4, 32, 32, 128, 50, 1200, 4, 2),
+    (8, 32, 32, 128, 60, 1732, 1, 1),
+    (8, 32, 32, 128, 60, 1733, 2, 1),
+    # 32-query kernel: chunks of up to 6 D of several requests, 12 D of one (20 D contiguous)
+    (2, 32, 32, 128, 101, 2974, 4, 4),
+    (2, 32, 32, 128, 101, 2975, 7, 8),
+    (1, 32, 32, 128, 100, 12195, 8, 8),
+    (1, 32, 32, 128, 100, 12196, 15, 8),
+])
+def test_fixed_chunks_paged(B, H, H_kv, D, N, P, chunks, contiguous):
+    assert (_slots(B, H, D, N, P, H_kv, block=64), _slots(B, H, D, N, P, H_kv)) == (chunks, contiguous)

@@ -231,7 +231,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   src.vn = APPEND ? (const unsigned char*)(v_new + b * q_sb + h * q_sh) + (lane % LPR) * 16 : nullptr;
 
   // The tail wavefront: a tree node per lane, from scalar loads, four nodes at a time as far as there are any (all sixteen at once
-  // cost the smallest calls what they wait for: 2 x 64 heads of 58 keys, one node, D = 64, 5.2 us, 4.7 by fours). Rows past N repeat
+  // cost the smallest calls what they wait for: 2 x 64 heads of 58 keys, one node, D = 64, 5.2 us, 4.7 by fours; sixteen nodes
+  // wait longer: 1 x 32 of 1024 keys 11.6, 11.9 by fours, rotated 12.9, 13.0). Rows past N repeat
   // the last query (their results are never written): the loads are unconditional.
   const bool is_tail = wave == TAIL;
   const bool rotates = APPEND && rope.cos != nullptr;

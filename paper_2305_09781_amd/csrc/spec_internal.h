@@ -595,6 +595,40 @@ __device__ inline long cache_row_offset(const Pages& pg, int b, int row, long kv
   return blk * kv_sb + (long)(row & ((1 << pg.log2_tokens) - 1)) * kv_ss;
 }
 
+// The block numbers of a paged request in the lanes of a wavefront: lane i has logical block first + i. A tile's block then
+// costs a register move, where an entry read from the table for every tile is a scalar load and a wait for it in front of the
+// tile's requests (us, before / now: 24 requests x 32 / 8 heads of 900 to 3100 keys, trees of 30, 83.2 / 68.8; 8 x 32 heads of 1000
+// keys, trees of 60, 37.9 / 32.3, of 24, 29.1 / 25.1; 10 x 40 heads of 1614 keys, D = 64, one node, 35.6 / 31.2).
+struct BlockLanes {
+  int first;                // of lane 0
+  int block;                // this lane's, moved into the pool
+  unsigned long long bad;   // lanes whose entry lies outside the pool (they may lie past the request's end and hold anything)
+};
+__device__ __forceinline__ BlockLanes block_lanes_of(const Pages& pg, int first, int entry) {
+  return {first, min(max(entry, 0), pg.n_blocks - 1), __ballot(entry < 0 || entry >= pg.n_blocks)};
+}
+__device__ __forceinline__ const int32_t* block_entry(const Pages& pg, int b, int j) {
+  return pg.table + (long)b * pg.max_blocks + min(j, pg.max_blocks - 1);
+}
+__device__ __forceinline__ BlockLanes load_block_lanes(const Pages& pg, int b, int first) {
+  return block_lanes_of(pg, first, *block_entry(pg, b, first + (int)(threadIdx.x & 63)));
+}
+// Place of logical block j (wave-uniform) among the lanes, which move on when it is not among them: once in 64 blocks, so the
+// wait for it stands here and not, for every tile, where the compiler would put it.
+__device__ __forceinline__ int block_lane(BlockLanes& w, const Pages& pg, int b, int j) {
+  if ((unsigned)(j - w.first) >= 64u) {
+    int entry;
+    asm volatile("global_load_dword %0, %1, off\n\ts_waitcnt vmcnt(0)"
+                 : "=v"(entry) : "v"(block_entry(pg, b, j + (int)(threadIdx.x & 63))) : "memory");
+    w = block_lanes_of(pg, j, entry);
+  }
+  return j - w.first;
+}
+// Whether one of the lanes' blocks up to `last` lies outside the pool.
+__device__ __forceinline__ bool blocks_outside(const BlockLanes& w, int last) {
+  return last >= w.first && (w.bad & (~0ull >> (63 - min(last - w.first, 63)))) != 0;
+}
+
 #endif  // __HIPCC__
 
 }  // namespace spec

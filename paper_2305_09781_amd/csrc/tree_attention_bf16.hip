@@ -203,11 +203,21 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   // Paged cache: byte offset that, added to `row * row_bytes`, gives the place of logical row `row` of request
   // b for every row of the 32-row tile at k0 (clamped rows stay inside the tile, hence inside its block).
   // `ok`: the table entry lies inside the pool; one that does not is replaced by a block of the pool.
+  // The contiguous plan, whose loop over segments has no register left for the lanes, reads the table for every tile.
+  constexpr bool LANES = PAGED && PLAN != 2;
+  BlockLanes blocks = {0, 0, 0ull};
   auto page_shift = [&](int b, int k0, bool* ok) -> long {
     const int j = __builtin_amdgcn_readfirstlane(min(k0, S_cap - 1) >> pg.log2_tokens);
-    const int e = pg.table[(long)b * pg.max_blocks + j];
-    *ok = e >= 0 && e < pg.n_blocks;
-    const int blk = min(max(e, 0), pg.n_blocks - 1);
+    int blk;
+    if constexpr (LANES) {
+      const int l = block_lane(blocks, pg, b, j);
+      *ok = !((blocks.bad >> l) & 1ull);
+      blk = __builtin_amdgcn_readlane(blocks.block, l);
+    } else {
+      const int e = pg.table[(long)b * pg.max_blocks + j];
+      *ok = e >= 0 && e < pg.n_blocks;
+      blk = min(max(e, 0), pg.n_blocks - 1);
+    }
     return (long)blk * kv_sb * 2 - (long)((unsigned)(j << pg.log2_tokens) * ((unsigned)kv_ss * 2u));
   };
 
@@ -229,6 +239,9 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   src.vc = (const unsigned char*)(v_cache + (PAGED ? 0 : b * kv_sb) + h * kv_sh) + (lane % LPR) * 16;
   src.kn = APPEND ? (const unsigned char*)(k_new + b * q_sb + h * q_sh) + g * 16 : nullptr;
   src.vn = APPEND ? (const unsigned char*)(v_new + b * q_sb + h * q_sh) + (lane % LPR) * 16 : nullptr;
+
+  const int first_block = LANES ? min(c0, S_cap - 1) >> pg.log2_tokens : 0;
+  if (LANES) blocks = load_block_lanes(pg, b, first_block);
 
   // The tail wavefront: a tree node per lane, from scalar loads, four nodes at a time as far as there are any (all sixteen at once
   // cost the smallest calls what they wait for: 2 x 64 heads of 58 keys, one node, D = 64, 5.2 us, 4.7 by fours; sixteen nodes
@@ -295,6 +308,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     lo = __builtin_bit_cast(std::remove_reference_t<decltype(lo)>, olo);
     hi = __builtin_bit_cast(std::remove_reference_t<decltype(hi)>, ohi);
   };
+  const int last_block = LANES ? (c1 - 1) >> pg.log2_tokens : 0;
+  if (LANES && is_tail && lane == 0 && blocks_outside(blocks, last_block)) set_status(status, b, SPEC_ST_BAD_BLOCK);
   // tiles of this wavefront: first and end (the streaming wavefronts take every SWAVES-th)
   const int ti_first = is_tail ? n_clean : wave;
   const int ti_end = is_tail ? n_tiles : n_clean;
@@ -519,8 +534,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   if (is_tail) {
     if (!bad_tree)
       for (int ti = ti_first; ti < ti_end; ++ti) tile_step(ti, ti + 1 < ti_end ? ti + 1 : -1, std::true_type{});
-    if (PAGED) {   // every block this segment reads must lie inside the pool (looked at last: nothing waits for these loads)
-      for (int j = (c0 >> pg.log2_tokens) + lane; j <= ((c1 - 1) >> pg.log2_tokens); j += 64) {
+    if (PAGED) {   // every block this segment reads must lie inside the pool (those not in the lanes looked at last: nothing waits)
+      for (int j = LANES ? first_block + 64 + lane : (c0 >> pg.log2_tokens) + lane; j <= (c1 - 1) >> pg.log2_tokens; j += 64) {
         const int e = pg.table[(long)b * pg.max_blocks + j];
         if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
       }

@@ -113,11 +113,12 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
   // request b for every row of the 64-row tile at k0 (rows clamped to the capacity or to the request's last
   // row stay inside the tile, hence inside its block). `ok`: the table entry lies inside the pool; one that
   // does not is replaced by a block of the pool.
+  BlockLanes blocks = {0, 0, 0ull};
   auto page_shift = [&](int b, int k0, bool* ok) -> long {
     const int j = __builtin_amdgcn_readfirstlane(min(k0, S_cap - 1) >> pg.log2_tokens);
-    const int e = pg.table[(long)b * pg.max_blocks + j];
-    *ok = e >= 0 && e < pg.n_blocks;
-    const int blk = min(max(e, 0), pg.n_blocks - 1);
+    const int l = block_lane(blocks, pg, b, j);
+    *ok = !((blocks.bad >> l) & 1ull);
+    const int blk = __builtin_amdgcn_readlane(blocks.block, l);
     return (long)blk * kv_sb * 2 - (long)((unsigned)(j << pg.log2_tokens) * cache_row_bytes);
   };
   auto issue_speculative = [&](u32x4 (&Kd)[NPT], u32x4 (&Vd)[NPT], const unsigned char* kbase, const unsigned char* vbase,
@@ -180,8 +181,10 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     // the tree words decides what the first wait leaves in flight (loads return in order): the tree words first, on the 2 x 2
     // shape the queries too (alternating builds on the same buffers: 145.8 -> 144.5 us on a ragged batch of
     // 8192-16384 keys, while the shapes with one key part per wavefront lose half a percent with the queries in front).
-    auto first_tiles = [&]() {
-      bool in_pool;   // entries past the request's end may hold anything: not judged here
+    const int first_block = PAGED ? min(c0, S_cap - 1) >> pg.log2_tokens : 0;
+    bool in_pool;
+    if (PAGED) blocks = load_block_lanes(pg, b, first_block);
+    auto first_tiles = [&]() {   // (entries past the request's end may hold anything: not judged here)
       issue_speculative(Kr[0], Vr[0], kc, vc, c0, PAGED ? page_shift(b, c0, &in_pool) : 0);
       issue_speculative(Kr[1], Vr[1], kc, vc, c0 + KT, PAGED ? page_shift(b, c0 + KT, &in_pool) : 0);
     };
@@ -267,10 +270,13 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     if (c0 >= len) return;
     const int c1 = min(c1_cap, len);
     const bool touches_tree = c1 > P;
-    // every block this segment reads must lie inside the pool: looked at last, so that nothing waits for these loads
+    // every block this segment reads must lie inside the pool; those past the first 64 are looked at last, so that nothing
+    // waits for their entries
+    const int last_block = PAGED ? (c1 - 1) >> pg.log2_tokens : 0;
+    if (PAGED && t == 0 && blocks_outside(blocks, last_block)) set_status(status, b, SPEC_ST_BAD_BLOCK);
     auto check_blocks = [&]() {
       if (PAGED) {
-        for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
+        for (int j = first_block + 64 + t; j <= last_block; j += NTHREADS) {
           const int e = pg.table[(long)b * pg.max_blocks + j];
           if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
         }
@@ -607,7 +613,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
       const int r = hv % (8 * n_qg), blk = hv / (8 * n_qg);
       hv = uniform((blk * 8 + r % 8) * n_qg + r / 8);
     }
-    if (heads_per_wg > 1) {   // several K/V heads per workgroup (host: one query group per head, no key split)
+    if (QW == 8 && heads_per_wg > 1) {   // several K/V heads per workgroup (host: one query group per head, no key split)
       hv *= heads_per_wg;
       segment(b, hv, 0, chunk_keys, -1, min(heads_per_wg, H_v - hv));
     } else {

@@ -122,11 +122,13 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
   const int v_xor = (((2 * (g & 1) + ((r16 & 3) >> 1)) ^ (v_row << 1)) << 4) | ((r16 & 1) << 3);
 
   const unsigned cache_row_bytes = (unsigned)kv_ss * 2u, new_row_bytes = (unsigned)n_sn * 2u;
+  // Paged: byte offset that, added to `row * cache_row_bytes`, gives the place of every logical row of the stage at k0.
+  BlockLanes blocks = {0, 0, 0ull};
   auto page_shift = [&](int b, int k0, bool* ok) -> long {
     const int j = __builtin_amdgcn_readfirstlane(min(k0, S_cap - 1) >> pg.log2_tokens);
-    const int e = pg.table[(long)b * pg.max_blocks + j];
-    *ok = e >= 0 && e < pg.n_blocks;
-    const int blk = min(max(e, 0), pg.n_blocks - 1);
+    const int l = block_lane(blocks, pg, b, j);
+    *ok = !((blocks.bad >> l) & 1ull);
+    const int blk = __builtin_amdgcn_readlane(blocks.block, l);
     return (long)blk * kv_sb * 2 - (long)((unsigned)(j << pg.log2_tokens) * cache_row_bytes);
   };
 
@@ -174,6 +176,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
         }
       }
     };
+    const int first_block = PAGED ? min(c0, S_cap - 1) >> pg.log2_tokens : 0;
+    if (PAGED) blocks = load_block_lanes(pg, b, first_block);
 #pragma unroll
     for (int s = 0; s < AHEAD; ++s) request(s, c0 + s * SK, std::integral_constant<int, 0>{}, 0, 0);
 
@@ -239,10 +243,13 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     }
     const int c1 = min(c1_cap, len);
     const bool touches_tree = c1 > P;
-    // every block this segment reads must lie inside the pool: looked at last, so that nothing waits for these loads
+    // every block this segment reads must lie inside the pool; those past the first 64 are looked at last, so that nothing
+    // waits for their entries
+    const int last_block = PAGED ? (c1 - 1) >> pg.log2_tokens : 0;
+    if (PAGED && t == 0 && blocks_outside(blocks, last_block)) set_status(status, b, SPEC_ST_BAD_BLOCK);
     auto check_blocks = [&]() {
       if (PAGED) {
-        for (int j = (c0 >> pg.log2_tokens) + t; j <= ((c1 - 1) >> pg.log2_tokens); j += NTHREADS) {
+        for (int j = first_block + 64 + t; j <= last_block; j += NTHREADS) {
           const int e = pg.table[(long)b * pg.max_blocks + j];
           if (e < 0 || e >= pg.n_blocks) set_status(status, b, SPEC_ST_BAD_BLOCK);
         }

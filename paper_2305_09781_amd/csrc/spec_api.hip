@@ -96,7 +96,6 @@ int compute_units() {
 AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
   AttnPlan p;
   p.balanced_wgs = 0;
-  p.balanced_tile = 0;
   p.contiguous = false;
   p.heads_per_wg = 1;
   p.m32 = false;
@@ -158,7 +157,6 @@ AttnPlan make_attn_plan(const spec_attn_desc_t& d, bool paged) {
     }
     if (wgs > 0) {
       p.balanced_wgs = wgs;
-      p.balanced_tile = tile;
       p.contiguous = !p.wide && wgs < 2 * groups;
       p.chunk_keys = 0;
       p.n_splits = (wgs + virtual_heads - 1) / virtual_heads + 1;   // a pair has at most this many chunks
@@ -433,7 +431,7 @@ static int tree_attention_impl(const spec_attn_desc_t* desc, const spec_kv_pages
   }
   if (e != hipSuccess) return SPEC_ERR_HIP;
   if (plan.n_splits > 1 || plan.balanced_wgs > 0) {
-    e = launch_attn_combine(d, plan, tree_parent, tree_depth, prefix_len, workspace, out, status, s);
+    e = launch_attn_combine(d, plan, prefix_len, workspace, out, status, s);
     if (e != hipSuccess) return SPEC_ERR_HIP;
   }
   return SPEC_OK;

@@ -21,7 +21,6 @@ struct AttnPlan {
   int chunk_keys;   // fixed chunks: keys per workgroup (multiple of 32)
   int n_splits;     // chunks covering max_prefix_len + N; balanced plan: partial slots per (request, head)
   int balanced_wgs; // > 0: balanced plan that aims at this many chunks (see balanced_deal), chunk_keys is 0
-  int balanced_tile;// keys per tile of the balanced deal (the tile of the kernel that runs the plan)
   bool contiguous;  // balanced plan as equal contiguous shares of all tiles (see contiguous_deal), few-query kernel only
   bool wide;        // bf16: the wide kernel runs the plan (several query tiles per K/V head, or k_new not laid out like q)
   int heads_per_wg; // wide kernel, whole key ranges: consecutive K/V heads of a request served by one workgroup
@@ -170,9 +169,8 @@ hipError_t launch_tree_attention_bf16_wide32(const spec_attn_desc_t& d, const At
                                              const int32_t* parent, const int32_t* depth, const int32_t* prefix_len,
                                              void* out, void* ws, int32_t* status, hipStream_t s,
                                              const Rope& rope = no_rope());
-hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, const int32_t* parent,
-                               const int32_t* depth, const int32_t* prefix_len, const void* ws, void* out,
-                               int32_t* status, hipStream_t s);
+hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, const int32_t* prefix_len, const void* ws,
+                               void* out, int32_t* status, hipStream_t s);
 hipError_t launch_expand_topk(int B, int F, int V, int logits_dtype, const void* logits, int k, const int32_t* child_slot,
                               int N, int32_t* tree_token, int32_t* status, hipStream_t s);
 hipError_t launch_tree_merge(int B, int M, int Nin, const int32_t* in_parent, const int32_t* in_token,
@@ -235,6 +233,17 @@ hipError_t launch_stochastic_walk(int B, int N, int V, int logits_dtype, const v
 template <bool BALANCED>
 __device__ __forceinline__ long partial_row(int b, int h, int slot, int B, int H, int N, int n_splits) {
   return BALANCED ? (((long)slot * B + b) * H + h) * N : (((long)b * H + h) * n_splits + slot) * N;
+}
+
+// What a partial says of itself, so that the merge needs neither the tree nor the deal: the sum of the chunk that ends its request
+// carries a sign (sums have none), which tells how many slots are filled, and a maximum of NaN (never a maximum: fmaxf drops NaN)
+// stands for a row with nothing to merge, whose "sum" says why.
+constexpr float PARTIAL_BAD_TREE = -0.f, PARTIAL_FINAL = -1.f;   // malformed tree; the only chunk, whose workgroup wrote the output
+__device__ __forceinline__ float partial_sum(float l, bool last) { return __builtin_copysignf(l, last ? -1.f : 1.f); }
+__device__ __forceinline__ bool partial_ends(float m, float l) { return m != m || (__float_as_int(l) < 0); }
+__device__ __forceinline__ void mark_partial(float* __restrict__ ws_ml, long row, float why) {
+  ws_ml[row * 2 + 0] = __int_as_float(0x7fc00000);
+  ws_ml[row * 2 + 1] = why;
 }
 
 // A workgroup-uniform value back in a scalar register. The compiler divides on the vector unit and leaves the quotient
@@ -485,21 +494,19 @@ __device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, in
 // workgroups in equal contiguous shares; a share that crosses from one pair into the next is two segments in a row. For the
 // few-query kernel, which runs one workgroup per compute unit, where there are fewer than two chunks per pair: whole
 // fractions of a pair would leave compute units idle (6 requests x 32 heads x 64 of 4500 keys, 192 pairs on 256 compute
-// units: 45.6 us, 51.3 in halves). `before`: tiles per head of the requests below b_before.
+// units: 45.6 us, 51.3 in halves).
 struct ContiguousDeal {
   long total;   // tiles over all requests and heads
   long share;   // tiles per workgroup (>= 1)
 };
 __device__ inline ContiguousDeal contiguous_deal(const int32_t* __restrict__ prefix_len, int B, int N, int H, int S_cap,
-                                                 int tile, int n_wg, int b_before = 0, long* before = nullptr) {
+                                                 int tile, int n_wg) {
   const int lane = threadIdx.x & 63;
-  long tiles = 0, low = 0;
+  long tiles = 0;
   for (int b0 = 0; b0 < B; b0 += 64) {
     const int v = b0 + lane < B ? request_tiles(prefix_len[b0 + lane], N, S_cap, tile) : 0;
     tiles += wave_sum_uniform(v);
-    if (before != nullptr) low += wave_sum_uniform(b0 + lane < b_before ? v : 0);
   }
-  if (before != nullptr) *before = low;
   ContiguousDeal r;
   r.total = tiles * H;
   r.share = max(1l, deal_div(r.total + n_wg - 1, n_wg));

@@ -566,6 +566,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
         if (n < N) out[b * q_sb + n * q_sn + h * q_sh + (i % D)] = __float2bfloat16(0.f);
       }
       if (h == 0 && qg == 0 && t == 0) set_status(status, b, SPEC_ST_BAD_TREE);
+    } else if (t < N) {
+      mark_partial(ws_ml, part_row + t, PARTIAL_BAD_TREE);
     }
     return;
   }
@@ -598,7 +600,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
       *(f32x4*)(ws_o + base * D + cg * 4) = o;
       if (cg == 0) {
         ws_ml[base * 2 + 0] = M;
-        ws_ml[base * 2 + 1] = l;
+        ws_ml[base * 2 + 1] = partial_sum(l, c1 == len);
       }
     }
   }
@@ -639,9 +641,11 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H, S_cap, TILE, work);
     if ((long)blockIdx.x >= deal.count) return;
     const DealChunk c = deal_find(prefix_len, B, N, H, 1, S_cap, TILE, deal, blockIdx.x);
-    if (c.n_tiles > 0)
+    if (c.n_tiles > 0) {
       segment(c.b, c.h, 0, c.tile0 * TILE, (c.tile0 + c.n_tiles) * TILE,
               c.chunks == 1 ? -1l : partial_row<true>(c.b, c.h, c.chunk, B, H, N, n_splits));
+      if (c.chunks == 1 && t < N) mark_partial(ws_ml, partial_row<true>(c.b, c.h, 0, B, H, N, n_splits) + t, PARTIAL_FINAL);
+    }
   }
 }
 

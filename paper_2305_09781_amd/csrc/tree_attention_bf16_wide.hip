@@ -132,6 +132,15 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     }
   };
 
+  // Slot `slot` of every query head that virtual head hv of request b serves: nothing to merge, for the reason given.
+  auto mark_rows = [&](int b, int hv, int slot, float why) {
+    const int h = uniform_div(hv, n_qg), qg = hv - h * n_qg, group = H / (H_v / n_qg);
+    for (int i = t; i < hpw * N; i += NTHREADS) {
+      const int hg = qg * hpw + i / N;
+      if (hg < group) mark_partial(ws_ml, partial_row<PLAN != PLAN_GRID>(b, h * group + hg, slot, B, H, N, n_splits) + i % N, why);
+    }
+  };
+
   // One segment: keys [c0, min(c1_cap, prefix_len + N)) of request b, virtual head hv = K/V head h and query
   // group qg (hpw of the H / H_kv query heads that share h). The result is the final output (slot < 0) or
   // float32 partials in slot `slot` of every query head served here.
@@ -261,6 +270,8 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
             if (hg < group) out[b * q_sb + n * q_sn + ((h + hi) * group + hg) * q_sh + (i % D)] = __float2bfloat16(0.f);
           }
         if (hv == 0 && t == 0) set_status(status, b, bit);
+      } else if (bit == SPEC_ST_BAD_TREE) {
+        mark_rows(b, hv, slot, PARTIAL_BAD_TREE);
       }
     };
     if (!cap_ok) {
@@ -596,7 +607,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
           for (int db = 0; db < DB; ++db) *(f32x4*)(ws_o + base * D + db * 16 + 4 * g) = O[nt][db];
           if (g == 0) {
             ws_ml[base * 2 + 0] = m_run[nt];
-            ws_ml[base * 2 + 1] = l_tot[nt];
+            ws_ml[base * 2 + 1] = partial_sum(l_tot[nt], c1 == len);
           }
         }
       }
@@ -624,7 +635,10 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, deal_wgs);
     if ((long)blockIdx.x >= deal.count) return;
     const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
-    if (c.n_tiles > 0) segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
+    if (c.n_tiles > 0) {
+      segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
+      if (c.chunks == 1) mark_rows(c.b, c.h, 0, PARTIAL_FINAL);
+    }
   }
 }
 

@@ -132,6 +132,15 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     return (long)blk * kv_sb * 2 - (long)((unsigned)(j << pg.log2_tokens) * cache_row_bytes);
   };
 
+  // Slot `slot` of every query head that virtual head hv of request b serves: nothing to merge, for the reason given.
+  auto mark_rows = [&](int b, int hv, int slot, float why) {
+    const int h = uniform_div(hv, n_qg), qg = hv - h * n_qg, group = H / (H_v / n_qg);
+    for (int i = t; i < hpw * N; i += NTHREADS) {
+      const int hg = qg * hpw + i / N;
+      if (hg < group) mark_partial(ws_ml, partial_row<PLAN != PLAN_GRID>(b, h * group + hg, slot, B, H, N, n_splits) + i % N, why);
+    }
+  };
+
   // One segment: keys [c0, min(c1_cap, prefix_len + N)) of request b, virtual head hv = K/V head h and query group
   // qg. The result is the final output (slot < 0) or float32 partials in slot `slot` of every query head served.
   auto segment = [&](const int b, const int hv, const int c0, const int c1_cap, const int slot) {
@@ -230,6 +239,8 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
           if (hz < group) out[b * q_sb + n * q_sn + (h * group + hz) * q_sh + (i % D)] = __float2bfloat16(0.f);
         }
         if (hv == 0 && t == 0) set_status(status, b, bit);
+      } else if (bit == SPEC_ST_BAD_TREE) {
+        mark_rows(b, hv, slot, PARTIAL_BAD_TREE);
       }
     };
     if (!cap_ok) {
@@ -502,7 +513,7 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
                 (f32x4){O[db][c4 * 4], O[db][c4 * 4 + 1], O[db][c4 * 4 + 2], O[db][c4 * 4 + 3]};
         if (hh == 0) {
           ws_ml[base * 2 + 0] = m_run;
-          ws_ml[base * 2 + 1] = l_tot;
+          ws_ml[base * 2 + 1] = partial_sum(l_tot, c1 == len);
         }
       }
     }
@@ -524,7 +535,10 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, deal_wgs);
     if ((long)blockIdx.x >= deal.count) return;
     const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
-    if (c.n_tiles > 0) segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk);
+    if (c.n_tiles > 0) {
+      segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk);
+      if (c.chunks == 1) mark_rows(c.b, c.h, 0, PARTIAL_FINAL);
+    }
   }
 }
 

@@ -84,7 +84,12 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   // query row qi of this workgroup: head in the group and node
   auto query_off = [&](int qi) { return b * q_sb + (long)(qi % N) * q_sn + (long)(hk * group + qi / N) * q_sh; };
   auto fail = [&](int bit) {   // a request without a result: zeros, from the workgroups that own final outputs
-    if (n_splits != 1) return;
+    if (n_splits != 1) {
+      const int qi = qg * QT + t;
+      if (bit == SPEC_ST_BAD_TREE && t < QT && qi < M)
+        mark_partial(ws_ml, partial_row<false>(b, hk * group + qi / N, split, B, H, N, n_splits) + qi % N, PARTIAL_BAD_TREE);
+      return;
+    }
     for (int i = t; i < QT * (D / 4); i += NTHREADS) {
       const int qi = qg * QT + i / (D / 4);
       if (qi < M) *(float4*)(out + query_off(qi) + (i % (D / 4)) * 4) = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -320,7 +325,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       *(float4*)(ws_o + slot * D + c) = o;
       if (c == 0) {
         ws_ml[slot * 2 + 0] = m_all;
-        ws_ml[slot * 2 + 1] = l;
+        ws_ml[slot * 2 + 1] = partial_sum(l, c1 == len);
       }
     }
   }
@@ -328,38 +333,32 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 
 // Merge of the partials of one (request, head): out = sum_s O_s 2^(m_s - M) / sum_s l_s 2^(m_s - M),
 // M = max_s m_s. grid = (H, B, ceil(N * D/4 / 256)), 256 threads; a thread owns 4 consecutive d of one
-// query. A pair has a block of N rows in each of `slots` slots; how many are filled follows from the plan: fixed
-// chunks (chunk_keys > 0) or the balanced deal (bal_wgs > 0). Also the place where a malformed request gets its defined
-// result (zeros) and its status bit. Bound by reading the filled slots once (32 requests x 64 heads x 16 nodes, two or
-// three slots each, 45 MB) and, under the balanced plans, by the deal that says how many those are: 18.9 us with all four
-// wavefronts of a workgroup working it out, behind the tree check, 13.8 with one beside it, 8.6 if it cost nothing; two
-// pieces per thread 13.5 and slower elsewhere (4 requests of 8192 to 16384 keys 6.1 -> 6.8), four spill.
+// query. A pair has a block of N rows in each of `slots` slots, filled from 0; which is the last, whether the tree was malformed
+// and whether the output is there already, the partials themselves say (see partial_sum). Also the place where a malformed
+// request gets its defined result (zeros) and its status bit. Bound by its launch and one trip to memory, and in large batches by
+// reading the filled slots once. (With a tree check, two barriers and under the balanced plans the deal in front of the merge: 32
+// layers of one request, 32 heads, 1024 keys, a pass 487 us, 476 now; 4 x 32 heads of 8192 to 16384 keys 137.3, 136.3.)
 template <bool BF16, bool BAL, int CH>   // CH: partial slots fetched together
 __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restrict__ ws_o, const float* __restrict__ ws_ml,
-                                                           const int32_t* __restrict__ parent,
-                                                           const int32_t* __restrict__ depth,
                                                            const int32_t* __restrict__ prefix_len, void* __restrict__ out,
-                                                           int32_t* status, int B, int N, int H, int H_kv, int n_qg,
-                                                           int D, int S_cap, int chunk_keys, int slots,
-                                                           int bal_wgs, int bal_tile, bool contiguous, long q_sb,
-                                                           long q_sn, long q_sh) {
-  __shared__ int s_flag, s_slots;
+                                                           int32_t* status, int B, int N, int H, int D, int S_cap, int chunk_keys,
+                                                           int slots, long q_sb, long q_sn, long q_sh) {
   const int h = blockIdx.x, b = blockIdx.y, t = threadIdx.x;
   const int CG = D / 4;
   const int idx = blockIdx.z * 256 + t;
-  const bool active = idx < N * CG;
-  const int n = active ? idx / CG : 0, cg = active ? idx % CG : 0;
+  if (idx >= N * CG) return;
+  const int n = idx / CG, cg = idx % CG;
   const long base = partial_row<BAL>(b, h, 0, B, H, N, slots) + n, slot_rows = BAL ? (long)B * H * N : N;
   // The first slots are fetched before anything is known about the request (every slot exists in the
-  // workspace, whatever it holds), so that the reads overlap the tree check and the slot count below: of fixed chunks
-  // up to eight, which a request near the stated maximum has filled (1 request of 8000 keys on 8 K/V heads, 31 slots: 23.3
-  // -> 21.9 us with attention; 5 slots: 13.6 -> 13.5), of a balanced deal two.
+  // workspace, whatever it holds): of fixed chunks up to eight, which a request near the stated maximum has filled (1 request of
+  // 8000 keys on 8 K/V heads, 31 slots: 23.3 -> 21.9 us with attention; 5 slots: 13.6 -> 13.5), of a balanced deal two, as most
+  // pairs have no more (a third is 17 MB for 32 requests x 64 heads x 16 nodes).
   float m_s[CH], l_s[CH];
   float4 o_s[CH];
-  auto fetch = [&](int s0, int from, int to) {
+  auto fetch = [&](int s0, int take) {
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      if (!BAL || (j >= from && j < to && s0 + j < slots)) {
+      if (j < take) {
         const long row = base + min(s0 + j, slots - 1) * slot_rows;
         const float2 ml = *(const float2*)(ws_ml + row * 2);
         m_s[j] = ml.x;
@@ -368,59 +367,55 @@ __global__ void __launch_bounds__(256) attn_combine_kernel(const float* __restri
       }
     }
   };
-  const int early = BAL ? 2 : CH;
-  fetch(0, 0, early);
+  int take = BAL ? 2 : CH;
+  fetch(0, take);
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
-  // How many slots of the pair are filled. The balanced plans' deal is some hundred instructions: one wavefront of the
-  // workgroup, not all four, while two others check the tree.
-  if (BAL && uniform(t >> 6) == 3) {
-    int filled = 0;
-    if (cap_ok) {
-      // the deal is over (request, virtual head) pairs: virtual head = K/V head and query group
-      const int tb = request_tiles(P, N, S_cap, bal_tile);
-      if (contiguous) {   // few-query kernel: one query head per pair
-        long before;
-        const ContiguousDeal deal = contiguous_deal(prefix_len, B, N, H, S_cap, bal_tile, bal_wgs, b, &before);
-        const long pair_start = before * H + (long)h * tb;
-        filled = (int)(deal_div(pair_start + tb - 1, deal.share) - deal_div(pair_start, deal.share)) + 1;
-      } else {
-        const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_kv * n_qg, S_cap, bal_tile, bal_wgs);
-        const int chunks = deal_chunks(tb, deal.share);
-        filled = chunks == 1 ? 0 : deal_chunks(tb, deal_chunk_tiles(tb, chunks));   // 0: the attention kernel wrote the final output
-      }
-    }
-    if ((t & 63) == 0) s_slots = filled;
-  }
-  const bool valid = tree_is_valid(parent + (long)b * N, depth + (long)b * N, N, &s_flag) && cap_ok;
-  if (!valid && h == 0 && blockIdx.z == 0 && t == 0) set_status(status, b, cap_ok ? SPEC_ST_BAD_TREE : SPEC_ST_CAPACITY);
-  int ns = 0;
-  if (valid) {
-    ns = BAL ? uniform(s_slots) : uniform(min(slots, (P + N + chunk_keys - 1) / chunk_keys));
-    if (BAL && ns == 0) return;
-  }
-  if (!active) return;
-  // online merge over chunks of CH slots (slots at and beyond ns hold nothing meaningful: skipped)
+  // fixed chunks: known from the length; balanced: until a slot says that it is the last
+  const int ns = !cap_ok ? 0 : BAL ? slots : min(slots, uniform_div(P + N + chunk_keys - 1, chunk_keys));
+  int bit = cap_ok ? 0 : SPEC_ST_CAPACITY;
+  // online merge over groups of slots (those behind the last one hold nothing meaningful)
   float M = -INFINITY, l = 0.f;
   float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < ns || s0 == 0; s0 += CH) {
-    if (BAL || s0 > 0) fetch(s0, s0 == 0 ? early : 0, ns - s0);
+  for (int s0 = 0; s0 < ns;) {
+    if (s0 > 0) fetch(s0, take);
+    int filled = min(take, ns - s0);
+    bool last = false;
+#pragma unroll
+    for (int j = 0; j < CH; ++j)
+      if (j < filled && uniform((int)(BAL ? partial_ends(m_s[j], l_s[j]) : m_s[j] != m_s[j])) != 0) {   // the same for a pair's rows
+        if (uniform((int)(m_s[j] != m_s[j])) != 0) {
+          if (BAL && l_s[j] == PARTIAL_FINAL) return;
+          bit = SPEC_ST_BAD_TREE;
+        }
+        filled = j + 1;   // (the slots behind it are not looked at any more)
+        last = true;
+      }
+    if (bit != 0) break;
     float Mc = M;
 #pragma unroll
     for (int j = 0; j < CH; ++j)
-      if (s0 + j < ns) Mc = fmaxf(Mc, m_s[j]);
+      if (j < filled) Mc = fmaxf(Mc, m_s[j]);
     const float keep = (M == -INFINITY) ? 0.f : exp2f(M - Mc);   // Mc = -inf only while nothing carried mass
     l *= keep;
     o.x *= keep; o.y *= keep; o.z *= keep; o.w *= keep;
 #pragma unroll
     for (int j = 0; j < CH; ++j) {
-      if (s0 + j < ns && m_s[j] != -INFINITY) {   // an all-masked partial carries nothing
+      if (j < filled && m_s[j] != -INFINITY) {   // an all-masked partial carries nothing
         const float w = exp2f(m_s[j] - Mc);
-        l = fmaf(l_s[j], w, l);
+        l = fmaf(fabsf(l_s[j]), w, l);
         o.x = fmaf(o_s[j].x, w, o.x); o.y = fmaf(o_s[j].y, w, o.y); o.z = fmaf(o_s[j].z, w, o.z); o.w = fmaf(o_s[j].w, w, o.w);
       }
     }
     M = Mc;
+    if (last) break;
+    s0 += take;
+    if (BAL && s0 >= 4) take = CH;
+  }
+  if (bit != 0) {
+    if (h == 0 && idx == 0) set_status(status, b, bit);
+    l = 0.f;
+    o = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   const float inv = (l > 0.f) ? 1.f / l : 0.f;
   o.x *= inv; o.y *= inv; o.z *= inv; o.w *= inv;
@@ -467,19 +462,15 @@ hipError_t launch_tree_attention_f32(const spec_attn_desc_t& d, const AttnPlan& 
   return hipGetLastError();
 }
 
-hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, const int32_t* parent,
-                               const int32_t* depth, const int32_t* prefix_len, const void* ws, void* out,
-                               int32_t* status, hipStream_t s) {
+hipError_t launch_attn_combine(const spec_attn_desc_t& d, const AttnPlan& plan, const int32_t* prefix_len, const void* ws,
+                               void* out, int32_t* status, hipStream_t s) {
   const float* ws_o = (const float*)((const char*)ws + plan.ws_o_off);
   const float* ws_ml = (const float*)((const char*)ws + plan.ws_ml_off);
   const int items = d.N * (d.D / 4);
-  const QueryGroups qg = attn_query_groups(d);
-  const int n_qg = d.dtype == SPEC_BF16 ? qg.n_qgroups : 1;
   dim3 grid(d.H, d.B, (items + 255) / 256);
-#define SPEC_COMBINE(BF, BL, CH)                                                                                            \
-  hipLaunchKernelGGL((attn_combine_kernel<BF, BL, CH>), grid, dim3(256), 0, s, ws_o, ws_ml, parent, depth, prefix_len, out,   \
-                     status, d.B, d.N, d.H, d.H_kv, n_qg, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, plan.balanced_wgs,    \
-                     plan.balanced_tile, plan.contiguous, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h)
+#define SPEC_COMBINE(BF, BL, CH)                                                                                              \
+  hipLaunchKernelGGL((attn_combine_kernel<BF, BL, CH>), grid, dim3(256), 0, s, ws_o, ws_ml, prefix_len, out, status, d.B, d.N, \
+                     d.H, d.D, d.S_cap, plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h)
   const bool many = plan.n_splits > 4;
   if (plan.balanced_wgs > 0) { SPEC_COMBINE(true, true, 4); }   // (bf16 only)
   else if (d.dtype == SPEC_BF16 && many) { SPEC_COMBINE(true, false, 8); }

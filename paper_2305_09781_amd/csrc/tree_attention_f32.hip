@@ -23,14 +23,17 @@
 // v_exp_f32: probabilities below 2^-126 of the largest are 0 instead of subnormal.
 //
 // What bounds it: float32 MFMA rate and the stream of K/V are close to each other (16 keys x 16 queries x 128
-// dimensions are 2048 cycles of one SIMD for 16 KB). Measured on 4 requests x 32 heads x 128, 300 to 1000 keys, trees of
-// 24 (95 MB): 37.6 us a layer, append and merge launch included (2.5 TB/s, 27 TFLOP/s), against
-// 304 us for the kernel before it, which read K uncoalesced per (query, key) and ran the softmax on N threads. Keeping the
-// queries in LDS to pay for a second K/V register set was slower: it spills at two query tiles (50 us) and gains nothing at
-// one.
+// dimensions are 2048 cycles of one SIMD for 16 KB); small calls, one trip to memory after the other. So the tree words are requested
+// before the tiles and the masks built by one wavefront (a parent chain walked after two barriers and a dependent load before), new rows go
+// to the cache from the registers of the tile that uses them (read a second time before), the scores wait for K and the queries but not
+// for V, and two tiles are on their way where the registers allow it. Measured, us a layer, before / now: 4 requests x 32 heads x 128, 300
+// to 1000 keys, trees of 24 (95 MB), append and merge launch included 37.2 / 34.1 (2.8 TB/s, 30 TFLOP/s; 304 for the kernel that read K
+// uncoalesced per (query, key) and ran the softmax on N threads); 1 x 4 heads x 64, 128 keys, trees of 8, 10.6 / 10.2. Keeping the
+// queries in LDS to pay for a second K/V register set at two query tiles was slower: it spills (50 us).
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "spec_internal.h"
 
@@ -60,9 +63,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   constexpr int OROW = D + 4;      // floats per merged output row in LDS (+4: rows start on different banks)
   __shared__ float s_o[F32_WAVES][QT][OROW];
   __shared__ float s_m[F32_WAVES][QT], s_l[F32_WAVES][QT];
-  __shared__ unsigned long long s_anc[SPEC_MAX_TREE_NODES][2];
-  __shared__ int s_parent[SPEC_MAX_TREE_NODES];
-  __shared__ int s_flag;
+  __shared__ TreeLds s_tree;
 
   // The query groups of one chunk read the same K/V: they are numbered eight apart, which puts them on one XCD (
   // workgroups go to the eight XCDs round-robin), close in time, so that the repeats can be hits of its L2.
@@ -76,6 +77,8 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   const int t = threadIdx.x, lane = t & 63, r16 = lane & 15, g = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
 
+  // the tree words first: what waits for them then leaves the tiles in flight
+  const int my_parent = parent[(long)b * N + min(t, N - 1)], my_depth = depth[(long)b * N + min(t, N - 1)];
   const int P = prefix_len[b];
   const bool cap_ok = (P >= 0) && (P <= S_cap - N);
   const int len = P + N;
@@ -107,7 +110,9 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   const float* kn = APPEND ? k_new + b * n_sb + hk * n_sh : nullptr;
   const float* vn = APPEND ? v_new + b * n_sb + hk * n_sh : nullptr;
   const int n_tiles = (c1 - c0 + F32_TK - 1) / F32_TK;
-  float4 kf[KJ], vf[4][VH];
+  // Two tiles are on their way where the registers allow it (not at D = 128 with two query tiles).
+  constexpr int SETS = D == 128 && NT == 2 ? 1 : 2;
+  float4 kf[SETS][KJ], vf[SETS][4][VH];
   // A tile starts at a multiple of 16 rows, so it lies inside one block of a paged cache; rows past the chunk repeat its
   // last one (their scores are masked).
   auto tile_base = [&](int k0) {
@@ -116,13 +121,13 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     if (!blk_ok && lane == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);
     return off;
   };
-  auto load_k = [&](int k0, long base) {
+  auto load_k = [&](float4 (&kf)[KJ], int k0, long base) {
     const int row = min(k0 + r16, c1 - 1);
     const float* p = (APPEND && row >= P) ? kn + (long)(row - P) * n_sn : k_cache + base + (long)row * kv_ss;
 #pragma unroll
     for (int j = 0; j < KJ; ++j) kf[j] = *(const float4*)(p + (4 * j + g) * 4);
   };
-  auto load_v = [&](int k0, long base) {
+  auto load_v = [&](float4 (&vf)[4][VH], int k0, long base) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = min(k0 + 4 * g + i, c1 - 1);
@@ -132,11 +137,11 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     }
   };
   int ti = wave;
-  if (ti < n_tiles) {
-    const long base = tile_base(c0 + ti * F32_TK);
-    load_k(c0 + ti * F32_TK, base);
-    load_v(c0 + ti * F32_TK, base);
-  }
+  // The first tile's K, the queries, its V (the scores need the first two only), then the second tile. (Unconditional, so that the
+  // compiler knows how many loads stand behind each: a wavefront with fewer tiles takes its first again, or the chunk's last.)
+  const int first = c0 + min(ti, n_tiles - 1) * F32_TK, second = ti + F32_WAVES < n_tiles ? first + F32_WAVES * F32_TK : first;
+  const long first_base = tile_base(first);
+  load_k(kf[0], first, first_base);
   float4 qf[NT][KJ];
   int node[NT];
 #pragma unroll
@@ -147,50 +152,43 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 #pragma unroll
     for (int j = 0; j < KJ; ++j) qf[nt][j] = *(const float4*)(p + (4 * j + g) * 4);
   }
+  load_v(vf[0], first, first_base);
+  if constexpr (SETS == 2) {
+    const long base = tile_base(second);
+    load_k(kf[1], second, base);
+    load_v(vf[1], second, base);
+  }
   const bool touches_tree = c1 > P;
   // one workgroup per request owns the final outputs' validity: every workgroup of a single chunk checks the tree; with
   // several chunks only those that reach it do (the combine step gives a malformed request its zeros)
   if (touches_tree) {
-    if (APPEND && qg == 0) {   // the chunk's new rows go to the cache
-      const int r0 = max(P, c0);
-      for (int i = t; i < (c1 - r0) * (D / 4); i += NTHREADS) {
-        const int row = r0 + i / (D / 4), c = (i % (D / 4)) * 4;
-        bool blk_ok;
-        const long dst = cache_row_offset(pg, b, row, kv_sb, kv_ss, &blk_ok) + hk * kv_sh + c;
-        if (!blk_ok && c == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);   // a row of a block outside the pool is not written
-        const float4 kk = *(const float4*)(kn + (long)(row - P) * n_sn + c), vv = *(const float4*)(vn + (long)(row - P) * n_sn + c);
-        if (blk_ok) {
-          *(float4*)(k_cache + dst) = kk;
-          *(float4*)(v_cache + dst) = vv;
+    if (t < N) {
+      s_tree.parent[t] = my_parent;
+      s_tree.depth[t] = my_depth;
+    }
+    f32_lds_barrier();
+    if (wave == 0) {
+      const bool bad = tree_masks_by_wave(s_tree, N, lane, my_parent, my_depth);
+      if (lane == 0) s_tree.bad[0] = bad;
+    }
+    f32_lds_barrier();
+    if (s_tree.bad[0]) {
+      if (APPEND && qg == 0) {   // the chunk's new rows go to the cache all the same
+        const int r0 = max(P, c0);
+        for (int i = t; i < (c1 - r0) * (D / 4); i += NTHREADS) {
+          const int row = r0 + i / (D / 4), c = (i % (D / 4)) * 4;
+          bool blk_ok;
+          const long dst = cache_row_offset(pg, b, row, kv_sb, kv_ss, &blk_ok) + hk * kv_sh + c;
+          if (!blk_ok && c == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);
+          if (blk_ok) {
+            *(float4*)(k_cache + dst) = *(const float4*)(kn + (long)(row - P) * n_sn + c);
+            *(float4*)(v_cache + dst) = *(const float4*)(vn + (long)(row - P) * n_sn + c);
+          }
         }
       }
-    }
-    int my_parent = -1, my_depth = 0;
-    if (t < N) {
-      my_parent = parent[(long)b * N + t];
-      my_depth = depth[(long)b * N + t];
-      s_parent[t] = my_parent;
-    }
-    if (t == 0) s_flag = 0;
-    f32_lds_barrier();
-    if (t < N) {
-      bool ok = t == 0 ? (my_parent == -1 && my_depth == 0) : (my_parent >= 0 && my_parent < t);
-      if (ok && t > 0) ok = my_depth == depth[(long)b * N + my_parent] + 1;
-      if (!ok) atomicOr(&s_flag, 1);
-    }
-    f32_lds_barrier();
-    if (s_flag != 0) {
       fail(SPEC_ST_BAD_TREE);
       return;
     }
-    if (t < N) {   // ancestor-or-self bitmask of every node: walk up the parent chain (parents have smaller indices)
-      unsigned long long lo = 0, hi = 0;
-      for (int u = t; u >= 0; u = s_parent[u])
-        if (u < 64) lo |= 1ull << u; else hi |= 1ull << (u - 64);
-      s_anc[t][0] = lo;
-      s_anc[t][1] = hi;
-    }
-    f32_lds_barrier();
   }
 
   f32x4 O[NT][VH * 4];
@@ -203,14 +201,25 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     for (int x = 0; x < VH * 4; ++x) O[nt][x] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
 
-  // ---- tiles of this wavefront. The next tile's K is requested when this tile's scores are done, its V when this
-  // tile's output products are: each load has the other product's time to arrive.
-  while (ti < n_tiles) {
+  // ---- tiles of this wavefront. The K of the tile that takes this one's registers is requested when this tile's scores are done,
+  // its V when this tile's output products are. With and without a request are two bodies: behind a branch around it the compiler
+  // would wait for more than it has to.
+  auto step = [&](float4 (&kf)[KJ], float4 (&vf)[4][VH], const int ti, auto refill_tag) {
+    constexpr bool REFILL = decltype(refill_tag)::value;
     const int k0 = c0 + ti * F32_TK;
-    const int next = ti + F32_WAVES;
-    const bool more = next < n_tiles;
-    const int k1 = c0 + (more ? next : ti) * F32_TK;
-    const long base1 = tile_base(k1);
+    const int k1 = c0 + (REFILL ? ti + SETS * F32_WAVES : ti) * F32_TK;
+    const long base1 = REFILL ? tile_base(k1) : 0;
+    const bool masked = k0 + F32_TK > min(P, c1);
+    // New rows go to the cache from the tile's registers (a row of a block outside the pool is not written).
+    bool dst_ok = false;
+    const long dst = APPEND && masked && qg == 0 ? cache_row_offset(pg, b, k0, kv_sb, kv_ss, &dst_ok) - k0 * kv_ss + hk * kv_sh : 0;
+    if (APPEND && dst_ok) {
+      const int row = k0 + r16;
+      if (row >= P && row < c1) {
+#pragma unroll
+        for (int j = 0; j < KJ; ++j) *(float4*)(k_cache + dst + (long)row * kv_ss + (4 * j + g) * 4) = kf[j];
+      }
+    }
     f32x4 sc[NT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {   // (one query tile after the other: eight sums at once do not fit the registers)
@@ -224,9 +233,8 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       }
       sc[nt] = (part[0] + part[1]) + (part[2] + part[3]);
     }
-    if (more) load_k(k1, base1);
+    if (REFILL) load_k(kf, k1, base1);
     float p[NT][4];
-    const bool masked = k0 + F32_TK > min(P, c1);
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
       float s[4];
@@ -237,7 +245,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
         for (int i = 0; i < 4; ++i) {
           const int key = k0 + 4 * g + i, rel = key - P;
           bool vis = key < c1;
-          if (vis && rel >= 0) vis = (s_anc[node[nt]][rel >> 6] >> (rel & 63)) & 1ull;
+          if (vis && rel >= 0) vis = (s_tree.anc[node[nt]][rel >> 6] >> (rel & 63)) & 1ull;
           if (!vis) s[i] = -INFINITY;
         }
       }
@@ -259,6 +267,16 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       for (int i = 0; i < 4; ++i) p[nt][i] = __builtin_amdgcn_exp2f(s[i] - m_use);
       l_run[nt] += (p[nt][0] + p[nt][1]) + (p[nt][2] + p[nt][3]);
     }
+    if (APPEND && dst_ok) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int row = k0 + 4 * g + i;
+        if (row >= P && row < c1) {
+#pragma unroll
+          for (int hv = 0; hv < VH; ++hv) *(float4*)(v_cache + dst + (long)row * kv_ss + r16 * 4 + 64 * hv) = vf[i][hv];
+        }
+      }
+    }
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -270,8 +288,27 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
           for (int nt = 0; nt < NT; ++nt)
             O[nt][hv * 4 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], p[nt][i], O[nt][hv * 4 + e], 0, 0, 0);
       }
-    if (more) load_v(k1, base1);
-    ti = next;
+    if (REFILL) load_v(vf, k1, base1);
+  };
+  constexpr std::true_type REFILL;
+  constexpr std::false_type LAST;
+  constexpr int W = F32_WAVES;
+  if constexpr (SETS == 1) {
+    for (; ti + W < n_tiles; ti += W) step(kf[0], vf[0], ti, REFILL);
+    if (ti < n_tiles) step(kf[0], vf[0], ti, LAST);
+  } else {
+    for (; ti + 3 * W < n_tiles; ti += 2 * W) {
+      step(kf[0], vf[0], ti, REFILL);
+      step(kf[1], vf[1], ti + W, REFILL);
+    }
+    if (ti + 2 * W < n_tiles) {   // three left
+      step(kf[0], vf[0], ti, REFILL);
+      step(kf[1], vf[1], ti + W, LAST);
+      step(kf[0], vf[0], ti + 2 * W, LAST);
+    } else {
+      if (ti < n_tiles) step(kf[0], vf[0], ti, LAST);
+      if (ti + W < n_tiles) step(kf[1], vf[1], ti + W, LAST);
+    }
   }
 
   // ---- merge of the four wavefronts: each scales its state to the common maximum, then all threads add the rows

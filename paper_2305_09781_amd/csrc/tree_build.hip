@@ -13,6 +13,7 @@
 namespace spec {
 
 constexpr int TOPK_THREADS = 1024;
+static_assert(SPEC_MAX_TOPK <= TOPK_THREADS, "a thread per pick");
 constexpr int TOPK_U = 8;        // groups a thread requests before it uses any
 
 // ---------------------------------------------------------------------------------------------
@@ -23,7 +24,8 @@ constexpr int TOPK_U = 8;        // groups a thread requests before it uses any
 //
 // What bounds it: one workgroup's latency, a launch, one trip to memory for 16 bytes x 8 per thread and two reductions. Eight
 // steps of 16 to 48 rows of 32000 float32 and the merge behind them: 58.6 us with a key and a 64-bit comparison per element,
-// 50.2 with one comparison per group; 11 to 33 rows of 93776: 93 and 71.
+// 49.6 with one comparison per group, 44.9 with reductions in register moves (exchanges through LDS before) and the slots requested
+// with the row; 11 to 33 rows of 93776: 93 and 71 with the first two.
 // VEC: 16 bytes of elements, from whatever element a row starts at; the last group ends with the row, and what it shares
 // with the group before it counts there (2 rows of 22115 float32: 6.1 us by single elements, 5.5). Rows of less: one.
 // ---------------------------------------------------------------------------------------------
@@ -33,13 +35,27 @@ __device__ __forceinline__ unsigned long long topk_key(float x, int i) {
   const unsigned ord = u ^ ((unsigned)((int)u >> 31) | 0x80000000u);
   return ((unsigned long long)ord << 32) | (unsigned)~i;
 }
+// Largest key of a wavefront (LANES 64) or of its first 16 lanes, in register moves: row shifts, then the last lane of each row of
+// 16 into the rows after it (0 where there is no source, which is no key). Every lane must be active; the result is uniform.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ unsigned long long max_moved(unsigned long long k) {
+  const unsigned lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)k, CTRL, ROWS, 0xf, false);
+  const unsigned hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(k >> 32), CTRL, ROWS, 0xf, false);
+  const unsigned long long v = ((unsigned long long)hi << 32) | lo;
+  return v > k ? v : k;
+}
+template <int LANES>
 __device__ __forceinline__ unsigned long long wave_max_key(unsigned long long k) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    const unsigned long long v = __shfl_xor(k, o);
-    if (v > k) k = v;
+  k = max_moved<0x111, 0xf>(k);   // row_shr:1, 2, 4, 8
+  k = max_moved<0x112, 0xf>(k);
+  k = max_moved<0x114, 0xf>(k);
+  k = max_moved<0x118, 0xf>(k);
+  if (LANES == 64) {
+    k = max_moved<0x142, 0xa>(k);   // row_bcast:15 into rows 1 and 3
+    k = max_moved<0x143, 0xc>(k);   // row_bcast:31 into rows 2 and 3
   }
-  return k;
+  const unsigned lo = __builtin_amdgcn_readlane((unsigned)k, LANES - 1), hi = __builtin_amdgcn_readlane((unsigned)(k >> 32), LANES - 1);
+  return ((unsigned long long)hi << 32) | lo;
 }
 
 template <bool BF16, int VEC, bool ODD>   // ODD: V is no multiple of VEC, or the rows are not 16-byte aligned
@@ -50,6 +66,8 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
   const int row = blockIdx.x, b = row / F, f = row % F, t = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6), lane = t & 63;
   const long base = (long)row * V;
+  // the slots first, one per thread: asked for at the pick they were a trip to memory of their own at the end of the launch
+  const int my_slot = t < k ? child_slot[(long)f * k + t] : 0;
   const int n_groups = (V + VEC - 1) / VEC;
   auto start = [&](int group) { return ODD ? min(group * VEC, V - VEC) : group * VEC; };
   typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
@@ -131,14 +149,15 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
       }
     }
   }
-  unsigned long long wave_best = wave_max_key(mine);
+  unsigned long long wave_best = wave_max_key<64>(mine);
   for (int j = 0; j < k; ++j) {
     if (lane == 0) s_best[j & 1][wave] = wave_best;
     __syncthreads();
-    const unsigned long long best = wave_max_key(lane < TOPK_THREADS / 64 ? s_best[j & 1][lane] : 0);
+    static_assert(TOPK_THREADS / 64 == 16, "one row of lanes holds the wavefronts' keys");
+    const unsigned long long best = wave_max_key<16>(s_best[j & 1][lane & 15]);
     const int pick = best == 0 ? -1 : (int)~(unsigned)best;
-    if (t == 0) {
-      const int slot = child_slot[f * k + j];
+    if (t == j) {
+      const int slot = my_slot;
       if (slot >= 0 && slot < N) tree_token[(long)b * N + slot] = pick;   // nothing left but NaN: -1, a padding node
       else set_status(status, b, SPEC_ST_BAD_TREE);
     }
@@ -154,9 +173,9 @@ __global__ void __launch_bounds__(TOPK_THREADS) expand_topk_kernel(const void* _
           if (key < best && key > next) next = key;
         }
       }
-      next = wave_max_key(next);
+      next = wave_max_key<64>(next);
       if (t == owner) mine = next;
-      wave_best = wave_max_key(mine);
+      wave_best = wave_max_key<64>(mine);
     }
   }
 }

@@ -32,6 +32,22 @@ def test_topk_row_lengths_and_alignments(spec, V, k, dt, offset):
     assert np.array_equal(tok.cpu().numpy(), want)
 
 
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+def test_topk_finds_the_largest_in_every_lane(spec, dt):
+    """One row per thread of a workgroup, whose largest element that thread owns; the second largest lies with its neighbour."""
+    vec, F = (4, 1024) if dt == "f32" else (8, 1024)
+    x = torch.zeros((1, F, 1024 * vec), dtype=torch.float32)
+    f = torch.arange(F)
+    x[0, f, f * vec + f % vec] = 9.0
+    x[0, f, (f * vec + vec) % (1024 * vec)] = 8.0
+    x = x.to(torch.bfloat16 if dt == "bf16" else torch.float32)
+    for f0 in range(0, F, 64):
+        tok = torch.full((1, 128), -5, dtype=torch.int32, device=DEV)
+        spec.spec_tree_expand_topk(x[:, f0:f0 + 64].contiguous().to(DEV), 2, torch.arange(128, dtype=torch.int32, device=DEV).view(64, 2), tok)
+        n = np.arange(f0, f0 + 64)
+        assert np.array_equal(tok.cpu().numpy().reshape(64, 2), np.stack([n * vec + n % vec, (n * vec + vec) % (1024 * vec)], 1))
+
+
 def test_topk_zeros_infinities_and_nan(spec):
     x = torch.full((1, 4, 12), -1.0)
     x[0, 0, 3], x[0, 0, 5] = 0.0, -0.0                    # equal: the lower id first

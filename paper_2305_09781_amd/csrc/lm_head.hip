@@ -17,13 +17,13 @@
 // (one per workgroup).
 //
 // What bounds it: the stream of W. Nothing but these loads takes 45.3 us for 32000 x 4096 (5.8 TB/s), 52.7 without the
-// non-temporal hint. Every workgroup reads the same k of rows that lie 8 KB apart; starting each workgroup at another k
-// takes 39.5, but then equal rows of W in different workgroups would be summed in different orders and could differ in the
-// last bit, which the arg-max rule (lowest token among equal logits) does not allow. Measured at 32000 x 4096 with six weight
-// matrices in turn (1.6 GB: W comes from HBM every time), arg-max only / with logits and statistics and the merge, us (before,
-// in the same run: W straight into registers, 16 rows per wavefront, `hidden` through LDS): 1 row 54.7 / 54.8 (55.8 / 56.8),
-// 16 rows 53.2 / 55.7 (55.5 / 58.0), 64 rows 53.2 / 56.2 (58.2 / 61.8), 128 rows 57.4 / 61.4 (70.0 / 75.7), 256 rows
-// 83.8 / 88.8 (124 / 137). Up to 32 rows of K = 256 to 512 over 4000 to 8000 vocabulary rows take up to 4 % (0.3 us) longer
+// non-temporal hint, when every workgroup reads the same k of rows that lie 8 KB apart. Starting each workgroup at another k
+// takes 39.5, but equal rows of W in different workgroups must not be summed in different orders: they could differ in the last bit,
+// which the arg-max rule (lowest token among equal logits) does not allow. A logit is therefore cut into two sums, and half of the
+// workgroups take them in the other order (see APART and the rule at its launch). Measured at 32000 x 4096 with six weight
+// matrices in turn (1.6 GB: W comes from HBM every time), with logits and statistics and the merge, us, in step / apart: 16 rows
+// 54.8 / 48.2, 128 rows 61.5 / 57.3, 250 rows 87.8 / 87.3. Of 4.1 million logits 1109 (in step) and 1084 (apart) are not the nearest
+// bfloat16 to the sum in float64. Up to 32 rows of K = 256 to 512 over 4000 to 8000 vocabulary rows take up to 4 % (0.3 us) longer
 // than they did.
 // The order of a logit's sum is a matter of V and K alone, so that a row of `hidden` has the same logits in a batch of any
 // size: the 64 x 32 tile (up to 32 rows, vocabularies up to 16384 on 256 compute units) has two wavefronts for each place of
@@ -48,6 +48,7 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 constexpr int KC = 64;                        // k per ring stage
 constexpr int ROWB = KC * 2;                  // LDS bytes per row of a stage
 constexpr int NTHREADS = 256;
+constexpr int HEAD = 16;                      // stages (2 KB of a row) that workgroups are apart where the sums are cut there
 
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 template <int N>
@@ -70,7 +71,9 @@ __device__ __forceinline__ bool beats(float v2, int i2, float v1, int i1) { retu
 // reading those logits will see (maximum and arg-max are then those of the rounded values too).
 // RING_KB: the ring's share of the LDS. 128: one workgroup per compute unit with as many stages in flight as fit; 64 (up to 32
 // rows): two workgroups, whose starts and ends overlap.
-template <int VT, int MT, int RING_KB, bool TWO, bool STATS>
+// APART: a logit is the sum over the first HEAD stages of k plus that over the others, and every other sixteen workgroups (two of an
+// XCD's) start with the others: a sum of two does not depend on its order, so equal rows of W have equal logits wherever they lie.
+template <int VT, int MT, int RING_KB, bool TWO, bool APART, bool STATS>
 __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argmax_kernel(const __hip_bfloat16* __restrict__ hidden,
                                                                     const __hip_bfloat16* __restrict__ weight,
                                                                     float* __restrict__ part_val, int32_t* __restrict__ part_idx,
@@ -112,9 +115,15 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
 #pragma unroll
   for (int j = 0; j < HL; ++j) hsrc[j] = (const unsigned char*)(hidden + (long)min(m0 + j * 32 + (t >> 3), M - 1) * K) + piece * 16;
   const unsigned wave_lds = (unsigned)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring + wave * 1024;
-  auto issue = [&](int c, int slot) {
+  // stages are requested in the order of their use: from `start` to the end, then from 0
+  const bool turned = APART && ((vt >> 4) & 1) != 0;
+  const int start = turned ? HEAD : 0;
+  int next = start;
+  auto issue = [&](int slot) {
     const unsigned dst = wave_lds + slot * STAGE;
-    const long k = (long)c * ROWB;
+    const long k = (long)next * ROWB;
+    ++next;
+    if (APART && next == NC) next = 0;
 #pragma unroll
     for (int j = 0; j < HL; ++j) load_to_lds<false>(hsrc[j] + k, dst + W_BYTES + j * 4096);
 #pragma unroll
@@ -122,7 +131,7 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
   };
 #pragma unroll
   for (int c = 0; c < AHEAD; ++c)
-    if (c < NC) issue(c, c);
+    if (c < NC) issue(c);
 
   // TWO: a logit is the sum of two, over the first and over the second two k-steps of every stage. The tile of 64 x 32 gives
   // them to two wavefronts. Where that tile serves the smallest M (V and K decide), the others take the same two sums, so that
@@ -141,28 +150,48 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
 #pragma unroll
   for (int ks = 0; ks < 4 / KW; ++ks) off[ks] = r * ROWB + (((2 * (kw * (4 / KW) + ks) + h) ^ ((r >> 1) & 7)) << 4);
 
-  int slot = 0;
-  for (int c = 0; c < NC; ++c) {
-    if (c + AHEAD <= NC) wait_loads_but<(AHEAD - 1) * LPS>();
-    else wait_loads_but<0>();
-    lds_barrier();   // stage c has landed for every lane, and every wavefront is done with stage c - 1, whose slot is free
-    if (c + AHEAD < NC) issue(c + AHEAD, slot == 0 ? NST - 1 : slot - 1);
-    const unsigned char* ws = ring + slot * STAGE + wv * TV * 32 * ROWB;
-    const unsigned char* hs = ring + slot * STAGE + W_BYTES + wm * TM * 32 * ROWB;
+  static_assert(!APART || SUMS == 1, "one sum per logit at a time");
+  int slot = 0, c = 0;
+  f32x16 sum_before[APART ? TV : 1][APART ? TM : 1];
 #pragma unroll
-    for (int ks = 0; ks < 4 / KW; ++ks) {
-      bf16x8 a[TV], b[TM];
+  for (int part = 0; part < (APART ? 2 : 1); ++part) {
+    for (const int end = !APART || part == 1 ? NC : turned ? NC - HEAD : HEAD; c < end; ++c) {
+      if (c + AHEAD <= NC) wait_loads_but<(AHEAD - 1) * LPS>();
+      else wait_loads_but<0>();
+      lds_barrier();   // stage c has landed for every lane, and every wavefront is done with stage c - 1, whose slot is free
+      if (c + AHEAD < NC) issue(slot == 0 ? NST - 1 : slot - 1);
+      const unsigned char* ws = ring + slot * STAGE + wv * TV * 32 * ROWB;
+      const unsigned char* hs = ring + slot * STAGE + W_BYTES + wm * TM * 32 * ROWB;
 #pragma unroll
-      for (int tv = 0; tv < TV; ++tv) a[tv] = *(const bf16x8*)(ws + tv * 32 * ROWB + off[ks]);
+      for (int ks = 0; ks < 4 / KW; ++ks) {
+        bf16x8 a[TV], b[TM];
 #pragma unroll
-      for (int tm = 0; tm < TM; ++tm) b[tm] = *(const bf16x8*)(hs + tm * 32 * ROWB + off[ks]);
+        for (int tv = 0; tv < TV; ++tv) a[tv] = *(const bf16x8*)(ws + tv * 32 * ROWB + off[ks]);
+#pragma unroll
+        for (int tm = 0; tm < TM; ++tm) b[tm] = *(const bf16x8*)(hs + tm * 32 * ROWB + off[ks]);
+#pragma unroll
+        for (int tv = 0; tv < TV; ++tv)
+#pragma unroll
+          for (int tm = 0; tm < TM; ++tm)
+            sums[ks / 2 % SUMS][tv][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tv], b[tm], sums[ks / 2 % SUMS][tv][tm], 0, 0, 0);
+      }
+      slot = slot == NST - 1 ? 0 : slot + 1;
+    }
+    if constexpr (APART) {
 #pragma unroll
       for (int tv = 0; tv < TV; ++tv)
 #pragma unroll
-        for (int tm = 0; tm < TM; ++tm)
-          sums[ks / 2 % SUMS][tv][tm] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[tv], b[tm], sums[ks / 2 % SUMS][tv][tm], 0, 0, 0);
+        for (int tm = 0; tm < TM; ++tm) {
+          f32x16& sum = sums[0][tv][tm];
+          if (part == 0) {
+            sum_before[tv][tm] = sum;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum[i] = 0.f;
+          } else {
+            sum += sum_before[tv][tm];
+          }
+        }
     }
-    slot = slot == NST - 1 ? 0 : slot + 1;
   }
 
   f32x16 (&acc)[TV][TM] = sums[0];
@@ -394,28 +423,38 @@ hipError_t launch_lm_head(int M, int K, int V, const void* hidden, const void* w
   // 24.5 / 16.9, where W straight into registers took 201, 107, 30 and 18.9). 64 x 32 tiles gain from two at every K (16000 x
   // 4096 30.0 / 28.3, 8000 x 512 8.4 / 8.1).
   const bool pairs = K <= 2048;
+  // Rows of W a multiple of 4 KB apart: workgroups that read the same k at the same time meet in the same few memory channels. Half
+  // of them 2 KB further on, us with logits and statistics, in step / apart, 16 and 128 rows over 32000: K = 2048 32.5 / 27.3, 39.3 /
+  // 35.8; 4096 54.8 / 48.2, 61.5 / 57.3; 6144 84.5 / 64.4, 100.1 / 83.7; 8192 103.9 / 94.0, 116.3 / 103.1 (4096 by 1 KB 50.9, 4 KB
+  // 53.2, each workgroup at another k 46.3, four quarters 47.4; every other eight instead of sixteen 59.1). No gain at K = 1024,
+  // 1536, 3072, 3328 and 5120, nor for 250 rows (arithmetic).
+  const bool apart = K % 2048 == 0;
   const int m_slices = (M + mt - 1) / mt;
   const int n_vtiles = (V + vt - 1) / vt;
   const int per_row = std::min(m_slices, 16);   // slices numbered eight apart within a grid row
   const dim3 grid((unsigned)((n_vtiles + 7) / 8 * 8) * per_row, (m_slices + per_row - 1) / per_row);
-#define SPEC_LMH(VTT, MT, RK, TW, ST)                                                                                         \
-  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, RK, TW, ST>), grid, dim3(lmh::NTHREADS), 0, s,                          \
+#define SPEC_LMH(VTT, MT, RK, TW, AP, ST)                                                                                     \
+  hipLaunchKernelGGL((lmh::lm_head_argmax_kernel<VTT, MT, RK, TW, AP, ST>), grid, dim3(lmh::NTHREADS), 0, s,                      \
                      (const __hip_bfloat16*)hidden, (const __hip_bfloat16*)weight, part_val, part_idx, part_sum,              \
                      (__hip_bfloat16*)logits_out, itl2, M, K, V, n_vtiles, per_row)
-#define SPEC_LMH_T(TW, ST)                              \
-  if (mt == 256) SPEC_LMH(128, 256, 128, TW, ST);            \
-  else if (vt == 128 && mt == 128) SPEC_LMH(128, 128, 128, TW, ST); \
-  else if (vt == 128) SPEC_LMH(128, 64, 128, TW, ST);        \
-  else if (mt == 128) SPEC_LMH(64, 128, 128, TW, ST);        \
-  else SPEC_LMH(64, 64, 128, TW, ST)
+#define SPEC_LMH_T(TW, AP, ST)                              \
+  if (mt == 256) SPEC_LMH(128, 256, 128, TW, AP, ST);            \
+  else if (vt == 128 && mt == 128) SPEC_LMH(128, 128, 128, TW, AP, ST); \
+  else if (vt == 128 && mt == 64) SPEC_LMH(128, 64, 128, TW, AP, ST);        \
+  else if (mt == 128) SPEC_LMH(64, 128, 128, TW, AP, ST);        \
+  else SPEC_LMH(64, 64, 128, TW, AP, ST)
+#define SPEC_LMH_1(AP, ST)                              \
+  if (mt == 32 && pairs) SPEC_LMH(128, 32, 64, false, AP, ST); \
+  else if (mt == 32) SPEC_LMH(128, 32, 128, false, AP, ST); \
+  else { SPEC_LMH_T(false, AP, ST); }
 #define SPEC_LMH_ST(ST)                                 \
-  if (mt == 32 && two) SPEC_LMH(64, 32, 64, true, ST);  \
-  else if (mt == 32 && pairs) SPEC_LMH(128, 32, 64, false, ST); \
-  else if (mt == 32) SPEC_LMH(128, 32, 128, false, ST); \
-  else if (two) { SPEC_LMH_T(true, ST); }               \
-  else { SPEC_LMH_T(false, ST); }
+  if (mt == 32 && two) SPEC_LMH(64, 32, 64, true, false, ST);  \
+  else if (two) { SPEC_LMH_T(true, false, ST); }               \
+  else if (apart) { SPEC_LMH_1(true, ST); }                  \
+  else { SPEC_LMH_1(false, ST); }
   if (stats) { SPEC_LMH_ST(true); } else { SPEC_LMH_ST(false); }
 #undef SPEC_LMH_ST
+#undef SPEC_LMH_1
 #undef SPEC_LMH_T
 #undef SPEC_LMH
   hipError_t e = hipGetLastError();

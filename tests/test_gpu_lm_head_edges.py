@@ -20,12 +20,13 @@ def test_lm_head_tile_edges(spec, M, K, V):
     _stats_case(spec, M, K, V, 0.9, seed=M * 7 + V)
 
 
-@pytest.mark.parametrize("M,V", [(12, 20000), (70, 20001), (130, 9000)])
-def test_equal_rows_of_the_weight_matrix_give_equal_logits(spec, M, V):
-    """The same row of W at places of different lanes, wavefronts and workgroups: bit-equal logits, so the lowest token
-    wins whatever its workgroup."""
-    h, w = _inputs(M, 1024, V, seed=V)
-    places = [V - 1, 5, 40, 70, 133, 5000, 5001]
+@pytest.mark.parametrize("M,V,K", [(12, 20000, 1024), (70, 20001, 1024), (130, 9000, 1024), (12, 20000, 2048), (70, 16385, 4096),
+                                   (100, 20001, 2048), (200, 20000, 2048)])
+def test_equal_rows_of_the_weight_matrix_give_equal_logits(spec, M, V, K):
+    """The same row of W at places of different lanes, wavefronts and workgroups (that start with different parts of K): bit-equal
+    logits, so the lowest token wins whatever its workgroup."""
+    h, w = _inputs(M, K, V, seed=V)
+    places = [V - 1, 5, 40, 70, 133, 2100, 5000, 5001]
     w[places] = w[17] * 40      # the largest logit of about half of the rows
     logits, arg, _, _ = spec.spec_lm_head_logits_stats(_dev(h), _dev(w))
     arg2, mx = spec.spec_lm_head_argmax(_dev(h), _dev(w), want_max=True)
@@ -48,7 +49,7 @@ def test_logits_at_an_eight_byte_aligned_address(spec):
     assert torch.equal(out[0], want) and torch.equal(out[1], arg) and torch.equal(out[3], se)
 
 
-@pytest.mark.parametrize("K,V", [(768, 1000), (1024, 8000), (512, 16384), (512, 16385), (768, 20000)])
+@pytest.mark.parametrize("K,V", [(768, 1000), (1024, 8000), (512, 16384), (512, 16385), (768, 20000), (2048, 16385), (4096, 17000)])
 def test_a_row_has_the_same_logits_in_a_batch_of_any_size(spec, K, V):
     """Every tile of `hidden` and of the vocabulary sums a logit in the same order: bit-equal maxima before rounding, logits and
     arg-max, from one row to three slices."""

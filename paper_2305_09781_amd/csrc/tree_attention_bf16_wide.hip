@@ -78,7 +78,7 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     const __hip_bfloat16* __restrict__ k_new, const __hip_bfloat16* __restrict__ v_new,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, const int32_t* __restrict__ prefix_len,
     __hip_bfloat16* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml, int32_t* status, int B, int N,
-    int H, int H_v, int n_qg, int hpw, int heads_per_wg, int S_cap, int chunk_keys, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh, long n_sb, long n_sn,
+    int H, int H_v, int n_qg, int hpw, int heads_per_wg, int S_cap, int work, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh, long n_sb, long n_sn,
     long n_sh, long kv_sb, long kv_sh, long kv_ss, float scale_log2, Pages pg, Rope rope) {
   static_assert(KW == 1 || KW == 2, "a 64-key tile is consumed as two 32-key halves");
   static_assert(DEPTH == 2 || DEPTH == 4, "register sets of tiles in flight");
@@ -626,15 +626,17 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     }
     if (QW == 8 && heads_per_wg > 1) {   // several K/V heads per workgroup (host: one query group per head, no key split)
       hv *= heads_per_wg;
-      segment(b, hv, 0, chunk_keys, -1, min(heads_per_wg, H_v - hv));
+      segment(b, hv, 0, work, -1, min(heads_per_wg, H_v - hv));
     } else {
-      segment(b, hv, split * chunk_keys, split * chunk_keys + chunk_keys, n_splits == 1 ? -1 : split, 1);
+      segment(b, hv, split * work, split * work + work, n_splits == 1 ? -1 : split, 1);
     }
   } else {
     // Every pair's tiles in equal chunks, as many as the request's length asks for; chunk i of a pair fills slot i.
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, deal_wgs);
     if ((long)blockIdx.x >= deal.count) return;
-    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
+    const bool sorted = B <= 64;   // (a lane per request; more as they stand)
+    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal,
+                                  sorted ? deal_place(blockIdx.x, deal.count, work) : (long)blockIdx.x, sorted);
     if (c.n_tiles > 0) {
       segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
       if (c.chunks == 1) mark_rows(c.b, c.h, 0, PARTIAL_FINAL);
@@ -662,6 +664,7 @@ hipError_t launch_tree_attention_bf16_wide(const spec_attn_desc_t& d, const Attn
   const NewStrides ns = attn_new_strides(d);
   const bool append = k_new != nullptr;
   const int mode = plan.balanced_wgs == 0 ? wide::PLAN_GRID : wide::PLAN_TILES;
+  const int work = mode == wide::PLAN_GRID ? plan.chunk_keys : compute_units();
   // Whole key ranges, one query group per K/V head, a wavefront per query tile: a workgroup may serve several
   // consecutive K/V heads of a request as one stream (the plan decides how many).
   const int heads_per_wg = (mode == wide::PLAN_GRID && plan.n_splits == 1 && qgr.n_qgroups == 1 && qw == 8)
@@ -674,7 +677,7 @@ hipError_t launch_tree_attention_bf16_wide(const spec_attn_desc_t& d, const Attn
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,                    \
                      (const __hip_bfloat16*)k_new, (const __hip_bfloat16*)v_new, parent, depth, prefix_len,           \
                      (__hip_bfloat16*)out, ws_o, ws_ml, status, d.B, d.N, d.H, virtual_heads, qgr.n_qgroups,           \
-                     qgr.heads_per_wg, heads_per_wg, d.S_cap, plan.chunk_keys, plan.balanced_wgs,                     \
+                     qgr.heads_per_wg, heads_per_wg, d.S_cap, work, plan.balanced_wgs,                     \
                      plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h, ns.b, ns.n, ns.h,     \
                      (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg, rope)
 #define SPEC_SHAPES(DD, APP, PLAN, PGD)                          \

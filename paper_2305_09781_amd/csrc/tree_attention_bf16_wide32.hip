@@ -95,13 +95,14 @@ __device__ __forceinline__ int opaque(int v) {
   return v;
 }
 
+// work: keys per chunk (PLAN_GRID), compute units the deal's chunks are paired for (PLAN_TILES).
 template <bool APPEND, int PLAN, bool PAGED, bool ROPE>
 __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel(
     const __hip_bfloat16* __restrict__ q, __hip_bfloat16* k_cache, __hip_bfloat16* v_cache,
     const __hip_bfloat16* __restrict__ k_new, const __hip_bfloat16* __restrict__ v_new,
     const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, const int32_t* __restrict__ prefix_len,
     __hip_bfloat16* __restrict__ out, float* __restrict__ ws_o, float* __restrict__ ws_ml, int32_t* status, int B, int N,
-    int H, int H_v, int n_qg, int hpw, int S_cap, int chunk_keys, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh,
+    int H, int H_v, int n_qg, int hpw, int S_cap, int work, int deal_wgs, int n_splits, long q_sb, long q_sn, long q_sh,
     long n_sb, long n_sn, long n_sh, long kv_sb, long kv_sh, long kv_ss, float scale_log2, Pages pg, Rope rope) {
   __shared__ __attribute__((aligned(1024))) unsigned char ring[NST * STAGE];
   __shared__ TreeLds s_tree;
@@ -528,13 +529,15 @@ __global__ void __launch_bounds__(NTHREADS, 2) tree_attention_bf16_wide32_kernel
       const int r = hv % (8 * n_qg), blk = hv / (8 * n_qg);
       hv = uniform((blk * 8 + r % 8) * n_qg + r / 8);
     }
-    segment(b, hv, split * chunk_keys, split * chunk_keys + chunk_keys, n_splits == 1 ? -1 : split);
+    segment(b, hv, split * work, split * work + work, n_splits == 1 ? -1 : split);
   } else {
     // Every pair's tiles in equal chunks, as many as the request's length asks for; chunk i of a pair fills slot i.
     constexpr int KT = SPEC_WIDE_TILE_KEYS;
     const BalancedDeal deal = balanced_deal(prefix_len, B, N, H_v, S_cap, KT, deal_wgs);
     if ((long)blockIdx.x >= deal.count) return;
-    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal, blockIdx.x);
+    const bool sorted = B <= 64;   // (a lane per request; more as they stand)
+    const DealChunk c = deal_find(prefix_len, B, N, H_v, n_qg, S_cap, KT, deal,
+                                  sorted ? deal_place(blockIdx.x, deal.count, work) : (long)blockIdx.x, sorted);
     if (c.n_tiles > 0) {
       segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk);
       if (c.chunks == 1) mark_rows(c.b, c.h, 0, PARTIAL_FINAL);
@@ -556,13 +559,14 @@ hipError_t launch_tree_attention_bf16_wide32(const spec_attn_desc_t& d, const At
   const NewStrides ns = attn_new_strides(d);
   const bool append = k_new != nullptr;
   const bool tiles_plan = plan.balanced_wgs > 0;
+  const int work = tiles_plan ? compute_units() : plan.chunk_keys;
   const dim3 grid = tiles_plan ? dim3(balanced_grid(plan, d.B, virtual_heads), 1, 1) : dim3(plan.n_splits, virtual_heads, d.B);
 #define SPEC_LAUNCH(APP, PLAN, PGD, RP)                                                                                  \
   hipLaunchKernelGGL((wide32::tree_attention_bf16_wide32_kernel<APP, PLAN, PGD, RP>), grid, dim3(wide32::NTHREADS), 0, s, \
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,                   \
                      (const __hip_bfloat16*)k_new, (const __hip_bfloat16*)v_new, parent, depth, prefix_len,          \
                      (__hip_bfloat16*)out, ws_o, ws_ml, status, d.B, d.N, d.H, virtual_heads, qgr.n_qgroups,          \
-                     qgr.heads_per_wg, d.S_cap, plan.chunk_keys, plan.balanced_wgs, plan.n_splits, (long)d.q_stride_b,                  \
+                     qgr.heads_per_wg, d.S_cap, work, plan.balanced_wgs, plan.n_splits, (long)d.q_stride_b,                  \
                      (long)d.q_stride_n, (long)d.q_stride_h, ns.b, ns.n, ns.h, (long)d.kv_stride_b,                  \
                      (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg, rope)
 #define SPEC_PLANS(APP, PGD, RP)                                          \

@@ -40,6 +40,15 @@ int main() {
       check(used <= chunks && (used > 1) == (chunks > 1), "count", tb, share, used);   // the merge relies on both
       check(per * (used - 1) < tb && tb <= per * used, "cover", tb, share, per);
     }
+  for (int cus : {1, 3, 256})   // every chunk once; two workgroups of a compute unit take chunks whose places add up to the same
+    for (long count : {1L, 2L, 5L, 6L, 7L, 255L, 256L, 257L, 400L, 511L, 512L, 513L, 1500L}) {
+      std::vector<int> seen(count, 0);
+      for (long id = 0; id < count; ++id) {
+        const long at = deal_place(id, count, cus);
+        check(at >= 0 && at < count && !seen[at]++, "place", (int)id, (int)count, cus);
+        if (count <= 2l * cus && id >= cus) check(at + deal_place(id - cus, count, cus) == count - 1, "pair", (int)id, (int)count, cus);
+      }
+    }
   // the kernels' division: float32 reciprocal (one unit off either way included) and one correction
   auto by_reciprocal = [](int a, int b, int ulp) {
     float rcp = 1.0f / (float)b;

@@ -174,7 +174,10 @@ __device__ __forceinline__ void issue_tile_loads(const TileSrc& s, int k0, int P
 // NT and n_qgroups are 1 (larger trees and grouped heads go to the wide kernels). Both stay written out: without n_qgroups the
 // first loads come in another order, which costs 8 requests of 1024 keys 1.2 % (trees of 16, rotary) to 2.3 % (trees of 7), and
 // without NT one request loses 0.9 %.
-template <int D, int NT, bool APPEND, int PLAN, bool PAGED>
+// EARLY: with the rotary embedding, the first tile moved to LDS while the queries are rotated (see s_k). The other instances keep the
+// embedding as a run-time branch: without it, as a template parameter, the first loads come in another order, which costs launches
+// that have no embedding 1 to 6 %.
+template <int D, int NT, bool APPEND, bool EARLY, int PLAN, bool PAGED>
 __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const __hip_bfloat16* __restrict__ q, __hip_bfloat16* k_cache, __hip_bfloat16* v_cache,
     const __hip_bfloat16* __restrict__ k_new, const __hip_bfloat16* __restrict__ v_new,
@@ -193,6 +196,14 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   __shared__ __attribute__((aligned(16))) unsigned char lds[T::LDS_BYTES];
   __shared__ __attribute__((aligned(16))) u32x4 s_q[APPEND ? KS * 64 : 1];
   __shared__ __attribute__((aligned(16))) float s_angle[APPEND ? 16 * ANGLE_ROW : 4];
+  // With the embedding the streaming wavefronts wait for the rotated queries with one tile on its way each. Their first tile moves to
+  // LDS meanwhile (V where it is staged anyway, a lane's pieces of K into slots of its own), and the second is requested into its
+  // registers. us, before / now, trees of 16: 1 x 32 heads of 1024 keys 12.7 / 12.0, of 4000 20.1 / 18.5; 4 x 32 of 300 11.8 / 10.7, of 900
+  // 18.4 / 16.8; 8 x 32 of 400 14.2 / 12.6, of 1024 29.4 / 27.9, of 2000 47.9 / 46.4; 24 x 40 of 1000 105.5 / 101.2, 20 x 40 of 150 (one or two
+  // tiles per wavefront) 42.5 / 42.0; paged 8 x 32 of 500, trees of 9, 16.9 / 15.8. Seven streaming wavefronts do as much for the
+  // wait, but then sum in another order than the call without the embedding, whose bits this one has. At D = 64 the LDS would cost a
+  // workgroup per compute unit, and the contiguous plan has no register left.
+  __shared__ __attribute__((aligned(16))) u32x4 s_k[EARLY ? SWAVES * 2 * KS * 64 : 1];
   __shared__ int s_bad_tree;
   static_assert(NT == 1, "a tree of at most 16 nodes: lane r16 holds node r16, which is also its query");
 
@@ -252,7 +263,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   // D = 64, 5.2 us, 4.7 by fours). Rows past N repeat
   // the last query (their results are never written): the loads are unconditional.
   const bool is_tail = wave == TAIL;
-  const bool rotates = APPEND && rope.cos != nullptr;
+  const bool rotates = EARLY || (APPEND && rope.cos != nullptr);
   int par = 0, dep = 0;
   if (is_tail && N == 16) {   // whole, in two loads
     const int32_t *pw = parent + (long)b * 16, *dw = depth + (long)b * 16;
@@ -352,6 +363,26 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
       }
     }
   }
+  unsigned char* vst = lds + wave * T::VTILE_BYTES;
+  if constexpr (EARLY) {
+    if (rotates && !is_tail && ti_first < ti_end) {
+      const int second = ti_first + SWAVES < ti_end ? ti_first + SWAVES : -1;
+      const int k1 = c0 + second * TILE;
+      const long shift = (PAGED && second >= 0) ? page_shift(b, k1, &in_pool) : 0;
+#pragma unroll
+      for (int j = 0; j < NVL; ++j) *(u32x4*)(vst + (j * RPI + lane / LPR) * VROW + (lane % LPR) * 16) = VA[j];
+      __builtin_amdgcn_sched_barrier(0);
+      if (second >= 0) issue_v_loads<D, NT, APPEND, true>(src, k1, P, last_row, lane, VA, shift);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s_k[((wave * 2 + hf) * KS + ks) * 64 + lane] = KA[hf][ks];
+      __builtin_amdgcn_sched_barrier(0);
+      if (second >= 0) issue_k_loads<D, NT, APPEND, true>(src, k1, P, last_row, r16, KA, shift);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
   if constexpr (APPEND) {
     if (rotates) {
       lds_barrier();
@@ -402,11 +433,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
       if (bad_tree && lane == 0) s_bad_tree = 1;
     }
   }
-  unsigned char* vst = lds + wave * T::VTILE_BYTES;
-
   // One tile: consume the buffer filled by earlier loads, refill it for the next step, S^T, softmax, O^T.
-  auto tile_step = [&](const int ti, const int ti_refill, auto masked_tag) {
-    constexpr bool MASKED = decltype(masked_tag)::value;
+  // MOVED: the tile lies in LDS and the buffer's loads are under way.
+  auto tile_step = [&](const int ti, const int ti_refill, auto masked_tag, auto moved_tag) {
+    constexpr bool MASKED = decltype(masked_tag)::value, MOVED = decltype(moved_tag)::value;
     const int k0 = c0 + ti * TILE;
     if (MASKED) {
       // rows at and beyond the end of the chunk hold stale data: their V must not reach the product
@@ -444,8 +474,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
         }
       }
     }
+    if (!MOVED) {
 #pragma unroll
-    for (int j = 0; j < NVL; ++j) *(u32x4*)(vst + (j * RPI + lane / LPR) * VROW + (lane % LPR) * 16) = VA[j];
+      for (int j = 0; j < NVL; ++j) *(u32x4*)(vst + (j * RPI + lane / LPR) * VROW + (lane % LPR) * 16) = VA[j];
+    }
     // Refill in place: V's registers are free once staged, K's once the S^T products have read them. The
     // scheduling fences keep the compiler from moving the requests above those uses: it would then need a second
     // set of registers for the rows in flight and copy it into the first on every tile, after the rows have arrived
@@ -466,7 +498,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
         f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks)
-          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, KA[hf][ks]), qB[nt][ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              __builtin_bit_cast(bf16x8, MOVED ? s_k[((wave * 2 + hf) * KS + ks) * 64 + lane] : KA[hf][ks]), qB[nt][ks], acc, 0, 0, 0);
         sc[nt][hf] = acc;
       }
     __builtin_amdgcn_sched_barrier(0);
@@ -545,7 +578,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
 
   if (is_tail) {
     if (!bad_tree)
-      for (int ti = ti_first; ti < ti_end; ++ti) tile_step(ti, ti + 1 < ti_end ? ti + 1 : -1, std::true_type{});
+      for (int ti = ti_first; ti < ti_end; ++ti) tile_step(ti, ti + 1 < ti_end ? ti + 1 : -1, std::true_type{}, std::false_type{});
     if (PAGED) {   // every block this segment reads must lie inside the pool (those not in the lanes looked at last: nothing waits)
       for (int j = LANES ? first_block + 64 + lane : (c0 >> pg.log2_tokens) + lane; j <= (c1 - 1) >> pg.log2_tokens; j += 64) {
         const int e = pg.table[(long)b * pg.max_blocks + j];
@@ -553,8 +586,15 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
       }
     }
   } else {
-    for (int ti = ti_first; ti < ti_end; ti += SWAVES)
-      tile_step(ti, ti + SWAVES < ti_end ? ti + SWAVES : -1, std::false_type{});
+    int ti = ti_first;
+    if constexpr (EARLY) {
+      if (rotates && ti < ti_end) {
+        tile_step(ti, -1, std::false_type{}, std::true_type{});
+        ti += SWAVES;
+      }
+    }
+    for (; ti < ti_end; ti += SWAVES)
+      tile_step(ti, ti + SWAVES < ti_end ? ti + SWAVES : -1, std::false_type{}, std::false_type{});
   }
 
   // ---- merge the five wavefronts through LDS: layout [wave][n][MROW] floats (O row, m, l)
@@ -677,24 +717,30 @@ hipError_t launch_tree_attention_bf16(const spec_attn_desc_t& d, const AttnPlan&
   const bool append = k_new != nullptr;
   const bool bal = plan.balanced_wgs > 0;
   const dim3 grid = plan.contiguous ? dim3(plan.balanced_wgs, 1, 1) : bal ? dim3(balanced_grid(plan, d.B, d.H), 1, 1) : dim3(plan.n_splits, d.H * n_qgroups, d.B);
-#define SPEC_LAUNCH(DD, NTT, APP, PLAN, PGD)                                                                     \
-  hipLaunchKernelGGL((tree_attention_bf16_kernel<DD, NTT, APP, PLAN, PGD>), grid, dim3(WAVES * 64), 0, s,         \
+#define SPEC_LAUNCH(DD, NTT, APP, EA, PLAN, PGD)                                                                     \
+  hipLaunchKernelGGL((tree_attention_bf16_kernel<DD, NTT, APP, EA, PLAN, PGD>), grid, dim3(WAVES * 64), 0, s,         \
                      (const __hip_bfloat16*)q, (__hip_bfloat16*)k_cache, (__hip_bfloat16*)v_cache,               \
                      (const __hip_bfloat16*)k_new, (const __hip_bfloat16*)v_new, parent, depth, prefix_len,      \
                      (__hip_bfloat16*)out, ws_o, ws_ml, status, d.B, d.N, d.H, d.S_cap, n_qgroups,               \
                      bal ? plan.balanced_wgs : plan.chunk_keys, plan.n_splits, (long)d.q_stride_b, (long)d.q_stride_n, (long)d.q_stride_h, \
                      (long)d.kv_stride_b, (long)d.kv_stride_h, (long)d.kv_stride_s, scale, pg, rope)
-#define SPEC_DIMS(APP, PLAN, PGD)                      \
-  if (d.D == 128) SPEC_LAUNCH(128, 1, APP, PLAN, PGD); \
-  else SPEC_LAUNCH(64, 1, APP, PLAN, PGD)
-#define SPEC_PAGED(APP, PLAN)                               \
-  if (pg.table != nullptr) { SPEC_DIMS(APP, PLAN, true); }  \
-  else { SPEC_DIMS(APP, PLAN, false); }
+#define SPEC_DIMS(APP, EA, PLAN, PGD)                      \
+  if (d.D == 128) SPEC_LAUNCH(128, 1, APP, EA, PLAN, PGD); \
+  else SPEC_LAUNCH(64, 1, APP, EA, PLAN, PGD)
+#define SPEC_PAGED(APP, EA, PLAN)                               \
+  if (pg.table != nullptr) { SPEC_DIMS(APP, EA, PLAN, true); }  \
+  else { SPEC_DIMS(APP, EA, PLAN, false); }
 #define SPEC_DISPATCH(APP)                                  \
-  if (plan.contiguous) { SPEC_PAGED(APP, 2); }              \
-  else if (bal) { SPEC_PAGED(APP, 1); }                     \
-  else { SPEC_PAGED(APP, 0); }
-  if (append) { SPEC_DISPATCH(true); } else { SPEC_DISPATCH(false); }
+  if (plan.contiguous) { SPEC_PAGED(APP, false, 2); }              \
+  else if (bal) { SPEC_PAGED(APP, false, 1); }                     \
+  else { SPEC_PAGED(APP, false, 0); }
+#define SPEC_EARLY(PLAN)                                                \
+  if (pg.table != nullptr) SPEC_LAUNCH(128, 1, true, true, PLAN, true); \
+  else SPEC_LAUNCH(128, 1, true, true, PLAN, false)
+  if (append && rope.cos != nullptr && d.D == 128 && !plan.contiguous) {
+    if (bal) { SPEC_EARLY(1); } else { SPEC_EARLY(0); }
+  } else if (append) { SPEC_DISPATCH(true); } else { SPEC_DISPATCH(false); }
+#undef SPEC_EARLY
 #undef SPEC_DISPATCH
 #undef SPEC_PAGED
 #undef SPEC_DIMS

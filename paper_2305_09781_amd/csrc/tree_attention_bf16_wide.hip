@@ -132,9 +132,8 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
     }
   };
 
-  // Slot `slot` of every query head that virtual head hv of request b serves: nothing to merge, for the reason given.
-  auto mark_rows = [&](int b, int hv, int slot, float why) {
-    const int h = uniform_div(hv, n_qg), qg = hv - h * n_qg, group = H / (H_v / n_qg);
+  // Slot `slot` of the query heads of K/V head h that query group qg serves: nothing to merge, for the reason given.
+  auto mark_rows = [&](int b, int h, int qg, int group, int slot, float why) {
     for (int i = t; i < hpw * N; i += NTHREADS) {
       const int hg = qg * hpw + i / N;
       if (hg < group) mark_partial(ws_ml, partial_row<PLAN != PLAN_GRID>(b, h * group + hg, slot, B, H, N, n_splits) + i % N, why);
@@ -270,8 +269,12 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
             if (hg < group) out[b * q_sb + n * q_sn + ((h + hi) * group + hg) * q_sh + (i % D)] = __float2bfloat16(0.f);
           }
         if (hv == 0 && t == 0) set_status(status, b, bit);
-      } else if (bit == SPEC_ST_BAD_TREE) {
-        mark_rows(b, hv, slot, PARTIAL_BAD_TREE);
+      } else if (bit == SPEC_ST_BAD_TREE) {   // the rows that this workgroup would have written
+#pragma unroll
+        for (int nt = 0; nt < NTW; ++nt)
+          if (kpart == 0 && g == 0 && tile_live[nt] && tile_node[nt] < N)
+            mark_partial(ws_ml, partial_row<PLAN != PLAN_GRID>(b, h * group + tile_head[nt], slot, B, H, N, n_splits) + tile_node[nt],
+                         PARTIAL_BAD_TREE);
       }
     };
     if (!cap_ok) {
@@ -639,7 +642,10 @@ __global__ void __launch_bounds__(QW * KW * 64, 2) tree_attention_bf16_wide_kern
                                   sorted ? deal_place(blockIdx.x, deal.count, work) : (long)blockIdx.x, sorted);
     if (c.n_tiles > 0) {
       segment(c.b, c.h, c.tile0 * KT, (c.tile0 + c.n_tiles) * KT, c.chunks == 1 ? -1 : c.chunk, 1);
-      if (c.chunks == 1) mark_rows(c.b, c.h, 0, PARTIAL_FINAL);
+      if (c.chunks == 1) {
+        const int h = uniform_div(c.h, n_qg);
+        mark_rows(c.b, h, c.h - h * n_qg, H / (H_v / n_qg), 0, PARTIAL_FINAL);
+      }
     }
   }
 }

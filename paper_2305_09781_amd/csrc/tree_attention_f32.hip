@@ -25,11 +25,16 @@
 // What bounds it: float32 MFMA rate and the stream of K/V are close to each other (16 keys x 16 queries x 128
 // dimensions are 2048 cycles of one SIMD for 16 KB); small calls, one trip to memory after the other. So the tree words are requested
 // before the tiles and the masks built by one wavefront (a parent chain walked after two barriers and a dependent load before), new rows go
-// to the cache from the registers of the tile that uses them (read a second time before), the scores wait for K and the queries but not
-// for V, and two tiles are on their way where the registers allow it. Measured, us a layer, before / now: 4 requests x 32 heads x 128, 300
-// to 1000 keys, trees of 24 (95 MB), append and merge launch included 37.2 / 34.1 (2.8 TB/s, 30 TFLOP/s; 304 for the kernel that read K
-// uncoalesced per (query, key) and ran the softmax on N threads); 1 x 4 heads x 64, 128 keys, trees of 8, 10.6 / 10.2. Keeping the
-// queries in LDS to pay for a second K/V register set at two query tiles was slower: it spills (50 us).
+// to the cache from the registers of the tile that uses them (read a second time before), and the scores wait for K and the queries but not
+// for V. Measured, us a layer as nodes of a graph over 600 MB of caches, before / now: 4 requests x 32 heads x 128, 300 to 1000 keys, trees
+// of 24 (95 MB), append and merge launch included 41.0 / 38.5 (2.5 TB/s, 27 TFLOP/s); 1 x 4 heads x 64, 128 keys, trees of 8, 7.8 / 7.5; 32 x
+// 32 heads x 128, 100 keys, trees of 8, 37.2 / 35.2; 8 x 32 heads x 64, 1000 keys, trees of 32, 47.5 / 39.5.
+// One tile is on its way per wavefront. A second register set was measured for every instance and is not used: it costs a wavefront per
+// SIMD (and spills at D = 128), and each wavefront requests a second tile whether it has one or not. us, one set / two: 32 x 32 heads of
+// 100 keys, trees of 8, D = 128 35.1 / 39.4, D = 64 19.4 / 22.6; 1 x 12 of 40 keys, 3, D = 128 6.3 / 7.4; 8 x 32 of 500-1000, 16, D = 128
+// 51.9 / 53.5; 16 x 32 of 300, 20, D = 64 26.2 / 28.7. The one gain is two query tiles at D = 64 over long uncut ranges with a workgroup
+// per compute unit (8 x 32 heads of 2000 keys: trees of 24 65.6 / 63.2, of 32 75.1 / 75.7), too narrow a range for an instance of its own.
+// Keeping the queries in LDS to pay for a second set at D = 128 with two query tiles spills too (50 us).
 #include <hip/hip_bf16.h>
 
 #include <algorithm>
@@ -110,9 +115,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   const float* kn = APPEND ? k_new + b * n_sb + hk * n_sh : nullptr;
   const float* vn = APPEND ? v_new + b * n_sb + hk * n_sh : nullptr;
   const int n_tiles = (c1 - c0 + F32_TK - 1) / F32_TK;
-  // Two tiles are on their way where the registers allow it (not at D = 128 with two query tiles).
-  constexpr int SETS = D == 128 && NT == 2 ? 1 : 2;
-  float4 kf[SETS][KJ], vf[SETS][4][VH];
+  float4 kf[KJ], vf[4][VH];   // one tile (see "What bounds it" for a second one)
   // A tile starts at a multiple of 16 rows, so it lies inside one block of a paged cache; rows past the chunk repeat its
   // last one (their scores are masked).
   auto tile_base = [&](int k0) {
@@ -121,13 +124,13 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     if (!blk_ok && lane == 0) set_status(status, b, SPEC_ST_BAD_BLOCK);
     return off;
   };
-  auto load_k = [&](float4 (&kf)[KJ], int k0, long base) {
+  auto load_k = [&](int k0, long base) {
     const int row = min(k0 + r16, c1 - 1);
     const float* p = (APPEND && row >= P) ? kn + (long)(row - P) * n_sn : k_cache + base + (long)row * kv_ss;
 #pragma unroll
     for (int j = 0; j < KJ; ++j) kf[j] = *(const float4*)(p + (4 * j + g) * 4);
   };
-  auto load_v = [&](float4 (&vf)[4][VH], int k0, long base) {
+  auto load_v = [&](int k0, long base) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int row = min(k0 + 4 * g + i, c1 - 1);
@@ -137,11 +140,11 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     }
   };
   int ti = wave;
-  // The first tile's K, the queries, its V (the scores need the first two only), then the second tile. (Unconditional, so that the
-  // compiler knows how many loads stand behind each: a wavefront with fewer tiles takes its first again, or the chunk's last.)
-  const int first = c0 + min(ti, n_tiles - 1) * F32_TK, second = ti + F32_WAVES < n_tiles ? first + F32_WAVES * F32_TK : first;
+  // The first tile's K, the queries, its V: the scores need the first two only. (Unconditional, so that the compiler knows how many
+  // loads stand behind each: a wavefront without a tile takes the chunk's last.)
+  const int first = c0 + min(ti, n_tiles - 1) * F32_TK;
   const long first_base = tile_base(first);
-  load_k(kf[0], first, first_base);
+  load_k(first, first_base);
   float4 qf[NT][KJ];
   int node[NT];
 #pragma unroll
@@ -152,12 +155,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
 #pragma unroll
     for (int j = 0; j < KJ; ++j) qf[nt][j] = *(const float4*)(p + (4 * j + g) * 4);
   }
-  load_v(vf[0], first, first_base);
-  if constexpr (SETS == 2) {
-    const long base = tile_base(second);
-    load_k(kf[1], second, base);
-    load_v(vf[1], second, base);
-  }
+  load_v(first, first_base);
   const bool touches_tree = c1 > P;
   // one workgroup per request owns the final outputs' validity: every workgroup of a single chunk checks the tree; with
   // several chunks only those that reach it do (the combine step gives a malformed request its zeros)
@@ -201,13 +199,13 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
     for (int x = 0; x < VH * 4; ++x) O[nt][x] = (f32x4){0.f, 0.f, 0.f, 0.f};
   }
 
-  // ---- tiles of this wavefront. The K of the tile that takes this one's registers is requested when this tile's scores are done,
-  // its V when this tile's output products are. With and without a request are two bodies: behind a branch around it the compiler
-  // would wait for more than it has to.
-  auto step = [&](float4 (&kf)[KJ], float4 (&vf)[4][VH], const int ti, auto refill_tag) {
+  // ---- tiles of this wavefront. The next tile's K is requested when this tile's scores are done, its V when this tile's output
+  // products are: each load has the other product's time to arrive. With and without a next tile are two bodies: behind a branch
+  // around the requests the compiler would wait for more than it has to.
+  auto step = [&](const int ti, auto refill_tag) {
     constexpr bool REFILL = decltype(refill_tag)::value;
     const int k0 = c0 + ti * F32_TK;
-    const int k1 = c0 + (REFILL ? ti + SETS * F32_WAVES : ti) * F32_TK;
+    const int k1 = c0 + (REFILL ? ti + F32_WAVES : ti) * F32_TK;
     const long base1 = REFILL ? tile_base(k1) : 0;
     const bool masked = k0 + F32_TK > min(P, c1);
     // New rows go to the cache from the tile's registers (a row of a block outside the pool is not written).
@@ -233,7 +231,7 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
       }
       sc[nt] = (part[0] + part[1]) + (part[2] + part[3]);
     }
-    if (REFILL) load_k(kf, k1, base1);
+    if (REFILL) load_k(k1, base1);
     float p[NT][4];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
@@ -288,28 +286,10 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
           for (int nt = 0; nt < NT; ++nt)
             O[nt][hv * 4 + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], p[nt][i], O[nt][hv * 4 + e], 0, 0, 0);
       }
-    if (REFILL) load_v(vf, k1, base1);
+    if (REFILL) load_v(k1, base1);
   };
-  constexpr std::true_type REFILL;
-  constexpr std::false_type LAST;
-  constexpr int W = F32_WAVES;
-  if constexpr (SETS == 1) {
-    for (; ti + W < n_tiles; ti += W) step(kf[0], vf[0], ti, REFILL);
-    if (ti < n_tiles) step(kf[0], vf[0], ti, LAST);
-  } else {
-    for (; ti + 3 * W < n_tiles; ti += 2 * W) {
-      step(kf[0], vf[0], ti, REFILL);
-      step(kf[1], vf[1], ti + W, REFILL);
-    }
-    if (ti + 2 * W < n_tiles) {   // three left
-      step(kf[0], vf[0], ti, REFILL);
-      step(kf[1], vf[1], ti + W, LAST);
-      step(kf[0], vf[0], ti + 2 * W, LAST);
-    } else {
-      if (ti < n_tiles) step(kf[0], vf[0], ti, LAST);
-      if (ti + W < n_tiles) step(kf[1], vf[1], ti + W, LAST);
-    }
-  }
+  for (; ti + F32_WAVES < n_tiles; ti += F32_WAVES) step(ti, std::true_type{});
+  if (ti < n_tiles) step(ti, std::false_type{});
 
   // ---- merge of the four wavefronts: each scales its state to the common maximum, then all threads add the rows
 #pragma unroll

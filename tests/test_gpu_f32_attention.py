@@ -25,6 +25,9 @@ pytestmark = pytest.mark.gpu
     (2, 6, 1, 64, (100, 130), 16),     # one K/V head for six: three workgroups of two heads
     (2, 4, 4, 128, (300, 447), 9),     # around the length from which the key range is cut
     (2, 4, 4, 128, (440, 700), 24),    # cut by default, chunks past the shorter request's end
+    (40, 7, 7, 128, (180, 400), 11),   # uncut: one query tile, up to seven tiles a wavefront
+    (40, 7, 7, 64, (180, 400), 11),
+    (33, 8, 8, 64, (180, 400), 19),    # two query tiles
 ], ids=lambda c: f"B{c[0]}H{c[1]}kv{c[2]}D{c[3]}P{c[4][0]}-{c[4][1]}N{c[5]}")
 def test_float32_attention_tile_edges(spec, case):
     B, H, H_kv, D, P, N = case

@@ -208,8 +208,8 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   static_assert(NT == 1, "a tree of at most 16 nodes: lane r16 holds node r16, which is also its query");
 
   // One argument from each 64-byte line of the argument block, all asked for at once: with branches in between, the compiler asks
-  // for a line where it is first used, one trip to memory after the other (with the tree words of a tree of sixteen in two loads: 8 x 32
-  // heads of 1024 keys, rotary, two layers 54.0 -> 53.2 us; 32 layers of 1 x 32 heads and what follows 473 -> 462).
+  // for a line where it is first used, one trip to memory after the other (with the tree words of a tree of sixteen in one wait: 8 x 32
+  // heads of 1024 keys, rotary, two layers 54.0 -> 53.2 us; 32 layers of 1 x 32 heads and what follows 473 -> 458 and 462 in two runs).
   asm("" : "+s"(N) : "s"(prefix_len), "s"(kv_ss), "s"(rope.len));
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
@@ -258,20 +258,25 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   const int first_block = LANES ? min(c0, S_cap - 1) >> pg.log2_tokens : 0;
   if (LANES) blocks = load_block_lanes(pg, b, first_block);
 
-  // The tail wavefront: a tree node per lane, from scalar loads: sixteen nodes in one load of 64 bytes per array, fewer four at a time as
-  // far as there are any (all sixteen at once, clamped, cost the smallest calls what they wait for: 2 x 64 heads of 58 keys, one node,
-  // D = 64, 5.2 us, 4.7 by fours). Rows past N repeat
-  // the last query (their results are never written): the loads are unconditional.
+  // The tail wavefront: a tree node per lane, from scalar loads. More than eight nodes: four groups of four in one wait, the last two
+  // moved up to end with the tree (1 x 32 heads of 1024 keys, trees of 16: 11.4 us, 11.9 rotated, the same as by one load of 64 bytes;
+  // 11.9 and 13.0 by groups one after the other; trees of 9 to 15 gain less than 1 %). Fewer: four at a time as far as
+  // there are any (all at once, clamped, cost the smallest calls what they wait for: 2 x 64 heads of 58 keys, one node, D = 64, 5.2 us,
+  // 4.7 by fours). Rows past N repeat the last query (their results are never written): the loads are unconditional.
   const bool is_tail = wave == TAIL;
   const bool rotates = EARLY || (APPEND && rope.cos != nullptr);
   int par = 0, dep = 0;
-  if (is_tail && N == 16) {   // whole, in two loads
-    const int32_t *pw = parent + (long)b * 16, *dw = depth + (long)b * 16;
+  if (is_tail && N > 8) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      const int p = pw[i], d = dw[i];
-      par = r16 == i ? p : par;
-      dep = r16 == i ? d : dep;
+    for (int i0 = 0; i0 < 16; i0 += 4) {
+      const int first = i0 < 8 ? i0 : min(i0, N - 4);
+      const int32_t *pw = parent + (long)b * N + first, *dw = depth + (long)b * N + first;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int p = pw[i], d = dw[i];
+        par = r16 == first + i ? p : par;
+        dep = r16 == first + i ? d : dep;
+      }
     }
   } else if (is_tail) {
 #pragma unroll

@@ -23,6 +23,7 @@ CASES = [
     (3, 4, 4, 128, (30, 200), 16, "expansion", 0, 0, 0),           # few-query kernel
     (2, 3, 3, 64, (0, 90), 9, "random_parent", 0, 0, 0),           # few-query kernel, D = 64, empty prefix possible
     (2, 4, 4, 128, (100, 400), 16, "expansion", 96, 0, 0),         # few-query kernel, chunks
+    (3, 2, 2, 128, (0, 150), 11, "random_branching", 0, 0, 0),     # ... its words in groups that overlap
     (3, 2, 2, 64, (20, 300), 12, "random_branching", 0, 5, 0),     # few-query kernel, balanced deal
     (2, 3, 3, 128, (0, 130), 30, "random_branching", 0, 0, 0),     # 2 x 2 wavefronts
     (2, 4, 4, 64, (50, 260), 64, "expansion", 0, 0, 0),            # 4 wavefronts, D = 64

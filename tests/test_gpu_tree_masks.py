@@ -1,7 +1,7 @@
 """Ancestor masks of trees whose nodes fill one 64-node half, or two: chains through the border, nodes of the upper half that hang
 on the lower one at once or by way of others, and malformed words in either half. Against the oracle, on the kernel for more
 than four query tiles (D = 128), the eight-wavefront one (D = 64), up to 64 nodes the one for fewer queries, and up to 16 the
-few-query kernel, whose tail wavefront reads the words of four nodes at a time."""
+few-query kernel, whose tail wavefront reads the words by groups of four, which end with the tree above eight nodes."""
 import numpy as np
 import pytest
 import torch
@@ -26,7 +26,7 @@ def _trees(N, rng):
 
 
 @pytest.mark.parametrize("D", [128, 64])
-@pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 12, 13, 16, 33, 63, 64, 65, 66, 96, 127, 128])
+@pytest.mark.parametrize("N", [1, 3, 4, 5, 8, 9, 10, 11, 12, 13, 14, 15, 16, 33, 63, 64, 65, 66, 96, 127, 128])
 def test_masks_of_either_half(spec, N, D):
     rng = np.random.default_rng(N + D)
     trees = _trees(N, rng)

@@ -174,9 +174,11 @@ __device__ __forceinline__ void issue_tile_loads(const TileSrc& s, int k0, int P
 // NT and n_qgroups are 1 (larger trees and grouped heads go to the wide kernels). Both stay written out: without n_qgroups the
 // first loads come in another order, which costs 8 requests of 1024 keys 1.2 % (trees of 16, rotary) to 2.3 % (trees of 7), and
 // without NT one request loses 0.9 %.
-// EARLY: with the rotary embedding, the first tile moved to LDS while the queries are rotated (see s_k). The other instances keep the
-// embedding as a run-time branch: without it, as a template parameter, the first loads come in another order, which costs launches
-// that have no embedding 1 to 6 %.
+// EARLY: with the rotary embedding, the first tile moved to LDS while the queries are rotated (see s_k): D = 128, PLAN 0 and 1. The
+// other instances have the embedding behind a run-time branch on rope.cos. D = 64 and PLAN 2 take it; for D = 128 under PLAN 0 and 1
+// rope.cos is always null there, and the branch with its 12.5 KB of LDS stays for what it does to the order of the first loads:
+// compiled out, launches without the embedding take up to 4 % longer (us, with the branch / without: 8 x 32 heads of 400 keys, trees
+// of 13, 12.8 / 13.2; 4 x 32 of 900, 16, 17.7 / 18.0; 24 x 40 of 1000, 16, 102.0 / 102.8; others the same).
 template <int D, int NT, bool APPEND, bool EARLY, int PLAN, bool PAGED>
 __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
     const __hip_bfloat16* __restrict__ q, __hip_bfloat16* k_cache, __hip_bfloat16* v_cache,
@@ -370,7 +372,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   }
   unsigned char* vst = lds + wave * T::VTILE_BYTES;
   if constexpr (EARLY) {
-    if (rotates && !is_tail && ti_first < ti_end) {
+    if (!is_tail && ti_first < ti_end) {
       const int second = ti_first + SWAVES < ti_end ? ti_first + SWAVES : -1;
       const int k1 = c0 + second * TILE;
       const long shift = (PAGED && second >= 0) ? page_shift(b, k1, &in_pool) : 0;
@@ -593,7 +595,7 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   } else {
     int ti = ti_first;
     if constexpr (EARLY) {
-      if (rotates && ti < ti_end) {
+      if (ti < ti_end) {
         tile_step(ti, -1, std::false_type{}, std::true_type{});
         ti += SWAVES;
       }

@@ -127,6 +127,10 @@ __host__ __device__ inline DealUnit deal_unit(int r, int n_qg, int units) {
   const int unit = deal_quotient(r, n_qg);
   return {unit, r - unit * n_qg};
 }
+// Whether the chunks of request i, of size_i tiles each, come before those of request j in descending order of size.
+__host__ __device__ inline bool deal_before(int size_i, int i, int size_j, int j) {
+  return size_i > size_j || (size_i == size_j && i < j);
+}
 // Place of workgroup id among the `count` chunks in descending order of size. A compute unit takes workgroups id and id + compute_units
 // when two fit it, and they share its rate: the longest chunk goes with the shortest, the second longest with the second shortest and
 // so on (32 requests x 64 / 8 heads of 900 to 4100 keys: 93.1 -> 89.9 us with the merge; the tiles of a compute unit were 28 to 52, are 38 to
@@ -482,7 +486,7 @@ __device__ inline DealChunk deal_find(const int32_t* __restrict__ prefix_len, in
       incl = v;
       for (int i = 0; i < B; ++i) {
         const int s_i = __builtin_amdgcn_readlane(size, i), v_i = __builtin_amdgcn_readlane(v, i);
-        incl += s_i > size || (s_i == size && i < lane) ? v_i : 0;
+        incl += deal_before(s_i, i, size, lane) ? v_i : 0;
       }
     } else {
       incl = wave_inclusive_sum(v);

@@ -1,5 +1,6 @@
 """The balanced deal's arithmetic on the host: which (K/V head, chunk, query group) a workgroup gets is a permutation, chunks
-cover a request's tiles. The functions are the kernels' own (csrc/spec_internal.h), compiled for the host."""
+cover a request's tiles, and in the order of their sizes every chunk of every request is found once. The functions are the kernels'
+own (csrc/spec_internal.h), compiled for the host."""
 import os
 import shutil
 import subprocess
@@ -37,7 +38,9 @@ int main() {
     for (int share = 1; share <= 90; ++share) {
       const int chunks = deal_chunks(tb, share), per = deal_chunk_tiles(tb, chunks), used = deal_chunks(tb, per);
       check(per >= 1 && per <= share, "share", tb, share, per);
-      check(used <= chunks && (used > 1) == (chunks > 1), "count", tb, share, used);   // the merge relies on both
+      check(used <= chunks && (used > 1) == (chunks > 1), "count", tb, share, used);
+      // (a workgroup whose request has one chunk writes the output, so one must be all that is used; the workgroup of a request's
+      // last key signs its partial, so no slot below it may be empty)
       check(per * (used - 1) < tb && tb <= per * used, "cover", tb, share, per);
     }
   for (int cus : {1, 3, 256})   // every chunk once; two workgroups of a compute unit take chunks whose places add up to the same
@@ -49,6 +52,43 @@ int main() {
         if (count <= 2l * cus && id >= cus) check(at + deal_place(id - cus, count, cus) == count - 1, "pair", (int)id, (int)count, cus);
       }
     }
+  // Batches of up to 64 requests in descending order of their chunks' sizes, as deal_find numbers them: the requests that come before
+  // a lane's own are added up by deal_before. Lengths all equal, few different ones, with requests that do not fit (no tiles).
+  unsigned seed = 1;
+  auto random = [&](int n) { return (int)((seed = seed * 1664525u + 1013904223u) >> 8) % n; };
+  for (int B : {1, 2, 3, 17, 40, 63, 64})
+    for (int kinds : {1, 2, 5, 200})
+      for (int share : {1, 3, 8, 300})
+        for (int n_qg : {1, 3}) {
+          const int kv_heads = 2, H = kv_heads * n_qg;
+          std::vector<int> tb(B), v(B), size(B), incl(B);
+          for (int b = 0; b < B; ++b) {
+            tb[b] = random(7) == 0 ? 0 : 1 + random(kinds);
+            v[b] = deal_chunks(tb[b], share);
+            size[b] = v[b] > 0 ? deal_chunk_tiles(tb[b], v[b]) : 0;
+          }
+          long count = 0;
+          for (int b = 0; b < B; ++b) {
+            incl[b] = v[b];
+            for (int i = 0; i < B; ++i) incl[b] += deal_before(size[i], i, size[b], b) ? v[i] : 0;
+            count += v[b] * H;
+          }
+          std::vector<std::vector<int>> seen(B);
+          for (int b = 0; b < B; ++b) seen[b].assign(H * v[b], 0);
+          int before = 1 << 30;
+          for (long id = 0; id < count; ++id) {
+            int b = -1, hits = 0;
+            for (int i = 0; i < B; ++i)
+              if ((long)incl[i] * H > id && (long)(incl[i] - v[i]) * H <= id) b = i, ++hits;
+            check(hits == 1, "one request", (int)id, B, share);
+            check(size[b] <= before, "descending", (int)id, B, share);
+            before = size[b];
+            const int r = (int)(id - (long)(incl[b] - v[b]) * H);
+            check(r >= 0 && r < H * v[b], "number in the request", r, B, share);
+            const DealUnit u = deal_unit(r, n_qg, kv_heads * v[b]);
+            check(!seen[b][u.unit * n_qg + u.qg]++, "chunk", (int)id, b, share);
+          }
+        }
   // the kernels' division: float32 reciprocal (one unit off either way included) and one correction
   auto by_reciprocal = [](int a, int b, int ulp) {
     float rcp = 1.0f / (float)b;

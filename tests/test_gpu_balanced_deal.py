@@ -1,5 +1,6 @@
-"""The balanced deal over more requests than a wavefront has lanes (lengths are read 64 requests at a time), with requests
-that contribute no tiles, on every bf16 kernel, pairs whole and cut. Bar: that of the other attention tests."""
+"""The balanced deal over up to as many and over more requests than a wavefront has lanes (lengths are read 64 requests at a time;
+the wide kernels take the chunks of up to 64 requests by size), with requests that contribute no tiles, on every bf16 kernel, pairs
+whole and cut, chunks on some, on most and on more than all of the compute units. Bar: that of the other attention tests."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +12,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,N,wgs", [(63, 5, 17), (64, 5, 200), (65, 20, 31), (130, 5, 300), (70, 70, 90), (30, 5, 130), (70, 16, 300),
-                                     (65, 20, 300), (70, 70, 320), (66, 100, 330)])
+                                     (65, 20, 300), (70, 70, 320), (66, 100, 330),
+                                     (30, 20, 90), (63, 70, 320), (64, 20, 300), (64, 70, 140), (40, 100, 300), (64, 100, 600), (30, 100, 70)])
 def test_deal_over_many_requests(spec, B, N, wgs):
     cfg = wl.Config(91, "deal", "bf16", B=B, H=2, D=128, P=(0, 200), N=N, tree="random_branching")
     inp = wl.make_attention_inputs(cfg, seed=4000 + B, S_cap=200 + N)

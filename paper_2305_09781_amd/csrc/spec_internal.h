@@ -169,7 +169,8 @@ hipError_t launch_tree_attention_bf16(const spec_attn_desc_t& d, const AttnPlan&
                                       void* v_cache, const void* k_new, const void* v_new, const int32_t* parent,
                                       const int32_t* depth, const int32_t* prefix_len, void* out, void* ws,
                                       int32_t* status, hipStream_t s, const Rope& rope = no_rope());
-// Wide trees (N > 32): the workgroup's wavefronts split the queries and share the K/V stream through LDS.
+// Several query tiles per K/V head, or k_new / v_new not laid out like q: the workgroup's wavefronts split the queries and share the
+// K/V stream through LDS.
 hipError_t launch_tree_attention_bf16_wide(const spec_attn_desc_t& d, const AttnPlan& plan, const Pages& pg, const void* q, void* k_cache,
                                            void* v_cache, const void* k_new, const void* v_new, const int32_t* parent,
                                            const int32_t* depth, const int32_t* prefix_len, void* out, void* ws,
@@ -263,23 +264,15 @@ __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirs
 // a / b of workgroup-uniform numbers; without the division, which stands before a kernel's first load, where b is 1
 __device__ __forceinline__ int uniform_div(int a, int b) { return b == 1 ? a : uniform(a / b); }
 
-// Validates one request's tree with the threads of a workgroup (blockDim.x >= N).
-// Returns true for every thread iff parent[0] == -1, 0 <= parent[i] < i and depth[i] == depth[parent[i]] + 1.
-// `flag` is one int of LDS. Contains two __syncthreads().
-__device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, const int32_t* __restrict__ depth, int N,
-                                     int* flag) {
+// Checks one request's parents with the threads of a workgroup (blockDim.x >= N): true for every thread iff parent[0] == -1 and
+// 0 <= parent[i] < i. `flag` is one int of LDS. Contains two __syncthreads().
+__device__ inline bool tree_is_valid(const int32_t* __restrict__ parent, int N, int* flag) {
   const int t = threadIdx.x;
   if (t == 0) *flag = 0;
   __syncthreads();
   if (t < N) {
     const int p = parent[t];
-    bool ok;
-    if (t == 0) {
-      ok = (p == -1) && (depth == nullptr || depth[0] == 0);
-    } else {
-      ok = (p >= 0) && (p < t);
-      if (ok && depth != nullptr) ok = depth[t] == depth[p] + 1;
-    }
+    const bool ok = t == 0 ? p == -1 : p >= 0 && p < t;
     if (!ok) atomicOr(flag, 1);
   }
   __syncthreads();
@@ -413,8 +406,8 @@ __device__ __forceinline__ bool tree_masks_by_two_waves(TreeLds& s, int N, int w
 // loop over segments: 32 requests x 64 / 8 heads, 900-4100 keys: 123 -> 103 us; 4 x 32 heads, 8192-16384: 147 -> 139 us). A request that does not fit
 // the cache capacity has no tiles.
 //
-// All functions read prefix_len[] with the 64 lanes of a wavefront at once (a scalar walk is one dependent load per
-// request: it cost the merge of 32 requests 40 of its 60 us). Every lane must be active; results are uniform.
+// All functions read prefix_len[] with the 64 lanes of a wavefront at once, as a workgroup has its first key only behind them (a
+// scalar walk is one dependent load per request: 40 us for 32 requests). Every lane must be active; results are uniform.
 // a / b of non-negative numbers, in 32 bits where they fit (a 64-bit division is some hundred instructions)
 __device__ inline long deal_div(long a, long b) {
   return ((a | b) >> 30) == 0 && (a >> 21) < b ? (long)deal_quotient((int)a, (int)b) : a / b;

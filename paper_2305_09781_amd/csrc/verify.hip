@@ -920,7 +920,7 @@ __global__ void __launch_bounds__(SW_THREADS) stochastic_walk_kernel(
   const int32_t* tok = token + (long)b * N;
   const int n_groups = (V + VEC - 1) / VEC;
 
-  bool valid = tree_is_valid(par, nullptr, N, &s_flag);
+  bool valid = tree_is_valid(par, N, &s_flag);
   __syncthreads();
   if (t == 0) s_flag = 0;
   __syncthreads();

@@ -24,8 +24,8 @@ constexpr int TOPK_U = 8;        // groups a thread requests before it uses any
 //
 // What bounds it: one workgroup's latency, a launch, one trip to memory for 16 bytes x 8 per thread and two reductions. Eight
 // steps of 16 to 48 rows of 32000 float32 and the merge behind them: 58.6 us with a key and a 64-bit comparison per element,
-// 49.6 with one comparison per group, 44.9 with reductions in register moves (exchanges through LDS before) and the slots requested
-// with the row; 11 to 33 rows of 93776: 93 and 71 with the first two.
+// 49.6 with one comparison per group, 44.9 to 46.7 over the machines seen with reductions in register moves (exchanges through LDS
+// before) and the slots requested with the row (as nodes of a graph 53.0 -> 46.4); 11 to 33 rows of 93776: 93 and 71 with the first two.
 // VEC: 16 bytes of elements, from whatever element a row starts at; the last group ends with the row, and what it shares
 // with the group before it counts there (2 rows of 22115 float32: 6.1 us by single elements, 5.5). Rows of less: one.
 // ---------------------------------------------------------------------------------------------

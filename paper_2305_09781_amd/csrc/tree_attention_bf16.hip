@@ -212,7 +212,10 @@ __global__ void __launch_bounds__(WAVES * 64, 2) tree_attention_bf16_kernel(
   // One argument from each 64-byte line of the argument block, all asked for at once: with branches in between, the compiler asks
   // for a line where it is first used, one trip to memory after the other (with the tree words of a tree of sixteen in one wait: 8 x 32
   // heads of 1024 keys, rotary, two layers 54.0 -> 53.2 us; 32 layers of 1 x 32 heads and what follows 473 -> 458 and 462 in two runs).
-  asm("" : "+s"(N) : "s"(prefix_len), "s"(kv_ss), "s"(rope.len));
+  // Not under the contiguous plan, where a hundred scalars are spilled already and arguments held from the start are more of them (us,
+  // with / without: 6 x 32 heads x 64 of 2251-4500 keys, trees of 11, rotary, 43.1 / 42.2, paged without it 49.1 / 48.3; 5 x 40 x 64 of
+  // 1559-3116, 2, rotary, 34.5 / 33.9; 7 x 32 x 64 of 3000-6000, one node, 54.6 / 53.9; 5 x 32 x 128 of 3000-6000, 12, 76.5 / 75.0).
+  if constexpr (PLAN != 2) asm("" : "+s"(N) : "s"(prefix_len), "s"(kv_ss), "s"(rope.len));
   const int t = threadIdx.x, lane = t & 63;
   const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
   const int r16 = lane & 15, g = lane >> 4;

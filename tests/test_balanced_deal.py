@@ -73,6 +73,15 @@ int main() {
             for (int i = 0; i < B; ++i) incl[b] += deal_before(size[i], i, size[b], b) ? v[i] : 0;
             count += v[b] * H;
           }
+          bool equal = true;   // chunks of one size are numbered as the requests stand
+          for (int b = 0, some = 0; b < B; ++b) {
+            if (size[b] > 0 && some > 0) equal = equal && size[b] == some;
+            some = size[b] > 0 ? size[b] : some;
+          }
+          for (int b = 0, sum = 0; b < B; ++b) {
+            sum += v[b];
+            if (equal && v[b] > 0) check(incl[b] == sum, "as they stand", b, B, share);
+          }
           std::vector<std::vector<int>> seen(B);
           for (int b = 0; b < B; ++b) seen[b].assign(H * v[b], 0);
           int before = 1 << 30;

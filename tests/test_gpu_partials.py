@@ -22,6 +22,7 @@ CASES = [
     ("bf16", 2, 2, 128, 30, (0, 40, 0)),
     ("bf16", 12, 2, 128, 40, (0, 90, 0)),      # three query groups of two heads
     ("bf16", 2, 2, 64, 100, (0, 30, 0)),       # eight wavefronts; the tree spans two chunks
+    ("bf16", 2, 2, 64, 100, (192, -1, 0)),     # ... under fixed chunks
     ("bf16", 2, 2, 128, 100, (128, -1, 0)),    # 32-query kernel
     ("bf16", 32, 2, 128, 16, (0, 80, 0)),      # two query groups
     ("f32", 4, 2, 128, 20, (128, 0, 0)),

@@ -119,10 +119,14 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
   const bool turned = APART && ((vt >> 4) & 1) != 0;
   const int start = turned ? HEAD : 0;
   int next = start;
-  auto issue = [&](int slot) {
+  // 64 x 64 tiles in step take the stage's number c from the loop: a counter of their own holds them up (us, counter / loop / before there was a
+  // counter: 40 rows, 8192 x 3000 40.8 / 38.9 / 39.3, 4096 x 8000 26.6 / 26.1 / 26.5); other tiles gain from it
+  // (300 rows, 8192 x 16500 165.5 / 170.3 / 170.9; 20 rows 74.9 / 78.7 / 76.4).
+  constexpr bool COUNTED = APART || VT != 64 || MT != 64;
+  auto issue = [&](int c, int slot) {
     const unsigned dst = wave_lds + slot * STAGE;
-    const long k = (long)next * ROWB;
-    ++next;
+    const long k = (long)(COUNTED ? next : c) * ROWB;
+    if (COUNTED) ++next;
     if (APART && next == NC) next = 0;
 #pragma unroll
     for (int j = 0; j < HL; ++j) load_to_lds<false>(hsrc[j] + k, dst + W_BYTES + j * 4096);
@@ -131,7 +135,7 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
   };
 #pragma unroll
   for (int c = 0; c < AHEAD; ++c)
-    if (c < NC) issue(c);
+    if (c < NC) issue(c, c);
 
   // TWO: a logit is the sum of two, over the first and over the second two k-steps of every stage. The tile of 64 x 32 gives
   // them to two wavefronts. Where that tile serves the smallest M (V and K decide), the others take the same two sums, so that
@@ -159,7 +163,7 @@ __global__ void __launch_bounds__(NTHREADS, RING_KB == 64 ? 2 : 1) lm_head_argma
       if (c + AHEAD <= NC) wait_loads_but<(AHEAD - 1) * LPS>();
       else wait_loads_but<0>();
       lds_barrier();   // stage c has landed for every lane, and every wavefront is done with stage c - 1, whose slot is free
-      if (c + AHEAD < NC) issue(slot == 0 ? NST - 1 : slot - 1);
+      if (c + AHEAD < NC) issue(c + AHEAD, slot == 0 ? NST - 1 : slot - 1);
       const unsigned char* ws = ring + slot * STAGE + wv * TV * 32 * ROWB;
       const unsigned char* hs = ring + slot * STAGE + W_BYTES + wm * TM * 32 * ROWB;
 #pragma unroll

@@ -141,8 +141,10 @@ __global__ void __launch_bounds__(F32_WAVES * 64, 2) tree_attention_f32_kernel(
   };
   int ti = wave;
   // The first tile's K, the queries, its V: the scores need the first two only. (Unconditional, so that the compiler knows how many
-  // loads stand behind each: a wavefront without a tile takes the chunk's last.)
-  const int first = c0 + min(ti, n_tiles - 1) * F32_TK;
+  // loads stand behind each: a wavefront without a tile takes the chunk's last row for all of its own, one line per load. us, before these
+  // loads were unconditional / with the last tile / now: 1 x 12 heads of 14 keys, one node, D = 128, 5.7 / 6.2 / 5.9, 8 x 32 of 12-14, 2, 6.1 /
+  // 6.5 / 6.2; 32 x 32 of 20, 8, D = 64, 9.0 / 9.5 / 9.3; 3 x 12 of 40-60, 2, D = 128, 7.0 / 6.4 / 6.4.)
+  const int first = ti < n_tiles ? c0 + ti * F32_TK : c1 - 1;
   const long first_base = tile_base(first);
   load_k(first, first_base);
   float4 qf[NT][KJ];
